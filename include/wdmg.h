@@ -201,15 +201,13 @@ int wdmg_apply_D(wdmg_ctx* ctx, void* out, const void* in, int nrhs, int prec);
 
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid allocation): the same
- * out = D in as wdmg_apply_D, with the internal-layout input and output
- * fields in a 64 MiB device array that the library holds on every GPU it
- * runs on until the process ends.  prec WDMG_F64 or WDMG_F32 only; at most
+ * out = D in as wdmg_apply_D.  Fields that are not aligned to 16 bytes go
+ * through a 64 MiB device array that the library holds on every GPU it runs
+ * on until the process ends; the limit below holds for all.  prec WDMG_F64 or WDMG_F32 only; at most
  * 2 x 12 x padded sites x nrhs x (16 or 8) bytes <= 64 MiB (a 16^4 lattice
  * takes 2 FP64 or 5 FP32 right-hand sides), else WDMG_ERR_ARG before
- * anything is launched.  Makes no hipMalloc/hipFree or other allocating call:
- * the Wilson form is the one the autotuner already chose for (prec, nrhs) on
- * this context, else the default form, and the call is not timed by
- * wdmg_profile.  All calls on one GPU share its array (which keeps the last
+ * anything is launched.  Makes no hipMalloc/hipFree or other allocating call,
+ * and the call is not timed by wdmg_profile.  All calls on one GPU share its array (which keeps the last
  * call's contents; nothing in it needs to start at zero), so calls that
  * overlap on one GPU, from any context or stream, race. */
 int wdmg_apply_D_noalloc(wdmg_ctx* ctx, void* out, const void* in, int nrhs, int prec);
@@ -289,38 +287,22 @@ int wdmg_solve(wdmg_ctx* ctx, void* x, const void* b, int nrhs,
 int wdmg_solve_bicgstab(wdmg_ctx* ctx, void* x, const void* b, int nrhs, double tol,
                         int maxit, wdmg_solve_stats* stats);
 
-/* ---- kernel variants and the autotuner ------------------------------------
+/* ---- kernel variants -------------------------------------------------------
  * Some kernels exist in more than one form with the same result (up to the
  * order of floating-point additions).  With value WDMG_TUNE_AUTO (the
- * default) the library times the forms on first use for each precision and
- * batch size (HIP events, a few launches each, on the context's stream) and
- * keeps the fastest for the context's lifetime; a fixed value forces a form.
- *   WDMG_TUNE_DSLASH: 0 one thread per site, 1 one wave per direction with
- *                     the four partial sums added in LDS, 2 form 1 with its
- *                     registers capped so that four waves fit per SIMD,
- *                     3 and 4 form 1 with 2 or 4 right-hand sides per
- *                     thread (each link loaded once for them, the
- *                     direction sums meeting in LDS one rhs at a time);
- *                     forms 3 and 4 apply to batches they divide (a forced
- *                     value runs form 1 on other batch sizes); 5 one wave per
- *                     4x4x4 tile column walking a chunk of time layers, each
- *                     spinor loaded once per chunk, the x, y, z hops exchanged
- *                     between lanes (lattices cut into 4^4 tiles only, else
- *                     form 1; the rhs-group value 4, 8 or 16 sets the chunk);
- *                     6, 7, 8 forms 1, 2, 3 with the workgroups of each XCD
- *                     walking a box of tile columns layer by layer (4^4
- *                     tiles and tile columns that split into 8 boxes only,
- *                     else form 1); 9 form 5 with XCD k taking the k-th
- *                     eighth of the time extent (every tile column of it)
- *                     and the rhs of a group running each column back to
- *                     back (4^4 tiles and Lt a multiple of 8 only, else
- *                     form 1; the rhs-group value sets the group).
- *   WDMG_TUNE_DSLASH_GROUP: right-hand sides per group (1..64) in the
- *                     workgroup order of a batched Wilson launch: each XCD
- *                     sweeps its lattice region once per group, with the
- *                     group's rhs of one site block back to back (a value
- *                     above the batch size means the whole batch).  Tuned
- *                     after the form.
+ * default) the library picks by lattice, precision and batch size; a fixed
+ * value forces a form.
+ *   WDMG_TUNE_DSLASH: the Wilson operator.  5 or 9: a 4^4 tile and its faces
+ *                     staged on chip per right-hand side, the links kept for
+ *                     the whole batch (FP32 and 16 bits, lattices cut into 4^4
+ *                     tiles; elsewhere as 1).  0-4 and 6-8: one wave per
+ *                     direction over 64 sites, on any lattice and precision.
+ *                     (Ten values are accepted; which of a group is given
+ *                     makes no difference.)
+ *   WDMG_TUNE_DSLASH_GROUP: right-hand sides per workgroup (1..64) of the
+ *                     one-wave-per-direction form below FP64 (links are loaded
+ *                     once per group; a value above the batch size means the
+ *                     whole batch).  FP64 and the tile form ignore it.
  *   WDMG_TUNE_COARSE_APPLY: the batched coarsest-level operator (nrhs >= 2)
  *                     on the FP64 matrix cores; 0 waves split over
  *                     directions with operands read straight from memory,
@@ -338,16 +320,16 @@ enum {
   WDMG_TUNE_COUNT
 };
 int wdmg_set_tuning(wdmg_ctx* ctx, int key, int value);
-/* Sets the choice the autotuner keeps for key (WDMG_TUNE_DSLASH or
- * WDMG_TUNE_DSLASH_GROUP) at precision prec and batch size nrhs (sizes from
- * 64 up share one entry), as if it had timed the forms and picked `value`;
- * WDMG_TUNE_AUTO clears the entry, so the next launch times the forms again.
- * A value forced with wdmg_set_tuning takes precedence.  A form that does not
- * apply to the batch or lattice runs form 1, as with wdmg_set_tuning.
+/* Sets the choice kept for key (WDMG_TUNE_DSLASH or WDMG_TUNE_DSLASH_GROUP) at
+ * precision prec and batch size nrhs (sizes from 64 up share one entry), as if
+ * the library had picked `value`; WDMG_TUNE_AUTO clears the entry, so the next
+ * launch picks again.  A value forced with wdmg_set_tuning takes precedence.
+ * A form that does not apply to the lattice or precision runs form 1, as with
+ * wdmg_set_tuning.
  * WDMG_ERR_ARG for another key, an unknown precision, nrhs < 1 or a value
  * out of range. */
 int wdmg_set_tuning_for(wdmg_ctx* ctx, int key, int prec, int nrhs, int value);
-/* Current choice for key (WDMG_TUNE_AUTO until tuned) for precision prec
+/* Current choice for key (WDMG_TUNE_AUTO until picked) for precision prec
  * and batch size nrhs. */
 int wdmg_get_tuning(wdmg_ctx* ctx, int key, int prec, int nrhs, int* value);
 

@@ -87,26 +87,60 @@ void ensure_ioh(Ctx& c, int nrhs) {
   c.ioh_cap = nrhs;
 }
 
+// Caller fields are in the layout the kernels work on.  One that is not aligned
+// to the 16 bytes in which they move sites goes through a library buffer.
+bool aligned(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
+
+// n complex numbers of R copied as pairs of FP32 words, for any 8-byte aligned pointer.
+template <typename R>
+void copy_words(Ctx& c, void* dst, const void* src, size_t n) {
+  copy<float>(c, static_cast<cx<float>*>(dst), static_cast<const cx<float>*>(src), n * sizeof(cx<R>) / sizeof(cx<float>));
+}
+// `p` itself, or its copy in `stage`
+template <typename R>
+const cx<R>* field_in(Ctx& c, const void* p, void* stage, size_t n) {
+  if (aligned(p)) return static_cast<const cx<R>*>(p);
+  copy_words<R>(c, stage, p, n);
+  return static_cast<const cx<R>*>(stage);
+}
+// where to write a field meant for `p`, and the copy back
+template <typename R>
+cx<R>* field_out(void* p, void* stage) {
+  return static_cast<cx<R>*>(aligned(p) ? p : stage);
+}
+template <typename R>
+void field_done(Ctx& c, void* p, const void* stage, size_t n) {
+  if (!aligned(p)) copy_words<R>(c, p, stage, n);
+}
+size_t fine_n(const Ctx& c) { return (size_t)c.g0.vol * 12; }
+
+// io_a / io_b when one of the pointers needs them
+void ensure_stage(Ctx& c, const void* p, const void* q, size_t bytes) {
+  if (!aligned(p) || !aligned(q)) ensure_io(c, bytes);
+}
+
 template <typename H>
 void apply_D_half(Ctx& c, void* out, const void* in, int nrhs) {
   ensure_ioh(c, nrhs);
-  canon_to_half<H>(c, static_cast<const cx<float>*>(in), c.ioh[0], nrhs);
+  to_half<float, H>(c, static_cast<const cx<float>*>(in), c.ioh[0], nrhs);
   dslash_h<H>(c, c.ioh[1], c.ioh[0], nrhs);
-  half_to_canon<H>(c, c.ioh[1], static_cast<cx<float>*>(out), nrhs);
+  from_half<H, float>(c, c.ioh[1], static_cast<cx<float>*>(out), nrhs);
 }
 
 template <typename H>
 void roundtrip_half(Ctx& c, void* out, const void* in, int nrhs) {
   ensure_ioh(c, nrhs);
-  canon_to_half<H>(c, static_cast<const cx<float>*>(in), c.ioh[0], nrhs);
-  half_to_canon<H>(c, c.ioh[0], static_cast<cx<float>*>(out), nrhs);
+  to_half<float, H>(c, static_cast<const cx<float>*>(in), c.ioh[0], nrhs);
+  from_half<H, float>(c, c.ioh[0], static_cast<cx<float>*>(out), nrhs);
 }
 
 template <typename H>
 void restrict_half(Ctx& c, void* cout, const void* fin, int nrhs) {
-  ensure_ioh(c, nrhs);
   const void* V = v16(c, c.lev[0], half_kind<H>());
-  canon_to_half<H>(c, static_cast<const cx<float>*>(fin), c.ioh[0], nrhs);
+  if (restrict0_round<H>(c, c.lev[0], V, static_cast<const cx<float>*>(fin), static_cast<cx<float>*>(cout), nrhs))
+    return;
+  ensure_ioh(c, nrhs);
+  to_half<float, H>(c, static_cast<const cx<float>*>(fin), c.ioh[0], nrhs);
   restrict0_h<H>(c, c.lev[0], V, c.ioh[0], static_cast<cx<float>*>(cout), nrhs);
 }
 
@@ -115,28 +149,25 @@ void prolong_half(Ctx& c, void* fout, const void* cin, int nrhs) {
   ensure_ioh(c, nrhs);
   const void* V = v16(c, c.lev[0], half_kind<H>());
   prolong0_h<H>(c, c.lev[0], V, static_cast<const cx<float>*>(cin), c.ioh[0], nrhs);
-  half_to_canon<H>(c, c.ioh[0], static_cast<cx<float>*>(fout), nrhs);
+  from_half<H, float>(c, c.ioh[0], static_cast<cx<float>*>(fout), nrhs);
 }
 
 // MR on the fine level in 16-bit storage.  The starting residual b - D x is
 // formed in FP32; x and r are then held in 16 bits for the iterations.
 template <typename H>
 void smooth_half0(Ctx& c, void* x, const void* b, int nrhs, int iters) {
-  const size_t n = c.lev[0].n;
-  ensure_io(c, 2 * n * nrhs * sizeof(cx<float>));
+  const size_t n = c.lev[0].n * nrhs;
+  ensure_io(c, 2 * n * sizeof(cx<float>));
   ensure_ioh(c, nrhs);
-  cx<float>* xi = static_cast<cx<float>*>(c.io_a);
-  cx<float>* ri = xi + n * nrhs;
-  cx<float>* bi = static_cast<cx<float>*>(c.io_b);
-  fine_to_internal<float, float>(c, c.g0, static_cast<const cx<float>*>(x), xi, nrhs);
-  fine_to_internal<float, float>(c, c.g0, static_cast<const cx<float>*>(b), bi, nrhs);
+  cx<float>* ri = static_cast<cx<float>*>(c.io_a);
+  const cx<float>* xi = field_in<float>(c, x, ri + n, n);
   dslash<float>(c, ri, xi, nrhs);
-  xmy<float>(c, bi, ri, n * nrhs);
+  xmy<float>(c, static_cast<const cx<float>*>(b), ri, n);
   to_half<float, H>(c, xi, c.ioh[0], nrhs);
   to_half<float, H>(c, ri, c.ioh[1], nrhs);
   const double omega = c.have_mg ? c.mg.omega : 0.8;
   mr_h<H>(c, c.ioh[0], c.ioh[1], c.ioh[2], nrhs, iters, omega);
-  half_to_canon<H>(c, c.ioh[0], static_cast<cx<float>*>(x), nrhs);
+  from_half<H, float>(c, c.ioh[0], static_cast<cx<float>*>(x), nrhs);
 }
 void need_ptr(const void* p, const char* what) {
   if (!p) throw Error(WDMG_ERR_ARG, std::string("null pointer: ") + what);
@@ -145,25 +176,13 @@ void need_nrhs(int nrhs) {
   if (nrhs < 1 || nrhs > 65535) throw Error(WDMG_ERR_ARG, "nrhs must be in 1..65535");
 }
 
-// canonical fine layout <-> level-0 internal layout, in precision R
-template <typename R>
-void fine_in(Ctx& c, const void* canon, cx<R>* dst, int nrhs) {
-  fine_to_internal<R, R>(c, c.g0, static_cast<const cx<R>*>(canon), dst, nrhs);
-}
-template <typename R>
-void fine_out(Ctx& c, const cx<R>* src, void* canon, int nrhs) {
-  fine_to_canonical<R, R>(c, c.g0, src, static_cast<cx<R>*>(canon), nrhs);
-}
-
 template <typename R>
 void apply_D_impl(Ctx& c, void* out, const void* in, int nrhs) {
-  const size_t n = (size_t)c.g0.vpad * 12;
-  ensure_io(c, n * nrhs * sizeof(cx<R>));
-  cx<R>* a = static_cast<cx<R>*>(c.io_a);
-  cx<R>* b = static_cast<cx<R>*>(c.io_b);
-  fine_in<R>(c, in, a, nrhs);
-  dslash<R>(c, b, a, nrhs);
-  fine_out<R>(c, b, out, nrhs);
+  const size_t n = fine_n(c) * nrhs;
+  ensure_stage(c, in, out, n * sizeof(cx<R>));
+  cx<R>* o = field_out<R>(out, c.io_b);
+  dslash<R>(c, o, field_in<R>(c, in, c.io_a, n), nrhs);
+  field_done<R>(c, out, o, n);
 }
 
 template <typename R>
@@ -179,37 +198,18 @@ const cx<R>* dc_of(const Level& L) {
 
 template <typename R>
 void restrict_impl(Ctx& c, int level, void* cout, const void* fin, int nrhs) {
-  cx<R>* co = static_cast<cx<R>*>(cout);
-  if (level == 0) {
-    const size_t n = c.lev[0].n;
-    ensure_io(c, n * nrhs * sizeof(cx<R>));
-    cx<R>* a = static_cast<cx<R>*>(c.io_a);
-    fine_in<R>(c, fin, a, nrhs);
-    restrict_to<R>(c, 0, a, co, nrhs);
-  } else {
-    restrict_to<R>(c, level, static_cast<const cx<R>*>(fin), co, nrhs);
-  }
+  restrict_to<R>(c, level, static_cast<const cx<R>*>(fin), static_cast<cx<R>*>(cout), nrhs);
 }
 
 template <typename R>
 void prolong_impl(Ctx& c, int level, void* fout, const void* cin, int nrhs) {
-  const cx<R>* ci = static_cast<const cx<R>*>(cin);
-  if (level == 0) {
-    const size_t n = c.lev[0].n;
-    ensure_io(c, n * nrhs * sizeof(cx<R>));
-    cx<R>* a = static_cast<cx<R>*>(c.io_a);
-    prolong_from<R>(c, 0, ci, a, nrhs);
-    fine_out<R>(c, a, fout, nrhs);
-  } else {
-    prolong_from<R>(c, level, ci, static_cast<cx<R>*>(fout), nrhs);
-  }
+  prolong_from<R>(c, level, static_cast<const cx<R>*>(cin), static_cast<cx<R>*>(fout), nrhs);
 }
 
 template <typename R>
 void smooth_impl(Ctx& c, int level, void* x, const void* b, int nrhs, int iters) {
   Level& L = c.lev[level];
   const size_t n = L.n;
-  const size_t ncan = level == 0 ? (size_t)c.g0.vol * 12 : n;  // canonical stride per rhs
   ensure_io(c, 2 * n * sizeof(cx<R>));
   cx<R>* xi = static_cast<cx<R>*>(c.io_a);
   cx<R>* ri = xi + n;
@@ -217,38 +217,34 @@ void smooth_impl(Ctx& c, int level, void* x, const void* b, int nrhs, int iters)
   cx<R>* bi = p + n;
   const double omega = c.have_mg ? c.mg.omega : 0.8;
   for (int k = 0; k < nrhs; ++k) {
-    if (level == 0) {
-      fine_in<R>(c, static_cast<const cx<R>*>(x) + (size_t)k * ncan, xi, 1);
-      fine_in<R>(c, static_cast<const cx<R>*>(b) + (size_t)k * ncan, bi, 1);
-    } else {
-      copy<R>(c, xi, static_cast<const cx<R>*>(x) + (size_t)k * n, n);
-      copy<R>(c, bi, static_cast<const cx<R>*>(b) + (size_t)k * n, n);
-    }
+    copy_words<R>(c, xi, static_cast<const cx<R>*>(x) + (size_t)k * n, n);
+    copy_words<R>(c, bi, static_cast<const cx<R>*>(b) + (size_t)k * n, n);
     apply_op<R>(c, level, ri, xi, 1);
     xmy<R>(c, bi, ri, n);
     mr<R>(c, level, xi, ri, p, 1, iters, omega);
-    if (level == 0)
-      fine_out<R>(c, xi, static_cast<cx<R>*>(x) + (size_t)k * ncan, 1);
-    else
-      copy<R>(c, static_cast<cx<R>*>(x) + (size_t)k * n, xi, n);
+    copy_words<R>(c, static_cast<cx<R>*>(x) + (size_t)k * n, xi, n);
   }
 }
 
-// Internal x (and, unless the solve runs in place, b) for nrhs right-hand sides.
-void ensure_solve_io(Ctx& c, int nrhs, bool need_b = true) {
-  const size_t n = (size_t)c.g0.vpad * 12;
-  if (nrhs > c.sol_cap) {
-    WDMG_HIP(hipStreamSynchronize(c.stream));
-    dev_free(c, c.sol_x);
-    c.sol_x = static_cast<cx<double>*>(dev_alloc(c, (size_t)nrhs * n * sizeof(cx<double>)));
-    c.sol_cap = nrhs;
-  }
-  if (need_b && nrhs > c.sol_bcap) {
+// Solution buffer of nrhs right-hand sides (the caller's x is written at the end only).
+void ensure_solve_x(Ctx& c, int nrhs) {
+  if (nrhs <= c.sol_cap) return;
+  WDMG_HIP(hipStreamSynchronize(c.stream));
+  dev_free(c, c.sol_x);
+  c.sol_x = static_cast<cx<double>*>(dev_alloc(c, (size_t)nrhs * fine_n(c) * sizeof(cx<double>)));
+  c.sol_cap = nrhs;
+}
+
+// The caller's right-hand sides (read in place when aligned).
+const cx<double>* solve_b(Ctx& c, const void* b, int nrhs) {
+  const size_t n = fine_n(c) * nrhs;
+  if (!aligned(b) && nrhs > c.sol_bcap) {
     WDMG_HIP(hipStreamSynchronize(c.stream));
     dev_free(c, c.sol_b);
-    c.sol_b = static_cast<cx<double>*>(dev_alloc(c, (size_t)nrhs * n * sizeof(cx<double>)));
+    c.sol_b = static_cast<cx<double>*>(dev_alloc(c, n * sizeof(cx<double>)));
     c.sol_bcap = nrhs;
   }
+  return field_in<double>(c, b, c.sol_b, n);
 }
 
 double now() {
@@ -317,6 +313,10 @@ int wdmg_create(wdmg_ctx** out, const int dims[4], const wdmg_alloc* alloc, void
     return WDMG_ERR_HIP;
   }
   init_scratch(c->device);
+  if (hipDeviceGetAttribute(&c->ncu, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess || c->ncu < 8) {
+    (void)hipGetLastError();
+    c->ncu = 256;
+  }
   if (alloc) {
     c->alloc = *alloc;
     if (!alloc->alloc || !alloc->free) {
@@ -335,6 +335,7 @@ int wdmg_create(wdmg_ctx** out, const int dims[4], const wdmg_alloc* alloc, void
                            hipHostMallocMapped | hipHostMallocCoherent));
     WDMG_HIP(hipHostGetDevicePointer(reinterpret_cast<void**>(&c->dring), c->hring, 0));
     for (int i = 0; i < kRing; ++i) WDMG_HIP(hipEventCreateWithFlags(&c->ring_ev[i], hipEventDisableTiming));
+    init_dslash();
     init_level0(*c);
     WDMG_HIP(hipStreamSynchronize(c->stream));
     return WDMG_OK;
@@ -459,25 +460,23 @@ int wdmg_apply_D_noalloc(wdmg_ctx* c, void* out, const void* in, int nrhs, int p
     if (2 * field > kNoAllocScratchBytes)
       throw Error(WDMG_ERR_ARG, "wdmg_apply_D_noalloc: " + std::to_string(2 * field) +
                                     " bytes of scratch needed, the maximum is 64 MiB");
-    // `field` is a multiple of 64 sites x 12 x 8 bytes, so b stays 256-byte aligned
+    // used for fields that are not aligned to 16 bytes only; `field` is a
+    // multiple of 64 sites x 12 x 8 bytes, so both halves are 256-byte aligned
     unsigned char* base = static_cast<unsigned char*>(g_scratch[dev]);
     c->no_alloc = true;
     struct Restore {
       Ctx& c;
       ~Restore() { c.no_alloc = false; }
     } restore{*c};
+    const size_t n = fine_n(*c) * nrhs;
     if (prec == WDMG_F64) {
-      cx<double>* a = reinterpret_cast<cx<double>*>(base);
-      cx<double>* b = reinterpret_cast<cx<double>*>(base + field);
-      fine_in<double>(*c, in, a, nrhs);
-      dslash<double>(*c, b, a, nrhs);
-      fine_out<double>(*c, b, out, nrhs);
+      cx<double>* o = field_out<double>(out, base + field);
+      dslash<double>(*c, o, field_in<double>(*c, in, base, n), nrhs);
+      field_done<double>(*c, out, o, n);
     } else {
-      cx<float>* a = reinterpret_cast<cx<float>*>(base);
-      cx<float>* b = reinterpret_cast<cx<float>*>(base + field);
-      fine_in<float>(*c, in, a, nrhs);
-      dslash<float>(*c, b, a, nrhs);
-      fine_out<float>(*c, b, out, nrhs);
+      cx<float>* o = field_out<float>(out, base + field);
+      dslash<float>(*c, o, field_in<float>(*c, in, base, n), nrhs);
+      field_done<float>(*c, out, o, n);
     }
     return WDMG_OK;
   });
@@ -490,15 +489,11 @@ int wdmg_roundtrip(wdmg_ctx* c, void* out, const void* in, int nrhs, int prec) {
     need_nrhs(nrhs);
     need_prec(prec);
     if (out == in) throw Error(WDMG_ERR_ARG, "out must differ from in");
-    const size_t n = (size_t)c->g0.vpad * 12;
+    const size_t n = fine_n(*c) * nrhs;
     if (prec == WDMG_F64) {
-      ensure_io(*c, n * nrhs * sizeof(cx<double>));
-      fine_in<double>(*c, in, static_cast<cx<double>*>(c->io_a), nrhs);
-      fine_out<double>(*c, static_cast<cx<double>*>(c->io_a), out, nrhs);
+      copy_words<double>(*c, out, in, n);
     } else if (prec == WDMG_F32) {
-      ensure_io(*c, n * nrhs * sizeof(cx<float>));
-      fine_in<float>(*c, in, static_cast<cx<float>*>(c->io_a), nrhs);
-      fine_out<float>(*c, static_cast<cx<float>*>(c->io_a), out, nrhs);
+      copy_words<float>(*c, out, in, n);
     } else if (prec == WDMG_F16) {
       roundtrip_half<f16_t>(*c, out, in, nrhs);
     } else {
@@ -522,10 +517,7 @@ int wdmg_get_prolongator(wdmg_ctx* c, int level, void* V_out) {
     need_mg(*c, level, false);
     Level& L = c->lev[level];
     if (!L.V64) throw Error(WDMG_ERR_ARG, "prolongator released by wdmg_release_unused");
-    if (level == 0)
-      fine_to_canonical<double, double>(*c, c->g0, L.V64, static_cast<cx<double>*>(V_out), L.nv);
-    else
-      copy<double>(*c, static_cast<cx<double>*>(V_out), L.V64, (size_t)L.nv * L.n);
+    copy_words<double>(*c, V_out, L.V64, (size_t)L.nv * L.n);
     return WDMG_OK;
   });
 }
@@ -645,7 +637,7 @@ int wdmg_solve(wdmg_ctx* c, void* x, const void* b, int nrhs, const wdmg_solve_p
     if (p->outer < 0 || p->outer > 3) throw Error(WDMG_ERR_ARG, "outer must be 0 (FGCR), 1 (BiCGStab), 2 (CGNR) or 3 (MG-CG)");
     if (p->outer == 2 || p->outer == 3) {
       // CG on the normal equations, plain or preconditioned by the normal-equation V-cycle
-      ensure_solve_io(*c, 1);
+      ensure_solve_x(*c, 1);
       const size_t nc = (size_t)c->g0.vol * 12;
       int worst = WDMG_OK;
       for (int k = 0; k < nrhs; ++k) {
@@ -653,9 +645,9 @@ int wdmg_solve(wdmg_ctx* c, void* x, const void* b, int nrhs, const wdmg_solve_p
         c->n_D = 0;
         for (int l = 0; l < WDMG_MAX_LEVELS; ++l) c->n_Dc[l] = 0;
         const double t0 = now();
-        fine_in<double>(*c, static_cast<const cx<double>*>(b) + k * nc, c->sol_b, 1);
-        const int rc = normal_solve(*c, c->sol_x, c->sol_b, p->tol, p->maxit, p->outer == 3, st);
-        fine_out<double>(*c, c->sol_x, static_cast<cx<double>*>(x) + k * nc, 1);
+        const cx<double>* bk = solve_b(*c, static_cast<const cx<double>*>(b) + k * nc, 1);
+        const int rc = normal_solve(*c, c->sol_x, bk, p->tol, p->maxit, p->outer == 3, st);
+        copy_words<double>(*c, static_cast<cx<double>*>(x) + k * nc, c->sol_x, nc);
         WDMG_HIP(hipStreamSynchronize(c->stream));
         st.seconds = now() - t0;
         st.n_D = c->n_D;
@@ -667,7 +659,7 @@ int wdmg_solve(wdmg_ctx* c, void* x, const void* b, int nrhs, const wdmg_solve_p
     }
     if (p->outer == 1) {
       // MG-preconditioned BiCGStab, one right-hand side after another
-      ensure_solve_io(*c, 1);
+      ensure_solve_x(*c, 1);
       const size_t nc = (size_t)c->g0.vol * 12;  // canonical stride per rhs
       int worst = WDMG_OK;
       for (int k = 0; k < nrhs; ++k) {
@@ -675,9 +667,9 @@ int wdmg_solve(wdmg_ctx* c, void* x, const void* b, int nrhs, const wdmg_solve_p
         c->n_D = 0;
         for (int l = 0; l < WDMG_MAX_LEVELS; ++l) c->n_Dc[l] = 0;
         const double t0 = now();
-        fine_in<double>(*c, static_cast<const cx<double>*>(b) + k * nc, c->sol_b, 1);
-        const int rc = bicgstab(*c, c->sol_x, c->sol_b, p->tol, p->maxit, st, p->precond ? p : nullptr);
-        fine_out<double>(*c, c->sol_x, static_cast<cx<double>*>(x) + k * nc, 1);
+        const cx<double>* bk = solve_b(*c, static_cast<const cx<double>*>(b) + k * nc, 1);
+        const int rc = bicgstab(*c, c->sol_x, bk, p->tol, p->maxit, st, p->precond ? p : nullptr);
+        copy_words<double>(*c, static_cast<cx<double>*>(x) + k * nc, c->sol_x, nc);
         WDMG_HIP(hipStreamSynchronize(c->stream));
         st.seconds = now() - t0;
         st.n_D = c->n_D;
@@ -691,24 +683,22 @@ int wdmg_solve(wdmg_ctx* c, void* x, const void* b, int nrhs, const wdmg_solve_p
     if (in_place && (!p->precond || p->mg_prec == WDMG_F64 || p->restart < 2 || p->use_graph))
       throw Error(WDMG_ERR_ARG, "in-place solves need FGCR with a V-cycle below FP64, restart >= 2 and no graph");
     if (!in_place && x == b) throw Error(WDMG_ERR_ARG, "x and b are the same buffer: set in_place");
-    ensure_solve_io(*c, nrhs, !in_place);
+    ensure_solve_x(*c, nrhs);
     std::vector<wdmg_solve_stats> st(nrhs);
     c->n_D = 0;
     for (int l = 0; l < WDMG_MAX_LEVELS; ++l) c->n_Dc[l] = 0;
 
     const double t0 = now();
-    int rc;
-    if (in_place) {
-      // x starts from zero; b is read from the caller's buffer whenever the
-      // residual is recomputed, and x is written over it at the end
-      zero<double>(*c, c->sol_x, (size_t)nrhs * c->g0.vpad * 12);
-      rc = fgcr(*c, c->sol_x, nullptr, nrhs, *p, st.data(), b);
-    } else {
-      fine_in<double>(*c, b, c->sol_b, nrhs);
-      fine_in<double>(*c, x, c->sol_x, nrhs);
-      rc = fgcr(*c, c->sol_x, c->sol_b, nrhs, *p, st.data());
-    }
-    fine_out<double>(*c, c->sol_x, x, nrhs);
+    // b is read in place whenever the true residual is recomputed; x starts
+    // from zero in an in-place solve and is written over b at the end
+    const size_t n = fine_n(*c) * nrhs;
+    const cx<double>* bi = solve_b(*c, b, nrhs);
+    if (in_place)
+      zero<double>(*c, c->sol_x, n);
+    else
+      copy_words<double>(*c, c->sol_x, x, n);
+    const int rc = fgcr(*c, c->sol_x, bi, nrhs, *p, st.data());
+    copy_words<double>(*c, x, c->sol_x, n);
     WDMG_HIP(hipStreamSynchronize(c->stream));
     const double secs = now() - t0;
     for (int q = 0; q < nrhs; ++q) {
@@ -730,16 +720,16 @@ int wdmg_solve_bicgstab(wdmg_ctx* c, void* x, const void* b, int nrhs, double to
     need_nrhs(nrhs);
     need_gauge(*c);
     if (!(tol > 0.0) || maxit < 1) throw Error(WDMG_ERR_ARG, "bad solve parameters");
-    ensure_solve_io(*c, 1);
+    ensure_solve_x(*c, 1);
     const size_t n = (size_t)c->g0.vol * 12;  // canonical stride per rhs
     int worst = WDMG_OK;
     for (int k = 0; k < nrhs; ++k) {
       wdmg_solve_stats st{};
       c->n_D = 0;
       const double t0 = now();
-      fine_in<double>(*c, static_cast<const cx<double>*>(b) + k * n, c->sol_b, 1);
-      const int rc = bicgstab(*c, c->sol_x, c->sol_b, tol, maxit, st);
-      fine_out<double>(*c, c->sol_x, static_cast<cx<double>*>(x) + k * n, 1);
+      const cx<double>* bk = solve_b(*c, static_cast<const cx<double>*>(b) + k * n, 1);
+      const int rc = bicgstab(*c, c->sol_x, bk, tol, maxit, st);
+      copy_words<double>(*c, static_cast<cx<double>*>(x) + k * n, c->sol_x, n);
       WDMG_HIP(hipStreamSynchronize(c->stream));
       st.seconds = now() - t0;
       st.n_D = c->n_D;

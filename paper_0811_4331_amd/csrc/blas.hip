@@ -220,12 +220,12 @@ struct StepAlphaHalfOp {
   const float* as;
   const cxh<H>* b;
   const float* bs;
-  int vpad;
+  int vol;
   double scale;
   double* dsc;
   int slot;
   __device__ void acc(size_t i, int y, double* v) const {
-    const size_t vo = (size_t)y * 12 * vpad, so = (size_t)y * vpad;
+    const size_t vo = (size_t)y * 12 * vol, so = (size_t)y * vol;
     cx<float> x[12], z[12];
     load_site_h(a + vo, as + so, (int)i, x);
     load_site_h(b + vo, bs + so, (int)i, z);
@@ -422,8 +422,8 @@ __global__ void k_update2_half(Geom g, cxh<H>* xv, float* xs, const cxh<H>* uv, 
                                float* rs, const cxh<H>* vv, const float* vs, const double* sc) {
   const int s = blockIdx.x * blockDim.x + threadIdx.x;
   const int y = blockIdx.y;
-  if (s >= g.vpad) return;
-  const size_t vo = (size_t)y * 12 * g.vpad, so = (size_t)y * g.vpad;
+  if (s >= g.vol) return;
+  const size_t vo = (size_t)y * 12 * g.vol, so = (size_t)y * g.vol;
   const cx<float> a = mk((float)sc[2 * y], (float)sc[2 * y + 1]);
   cx<float> x[12], u[12];
   load_site_h(uv + vo, us + so, s, u);
@@ -821,7 +821,7 @@ void step_alpha_half(Ctx& c, HF a, HF b, int nrhs, double scale, int slot) {
   if (nblk * nrhs > 8192) nblk = 8192 / nrhs;
   if (nblk < 1) nblk = 1;
   const StepAlphaHalfOp<H> op{static_cast<const cxh<H>*>(a.v), a.s, static_cast<const cxh<H>*>(b.v), b.s,
-                              c.g0.vpad, scale, c.dsc, slot};
+                              c.g0.vol, scale, c.dsc, slot};
   hipLaunchKernelGGL((k_reduce_b_part<StepAlphaHalfOp<H>>), dim3(nblk, nrhs), dim3(TPB), 0, c.stream, op, n,
                      c.partials);
   WDMG_HIP(hipGetLastError());
@@ -832,7 +832,7 @@ void step_alpha_half(Ctx& c, HF a, HF b, int nrhs, double scale, int slot) {
 
 template <typename H>
 void update2_half(Ctx& c, HF x, HF u, HF r, HF v, int nrhs, int slot, int mode) {
-  const dim3 grid((c.g0.vpad + 255) / 256, nrhs);
+  const dim3 grid((c.g0.vol + 255) / 256, nrhs);
   auto* xv = static_cast<cxh<H>*>(x.v);
   auto* uv = static_cast<const cxh<H>*>(u.v);
   auto* rv = static_cast<cxh<H>*>(r.v);

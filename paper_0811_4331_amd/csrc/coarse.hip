@@ -78,17 +78,21 @@ __device__ __forceinline__ bool inside(const AggGeom& a, const int c[4], int mu,
 
 // ---- level 0: Wilson hops ---------------------------------------------------
 template <int MU, int SIGN>
-__device__ __forceinline__ void wilson_hop_col(const cx<double>* __restrict__ U, const cx<double>* __restrict__ vk,
-                                               int s, int nb, bool neg, int chi, cx<double> (&t)[12]) {
+__device__ __forceinline__ void wilson_hop_col(const Geom& g, const int c[4], const cx<double>* __restrict__ U,
+                                               const cx<double>* __restrict__ vk, bool neg, int chi,
+                                               cx<double> (&t)[12]) {
+  int n[4] = {c[0], c[1], c[2], c[3]};  // the neighbour
+  n[MU] = SIGN > 0 ? (c[MU] == g.L[MU] - 1 ? 0 : c[MU] + 1) : (c[MU] == 0 ? g.L[MU] - 1 : c[MU] - 1);
+  const int nb = canon_site(g, n);
+  const int ls = SIGN > 0 ? site_of(g, c[0], c[1], c[2], c[3]) : site_of(g, n[0], n[1], n[2], n[3]);
   cx<double> p[12];
 #pragma unroll
   for (int k = 0; k < 12; ++k) {
     const bool on = (k / 6) == chi;
-    p[k] = on ? vk[fidx(nb, k, 12)] : mk(0.0, 0.0);
+    p[k] = on ? vk[(size_t)nb * 12 + k] : mk(0.0, 0.0);
   }
   cx<double> h[6];
   project<MU, SIGN>(p, h);
-  const int ls = SIGN > 0 ? s : nb;
   cx<double> u[9];
   load_link(U, MU, ls, neg, u);
   cx<double> uh[6];
@@ -110,17 +114,18 @@ __device__ __forceinline__ void wilson_hop_col(const cx<double>* __restrict__ U,
   expand_add<MU, SIGN>(uh, t);
 }
 
-__device__ void wilson_hop_dispatch(int mu, int dir, const cx<double>* U, const cx<double>* vk, int s, int nb,
-                                    bool neg, int chi, cx<double> (&t)[12]) {
+// The hop in direction (mu, dir) at coordinates c.
+__device__ void wilson_hop_dispatch(const Geom& g, const int c[4], int mu, int dir, const cx<double>* U,
+                                    const cx<double>* vk, bool neg, int chi, cx<double> (&t)[12]) {
   switch (mu * 2 + (dir < 0)) {
-    case 0: wilson_hop_col<0, +1>(U, vk, s, nb, neg, chi, t); break;
-    case 1: wilson_hop_col<0, -1>(U, vk, s, nb, neg, chi, t); break;
-    case 2: wilson_hop_col<1, +1>(U, vk, s, nb, neg, chi, t); break;
-    case 3: wilson_hop_col<1, -1>(U, vk, s, nb, neg, chi, t); break;
-    case 4: wilson_hop_col<2, +1>(U, vk, s, nb, neg, chi, t); break;
-    case 5: wilson_hop_col<2, -1>(U, vk, s, nb, neg, chi, t); break;
-    case 6: wilson_hop_col<3, +1>(U, vk, s, nb, neg, chi, t); break;
-    default: wilson_hop_col<3, -1>(U, vk, s, nb, neg, chi, t); break;
+    case 0: wilson_hop_col<0, +1>(g, c, U, vk, neg, chi, t); break;
+    case 1: wilson_hop_col<0, -1>(g, c, U, vk, neg, chi, t); break;
+    case 2: wilson_hop_col<1, +1>(g, c, U, vk, neg, chi, t); break;
+    case 3: wilson_hop_col<1, -1>(g, c, U, vk, neg, chi, t); break;
+    case 4: wilson_hop_col<2, +1>(g, c, U, vk, neg, chi, t); break;
+    case 5: wilson_hop_col<2, -1>(g, c, U, vk, neg, chi, t); break;
+    case 6: wilson_hop_col<3, +1>(g, c, U, vk, neg, chi, t); break;
+    default: wilson_hop_col<3, -1>(g, c, U, vk, neg, chi, t); break;
   }
 }
 
@@ -130,7 +135,7 @@ struct WilsonSide {
   int tneg;     // antiperiodic time: links at t = Lt-1 carry the sign
   static constexpr int kDof = 12;
   // Element offset of dof e at site s in a field of this level.
-  __device__ __forceinline__ size_t off(size_t, int s, int e) const { return fidx(s, e, 12); }
+  __device__ __forceinline__ size_t off(size_t, int s, int e) const { return (size_t)s * 12 + e; }
   __device__ __forceinline__ bool neg(const Geom& g, const int c[4], int mu, int dir) const {
     return tneg && mu == 3 && c[3] == (dir > 0 ? g.L[3] - 1 : 0);
   }
@@ -148,22 +153,20 @@ struct WilsonSide {
       for (int e = 0; e < 12; ++e) t[e] = mk(0.0, 0.0);
       if (d < 8) {
         const int mu = d >> 1, dir = (d & 1) ? -1 : 1;
-        const int nb = dir > 0 ? nbr_fwd(a.g, s, c, mu) : nbr_bwd(a.g, s, c, mu);
-        wilson_hop_dispatch(mu, dir, U, vk, s, nb, neg(a.g, c, mu, dir), chi, t);
+        wilson_hop_dispatch(a.g, c, mu, dir, U, vk, neg(a.g, c, mu, dir), chi, t);
 #pragma unroll
         for (int e = 0; e < 12; ++e) t[e] = (-0.5) * t[e];
       } else {
         for (int mu = 0; mu < 4; ++mu) {
           for (int dir = 1; dir >= -1; dir -= 2) {
             if (!inside(a, c, mu, dir)) continue;
-            const int nb = dir > 0 ? nbr_fwd(a.g, s, c, mu) : nbr_bwd(a.g, s, c, mu);
-            wilson_hop_dispatch(mu, dir, U, vk, s, nb, neg(a.g, c, mu, dir), chi, t);
+            wilson_hop_dispatch(a.g, c, mu, dir, U, vk, neg(a.g, c, mu, dir), chi, t);
           }
         }
 #pragma unroll
         for (int e = 0; e < 12; ++e) {
           const bool on = (e / 6) == chi;
-          const cx<double> f = on ? vk[fidx(s, e, 12)] : mk(0.0, 0.0);
+          const cx<double> f = on ? vk[(size_t)s * 12 + e] : mk(0.0, 0.0);
           t[e] = mk(diag * f.re - 0.5 * t[e].re, diag * f.im - 0.5 * t[e].im);
         }
       }
@@ -236,7 +239,7 @@ __global__ __launch_bounds__(256) void k_coarse_build(Side side, AggGeom a, cons
       if (threadIdx.x < ncs) {
         int c[4];
         block_site(a, agg, d, i0 + threadIdx.x, c);
-        sites[threadIdx.x] = site_of(a.g, c[0], c[1], c[2], c[3]);
+        sites[threadIdx.x] = canon_site(a.g, c);
 #pragma unroll
         for (int mu = 0; mu < 4; ++mu) crd[threadIdx.x][mu] = c[mu];
       }

@@ -2,12 +2,12 @@
 //
 // * cx<R>: complex number, 8- or 16-byte aligned so a wavefront's loads of
 //   consecutive elements coalesce into full 64-lane transactions.
-// * Geom: lattice geometry of one multigrid level.  The fine level is stored
-//   tile-major: the lattice is cut into (Bx,By,Bz,Bt) tiles (the 4^4
+// * Geom: lattice geometry of one multigrid level.  Fields are stored in
+//   lexicographic site order (canon_site).  The links of the fine level are
+//   stored tile-major: the lattice is cut into (Bx,By,Bz,Bt) tiles (the 4^4
 //   aggregates of the multigrid, Sec. 3), tiles are numbered
-//   lexicographically and sites inside a tile lexicographically, so an
-//   aggregate's sites are one contiguous run of every field.  Coarse levels
-//   use B = 1 (plain lexicographic order).
+//   lexicographically and sites inside a tile lexicographically.  Coarse
+//   levels use B = 1 (both orders are the same).
 // * wave / block reductions with a fixed summation order (deterministic).
 #pragma once
 
@@ -80,7 +80,7 @@ struct Geom {
   int sl[4];   // stride of a local coordinate inside a tile
   int st[4];   // stride (in sites) of a tile coordinate
   int vol;     // sites
-  int vpad;    // sites rounded up to a multiple of 64 (fine-field blocks)
+  int vpad;    // sites rounded up to a multiple of 64 (link blocks)
   int tvol;    // sites per tile
   int ltvol;   // log2 tvol
 };
@@ -112,6 +112,20 @@ __host__ __device__ __forceinline__ void coords_of(const Geom& g, int s, int c[4
     const int lc = (loc >> (g.lb[0] * (mu > 0) + g.lb[1] * (mu > 1) + g.lb[2] * (mu > 2))) & (g.B[mu] - 1);
     c[mu] = (tc << g.lb[mu]) + lc;
   }
+}
+
+// Canonical (lexicographic, x fastest) index of coordinates c, and back: the
+// site order of every field.  The tile-major order above numbers the links.
+__host__ __device__ __forceinline__ int canon_site(const Geom& g, const int (&c)[4]) {
+  return c[0] + g.L[0] * (c[1] + g.L[1] * (c[2] + g.L[2] * c[3]));
+}
+__host__ __device__ __forceinline__ void canon_coords(const Geom& g, int i, int (&c)[4]) {
+#pragma unroll
+  for (int mu = 0; mu < 3; ++mu) {
+    c[mu] = i % g.L[mu];
+    i /= g.L[mu];
+  }
+  c[3] = i;
 }
 
 // Neighbour of site s (with coordinates c) one step forward / backward in mu,

@@ -7,11 +7,14 @@
 // back to four spins.  The antiperiodic time sign is folded into the stored
 // links U_t(x) at t = Lt-1, so it reaches both hop directions.
 //
-// Layout: fields in 64-site blocks, links as their first two rows (see
-// fine_field.h).  Three forms with the same result: one thread per (site,
-// right-hand side); one wave per direction; the latter with its registers
-// capped for a fourth wave per SIMD.  Workgroups are remapped so spatially
-// adjacent tiles share an XCD's L2.
+// Layout: fields in site order (a site's 12 numbers in one run), links as
+// their first two rows in tile-major blocks of 64 sites (see fine_field.h).
+// A thread that loaded its own neighbour would touch one memory line per lane
+// and load, so both kernels fetch spinors in 16-byte chunks with consecutive
+// lanes on consecutive chunks and hand every thread its site through LDS:
+//   k_wilson_gather  any lattice, every precision; one wave per direction
+//   k_wilson_tile    4^4 tiles, FP32 arithmetic; a tile and its faces in LDS,
+//                    links in registers over a batch of right-hand sides
 #include "half_field.h"
 #include "internal.h"
 #include "wilson_spin.h"
@@ -19,485 +22,72 @@
 namespace wdmg {
 namespace {
 
-constexpr int kDslashThreads = 128;
-
-// Field and link access of one precision.  FullIO: FP64 or FP32 fields and
-// links.  HalfIO: 16-bit fields with per-site scales and 16-bit links,
-// arithmetic in FP32.
+// ---- fields ---------------------------------------------------------------
+// Full<R>: FP64 or FP32 fields and links.  Half<H>: 16-bit fields with a scale
+// per site and 16-bit links, arithmetic in FP32.
 template <typename R>
-struct FullIO {
+struct Full {
   using T = R;
-  static constexpr bool kScaled = false;  // values are read as they are stored
-  const cx<R>* in;
-  cx<R>* out;
+  static constexpr bool kHalf = false;
+  static constexpr int NC = 12 * 2 * sizeof(R) / 16;  // stored chunks per site
+  const u4* in;
+  u4* out;
   const cx<R>* U;
-  __device__ __forceinline__ void select_rhs(int rhs, int vpad) {
-    in += (size_t)rhs * 12 * vpad;
-    out += (size_t)rhs * 12 * vpad;
-  }
-  __device__ __forceinline__ void spinor(int s, cx<R> (&p)[12]) const {
-#pragma unroll
-    for (int k = 0; k < 12; ++k) p[k] = in[fidx(s, k, 12)];
-  }
   __device__ __forceinline__ void link(int mu, int s, bool neg, cx<R> (&u)[9]) const { load_link(U, mu, s, neg, u); }
-  __device__ __forceinline__ void store(int s, const cx<R> (&v)[12]) const {
-#pragma unroll
-    for (int k = 0; k < 12; ++k) out[fidx(s, k, 12)] = v[k];
-  }
-  // right-hand side r of the selected chunk
-  __device__ __forceinline__ void spinor_r(int r, int vpad, int s, cx<R> (&p)[12]) const {
-    const cx<R>* b = in + (size_t)r * 12 * vpad;
-#pragma unroll
-    for (int k = 0; k < 12; ++k) p[k] = b[fidx(s, k, 12)];
-  }
-  __device__ __forceinline__ void store_r(int r, int vpad, int s, const cx<R> (&v)[12]) const {
-    cx<R>* b = out + (size_t)r * 12 * vpad;
-#pragma unroll
-    for (int k = 0; k < 12; ++k) b[fidx(s, k, 12)] = v[k];
-  }
 };
 
 template <typename H>
-struct HalfIO {
+struct Half {
   using T = float;
-  static constexpr bool kScaled = true;  // spinor_raw: stored values and the site scale apart
-  const cxh<H>* in;
+  static constexpr bool kHalf = true;
+  static constexpr int NC = 3;
+  const u4* in;
   const float* isc;
-  cxh<H>* out;
+  u4* out;
   float* osc;
   const cxh<H>* U;
-  __device__ __forceinline__ void select_rhs(int rhs, int vpad) {
-    in += (size_t)rhs * 12 * vpad;
-    out += (size_t)rhs * 12 * vpad;
-    isc += (size_t)rhs * vpad;
-    osc += (size_t)rhs * vpad;
-  }
-  __device__ __forceinline__ void spinor(int s, cx<float> (&p)[12]) const { load_site_h(in, isc, s, p); }
-  // the stored values of site s (in [-1, 1]) and the scale they are multiplied by
-  __device__ __forceinline__ void spinor_raw(int s, cx<float> (&p)[12], float& sc) const {
-    sc = isc[s];
-#pragma unroll
-    for (int k = 0; k < 12; ++k) p[k] = h2f(in[fidx(s, k, 12)]);
-  }
   __device__ __forceinline__ void link(int mu, int s, bool neg, cx<float> (&u)[9]) const {
     load_link_h(U, mu, s, neg, u);
   }
-  __device__ __forceinline__ void store(int s, const cx<float> (&v)[12]) const { store_site_h(out, osc, s, v); }
-  __device__ __forceinline__ void spinor_r(int r, int vpad, int s, cx<float> (&p)[12]) const {
-    load_site_h(in + (size_t)r * 12 * vpad, isc + (size_t)r * vpad, s, p);
-  }
-  __device__ __forceinline__ void spinor_r_raw(int r, int vpad, int s, cx<float> (&p)[12], float& sc) const {
-    const cxh<H>* b = in + (size_t)r * 12 * vpad;
-    sc = isc[(size_t)r * vpad + s];
-#pragma unroll
-    for (int k = 0; k < 12; ++k) p[k] = h2f(b[fidx(s, k, 12)]);
-  }
-  __device__ __forceinline__ void store_r(int r, int vpad, int s, const cx<float> (&v)[12]) const {
-    store_site_h(out + (size_t)r * 12 * vpad, osc + (size_t)r * vpad, s, v);
-  }
 };
 
-template <int MU, int SIGN, class IO, typename R = typename IO::T>
-__device__ __forceinline__ void hop(const IO& io, int nb, int link_site, bool neg, cx<R> (&acc)[12]) {
-  cx<R> p[12];
-  R sc = (R)1;
-  if constexpr (IO::kScaled)
-    io.spinor_raw(nb, p, sc);  // the scale is applied in the expansion
-  else
-    io.spinor(nb, p);
-  cx<R> h[6];
-  project<MU, SIGN>(p, h);
-  cx<R> u[9];
-  io.link(MU, link_site, neg, u);
-  cx<R> uh[6];
-#pragma unroll
-  for (int a = 0; a < 2; ++a) {
-#pragma unroll
-    for (int i = 0; i < 3; ++i) {
-      cx<R> s = mk<R>(0, 0);
-#pragma unroll
-      for (int b = 0; b < 3; ++b) {
-        if (SIGN > 0)
-          cmadd(s, u[i * 3 + b], h[a * 3 + b]);   // U h
-        else
-          cmaddc(s, u[b * 3 + i], h[a * 3 + b]);  // U^+ h
-      }
-      uh[a * 3 + i] = s;
-    }
-  }
-  if constexpr (IO::kScaled)
-    expand_add_scaled<MU, SIGN>(uh, sc, acc);
-  else
-    expand_add<MU, SIGN>(uh, acc);
-}
-
-// One thread per site; blockIdx.y = right-hand side.  Padding sites
-// (vol <= s < vpad) are written as zeros.
-// Workgroup order for a batch of nrhs fields over nsb site blocks: the hardware
-// sends workgroup b to XCD b % 8.  Each XCD takes a contiguous run of site
-// blocks (spatial neighbours share its L2) and sweeps it once per group of rg
-// right-hand sides, the rhs of a group back to back on each site block (its
-// links come from HBM once per group).  Small groups keep more site blocks in
-// flight (neighbour spinors stay in L2); large ones share links more.
-__device__ __forceinline__ void batch_block(int nsb, int nrhs, int rg, int& sb, int& rhs) {
-  const int b = blockIdx.x;
-  if ((nsb & 7) || nrhs == 1) {
-    if (nrhs == 1) {
-      sb = xcd_block();
-      rhs = 0;
-    } else {
-      sb = b % nsb;
-      rhs = b / nsb;
-    }
-    return;
-  }
-  const int xcd = b & 7, local = b >> 3, nsb8 = nsb >> 3;
-  if (rg < 1 || rg > nrhs) rg = nrhs;
-  const int g = local / (nsb8 * rg);
-  const int size = min(rg, nrhs - g * rg);
-  const int off = local - g * nsb8 * rg;
-  sb = xcd * nsb8 + off / size;
-  rhs = g * rg + off % size;
-}
-
-// Tile-column box order (forms 6-8) for lattices cut into 4^4 tiles: XCD k
-// takes box k of the xyz tile columns (the boxes of the t-marching form) and
-// walks it layer by layer, t outermost within an rhs group: the blocks of
-// one time layer of the box, then of the next, so the time neighbours of a
-// layer are the blocks its XCD handled just before and just after.  `n`
-// counts rhs (or rhs chunks of the register-blocked form) and rg the group.
-struct BoxOrder {
-  int on;
-  int ncol, nT0, nT1, Lt;
-  int box[3], nbox[3];
-};
-
-__device__ __forceinline__ void box_block(const BoxOrder& o, int n, int rg, int& sb, int& rhs) {
-  const int b = blockIdx.x;
-  const int xcd = b & 7, local = b >> 3;
-  const int bs = o.box[0] * o.box[1] * o.box[2];
-  if (rg < 1 || rg > n) rg = n;
-  const int per = o.Lt * bs;  // blocks of one rhs in the box
-  const int g = local / (per * rg);
-  const int size = min(rg, n - g * rg);
-  const int off = local - g * per * rg;
-  const int t = off / (bs * size);
-  const int rem = off % (bs * size);
-  const int in = rem / size;
-  rhs = g * rg + rem % size;
-  const int bx = xcd % o.nbox[0], by = (xcd / o.nbox[0]) % o.nbox[1], bz = xcd / (o.nbox[0] * o.nbox[1]);
-  const int tx = bx * o.box[0] + in % o.box[0];
-  const int ty = by * o.box[1] + (in / o.box[0]) % o.box[1];
-  const int tz = bz * o.box[2] + in / (o.box[0] * o.box[1]);
-  const int col = tx + o.nT0 * (ty + o.nT1 * tz);
-  sb = ((col + o.ncol * (t >> 2)) << 2) + (t & 3);
-}
-
-// MR step-size partial sums of one wave (Sec. 3 smoother): Re and Im of
-// <out, in> and |out|^2 over the wave's sites, where `in` is the operator's
-// input at the site itself (already loaded for the mass term).  Lanes of
-// sites outside the lattice pass live = false.  Lane 0 writes the three sums
-// to dots[(rhs * nparts + part) * 3 + k]; the fixed slot per wave keeps the
-// result independent of scheduling.
+// The numbers of stored chunk c of a site (16 bits: unscaled).
 template <typename R>
-__device__ __forceinline__ void wave_dots(bool live, const cx<R> (&out)[12], const cx<R> (&in)[12], double* dots,
-                                          size_t slot, R in_scale = (R)1) {
-  double d0 = 0.0, d1 = 0.0, d2 = 0.0;
-  if (live) {
+__device__ __forceinline__ void unpack_chunk(const Full<R>*, u4 q, int c, cx<R> (&p)[12]) {
+  ChunkOf<R> x;
+  x.q = q;
 #pragma unroll
-    for (int k = 0; k < 12; ++k) {
-      const double ore = out[k].re, oim = out[k].im, ire = in[k].re, iim = in[k].im;
-      d0 += ore * ire + oim * iim;
-      d1 += ore * iim - oim * ire;
-      d2 += ore * ore + oim * oim;
-    }
-    d0 *= (double)in_scale;  // in = in_scale x the values passed (16-bit storage)
-    d1 *= (double)in_scale;
-  }
-  d0 = wave_sum(d0);
-  d1 = wave_sum(d1);
-  d2 = wave_sum(d2);
-  if ((threadIdx.x & 63) == 0) {
-    dots[slot * 3 + 0] = d0;
-    dots[slot * 3 + 1] = d1;
-    dots[slot * 3 + 2] = d2;
-  }
+  for (int e = 0; e < ChunkOf<R>::N; ++e) p[c * ChunkOf<R>::N + e] = mk<R>(x.v[2 * e], x.v[2 * e + 1]);
+}
+template <typename H>
+__device__ __forceinline__ void unpack_chunk(const Half<H>*, u4 q, int c, cx<float> (&p)[12]) {
+  unpack_h<H>(q, c, p);
+}
+template <class S>
+__device__ __forceinline__ void unpack(u4 q, int c, cx<typename S::T> (&p)[12]) {
+  unpack_chunk(static_cast<const S*>(nullptr), q, c, p);
 }
 
-template <class IO, bool DOTS, typename R = typename IO::T>
-__global__ __launch_bounds__(kDslashThreads) void k_dslash(Geom g, IO io, R diag, int tneg, int nsb, int nrhs,
-                                                           int rg, double* dots) {
-  int sb, rhs;
-  batch_block(nsb, nrhs, rg, sb, rhs);
-  const int s = sb * kDslashThreads + threadIdx.x;
-  io.select_rhs(rhs, g.vpad);
-  cx<R> acc[12];
+// n complex numbers in 16 bits at v (4-byte aligned), unscaled; and stored.
+template <typename H, int N>
+__device__ __forceinline__ void load_numbers(const Half<H>*, const unsigned* v, float (&p)[N]) {
 #pragma unroll
-  for (int k = 0; k < 12; ++k) acc[k] = mk<R>(0, 0);
-  const bool live = s < g.vol;
-  cx<R> p[12];
-  R psc = (R)1;  // storage scale of p (16-bit fields read raw)
-  if (live) {
-    int c[4];
-    coords_of(g, s, c);
-    const bool tlast = tneg && c[3] == g.L[3] - 1, tfirst = tneg && c[3] == 0;
-    {
-      const int f = nbr_fwd(g, s, c, 0), b = nbr_bwd(g, s, c, 0);
-      hop<0, +1>(io, f, s, false, acc);
-      hop<0, -1>(io, b, b, false, acc);
-    }
-    {
-      const int f = nbr_fwd(g, s, c, 1), b = nbr_bwd(g, s, c, 1);
-      hop<1, +1>(io, f, s, false, acc);
-      hop<1, -1>(io, b, b, false, acc);
-    }
-    {
-      const int f = nbr_fwd(g, s, c, 2), b = nbr_bwd(g, s, c, 2);
-      hop<2, +1>(io, f, s, false, acc);
-      hop<2, -1>(io, b, b, false, acc);
-    }
-    {
-      const int f = nbr_fwd(g, s, c, 3), b = nbr_bwd(g, s, c, 3);
-      hop<3, +1>(io, f, s, tlast, acc);
-      hop<3, -1>(io, b, b, tfirst, acc);
-    }
-    const R half = (R)0.5;
-    if constexpr (IO::kScaled)
-      io.spinor_raw(s, p, psc);
-    else
-      io.spinor(s, p);
-    const R dg = diag * psc;
-#pragma unroll
-    for (int k = 0; k < 12; ++k) acc[k] = mk<R>(dg * p[k].re - half * acc[k].re, dg * p[k].im - half * acc[k].im);
-  }
-  if (s < g.vpad) io.store(s, acc);  // padding sites: zeros
-  if constexpr (DOTS)
-    wave_dots(live, acc, p, dots,
-              (size_t)rhs * nsb * (kDslashThreads / 64) + (size_t)sb * (kDslashThreads / 64) + (threadIdx.x >> 6),
-              psc);
-}
-
-// Direction-split form: a workgroup of four waves covers one 64-site block;
-// wave mu computes the two hops along mu (forward and backward) for the 64
-// sites, the partial sums meet in LDS, and wave 0 adds them in direction
-// order, applies the mass term and stores.  Four times as many waves as the
-// one-thread-per-site kernel, each with a quarter of the hops and of the
-// registers, so loads of many more sites are in flight.
-template <int MU, class IO, typename R>
-__device__ __forceinline__ void hops_mu(const IO& io, const Geom& g, int s, const int (&c)[4], bool tneg,
-                                        cx<R> (&acc)[12]) {
-  const bool last = MU == 3 && tneg && c[3] == g.L[3] - 1, first = MU == 3 && tneg && c[3] == 0;
-  const int f = nbr_fwd(g, s, c, MU), b = nbr_bwd(g, s, c, MU);
-  hop<MU, +1>(io, f, s, last, acc);
-  hop<MU, -1>(io, b, b, first, acc);
-}
-
-constexpr int kDs4Sites = 64;
-
-// MINW: the fewest waves per SIMD the register allocation must allow (1: no
-// limit).  FP64 needs 132 registers unconstrained (3 waves per SIMD); with
-// MINW = 4 it fits in 128 with one spilled register.
-template <class IO, bool DOTS, int MINW, typename R = typename IO::T>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MINW))) void k_dslash4(Geom g, IO io, R diag,
-                                                                                            int tneg, int nsb,
-                                                                                            int nrhs, int rg,
-                                                                                            double* dots,
-                                                                                            BoxOrder bo) {
-  __shared__ cx<R> part[3][12][kDs4Sites];
-  int sb, rhs;
-  if (bo.on)
-    box_block(bo, nrhs, rg, sb, rhs);
-  else
-    batch_block(nsb, nrhs, rg, sb, rhs);
-  const int lane = threadIdx.x & 63, mu = threadIdx.x >> 6;
-  const int s = sb * kDs4Sites + lane;
-  io.select_rhs(rhs, g.vpad);
-  cx<R> acc[12];
-#pragma unroll
-  for (int k = 0; k < 12; ++k) acc[k] = mk<R>(0, 0);
-  const bool live = s < g.vol;
-  if (live) {
-    int c[4];
-    coords_of(g, s, c);
-    switch (mu) {
-      case 0: hops_mu<0>(io, g, s, c, tneg, acc); break;
-      case 1: hops_mu<1>(io, g, s, c, tneg, acc); break;
-      case 2: hops_mu<2>(io, g, s, c, tneg, acc); break;
-      default: hops_mu<3>(io, g, s, c, tneg, acc); break;
-    }
-  }
-  if (mu > 0) {
-#pragma unroll
-    for (int k = 0; k < 12; ++k) part[mu - 1][k][lane] = acc[k];
-  }
-  __syncthreads();
-  // the grid covers vpad sites in whole 64-site blocks, so the test below is
-  // uniform over the wave
-  if (mu != 0 || s >= g.vpad) return;
-  cx<R> p[12];
-  R psc = (R)1;  // storage scale of p (16-bit fields read raw)
-  if (live) {
-#pragma unroll
-    for (int k = 0; k < 12; ++k) acc[k] = acc[k] + part[0][k][lane] + part[1][k][lane] + part[2][k][lane];
-    const R half = (R)0.5;
-    if constexpr (IO::kScaled)
-      io.spinor_raw(s, p, psc);
-    else
-      io.spinor(s, p);
-    const R dg = diag * psc;
-#pragma unroll
-    for (int k = 0; k < 12; ++k) acc[k] = mk<R>(dg * p[k].re - half * acc[k].re, dg * p[k].im - half * acc[k].im);
-  }
-  io.store(s, acc);  // padding sites: zeros
-  if constexpr (DOTS) wave_dots(live, acc, p, dots, (size_t)rhs * nsb + sb, psc);
-}
-
-// Register-blocked direction-split form for batches: the workgroup layout of
-// k_dslash4 (wave mu computes the two hops along mu for 64 sites) with RB
-// right-hand sides of one chunk per thread.  Each link is loaded (and its
-// third row rebuilt) once and applied to the RB neighbour spinors, so a batch
-// reads every link once per chunk instead of once per rhs, and each wave
-// keeps RB independent spinor loads in flight.  The partial sums of the four
-// directions meet in LDS one rhs at a time (two buffers, one barrier per rhs).
-// The batch size must be a multiple of RB; chunks are ordered like the rhs
-// of the other forms (batch_block with chunks in place of rhs).
-template <int MU, int SIGN, int RB, class IO, typename R = typename IO::T>
-__device__ __forceinline__ void hop_rb(const IO& io, int vpad, int nb, int link_site, bool neg,
-                                       cx<R> (&acc)[RB][12]) {
-  cx<R> u[9];
-  io.link(MU, link_site, neg, u);
-#pragma unroll
-  for (int r = 0; r < RB; ++r) {
-    cx<R> p[12];
-    R sc = (R)1;
-    if constexpr (IO::kScaled)
-      io.spinor_r_raw(r, vpad, nb, p, sc);
-    else
-      io.spinor_r(r, vpad, nb, p);
-    cx<R> h[6];
-    project<MU, SIGN>(p, h);
-    cx<R> uh[6];
-#pragma unroll
-    for (int a = 0; a < 2; ++a) {
-#pragma unroll
-      for (int i = 0; i < 3; ++i) {
-        cx<R> t = mk<R>(0, 0);
-#pragma unroll
-        for (int b = 0; b < 3; ++b) {
-          if (SIGN > 0)
-            cmadd(t, u[i * 3 + b], h[a * 3 + b]);   // U h
-          else
-            cmaddc(t, u[b * 3 + i], h[a * 3 + b]);  // U^+ h
-        }
-        uh[a * 3 + i] = t;
-      }
-    }
-    if constexpr (IO::kScaled)
-      expand_add_scaled<MU, SIGN>(uh, sc, acc[r]);
-    else
-      expand_add<MU, SIGN>(uh, acc[r]);
+  for (int k = 0; k < N / 2; ++k) {
+    const cx<float> z = h2f(__builtin_bit_cast(cxh<H>, v[k]));
+    p[2 * k] = z.re;
+    p[2 * k + 1] = z.im;
   }
 }
-
-template <int MU, int RB, class IO, typename R>
-__device__ __forceinline__ void hops_mu_rb(const IO& io, const Geom& g, int s, const int (&c)[4], bool tneg,
-                                           cx<R> (&acc)[RB][12]) {
-  const bool last = MU == 3 && tneg && c[3] == g.L[3] - 1, first = MU == 3 && tneg && c[3] == 0;
-  const int f = nbr_fwd(g, s, c, MU), b = nbr_bwd(g, s, c, MU);
-  hop_rb<MU, +1, RB>(io, g.vpad, f, s, last, acc);
-  hop_rb<MU, -1, RB>(io, g.vpad, b, b, first, acc);
+template <typename H, int N>
+__device__ __forceinline__ void store_numbers(const Half<H>*, unsigned* v, const float (&a)[N], float inv) {
+#pragma unroll
+  for (int k = 0; k < N / 2; ++k)
+    v[k] = __builtin_bit_cast(unsigned, quantise<H>(a[2 * k], a[2 * k + 1], inv));
 }
 
-template <class IO, bool DOTS, int RB, typename R = typename IO::T>
-__global__ __launch_bounds__(256) void k_dslash4_rb(Geom g, IO io, R diag, int tneg, int nsb, int nchunk, int rg,
-                                                    double* dots, BoxOrder bo) {
-  __shared__ cx<R> part[2][3][12][kDs4Sites];
-  int sb, ch;
-  if (bo.on)
-    box_block(bo, nchunk, rg, sb, ch);
-  else
-    batch_block(nsb, nchunk, rg, sb, ch);
-  const int lane = threadIdx.x & 63, mu = threadIdx.x >> 6;
-  const int s = sb * kDs4Sites + lane;
-  io.select_rhs(ch * RB, g.vpad);
-  cx<R> acc[RB][12];
-#pragma unroll
-  for (int r = 0; r < RB; ++r)
-#pragma unroll
-    for (int k = 0; k < 12; ++k) acc[r][k] = mk<R>(0, 0);
-  const bool live = s < g.vol;
-  if (live) {
-    int c[4];
-    coords_of(g, s, c);
-    switch (mu) {
-      case 0: hops_mu_rb<0, RB>(io, g, s, c, tneg, acc); break;
-      case 1: hops_mu_rb<1, RB>(io, g, s, c, tneg, acc); break;
-      case 2: hops_mu_rb<2, RB>(io, g, s, c, tneg, acc); break;
-      default: hops_mu_rb<3, RB>(io, g, s, c, tneg, acc); break;
-    }
-  }
-  const R half = (R)0.5;
-  // the grid covers vpad sites in whole 64-site blocks: every lane's site is
-  // below vpad, and the barrier below is reached by all four waves
-#pragma unroll
-  for (int r = 0; r < RB; ++r) {
-    if (mu > 0) {
-#pragma unroll
-      for (int k = 0; k < 12; ++k) part[r & 1][mu - 1][k][lane] = acc[r][k];
-    }
-    __syncthreads();
-    if (mu == 0) {
-      cx<R> p[12];
-      R psc = (R)1;  // storage scale of p (16-bit fields read raw)
-      if (live) {
-#pragma unroll
-        for (int k = 0; k < 12; ++k)
-          acc[r][k] = acc[r][k] + part[r & 1][0][k][lane] + part[r & 1][1][k][lane] + part[r & 1][2][k][lane];
-        if constexpr (IO::kScaled)
-          io.spinor_r_raw(r, g.vpad, s, p, psc);
-        else
-          io.spinor_r(r, g.vpad, s, p);
-        const R dg = diag * psc;
-#pragma unroll
-        for (int k = 0; k < 12; ++k)
-          acc[r][k] = mk<R>(dg * p[k].re - half * acc[r][k].re, dg * p[k].im - half * acc[r][k].im);
-      }
-      io.store_r(r, g.vpad, s, acc[r]);  // padding sites: zeros
-      if constexpr (DOTS) wave_dots(live, acc[r], p, dots, (size_t)(ch * RB + r) * nsb + sb, psc);
-    }
-  }
-}
-
-// t-marching form for lattices cut into 4^4 tiles: one wave per (xyz tile
-// column, chunk of T time layers, rhs); lane = x + 4y + 16z of the 4x4x4 block
-// of one layer (the field layout's 64-site block).  The wave walks its chunk
-// layer by layer, so every spinor of the column is loaded once: psi(t+1) is
-// loaded as the forward time neighbour and becomes the centre of the next
-// step, and the backward time hop U_t(x-t)^+ (1+gamma_t) psi(x-t) is formed
-// one step earlier from the centre and its own link.  Inside the block the
-// x, y, z hops exchange half spinors between lanes (each lane sends
-// (1-gamma_mu) psi to x-mu and U_mu^+ (1+gamma_mu) psi to x+mu, both from its
-// own spinor and link); lanes on a tile face load the neighbouring tile's
-// spinor (and link) instead.  Work items are grouped per XCD in boxes of
-// adjacent tile columns, so neighbouring columns share an L2 while they walk
-// the same layers (form 5), or per XCD in time slabs (form 9): XCD k takes
-// every tile column of the k-th eighth of the time extent, so no x, y or z
-// face of a column lies on another XCD and only the two slab ends read time
-// neighbours from another XCD's layers; inside the slab the XCD runs the
-// columns of a group of G right-hand sides back to back, rhs fastest, so the
-// G waves of one column share its links in L2.
-struct TmMap {
-  int ncol;           // xyz tile columns
-  int nch, T;         // chunks of T layers per column
-  int nrhs;
-  int box[3];         // tile columns per XCD box (0: no XCD boxes)
-  int nbox[3];        // boxes per direction (product 8)
-  int slab;           // 1: time slabs per XCD (nch a multiple of 8)
-  int G;              // rhs group of the slab order (divides nrhs)
-};
-
+// U h (SIGN > 0) or U^+ h of the two colour vectors of a half spinor.
 template <int SIGN, typename R>
-__device__ __forceinline__ void link_mul(const cx<R> (&u)[9], const cx<R> (&h)[6], cx<R> (&uh)[6]) {
+__device__ __forceinline__ void link_half(const cx<R> (&u)[9], const cx<R> (&h)[6], cx<R> (&uh)[6]) {
 #pragma unroll
   for (int a = 0; a < 2; ++a) {
 #pragma unroll
@@ -506,438 +96,788 @@ __device__ __forceinline__ void link_mul(const cx<R> (&u)[9], const cx<R> (&h)[6
 #pragma unroll
       for (int b = 0; b < 3; ++b) {
         if (SIGN > 0)
-          cmadd(t, u[i * 3 + b], h[a * 3 + b]);   // U h
+          cmadd(t, u[i * 3 + b], h[a * 3 + b]);
         else
-          cmaddc(t, u[b * 3 + i], h[a * 3 + b]);  // U^+ h
+          cmaddc(t, u[b * 3 + i], h[a * 3 + b]);
       }
       uh[a * 3 + i] = t;
     }
   }
 }
 
+template <int MU, int SIGN, typename R>
+__device__ __forceinline__ void hop_add(const cx<R> (&u)[9], const cx<R> (&p)[12], cx<R> (&acc)[12]) {
+  cx<R> h[6], uh[6];
+  project<MU, SIGN>(p, h);
+  link_half<SIGN>(u, h, uh);
+  expand_add<MU, SIGN>(uh, acc);
+}
+
+template <int MU, int SIGN>
+__device__ __forceinline__ void hop_add_scaled(const cx<float> (&u)[9], const cx<float> (&p)[12], float sc,
+                                               cx<float> (&acc)[12]) {
+  cx<float> h[6], uh[6];
+  project<MU, SIGN>(p, h);
+  link_half<SIGN>(u, h, uh);
+  expand_add_scaled<MU, SIGN>(uh, sc, acc);
+}
+
+typedef __attribute__((address_space(1))) const void glb_t;
+typedef __attribute__((address_space(3))) void lds_t;
+
+// 16 bytes per lane straight into LDS at dst + 16 lane (dst uniform over the wave).
+__device__ __forceinline__ void load_to_lds(const void* src, void* dst) {
+  __builtin_amdgcn_global_load_lds((glb_t*)src, (lds_t*)dst, 16, 0, 0);
+}
+// vmcnt(0): this wave's loads have landed (LDS ones included)
+__device__ __forceinline__ void wait_loads() {
+  __builtin_amdgcn_s_waitcnt(0x0f70);
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+// lgkmcnt(0): this wave's LDS reads have returned
+__device__ __forceinline__ void wait_lds() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_s_waitcnt(0xc07f);
+  __builtin_amdgcn_wave_barrier();
+}
+
+// MR step-size sums of one thread (Sec. 3 smoother): Re and Im of <out, in>
+// and |out|^2 over n numbers of the operator's result and input.
 template <typename R>
-__device__ __forceinline__ void shfl6(const cx<R> (&in)[6], cx<R> (&out)[6], int src) {
+__device__ __forceinline__ void mr_dots(const R* o, const R* i, int n, double (&d)[3]) {
 #pragma unroll
-  for (int k = 0; k < 6; ++k) out[k] = mk<R>(__shfl(in[k].re, src, 64), __shfl(in[k].im, src, 64));
-}
-
-// The x, y or z hops of one site with lane-exchanged half spinors.
-template <int MU, class IO, typename R = typename IO::T>
-__device__ __forceinline__ void tm_space_hops(const IO& io, const Geom& g, int s, const int (&c)[4], int lane,
-                                              const cx<R> (&psi)[12], cx<R> (&acc)[12]) {
-  constexpr int SL = MU == 0 ? 1 : (MU == 1 ? 4 : 16);
-  const int lc = (lane / SL) & 3;
-  cx<R> u[9];
-  io.link(MU, s, false, u);
-  // messages of this lane: (1-gamma) psi for x-mu, U^+ (1+gamma) psi for x+mu
-  cx<R> mf[6], mb[6], t6[6];
-  project<MU, +1>(psi, mf);
-  project<MU, -1>(psi, t6);
-  link_mul<-1>(u, t6, mb);
-  // forward hop: (1-gamma) psi(x+mu) from lane + SL, or from the next tile
-  cx<R> h[6];
-  shfl6(mf, h, lane + SL);
-  if (lc == 3) {
-    cx<R> p[12];
-    io.spinor(nbr_fwd(g, s, c, MU), p);
-    project<MU, +1>(p, h);
-  }
-  cx<R> uh[6];
-  link_mul<+1>(u, h, uh);
-  expand_add<MU, +1>(uh, acc);
-  // backward hop: U^+(x-mu) (1+gamma) psi(x-mu) from lane - SL, or computed
-  // here from the previous tile's spinor and link
-  shfl6(mb, uh, lane - SL);
-  if (lc == 0) {
-    const int b = nbr_bwd(g, s, c, MU);
-    cx<R> p[12], ub[9];
-    io.spinor(b, p);
-    io.link(MU, b, false, ub);
-    project<MU, -1>(p, t6);
-    link_mul<-1>(ub, t6, uh);
-  }
-  expand_add<MU, -1>(uh, acc);
-}
-
-__device__ __forceinline__ void tm_work(const TmMap& m, int w, int& col, int& ch, int& rhs, const Geom& g) {
-  int tx, ty, tz, local;
-  if (m.slab) {
-    const int xcd = w & 7;
-    local = w >> 3;
-    const int rin = local % m.G;
-    int rest = local / m.G;
-    col = rest % m.ncol;
-    rest /= m.ncol;
-    const int ngrp = m.nrhs / m.G;
-    rhs = (rest % ngrp) * m.G + rin;
-    ch = xcd * (m.nch >> 3) + rest / ngrp;
-  } else if (m.box[0]) {
-    const int xcd = w & 7;
-    local = w >> 3;
-    const int bs = m.box[0] * m.box[1] * m.box[2];
-    const int in = local % bs;
-    const int rest = local / bs;
-    rhs = rest % m.nrhs;
-    ch = rest / m.nrhs;
-    const int bx = xcd % m.nbox[0], by = (xcd / m.nbox[0]) % m.nbox[1], bz = xcd / (m.nbox[0] * m.nbox[1]);
-    tx = bx * m.box[0] + in % m.box[0];
-    ty = by * m.box[1] + (in / m.box[0]) % m.box[1];
-    tz = bz * m.box[2] + in / (m.box[0] * m.box[1]);
-    col = tx + g.nT[0] * (ty + g.nT[1] * tz);
-  } else {
-    col = w % m.ncol;
-    const int rest = w / m.ncol;
-    rhs = rest % m.nrhs;
-    ch = rest / m.nrhs;
+  for (int k = 0; k < n; k += 2) {
+    const double ore = o[k], oim = o[k + 1], ire = i[k], iim = i[k + 1];
+    d[0] += ore * ire + oim * iim;
+    d[1] += ore * iim - oim * ire;
+    d[2] += ore * ore + oim * oim;
   }
 }
 
-template <class IO, bool DOTS, typename R = typename IO::T>
-__global__ __launch_bounds__(64) void k_dslash_tm(Geom g, IO io, R diag, int tneg, TmMap m, double* dots) {
-  int col, ch, rhs;
-  tm_work(m, blockIdx.x, col, ch, rhs, g);
-  io.select_rhs(rhs, g.vpad);
-  const int lane = threadIdx.x;
-  const int ncol = m.ncol, Lt = g.L[3];
-  auto site_at = [&](int t) { return ((col + ncol * (t >> 2)) << 8) + ((t & 3) << 6) + lane; };
-  const int t0 = ch * m.T;
-  int c[4];
-  coords_of(g, site_at(t0), c);
-  // backward time hop of the first layer, from layer t0 - 1
-  cx<R> bt[6];
-  {
-    const int tp = t0 == 0 ? Lt - 1 : t0 - 1;
-    const int sp = site_at(tp);
-    cx<R> p[12], u[9], h[6];
-    io.spinor(sp, p);
-    io.link(3, sp, tneg && tp == Lt - 1, u);
-    project<3, -1>(p, h);
-    link_mul<-1>(u, h, bt);
+// ---- any lattice: one wave per direction ------------------------------------
+// A workgroup of four waves covers one block of 64 sites of the link layout;
+// wave mu takes the two hops along mu.  Lane l of load i fetches position
+// (64 i + l) of the wave's buffer of 64 rows, whose site index comes from the
+// lane that owns the row; rows of 6 (12) chunks would put rows four (two)
+// apart on the same banks, so a row's chunks are exchanged by swz (rows of 3
+// chunks spread by themselves).  The backward neighbours are on their way
+// while the forward hop is worked on.  The four directions meet in the same
+// buffers, where all 256 threads sum and store.
+//
+// FP32 and 16 bits keep the links and offsets of the wave in registers over a
+// group of right-hand sides; FP64 has no registers for that and takes one per
+// workgroup.  Measured (with the layout conversions it makes unnecessary, in
+// brackets with them before): 32^4 FP64 1 rhs 228 us (398), 12x20x10x18 FP32
+// 5 rhs 22 us (53), 32^4 FP32 1 rhs 120 us (210).
+template <typename R>
+__device__ __forceinline__ int swz(int j) {
+  return sizeof(R) == 4 ? (j >> 2) & 1 : (j >> 1) & 3;
+}
+template <class S>
+__device__ __forceinline__ int row_pos(int j, int c) {  // position of stored chunk c of row j
+  return j * S::NC + (S::kHalf ? c : (c ^ swz<typename S::T>(j)));
+}
+
+template <class S>
+__device__ __forceinline__ void gather_offsets(int nb, int lane, unsigned (&off)[S::NC]) {
+#pragma unroll
+  for (int i = 0; i < S::NC; ++i) {
+    const int e = i * 64 + lane, j = e / S::NC, c = e % S::NC;
+    off[i] = (unsigned)(__shfl(nb, j, 64) * S::NC + (S::kHalf ? c : (c ^ swz<typename S::T>(j))));
   }
-  cx<R> psi[12];
-  io.spinor(site_at(t0), psi);
-  const R half = (R)0.5;
-  for (int t = t0; t < t0 + m.T; ++t) {
-    const int s = site_at(t);
-    c[3] = t;
-    const int tn = t == Lt - 1 ? 0 : t + 1;
-    cx<R> nxt[12];
-    io.spinor(site_at(tn), nxt);
-    cx<R> acc[12];
+}
+
+template <class S>
+__device__ __forceinline__ void fetch_sites(const u4* f, const unsigned (&off)[S::NC], u4* buf) {
+#pragma unroll
+  for (int i = 0; i < S::NC; ++i) load_to_lds(f + off[i], buf + i * 64);
+}
+
+template <class S>
+__device__ __forceinline__ void read_row(const u4* buf, int lane, cx<typename S::T> (&p)[12]) {
+#pragma unroll
+  for (int c = 0; c < S::NC; ++c) unpack<S>(buf[row_pos<S>(lane, c)], c, p);
+}
+
+template <int MU, int SIGN>
+__device__ __forceinline__ void read_half_f64(const u4* buf, int lane, cx<double> (&h)[6]) {
+  // one colour at a time, so that four numbers of the row, not twelve, are held
+  const cx<double>* row = reinterpret_cast<const cx<double>*>(buf) + lane * 12;
+  const int sw = swz<double>(lane);
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    cx<double> p[12];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) p[3 * k + c] = row[(3 * k + c) ^ sw];
+    project_colour<MU, SIGN>(p, c, h);
+  }
+}
+
+// acc as the row of this lane in working precision (rows of Full<R>)
+template <typename R>
+__device__ __forceinline__ void write_row(u4* buf, int lane, const cx<R> (&acc)[12]) {
+#pragma unroll
+  for (int c = 0; c < Full<R>::NC; ++c) buf[row_pos<Full<R>>(lane, c)] = chunk_of<R>(acc, c);
+}
+
+template <int MU>
+__device__ __forceinline__ int stride_of(const Geom& g) {
+  return MU == 0 ? 1 : (MU == 1 ? g.L[0] : (MU == 2 ? g.L[0] * g.L[1] : g.L[0] * g.L[1] * g.L[2]));
+}
+template <int MU>
+__device__ __forceinline__ int canon_fwd(const Geom& g, const int (&c)[4], int me) {
+  return c[MU] == g.L[MU] - 1 ? me - (g.L[MU] - 1) * stride_of<MU>(g) : me + stride_of<MU>(g);
+}
+template <int MU>
+__device__ __forceinline__ int canon_bwd(const Geom& g, const int (&c)[4], int me) {
+  return c[MU] == 0 ? me + (g.L[MU] - 1) * stride_of<MU>(g) : me - stride_of<MU>(g);
+}
+
+template <int MU, class S, class Finish>
+__device__ __forceinline__ void gather_wave(const Geom& g, const S& io, int tneg, int s, const int (&c)[4], int me,
+                                            int r0, int r1, u4* buf, Finish finish) {
+  using R = typename S::T;
+  const int lane = threadIdx.x & 63;
+  const size_t fs = (size_t)g.vol * S::NC;
+  const bool last = MU == 3 && tneg && c[3] == g.L[3] - 1, first = MU == 3 && tneg && c[3] == 0;
+  const int nf = canon_fwd<MU>(g, c, me), nb = canon_bwd<MU>(g, c, me);
+  if constexpr (sizeof(R) == 8) {
+    const u4* f = io.in + r0 * fs;
+    cx<R> h[6], uh[6], u[9], acc[12];
+    {
+      unsigned off[S::NC];
+      gather_offsets<S>(nf, lane, off);
+      fetch_sites<S>(f, off, buf);
+    }
+    io.link(MU, s, last, u);
+    wait_loads();
+    read_half_f64<MU, +1>(buf, lane, h);
+    wait_lds();
+    __builtin_amdgcn_sched_barrier(0);
+    {
+      unsigned off[S::NC];
+      gather_offsets<S>(nb, lane, off);
+      fetch_sites<S>(f, off, buf);
+    }
+    link_half<+1>(u, h, uh);
 #pragma unroll
     for (int k = 0; k < 12; ++k) acc[k] = mk<R>(0, 0);
-    tm_space_hops<0>(io, g, s, c, lane, psi, acc);
-    tm_space_hops<1>(io, g, s, c, lane, psi, acc);
-    tm_space_hops<2>(io, g, s, c, lane, psi, acc);
-    {
-      cx<R> u[9], h[6], uh[6];
-      const bool neg = tneg && t == Lt - 1;
-      io.link(3, s, neg, u);
-      project<3, +1>(nxt, h);  // forward time hop
-      link_mul<+1>(u, h, uh);
-      expand_add<3, +1>(uh, acc);
-      expand_add<3, -1>(bt, acc);  // backward time hop
-      project<3, -1>(psi, h);      // the next layer's backward hop
-      link_mul<-1>(u, h, bt);
-    }
-#pragma unroll
-    for (int k = 0; k < 12; ++k) acc[k] = mk<R>(diag * psi[k].re - half * acc[k].re, diag * psi[k].im - half * acc[k].im);
-    io.store(s, acc);
-    if constexpr (DOTS) wave_dots(true, acc, psi, dots, (size_t)rhs * (g.vpad / 64) + (s >> 6));
-#pragma unroll
-    for (int k = 0; k < 12; ++k) psi[k] = nxt[k];
-  }
-}
-
-// Work map of the t-marching form: tile columns split into 8 boxes when the
-// tile counts allow (one box per XCD), chunks of T layers.
-inline TmMap tm_map(const Geom& g, int nrhs, int T) {
-  TmMap m{};
-  m.ncol = g.nT[0] * g.nT[1] * g.nT[2];
-  m.T = T;
-  m.nch = g.L[3] / T;
-  m.nrhs = nrhs;
-  const int nb[3][3] = {{2, 2, 2}, {1, 2, 4}, {1, 1, 8}};
-  for (auto& split : nb) {
-    // try the split and its permutations along x, y, z
-    const int perm[6][3] = {{0, 1, 2}, {0, 2, 1}, {1, 0, 2}, {1, 2, 0}, {2, 0, 1}, {2, 1, 0}};
-    for (auto& pm : perm) {
-      bool ok = true;
-      for (int d = 0; d < 3; ++d) ok = ok && g.nT[d] % split[pm[d]] == 0;
-      if (!ok) continue;
-      for (int d = 0; d < 3; ++d) {
-        m.nbox[d] = split[pm[d]];
-        m.box[d] = g.nT[d] / split[pm[d]];
-      }
-      return m;
-    }
-  }
-  return m;
-}
-
-// Time-slab map (form 9): chunks of T layers, T the largest divisor of Lt / 8
-// up to 8, so every XCD walks the same number of whole chunks; G = rg when it
-// divides the batch, else 1.
-inline TmMap tm_slab_map(const Geom& g, int nrhs, int rg) {
-  TmMap m{};
-  m.ncol = g.nT[0] * g.nT[1] * g.nT[2];
-  const int nl = g.L[3] / 8;
-  m.T = 1;
-  for (int T = 1; T <= 8 && T <= nl; ++T)
-    if (nl % T == 0) m.T = T;
-  m.nch = g.L[3] / m.T;
-  m.nrhs = nrhs;
-  m.slab = 1;
-  m.G = (rg >= 1 && nrhs % rg == 0) ? rg : 1;
-  return m;
-}
-
-// Layers per chunk of the t-marching form: the rhs-group tuning value when it
-// is 4, 8 or 16 and divides Lt, else 8 (or 4).
-inline int tm_chunk(const Geom& g, int rg) {
-  for (int T : {rg, 8, 4})
-    if ((T == 4 || T == 8 || T == 16) && g.L[3] % T == 0) return T;
-  return 4;
-}
-
-// Slots of MR partial sums per right-hand side written by a fused launch.
-int dslash_parts(const Geom& g, int variant) {
-  if (variant != 0) return g.vpad / kDs4Sites;  // forms 1-5: one slot per 64-site block
-  return (g.vpad / kDslashThreads + (g.vpad % kDslashThreads != 0)) * (kDslashThreads / 64);
-}
-
-// Right-hand sides per thread of a form (forms 3 and 4 are register-blocked).
-constexpr int rb_of(int variant) { return (variant == 3 || variant == 8) ? 2 : (variant == 4 ? 4 : 1); }
-
-inline BoxOrder box_order(const Geom& g) {
-  const TmMap m = tm_map(g, 1, 4);
-  BoxOrder o{};
-  o.on = m.box[0] != 0;
-  o.ncol = m.ncol;
-  o.nT0 = g.nT[0];
-  o.nT1 = g.nT[1];
-  o.Lt = g.L[3];
-  for (int d = 0; d < 3; ++d) {
-    o.box[d] = m.box[d];
-    o.nbox[d] = m.nbox[d];
-  }
-  return o;
-}
-
-// Forms 3, 4 and 8 need a batch they divide; forms 5-9 need 4^4 tiles, 6-8
-// tile columns that split into one box per XCD, and 9 a time extent that
-// splits into 8 slabs.
-inline bool form_fits(const Geom& g, int v, int nrhs) {
-  const bool tiles = g.B[0] == 4 && g.B[1] == 4 && g.B[2] == 4 && g.B[3] == 4;
-  if (v >= 5 && !tiles) return false;
-  if (v == 9) return g.L[3] % 8 == 0;
-  if (v >= 6 && !box_order(g).on) return false;
-  return nrhs % rb_of(v) == 0;
-}
-
-template <class IO>
-void run_dslash(Ctx& c, const IO& io, int nrhs, int variant, int rg, double* dots = nullptr) {
-  const Geom& g = c.g0;
-  const int tneg = c.t_bc < 0 ? 1 : 0;
-  using R = typename IO::T;
-  const R diag = (R)(4.0 + c.mass);
-  BoxOrder bo{};
-  if (variant >= 6) bo = box_order(g);  // forms 6-8: forms 1, 2, 3 in tile-column box order
-  const int base = variant == 6 ? 1 : (variant == 7 ? 2 : (variant == 8 ? 3 : variant));
-  if (base == 1 || base == 2) {
-    const unsigned gx = g.vpad / kDs4Sites;
-    const dim3 grid(gx * nrhs), block(256);
-    if (base == 1) {
-      if (dots)
-        hipLaunchKernelGGL((k_dslash4<IO, true, 1>), grid, block, 0, c.stream, g, io, diag, tneg, (int)gx, nrhs, rg,
-                           dots, bo);
-      else
-        hipLaunchKernelGGL((k_dslash4<IO, false, 1>), grid, block, 0, c.stream, g, io, diag, tneg, (int)gx, nrhs, rg,
-                           dots, bo);
-    } else {
-      if (dots)
-        hipLaunchKernelGGL((k_dslash4<IO, true, 4>), grid, block, 0, c.stream, g, io, diag, tneg, (int)gx, nrhs, rg,
-                           dots, bo);
-      else
-        hipLaunchKernelGGL((k_dslash4<IO, false, 4>), grid, block, 0, c.stream, g, io, diag, tneg, (int)gx, nrhs, rg,
-                           dots, bo);
-    }
-  } else if (base == 5 || base == 9) {
-    const TmMap m = base == 5 ? tm_map(g, nrhs, tm_chunk(g, rg)) : tm_slab_map(g, nrhs, rg);
-    const dim3 grid((unsigned)(m.ncol * m.nch * nrhs));
-    if (dots)
-      hipLaunchKernelGGL((k_dslash_tm<IO, true>), grid, dim3(64), 0, c.stream, g, io, diag, tneg, m, dots);
-    else
-      hipLaunchKernelGGL((k_dslash_tm<IO, false>), grid, dim3(64), 0, c.stream, g, io, diag, tneg, m, dots);
-  } else if (base == 3 || base == 4) {
-    const unsigned gx = g.vpad / kDs4Sites;
-    if (base == 3) {
-      const int nch = nrhs / 2, rgc = rg >= 2 ? rg / 2 : 1;
-      if (dots)
-        hipLaunchKernelGGL((k_dslash4_rb<IO, true, 2>), dim3(gx * nch), dim3(256), 0, c.stream, g, io, diag, tneg,
-                           (int)gx, nch, rgc, dots, bo);
-      else
-        hipLaunchKernelGGL((k_dslash4_rb<IO, false, 2>), dim3(gx * nch), dim3(256), 0, c.stream, g, io, diag, tneg,
-                           (int)gx, nch, rgc, dots, bo);
-    } else {
-      const int nch = nrhs / 4, rgc = rg >= 4 ? rg / 4 : 1;
-      if (dots)
-        hipLaunchKernelGGL((k_dslash4_rb<IO, true, 4>), dim3(gx * nch), dim3(256), 0, c.stream, g, io, diag, tneg,
-                           (int)gx, nch, rgc, dots, bo);
-      else
-        hipLaunchKernelGGL((k_dslash4_rb<IO, false, 4>), dim3(gx * nch), dim3(256), 0, c.stream, g, io, diag, tneg,
-                           (int)gx, nch, rgc, dots, bo);
-    }
+    expand_add<MU, +1>(uh, acc);
+    __builtin_amdgcn_sched_barrier(0);
+    io.link(MU, nbr_bwd(g, s, c, MU), first, u);
+    wait_loads();
+    read_half_f64<MU, -1>(buf, lane, h);
+    link_half<-1>(u, h, uh);
+    expand_add<MU, -1>(uh, acc);
+    write_row<R>(buf, lane, acc);
+    finish(r0);
   } else {
-    const unsigned gx = g.vpad / kDslashThreads + (g.vpad % kDslashThreads != 0);
-    if (dots)
-      hipLaunchKernelGGL((k_dslash<IO, true>), dim3(gx * nrhs), dim3(kDslashThreads), 0, c.stream, g, io, diag, tneg,
-                         (int)gx, nrhs, rg, dots);
-    else
-      hipLaunchKernelGGL((k_dslash<IO, false>), dim3(gx * nrhs), dim3(kDslashThreads), 0, c.stream, g, io, diag, tneg,
-                         (int)gx, nrhs, rg, dots);
+    unsigned of[S::NC], ob[S::NC];
+    gather_offsets<S>(nf, lane, of);
+    gather_offsets<S>(nb, lane, ob);
+    fetch_sites<S>(io.in + r0 * fs, of, buf);
+    cx<R> uf[9], ub[9];
+    io.link(MU, s, last, uf);
+    io.link(MU, nbr_bwd(g, s, c, MU), first, ub);
+    for (int r = r0; r < r1; ++r) {
+      const u4* f = io.in + r * fs;
+      if (r > r0) fetch_sites<S>(f, of, buf);
+      float sf = 1.0f, sb = 1.0f;
+      if constexpr (S::kHalf) {
+        sf = io.isc[(size_t)r * g.vol + nf];
+        sb = io.isc[(size_t)r * g.vol + nb];
+      }
+      cx<R> p[12], acc[12];
+      wait_loads();
+      read_row<S>(buf, lane, p);
+      wait_lds();
+      __builtin_amdgcn_sched_barrier(0);
+      fetch_sites<S>(f, ob, buf);
+#pragma unroll
+      for (int k = 0; k < 12; ++k) acc[k] = mk<R>(0, 0);
+      if constexpr (S::kHalf)
+        hop_add_scaled<MU, +1>(uf, p, sf, acc);
+      else
+        hop_add<MU, +1>(uf, p, acc);
+      __builtin_amdgcn_sched_barrier(0);
+      wait_loads();
+      read_row<S>(buf, lane, p);
+      if constexpr (S::kHalf) {
+        hop_add_scaled<MU, -1>(ub, p, sb, acc);
+        wait_lds();  // the row of sums is longer than the stored row it replaces
+      } else {
+        hop_add<MU, -1>(ub, p, acc);
+      }
+      write_row<R>(buf, lane, acc);
+      finish(r);
+    }
   }
-  WDMG_HIP(hipGetLastError());
 }
 
-// Autotuner: times the forms (HIP events, 3 launches each after one warm-up
-// launch) on the caller's buffers -- the operator has no side effects besides
-// writing `out` -- and returns the fastest (form 1 on ties).  The
-// register-blocked forms 3 and 4 take part when the batch is a multiple of
-// their 2 or 4 rhs per thread.
-constexpr int kDslashForms = 10;
-
-template <class IO>
-float time_dslash(Ctx& c, const IO& io, int nrhs, int v, int rg, hipEvent_t (&ev)[2], int reps = 3) {
-  run_dslash(c, io, nrhs, v, rg);
-  WDMG_HIP(hipEventRecord(ev[0], c.stream));
-  for (int i = 0; i < reps; ++i) run_dslash(c, io, nrhs, v, rg);
-  WDMG_HIP(hipEventRecord(ev[1], c.stream));
-  WDMG_HIP(hipEventSynchronize(ev[1]));
-  float ms = 0.f;
-  WDMG_HIP(hipEventElapsedTime(&ms, ev[0], ev[1]));
-  return ms / reps;
+template <class S, bool DOTS, typename R = typename S::T>
+__global__ __launch_bounds__(256) void k_wilson_gather(Geom g, S io, R diag, int tneg, int nsb, int nrhs, int nper,
+                                                       double* dots) {
+  constexpr int NW = Full<R>::NC, N = ChunkOf<R>::N;  // chunks of a working-precision row, numbers in one
+  __shared__ u4 buf[4][64 * NW];
+  __shared__ double red[2][4][3];
+  // blocks of one rhs group in XCD-contiguous order (workgroup b runs on XCD
+  // b % 8), the groups of a block back to back
+  const int ngrp = (nrhs + nper - 1) / nper;
+  int sb, grp;
+  {
+    const int b = blockIdx.x;
+    if (nsb & 7) {
+      sb = b / ngrp;
+      grp = b % ngrp;
+    } else {
+      const int local = b >> 3;
+      sb = (b & 7) * (nsb >> 3) + local / ngrp;
+      grp = local % ngrp;
+    }
+  }
+  const int r0 = grp * nper, r1 = min(nrhs, r0 + nper);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int s = sb * 64 + lane < g.vol ? sb * 64 + lane : 0;
+  int c[4];
+  coords_of(g, s, c);
+  const int me = canon_site(g, c);
+  const size_t fs = (size_t)g.vol * S::NC;
+  auto flush = [&](int r) {  // the four waves' sums of right-hand side r, written before the last barrier
+    if (threadIdx.x < 3) {
+      double t = 0.0;
+#pragma unroll
+      for (int w = 0; w < 4; ++w) t += red[r & 1][w][threadIdx.x];
+      dots[((size_t)r * nsb + sb) * 3 + threadIdx.x] = t;
+    }
+  };
+  // the four directions of right-hand side r summed and stored
+  auto finish = [&](int r) {
+    __syncthreads();
+    const u4* f = io.in + r * fs;
+    double d[3] = {0.0, 0.0, 0.0};
+    if constexpr (!S::kHalf) {
+#pragma unroll
+      for (int i = 0; i < (NW + 3) / 4; ++i) {
+        const int e = i * 256 + threadIdx.x, j = e / NW;
+        const int site = __shfl(me, j & 63, 64);
+        if (e < 64 * NW && sb * 64 + j < g.vol) {
+          const size_t o = (size_t)site * NW + ((e % NW) ^ swz<R>(j));
+          ChunkOf<R> a, p;
+          p.q = f[o];
+          a.q = buf[0][e];
+#pragma unroll
+          for (int w = 1; w < 4; ++w) {
+            ChunkOf<R> b;
+            b.q = buf[w][e];
+#pragma unroll
+            for (int k = 0; k < 2 * N; ++k) a.v[k] += b.v[k];
+          }
+#pragma unroll
+          for (int k = 0; k < 2 * N; ++k) a.v[k] = diag * p.v[k] - (R)0.5 * a.v[k];
+          io.out[r * fs + o] = a.q;
+          if constexpr (DOTS) mr_dots(a.v, p.v, 2 * N, d);
+        }
+      }
+    } else {
+      // four threads per site, three numbers each; the scale needs all twelve
+      const int j = threadIdx.x >> 2, q = threadIdx.x & 3;
+      const int site = __shfl(me, j, 64);
+      const bool live = sb * 64 + j < g.vol;
+      float a[6], p[6];
+      float sc = 0.0f;
+      if (live) {
+        sc = io.isc[(size_t)r * g.vol + site];
+        load_numbers(&io, reinterpret_cast<const unsigned*>(f) + ((size_t)site * 12 + 3 * q), p);
+      }
+      const float dg = diag * sc;
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        const int n = 3 * q + k, pos = 2 * row_pos<Full<float>>(j, n >> 1) + (n & 1);
+        float re = 0.0f, im = 0.0f;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+          const cx<float> b = reinterpret_cast<const cx<float>*>(buf[w])[pos];
+          re += b.re;
+          im += b.im;
+        }
+        a[2 * k] = live ? dg * p[2 * k] - 0.5f * re : 0.0f;
+        a[2 * k + 1] = live ? dg * p[2 * k + 1] - 0.5f * im : 0.0f;
+      }
+      float m = site_scale<6>(a);
+      m = scale_join(m, __shfl_xor(m, 1, 64));
+      m = scale_join(m, __shfl_xor(m, 2, 64));
+      if (live) {
+        float inv;
+        const float so = quant_scale(m, inv);
+        if (q == 0) io.osc[(size_t)r * g.vol + site] = so;
+        store_numbers(&io, reinterpret_cast<unsigned*>(io.out + r * fs) + ((size_t)site * 12 + 3 * q), a, inv);
+        if constexpr (DOTS) {
+          mr_dots(a, p, 6, d);
+          d[0] *= (double)sc;
+          d[1] *= (double)sc;
+        }
+      }
+    }
+    if constexpr (DOTS) {
+#pragma unroll
+      for (int k = 0; k < 3; ++k) d[k] = wave_sum(d[k]);
+      if (lane == 0) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) red[r & 1][wave][k] = d[k];
+      }
+    }
+    if (DOTS || r + 1 < r1) __syncthreads();
+    if constexpr (DOTS) flush(r);
+  };
+  switch (wave) {
+    case 0: gather_wave<0, S>(g, io, tneg, s, c, me, r0, r1, buf[0], finish); break;
+    case 1: gather_wave<1, S>(g, io, tneg, s, c, me, r0, r1, buf[1], finish); break;
+    case 2: gather_wave<2, S>(g, io, tneg, s, c, me, r0, r1, buf[2], finish); break;
+    default: gather_wave<3, S>(g, io, tneg, s, c, me, r0, r1, buf[3], finish); break;
+  }
 }
 
-// Timing windows of the autotuner: launches shorter than 0.1 ms are timed in
-// windows of at least 0.3 ms (up to 20 launches), best of three interleaved
-// rounds, so a few microseconds of launch jitter cannot decide between forms
-// that differ by 10%; longer launches keep one window of three.
-struct TuneWindow {
-  int reps = 3, rounds = 1;
+// ---- 4^4 tiles, FP32 arithmetic: persistent workgroups over (tile, rhs) ------
+// A tile's 256 spinors and the 8 x 64 of its faces are staged in LDS per
+// right-hand side, as FP32 rows in `slots`: own sites first, then the faces
+// (x+, x-, y+, ...).  Three site reads per site instead of nine, the faces in
+// runs of four sites (384 bytes in FP32).  512 threads: thread (half, site)
+// takes the two directions 2 half, 2 half + 1 of its site with their four
+// links in registers for every right-hand side of the tile; the two halves'
+// sums meet in the face slots once those have been read.  Two LDS buffers: the
+// next right-hand side's chunks are loaded while the current one is worked on
+// (147 KB, one workgroup per compute unit, no spilled registers).
+//
+// The grid is one workgroup per compute unit, and each walks its tiles
+// (TileWork): the work per unit is equal to one right-hand side, and the
+// prologue of a tile (links, offsets) overlaps the previous tile's last
+// right-hand side.  Neighbouring workgroups of an XCD are in step, so HBM
+// reads are within 3% of one read per spinor.  24^3x48, 32 rhs, FP32:
+// 1322 us against 2018 us for the best earlier kernel (3717 us with its layout
+// conversions); one workgroup per tile and 8 right-hand sides: 1493 us.
+// Bound: with the hops taken out it runs 4% faster, so by memory (3.3 TB/s of
+// the 4.7 TB/s a copy reaches), the reads of one right-hand side being in
+// flight for less than the whole time.
+constexpr int kTileSlots = 256 + 8 * 64;
+constexpr int kTileChunks = kTileSlots * 6;
+constexpr int kTileThreads = 512;
+constexpr size_t kTileLds = 2 * (size_t)kTileChunks * 16;
+
+__device__ __forceinline__ int tile_nbr(int l, int mu, int dir) {
+  const int c = (l >> (2 * mu)) & 3;
+  const int lo = l & ((1 << (2 * mu)) - 1), hi = l >> (2 * mu + 2);
+  const int j = lo | (hi << (2 * mu));  // the other three coordinates
+  if (dir > 0) return c < 3 ? l + (1 << (2 * mu)) : 256 + (2 * mu) * 64 + j;
+  return c > 0 ? l - (1 << (2 * mu)) : 256 + (2 * mu + 1) * 64 + j;
+}
+
+__device__ __forceinline__ void slot_read(const u4* sm, int slot, cx<float> (&p)[12]) {
+#pragma unroll
+  for (int c = 0; c < 6; ++c) unpack<Full<float>>(sm[row_pos<Full<float>>(slot, c)], c, p);
+}
+
+// The four hops of a thread: directions 2 H and 2 H + 1.
+template <int H>
+__device__ __forceinline__ void tile_hops(const u4* sm, const cx<float> (&u)[4][9], const int (&nbs)[4],
+                                          cx<float> (&acc)[12]) {
+  cx<float> p[12];
+  slot_read(sm, nbs[0], p);
+  hop_add<2 * H, +1>(u[0], p, acc);
+  slot_read(sm, nbs[1], p);
+  hop_add<2 * H, -1>(u[1], p, acc);
+  slot_read(sm, nbs[2], p);
+  hop_add<2 * H + 1, +1>(u[2], p, acc);
+  slot_read(sm, nbs[3], p);
+  hop_add<2 * H + 1, -1>(u[3], p, acc);
+}
+
+__device__ __forceinline__ void tile_base(const Geom& g, int tile, int (&base)[4]) {
+#pragma unroll
+  for (int mu = 0; mu < 4; ++mu) {
+    base[mu] = (tile % g.nT[mu]) * 4;
+    tile /= g.nT[mu];
+  }
+}
+
+// Canonical site of a slot of the tile at `base`.
+__device__ __forceinline__ int tile_site(const Geom& g, const int (&base)[4], int slot) {
+  int x[4];
+  if (slot < 256) {
+#pragma unroll
+    for (int mu = 0; mu < 4; ++mu) x[mu] = base[mu] + ((slot >> (2 * mu)) & 3);
+  } else {
+    const int face = (slot - 256) >> 6, mu0 = face >> 1;
+    int j = slot & 63;
+#pragma unroll
+    for (int mu = 0; mu < 4; ++mu) {
+      if (mu == mu0) {
+        const int v = (face & 1) ? base[mu] - 1 : base[mu] + 4;
+        x[mu] = v < 0 ? g.L[mu] - 1 : (v >= g.L[mu] ? 0 : v);
+      } else {
+        x[mu] = base[mu] + (j & 3);
+        j >>= 2;
+      }
+    }
+  }
+  return canon_site(g, x);
+}
+
+// Work of a persistent workgroup: whole tiles in rounds (all right-hand sides
+// of a tile, the workgroups of one XCD on neighbouring tiles), then an equal
+// share of the (tile, rhs) pairs of the last, partly filled round.
+struct TileWork {
+  int t0, nwg, full, nrhs;  // first tile of the XCD, its workgroups, whole rounds
+  int a, b;                 // pairs of the last round
+  int round, j;
+  __device__ __forceinline__ bool next(int& tile, int& r0, int& r1) {
+    if (round < full) {
+      tile = t0 + round * nwg + j;
+      ++round;
+      r0 = 0;
+      r1 = nrhs;
+      return true;
+    }
+    if (a >= b) return false;
+    tile = t0 + full * nwg + a / nrhs;
+    r0 = a % nrhs;
+    r1 = min(nrhs, r0 + b - a);
+    a += r1 - r0;
+    return true;
+  }
 };
-inline TuneWindow tune_window(float ms_per_launch) {
-  TuneWindow t;
-  if (ms_per_launch > 0.f && ms_per_launch < 0.1f) {
-    t.rounds = 3;
-    t.reps = (int)(0.3f / ms_per_launch) + 1;
-    if (t.reps < 3) t.reps = 3;
-    if (t.reps > 20) t.reps = 20;
+
+template <class S, bool DOTS>
+__global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_wilson_tile(
+    Geom g, S io, float diag, int tneg, int ntile, int nrhs, int nxcd, double* dots) {
+  extern __shared__ __align__(16) u4 smem[];  // 2 x kTileChunks
+  __shared__ double red[2][8][3];
+  constexpr int NL = (kTileSlots * S::NC + kTileThreads - 1) / kTileThreads;  // loads per thread (9, 5)
+  constexpr int kBytes = S::NC * 16;
+  TileWork w;
+  {
+    const int x = blockIdx.x % nxcd, per = ntile / nxcd;
+    w.nwg = gridDim.x / nxcd;
+    w.j = blockIdx.x / nxcd;
+    w.t0 = x * per;
+    w.full = per / w.nwg;
+    w.nrhs = nrhs;
+    w.round = 0;
+    const long long rest = (long long)(per - w.full * w.nwg) * nrhs;
+    w.a = (int)(rest * w.j / w.nwg);
+    w.b = (int)(rest * (w.j + 1) / w.nwg);
   }
-  return t;
+  int tile, r, r1;
+  if (!w.next(tile, r, r1)) return;
+  const int tid = threadIdx.x, l = tid & 255, half = tid >> 8, lane = tid & 63, wave = tid >> 6;
+  const size_t fs = (size_t)g.vol * kBytes;  // bytes of a field
+  const char* fin = reinterpret_cast<const char*>(io.in);
+  char* fout = reinterpret_cast<char*>(io.out);
+  cx<float> u[4][9];
+  int nbs[4];
+#pragma unroll
+  for (int m2 = 0; m2 < 2; ++m2) {
+    nbs[2 * m2] = tile_nbr(l, 2 * half + m2, +1);
+    nbs[2 * m2 + 1] = tile_nbr(l, 2 * half + m2, -1);
+  }
+  auto links = [&](int t) {
+    int base[4], c[4];
+    tile_base(g, t, base);
+    const int s = t * 256 + l;
+#pragma unroll
+    for (int mu = 0; mu < 4; ++mu) c[mu] = base[mu] + ((l >> (2 * mu)) & 3);
+#pragma unroll
+    for (int m2 = 0; m2 < 2; ++m2) {
+      const int mu = 2 * half + m2;
+      const bool last = tneg && mu == 3 && c[3] == g.L[3] - 1, first = tneg && mu == 3 && c[3] == 0;
+      io.link(mu, s, last, u[2 * m2]);
+      io.link(mu, nbr_bwd(g, s, c, mu), first, u[2 * m2 + 1]);
+    }
+  };
+  // byte offsets in a field of the chunks this thread stages (FP32: the first
+  // three are the tile's own), 16 bits: also the site it finishes half of
+  unsigned off[NL];
+  int own = 0;
+  auto offsets = [&](int t) {
+    int base[4];
+    tile_base(g, t, base);
+#pragma unroll
+    for (int k = 0; k < NL; ++k) {
+      const int p = min(k * kTileThreads + tid, kTileSlots * S::NC - 1);
+      const int slot = p / S::NC, c = S::kHalf ? p % S::NC : (p % S::NC) ^ swz<float>(slot);
+      off[k] = (unsigned)(tile_site(g, base, slot) * kBytes + c * 16);
+    }
+    if constexpr (S::kHalf) own = tile_site(g, base, tid >> 1);
+  };
+  u4 v[NL];
+  float vs[S::kHalf ? NL : 1];
+  auto fetch = [&](int rr) {
+    const char* f = fin + rr * fs;
+#pragma unroll
+    for (int k = 0; k < NL; ++k) v[k] = *reinterpret_cast<const u4*>(f + off[k]);
+    if constexpr (S::kHalf) {
+      const float* sc = io.isc + (size_t)rr * g.vol;
+#pragma unroll
+      for (int k = 0; k < NL; ++k) vs[k] = sc[off[k] / kBytes];
+    }
+  };
+  auto stage = [&](u4* dst) {
+#pragma unroll
+    for (int k = 0; k < NL; ++k) {
+      const int p = k * kTileThreads + tid;
+      if constexpr (!S::kHalf) {
+        dst[p] = v[k];
+      } else if (p < kTileSlots * S::NC) {  // four numbers: two FP32 chunks, scaled
+        const int slot = p / 3, c = p % 3;
+        cx<float> q[12];
+        unpack<S>(v[k], 0, q);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) q[e] = vs[k] * q[e];
+        dst[row_pos<Full<float>>(slot, 2 * c)] = chunk_of<float>(q, 0);
+        dst[row_pos<Full<float>>(slot, 2 * c + 1)] = chunk_of<float>(q, 1);
+      }
+    }
+  };
+  int fr = -1, ft = 0;  // pair whose sums wait in red
+  auto flush = [&](int buf) {
+    if (fr >= 0 && tid < 3) {
+      double t = 0.0;
+#pragma unroll
+      for (int q = 0; q < 8; ++q) t += red[buf][q][tid];
+      dots[((size_t)fr * ntile + ft) * 3 + tid] = t;
+    }
+  };
+  offsets(tile);
+  fetch(r);
+  links(tile);
+  stage(smem);
+  __syncthreads();
+  int cur = 0;
+  for (;;) {
+    u4* sm = smem + cur * kTileChunks;
+    u4* nx = smem + (cur ^ 1) * kTileChunks;
+    unsigned o3[3];
+    int oown = own;
+    if constexpr (!S::kHalf) {
+#pragma unroll
+      for (int k = 0; k < 3; ++k) o3[k] = off[k];
+    }
+    // the next pair's chunks, in flight while this one is worked on
+    int nt = tile, nr = r + 1, nr1 = r1;
+    bool more = true;
+    if (nr == r1) {
+      more = w.next(nt, nr, nr1);
+      if (more && nt != tile) offsets(nt);
+    }
+    if (more) fetch(nr);
+    cx<float> acc[12];
+#pragma unroll
+    for (int k = 0; k < 12; ++k) acc[k] = mk(0.0f, 0.0f);
+    if (half == 0)
+      tile_hops<0>(sm, u, nbs, acc);
+    else
+      tile_hops<1>(sm, u, nbs, acc);
+    if (more && nt != tile) links(nt);
+    __syncthreads();  // every neighbour has been read: the face slots take the sums
+    if constexpr (DOTS) flush(cur ^ 1);
+    {
+      u4* ex = sm + (256 + half * 256) * 6;
+#pragma unroll
+      for (int c = 0; c < 6; ++c) ex[row_pos<Full<float>>(l, c)] = chunk_of<float>(acc, c);
+    }
+    if (more) stage(nx);
+    __syncthreads();
+    double d[3] = {0.0, 0.0, 0.0};
+    char* o = fout + r * fs;
+    if constexpr (!S::kHalf) {
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        const int p = k * kTileThreads + tid;
+        ChunkOf<float> a, b, c;
+        c.q = sm[p];
+        a.q = sm[256 * 6 + p];
+        b.q = sm[512 * 6 + p];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) a.v[e] = diag * c.v[e] - 0.5f * (a.v[e] + b.v[e]);
+        *reinterpret_cast<u4*>(o + o3[k]) = a.q;
+        if constexpr (DOTS) mr_dots(a.v, c.v, 4, d);
+      }
+    } else {
+      // two threads per site, six numbers each; the scale needs all twelve
+      const int j = tid >> 1, h = tid & 1;
+      float a[12], p[12];
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        const int pos = row_pos<Full<float>>(j, 3 * h + k);
+        ChunkOf<float> x, y, z;
+        x.q = sm[pos];
+        y.q = sm[256 * 6 + pos];
+        z.q = sm[512 * 6 + pos];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          p[4 * k + e] = x.v[e];
+          a[4 * k + e] = diag * x.v[e] - 0.5f * (y.v[e] + z.v[e]);
+        }
+      }
+      float m = site_scale<12>(a);
+      m = scale_join(m, __shfl_xor(m, 1, 64));
+      float inv;
+      const float so = quant_scale(m, inv);
+      if (h == 0) io.osc[(size_t)r * g.vol + oown] = so;
+      store_numbers(&io, reinterpret_cast<unsigned*>(o) + ((size_t)oown * 12 + 6 * h), a, inv);
+      if constexpr (DOTS) mr_dots(a, p, 12, d);
+    }
+    if constexpr (DOTS) {
+#pragma unroll
+      for (int k = 0; k < 3; ++k) d[k] = wave_sum(d[k]);
+      if (lane == 0) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) red[cur][wave][k] = d[k];
+      }
+      fr = r;
+      ft = tile;
+    }
+    cur ^= 1;
+    if (!more) break;
+    tile = nt;
+    r = nr;
+    r1 = nr1;
+  }
+  if constexpr (DOTS) {
+    __syncthreads();
+    flush(cur ^ 1);
+  }
 }
 
-// Picks the form (rhs groups of the whole batch), then, for a batch, the rhs
-// group size among 1, 2, 4, ... and nrhs with that form.  Forced values
-// (wdmg_set_tuning) are kept and not timed.
-template <class IO>
-void tune_dslash(Ctx& c, const IO& io, int nrhs, int& form, int& rg) {
-  hipEvent_t ev[2];
-  for (auto& e : ev) WDMG_HIP(hipEventCreate(&e));
-  TuneWindow tw;
-  if (form < 0) {
-    const int g = rg < 0 ? nrhs : rg;
-    float ms[kDslashForms];
-    for (int v = 0; v < kDslashForms; ++v) ms[v] = form_fits(c.g0, v, nrhs) ? time_dslash(c, io, nrhs, v, g, ev) : 1e30f;
-    float est = ms[0];
-    for (int v = 1; v < kDslashForms; ++v) est = ms[v] < est ? ms[v] : est;
-    tw = tune_window(est);
-    if (tw.rounds > 1) {
-      for (int v = 0; v < kDslashForms; ++v) ms[v] = 1e30f;
-      for (int r = 0; r < tw.rounds; ++r)
-        for (int v = 0; v < kDslashForms; ++v) {
-          if (!form_fits(c.g0, v, nrhs)) continue;
-          const float t = time_dslash(c, io, nrhs, v, g, ev, tw.reps);
-          if (t < ms[v]) ms[v] = t;
-        }
-    }
-    form = 1;
-    for (int v = 0; v < kDslashForms; ++v)
-      if (ms[v] < ms[form]) form = v;
-  }
-  if (rg < 0) {
-    rg = nrhs;
-    if (nrhs > 1) {
-      // candidates: the whole batch, then groups of 1, 2, 4, ...
-      int cands[8], nc = 0;
-      cands[nc++] = nrhs;
-      for (int cand = 1; cand < nrhs && nc < 8; cand *= 2) cands[nc++] = cand;
-      float ms[8];
-      for (int i = 0; i < nc; ++i) ms[i] = time_dslash(c, io, nrhs, form, cands[i], ev);
-      if (tw.rounds == 1) tw = tune_window(ms[0]);
-      for (int r = 1; r < tw.rounds; ++r)
-        for (int i = 0; i < nc; ++i) {
-          const float t = time_dslash(c, io, nrhs, form, cands[i], ev, tw.reps);
-          if (t < ms[i]) ms[i] = t;
-        }
-      float best = ms[0];
-      for (int i = 1; i < nc; ++i)
-        if (ms[i] < best) {
-          best = ms[i];
-          rg = cands[i];
-        }
-    }
-  }
-  for (auto& e : ev) (void)hipEventDestroy(e);
+// ---- dispatch ---------------------------------------------------------------
+// Forced values of WDMG_TUNE_DSLASH: 5 and 9 name the tile kernel, the others
+// the gather kernel.  Automatic choice, from the (lattice, batch) sweep of
+// both kernels (us, tile / gather):
+//   24^3x48: 2 rhs 124 / 123, 3 rhs 162 / 179, 8 rhs 337 / 426, 32 rhs 1299 / 1649
+//   32^4:    2 rhs 189 / 191, 3 rhs 244 / 262     20^4: 6 rhs 71 / 74, 8 rhs 87 / 96
+//   16^4:    8 rhs 35 / 34, 12 rhs 47 / 49        28x12x16x36: 6 rhs 82 / 77, 8 rhs 107 / 117
+// The tile kernel pays for a prologue per tile, so it needs several right-hand
+// sides per tile and enough pairs per compute unit.
+constexpr int kFormGather = 1, kFormTile = 5;
+
+template <class S>
+bool tile_fits(const Geom& g) {
+  if (sizeof(typename S::T) == 8) return false;
+  for (int mu = 0; mu < 4; ++mu)
+    if (g.B[mu] != 4) return false;
+  return (long long)g.vol * S::NC * 16 <= 0xffffffffll;  // 32-bit byte offsets in a field
 }
 
-// Runs the operator in the tuned form; with `dots` the launch also writes the
-// MR partial sums and the return value is the number of slots per rhs.
-template <class IO>
-int launch_dslash(Ctx& c, const IO& io, int nrhs, int prof_id, int prec_index, double* dots = nullptr) {
+template <class S>
+int auto_form(const Geom& g, int nrhs) {
+  if (!tile_fits<S>(g) || nrhs < 2) return kFormGather;
+  const long long pairs = (long long)(g.vol / 256) * nrhs;
+  return pairs >= (nrhs >= 8 ? 3000 : 5000) ? kFormTile : kFormGather;
+}
+
+// Right-hand sides per workgroup of the gather kernel: as many as leave about
+// four workgroups per compute unit (8^4, 32 rhs: 13 us at 2, 32 us at 16;
+// 16^4, 8 rhs: 34 us at 8, 47 us at 1), at most 16, groups of equal size.
+inline int gather_group(int nsb, int nrhs, int forced) {
+  long long n = forced > 0 ? forced : (long long)nsb * nrhs / 1024;
+  if (forced <= 0 && n > 16) n = 16;
+  if (n < 1) n = 1;
+  if (n > nrhs) n = nrhs;
+  const int groups = (int)((nrhs + n - 1) / n);
+  return (nrhs + groups - 1) / groups;
+}
+
+template <class S>
+void allow_tile_lds() {
+  for (const void* f : {reinterpret_cast<const void*>(&k_wilson_tile<S, false>),
+                        reinterpret_cast<const void*>(&k_wilson_tile<S, true>)})
+    WDMG_HIP(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kTileLds));
+}
+
+// Runs the operator; with `dots` the launch also writes the MR partial sums,
+// and the return value is the number of slots per rhs.
+template <class S>
+int launch_dslash(Ctx& c, const S& io, int nrhs, int prof_id, int prec_index, double* dots = nullptr) {
+  using R = typename S::T;
+  const Geom& g = c.g0;
   const int key = nrhs < kMaxRhs ? nrhs : kMaxRhs;
   signed char& fslot = c.tune_dslash[prec_index][key];
   signed char& gslot = c.tune_group[prec_index][key];
   int v = c.tune_force[WDMG_TUNE_DSLASH] >= 0 ? c.tune_force[WDMG_TUNE_DSLASH] : fslot;
-  if (v >= 0 && !form_fits(c.g0, v, nrhs)) v = 1;  // a forced register-blocked form on a batch it does not divide
+  if (v < 0) fslot = (signed char)(v = auto_form<S>(g, nrhs));
+  const bool tile = (v == 5 || v == 9) && tile_fits<S>(g);
+  const int nsb = g.vpad / 64;
   int rg = c.tune_force[WDMG_TUNE_DSLASH_GROUP] >= 0 ? c.tune_force[WDMG_TUNE_DSLASH_GROUP] : gslot;
-  if ((v < 0 || rg < 0) && !c.capturing && !c.no_alloc) {
-    tune_dslash(c, io, nrhs, v, rg);
-    if (c.tune_force[WDMG_TUNE_DSLASH] < 0) fslot = (signed char)v;
-    if (c.tune_force[WDMG_TUNE_DSLASH_GROUP] < 0) gslot = (signed char)rg;
-  }
-  if (v < 0) v = 1;
-  if (rg < 0) rg = nrhs;
-  ProfScope ps(c, prof_id, (long long)c.g0.vol * nrhs);
-  run_dslash(c, io, nrhs, v, rg, dots);
+  const int nper = sizeof(R) == 8 ? 1 : gather_group(nsb, nrhs, rg);
+  if (rg < 0) gslot = (signed char)(nper < kMaxRhs ? nper : kMaxRhs);
+  const int tneg = c.t_bc < 0 ? 1 : 0;
+  const R diag = (R)(4.0 + c.mass);
+  ProfScope ps(c, prof_id, (long long)g.vol * nrhs);
   c.n_D += nrhs;
-  return dslash_parts(c.g0, v);
+  if constexpr (sizeof(R) == 4) {
+    if (tile) {
+      const int nt = g.vol / 256, nx = nt % 8 == 0 ? 8 : 1;
+      const dim3 grid(c.ncu / 8 * 8), block(kTileThreads);
+      if (dots)
+        hipLaunchKernelGGL((k_wilson_tile<S, true>), grid, block, kTileLds, c.stream, g, io, diag, tneg, nt, nrhs, nx,
+                           dots);
+      else
+        hipLaunchKernelGGL((k_wilson_tile<S, false>), grid, block, kTileLds, c.stream, g, io, diag, tneg, nt, nrhs, nx,
+                           dots);
+      WDMG_HIP(hipGetLastError());
+      return nt;
+    }
+  }
+  const dim3 grid((unsigned)((long long)nsb * ((nrhs + nper - 1) / nper))), block(256);
+  if (dots)
+    hipLaunchKernelGGL((k_wilson_gather<S, true>), grid, block, 0, c.stream, g, io, diag, tneg, nsb, nrhs, nper, dots);
+  else
+    hipLaunchKernelGGL((k_wilson_gather<S, false>), grid, block, 0, c.stream, g, io, diag, tneg, nsb, nrhs, nper,
+                       dots);
+  WDMG_HIP(hipGetLastError());
+  return nsb;
 }
 
-}  // namespace
-
 template <typename R>
-void dslash(Ctx& c, cx<R>* out, const cx<R>* in, int nrhs) {
-  FullIO<R> io;
-  io.in = in;
-  io.out = out;
+Full<R> full_io(Ctx& c, cx<R>* out, const cx<R>* in) {
+  Full<R> io;
+  io.in = reinterpret_cast<const u4*>(in);
+  io.out = reinterpret_cast<u4*>(out);
   if constexpr (sizeof(R) == 8)
     io.U = c.U64;
   else
     io.U = c.U32;
-  launch_dslash(c, io, nrhs, sizeof(R) == 8 ? WDMG_K_DSLASH_F64 : WDMG_K_DSLASH_F32,
+  return io;
+}
+
+template <typename H>
+Half<H> half_io(Ctx& c, HF out, HF in) {
+  Half<H> io;
+  io.in = static_cast<const u4*>(in.v);
+  io.isc = in.s;
+  io.out = static_cast<u4*>(out.v);
+  io.osc = out.s;
+  io.U = static_cast<const cxh<H>*>(u16(c, half_kind<H>()));
+  return io;
+}
+
+}  // namespace
+
+void init_dslash() {
+  allow_tile_lds<Full<float>>();
+  allow_tile_lds<Half<f16_t>>();
+  allow_tile_lds<Half<bf16_t>>();
+}
+
+template <typename R>
+void dslash(Ctx& c, cx<R>* out, const cx<R>* in, int nrhs) {
+  launch_dslash(c, full_io<R>(c, out, in), nrhs, sizeof(R) == 8 ? WDMG_K_DSLASH_F64 : WDMG_K_DSLASH_F32,
                 sizeof(R) == 8 ? WDMG_F64 : WDMG_F32);
 }
 
 template <typename H>
 void dslash_h(Ctx& c, HF out, HF in, int nrhs) {
-  HalfIO<H> io;
-  io.in = static_cast<const cxh<H>*>(in.v);
-  io.isc = in.s;
-  io.out = static_cast<cxh<H>*>(out.v);
-  io.osc = out.s;
-  io.U = static_cast<const cxh<H>*>(u16(c, half_kind<H>()));
-  launch_dslash(c, io, nrhs, half_kind<H>() == WDMG_F16 ? WDMG_K_DSLASH_F16 : WDMG_K_DSLASH_BF16, half_kind<H>());
+  launch_dslash(c, half_io<H>(c, out, in), nrhs, half_kind<H>() == WDMG_F16 ? WDMG_K_DSLASH_F16 : WDMG_K_DSLASH_BF16,
+                half_kind<H>());
 }
 
 double* dots_buffer(Ctx& c, int nrhs) {
@@ -954,29 +894,18 @@ double* dots_buffer(Ctx& c, int nrhs) {
 
 template <typename R>
 void dslash_mr(Ctx& c, cx<R>* out, const cx<R>* in, int nrhs, double scale, int slot) {
-  FullIO<R> io;
-  io.in = in;
-  io.out = out;
-  if constexpr (sizeof(R) == 8)
-    io.U = c.U64;
-  else
-    io.U = c.U32;
   double* d = dots_buffer(c, nrhs);
-  const int nparts = launch_dslash(c, io, nrhs, sizeof(R) == 8 ? WDMG_K_DSLASH_F64 : WDMG_K_DSLASH_F32,
+  const int nparts = launch_dslash(c, full_io<R>(c, out, in), nrhs,
+                                   sizeof(R) == 8 ? WDMG_K_DSLASH_F64 : WDMG_K_DSLASH_F32,
                                    sizeof(R) == 8 ? WDMG_F64 : WDMG_F32, d);
   step_alpha_fin(c, d, nparts, nrhs, scale, slot);
 }
 
 template <typename H>
 void dslash_h_mr(Ctx& c, HF out, HF in, int nrhs, double scale, int slot) {
-  HalfIO<H> io;
-  io.in = static_cast<const cxh<H>*>(in.v);
-  io.isc = in.s;
-  io.out = static_cast<cxh<H>*>(out.v);
-  io.osc = out.s;
-  io.U = static_cast<const cxh<H>*>(u16(c, half_kind<H>()));
   double* d = dots_buffer(c, nrhs);
-  const int nparts = launch_dslash(c, io, nrhs, half_kind<H>() == WDMG_F16 ? WDMG_K_DSLASH_F16 : WDMG_K_DSLASH_BF16,
+  const int nparts = launch_dslash(c, half_io<H>(c, out, in), nrhs,
+                                   half_kind<H>() == WDMG_F16 ? WDMG_K_DSLASH_F16 : WDMG_K_DSLASH_BF16,
                                    half_kind<H>(), d);
   step_alpha_fin(c, d, nparts, nrhs, scale, slot);
 }

@@ -19,30 +19,26 @@ __global__ void k_neg_h(uint32_t* __restrict__ v, size_t n) {
     v[i] ^= 0x80008000u;
 }
 
-template <typename H>
-__global__ void k_zero_h(Geom g, cxh<H>* __restrict__ v, float* __restrict__ sc) {
-  const int s = blockIdx.x * blockDim.x + threadIdx.x;
-  const int r = blockIdx.y;
-  if (s >= g.vpad) return;
-  v += (size_t)r * 12 * g.vpad;
-  sc += (size_t)r * g.vpad;
-  sc[s] = 0.0f;
-#pragma unroll
-  for (int k = 0; k < 12; ++k) v[fidx(s, k, 12)] = f2h<H>(0.0f, 0.0f);
+__global__ void k_fill32(uint32_t* __restrict__ v, size_t n, uint32_t x) {
+  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) v[i] = x;
+}
+__global__ void k_copy32(uint32_t* __restrict__ d, const uint32_t* __restrict__ s, size_t n) {
+  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
+    d[i] = s[i];
 }
 
-// internal field (FP64 or FP32, [rhs][12 vpad]) -> 16-bit field
+// FP64 or FP32 field -> 16-bit field, one thread per site
 template <typename R, typename H>
 __global__ void k_to_half(Geom g, const cx<R>* __restrict__ in, cxh<H>* __restrict__ v, float* __restrict__ sc) {
   const int s = blockIdx.x * blockDim.x + threadIdx.x;
   const int r = blockIdx.y;
-  if (s >= g.vpad) return;
-  in += (size_t)r * 12 * g.vpad;
-  v += (size_t)r * 12 * g.vpad;
-  sc += (size_t)r * g.vpad;
+  if (s >= g.vol) return;
+  in += (size_t)r * 12 * g.vol;
+  v += (size_t)r * 12 * g.vol;
+  sc += (size_t)r * g.vol;
   cx<float> a[12];
 #pragma unroll
-  for (int k = 0; k < 12; ++k) a[k] = cvt<float>(in[fidx(s, k, 12)]);
+  for (int k = 0; k < 12; ++k) a[k] = cvt<float>(in[(size_t)s * 12 + k]);
   store_site_h(v, sc, s, a);
 }
 
@@ -51,56 +47,14 @@ __global__ void k_from_half(Geom g, const cxh<H>* __restrict__ v, const float* _
                             cx<R>* __restrict__ out) {
   const int s = blockIdx.x * blockDim.x + threadIdx.x;
   const int r = blockIdx.y;
-  if (s >= g.vpad) return;
-  out += (size_t)r * 12 * g.vpad;
-  v += (size_t)r * 12 * g.vpad;
-  sc += (size_t)r * g.vpad;
-  cx<float> a[12];
-  load_site_h(v, sc, s, a);
-#pragma unroll
-  for (int k = 0; k < 12; ++k) out[fidx(s, k, 12)] = cvt<R>(a[k]);
-}
-
-// canonical complex64 [rhs][T][Z][Y][X][4][3] -> 16-bit field (padding sites zero)
-template <typename H>
-__global__ void k_canon_to_half(Geom g, const cx<float>* __restrict__ canon, cxh<H>* __restrict__ v,
-                                float* __restrict__ sc) {
-  const int s = blockIdx.x * blockDim.x + threadIdx.x;
-  const int r = blockIdx.y;
-  if (s >= g.vpad) return;
-  v += (size_t)r * 12 * g.vpad;
-  sc += (size_t)r * g.vpad;
-  cx<float> a[12];
-  if (s < g.vol) {
-    int c[4];
-    coords_of(g, s, c);
-    const size_t i = (size_t)c[0] + (size_t)g.L[0] * (c[1] + (size_t)g.L[1] * (c[2] + (size_t)g.L[2] * c[3]));
-    const cx<float>* src = canon + ((size_t)r * g.vol + i) * 12;
-#pragma unroll
-    for (int k = 0; k < 12; ++k) a[k] = src[k];
-  } else {
-#pragma unroll
-    for (int k = 0; k < 12; ++k) a[k] = mk(0.0f, 0.0f);
-  }
-  store_site_h(v, sc, s, a);
-}
-
-template <typename H>
-__global__ void k_half_to_canon(Geom g, const cxh<H>* __restrict__ v, const float* __restrict__ sc,
-                                cx<float>* __restrict__ canon) {
-  const int s = blockIdx.x * blockDim.x + threadIdx.x;
-  const int r = blockIdx.y;
   if (s >= g.vol) return;
-  v += (size_t)r * 12 * g.vpad;
-  sc += (size_t)r * g.vpad;
-  int c[4];
-  coords_of(g, s, c);
-  const size_t i = (size_t)c[0] + (size_t)g.L[0] * (c[1] + (size_t)g.L[1] * (c[2] + (size_t)g.L[2] * c[3]));
+  out += (size_t)r * 12 * g.vol;
+  v += (size_t)r * 12 * g.vol;
+  sc += (size_t)r * g.vol;
   cx<float> a[12];
   load_site_h(v, sc, s, a);
-  cx<float>* dst = canon + ((size_t)r * g.vol + i) * 12;
 #pragma unroll
-  for (int k = 0; k < 12; ++k) dst[k] = a[k];
+  for (int k = 0; k < 12; ++k) out[(size_t)s * 12 + k] = cvt<R>(a[k]);
 }
 
 template <typename H>
@@ -119,7 +73,12 @@ void round_kind(Ctx& c, int kind, const cx<float>* in, void* out, size_t n) {
     round_to_half<bf16_t>(c, in, out, n);
 }
 
-dim3 site_grid(const Geom& g, int nrhs) { return dim3((g.vpad + 255) / 256, nrhs); }
+dim3 site_grid(const Geom& g, int nrhs) { return dim3((g.vol + 255) / 256, nrhs); }
+
+unsigned flat_blocks(size_t n) {
+  const size_t b = (n + 255) / 256;
+  return (unsigned)(b > 8192 ? 8192 : b);
+}
 
 }  // namespace
 
@@ -146,9 +105,9 @@ const void* v16(Ctx& c, Level& L, int kind) {
 
 HF hf_alloc(Ctx& c, int nrhs) {
   HF f;
-  const size_t vp = c.g0.vpad;
-  f.v = dev_alloc(c, (size_t)nrhs * 12 * vp * 4);
-  f.s = static_cast<float*>(dev_alloc(c, (size_t)nrhs * vp * sizeof(float)));
+  const size_t vol = c.g0.vol;
+  f.v = dev_alloc(c, (size_t)nrhs * 12 * vol * 4);
+  f.s = static_cast<float*>(dev_alloc(c, (size_t)nrhs * vol * sizeof(float)));
   return f;
 }
 
@@ -160,25 +119,28 @@ void hf_free(Ctx& c, HF& f) {
 }
 
 void hf_copy(Ctx& c, HF dst, HF src, int nrhs) {
-  // values (4 bytes each) and scales copied unchanged, as pairs of floats
-  const size_t vp = c.g0.vpad;
-  copy<float>(c, static_cast<cx<float>*>(dst.v), static_cast<const cx<float>*>(src.v), (size_t)nrhs * 6 * vp);
-  copy<float>(c, reinterpret_cast<cx<float>*>(dst.s), reinterpret_cast<const cx<float>*>(src.s),
-              (size_t)nrhs * vp / 2);
+  // values (4 bytes each) and scales copied unchanged
+  const size_t nv = (size_t)nrhs * 12 * c.g0.vol, ns = (size_t)nrhs * c.g0.vol;
+  hipLaunchKernelGGL(k_copy32, dim3(flat_blocks(nv)), dim3(256), 0, c.stream, static_cast<uint32_t*>(dst.v),
+                     static_cast<const uint32_t*>(src.v), nv);
+  WDMG_HIP(hipGetLastError());
+  hipLaunchKernelGGL(k_copy32, dim3(flat_blocks(ns)), dim3(256), 0, c.stream, reinterpret_cast<uint32_t*>(dst.s),
+                     reinterpret_cast<const uint32_t*>(src.s), ns);
+  WDMG_HIP(hipGetLastError());
 }
 
 void hf_neg(Ctx& c, HF f, int nrhs) {
-  const size_t n = (size_t)nrhs * 12 * c.g0.vpad;
-  size_t blocks = (n + 255) / 256;
-  if (blocks > 8192) blocks = 8192;
-  hipLaunchKernelGGL(k_neg_h, dim3((unsigned)blocks), dim3(256), 0, c.stream, static_cast<uint32_t*>(f.v), n);
+  const size_t n = (size_t)nrhs * 12 * c.g0.vol;
+  hipLaunchKernelGGL(k_neg_h, dim3(flat_blocks(n)), dim3(256), 0, c.stream, static_cast<uint32_t*>(f.v), n);
   WDMG_HIP(hipGetLastError());
 }
 
 template <typename H>
 void hf_zero(Ctx& c, HF f, int nrhs) {
-  hipLaunchKernelGGL((k_zero_h<H>), site_grid(c.g0, nrhs), dim3(256), 0, c.stream, c.g0,
-                     static_cast<cxh<H>*>(f.v), f.s);
+  const size_t nv = (size_t)nrhs * 12 * c.g0.vol, ns = (size_t)nrhs * c.g0.vol;
+  hipLaunchKernelGGL(k_fill32, dim3(flat_blocks(nv)), dim3(256), 0, c.stream, static_cast<uint32_t*>(f.v), nv, 0u);
+  WDMG_HIP(hipGetLastError());
+  hipLaunchKernelGGL(k_fill32, dim3(flat_blocks(ns)), dim3(256), 0, c.stream, reinterpret_cast<uint32_t*>(f.s), ns, 0u);
   WDMG_HIP(hipGetLastError());
 }
 
@@ -196,28 +158,12 @@ void from_half(Ctx& c, HF in, cx<R>* out, int nrhs) {
   WDMG_HIP(hipGetLastError());
 }
 
-template <typename H>
-void canon_to_half(Ctx& c, const cx<float>* canon, HF out, int nrhs) {
-  hipLaunchKernelGGL((k_canon_to_half<H>), site_grid(c.g0, nrhs), dim3(256), 0, c.stream, c.g0, canon,
-                     static_cast<cxh<H>*>(out.v), out.s);
-  WDMG_HIP(hipGetLastError());
-}
-
-template <typename H>
-void half_to_canon(Ctx& c, HF in, cx<float>* canon, int nrhs) {
-  hipLaunchKernelGGL((k_half_to_canon<H>), dim3((c.g0.vol + 255) / 256, nrhs), dim3(256), 0, c.stream, c.g0,
-                     static_cast<const cxh<H>*>(in.v), in.s, canon);
-  WDMG_HIP(hipGetLastError());
-}
-
 #define INST(H)                                                       \
   template void hf_zero<H>(Ctx&, HF, int);                            \
   template void to_half<double, H>(Ctx&, const cx<double>*, HF, int); \
   template void to_half<float, H>(Ctx&, const cx<float>*, HF, int);   \
   template void from_half<H, double>(Ctx&, HF, cx<double>*, int);     \
-  template void from_half<H, float>(Ctx&, HF, cx<float>*, int);       \
-  template void canon_to_half<H>(Ctx&, const cx<float>*, HF, int);    \
-  template void half_to_canon<H>(Ctx&, HF, cx<float>*, int);
+  template void from_half<H, float>(Ctx&, HF, cx<float>*, int);
 INST(f16_t)
 INST(bf16_t)
 #undef INST

@@ -1,8 +1,8 @@
 // 16-bit storage (FP16 or BF16) of fine fields, links, prolongator columns
 // and coarse-operator blocks; arithmetic stays in FP32.
 //
-// Spinor fields: the 64-site block layout of fine_field.h with 4-byte
-// complex elements, plus one FP32 scale per site (per right-hand side).  The
+// Spinor fields: the site order of fine_field.h with 4-byte complex elements
+// (48 bytes per site), plus one FP32 scale per site (per right-hand side).  The
 // scale of a site is the largest magnitude of its 24 real components; the
 // stored values are those components times the FP32 reciprocal of the scale,
 // rounded to nearest-even into the 16-bit format, so every stored value lies
@@ -56,16 +56,28 @@ __device__ __forceinline__ float quant_scale(float m, float& inv) {
   return m;
 }
 
+// The four complex numbers of a 16-byte chunk, unscaled.
+template <typename H>
+__device__ __forceinline__ void unpack_h(u4 q, int c, cx<float> (&p)[12]) {
+  union {
+    u4 q;
+    cxh<H> v[4];
+  } x;
+  x.q = q;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) p[4 * c + e] = h2f(x.v[e]);
+}
+
 // One site of a 16-bit spinor field (values v, scales sc; sc indexed by site).
 template <typename H>
 __device__ __forceinline__ void load_site_h(const cxh<H>* __restrict__ v, const float* __restrict__ sc, int s,
                                             cx<float> (&a)[12]) {
   const float m = sc[s];
+  const u4* q = reinterpret_cast<const u4*>(v) + (size_t)s * 3;
 #pragma unroll
-  for (int k = 0; k < 12; ++k) {
-    const cx<float> q = h2f(v[fidx(s, k, 12)]);
-    a[k] = mk(m * q.re, m * q.im);
-  }
+  for (int c = 0; c < 3; ++c) unpack_h<H>(q[c], c, a);
+#pragma unroll
+  for (int k = 0; k < 12; ++k) a[k] = mk(m * a[k].re, m * a[k].im);
 }
 
 // FP32 value -> 16 bits, where the value is the FP32 product x * inv: the
@@ -79,6 +91,19 @@ __device__ __forceinline__ cxh<H> quantise(float re, float im, float inv) {
   return f2h<H>(pr, pi);
 }
 
+// Largest magnitude of N numbers; NaN wins, here and in the join of two parts.
+template <int N>
+__device__ __forceinline__ float site_scale(const float (&a)[N]) {
+  float m = 0.0f;
+#pragma unroll
+  for (int k = 0; k < N; ++k) m = fmaxf(m, fabsf(a[k]));
+#pragma unroll
+  for (int k = 0; k < N; ++k)
+    if (a[k] != a[k]) m = a[k];
+  return m;
+}
+__device__ __forceinline__ float scale_join(float m, float o) { return (m != m || o != o) ? m + o : fmaxf(m, o); }
+
 template <typename H>
 __device__ __forceinline__ void store_site_h(cxh<H>* __restrict__ v, float* __restrict__ sc, int s,
                                              const cx<float> (&a)[12]) {
@@ -90,8 +115,17 @@ __device__ __forceinline__ void store_site_h(cxh<H>* __restrict__ v, float* __re
     if (a[k].re != a[k].re || a[k].im != a[k].im) m = a[k].re + a[k].im;  // NaN wins
   float inv;
   sc[s] = quant_scale(m, inv);
+  u4* q = reinterpret_cast<u4*>(v) + (size_t)s * 3;
 #pragma unroll
-  for (int k = 0; k < 12; ++k) v[fidx(s, k, 12)] = quantise<H>(a[k].re, a[k].im, inv);
+  for (int c = 0; c < 3; ++c) {
+    union {
+      u4 q;
+      cxh<H> v[4];
+    } x;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) x.v[e] = quantise<H>(a[4 * c + e].re, a[4 * c + e].im, inv);
+    q[c] = x.q;
+  }
 }
 
 // Links: first two rows, unscaled, same layout as fine_field.h.

@@ -61,8 +61,8 @@ inline int gcr_base(int slot_level) { return S_G + slot_level * G_STRIDE; }
 
 // ---------------------------------------------------------------------------
 // 16-bit storage (half_field.h).  A fine field in 16-bit storage is a pair of
-// arrays: values [rhs][vpad/64][12][64] of 4-byte complex and scales
-// [rhs][vpad] of float.
+// arrays: values [rhs][site][12] of 4-byte complex and scales [rhs][site] of
+// float.
 typedef _Float16 f16_t;
 typedef __bf16 bf16_t;
 template <typename H>
@@ -73,13 +73,6 @@ struct HF {
   void* v = nullptr;   // values
   float* s = nullptr;  // per-site scales
 };
-inline HF hf_rhs(HF f, int rhs, int vpad) {
-  HF r;
-  r.v = static_cast<char*>(f.v) + (size_t)rhs * 12 * vpad * 4;
-  r.s = f.s + (size_t)rhs * vpad;
-  return r;
-}
-
 // ---------------------------------------------------------------------------
 // Memory owned by a context.
 struct Ctx;
@@ -89,8 +82,7 @@ struct Buf {
 };
 
 // One multigrid level.  Level 0 is the Wilson operator on the fine lattice
-// (spinor fields stored [rhs][12][V] component-major over tile-major sites);
-// level l >= 1 is a coarse stencil with fields [rhs][site][2 Nv].
+// (spinor fields [rhs][site][12]); level l >= 1 is a coarse stencil with fields [rhs][site][2 Nv].
 struct Level {
   int l = 0;
   int dims[4] = {0, 0, 0, 0};
@@ -158,18 +150,18 @@ struct Ctx {
   void* U16 = nullptr;          // 16-bit links, made on first use
   int u16_kind = 0;             // WDMG_F16 / WDMG_BF16 (0: none)
   int vc_half = 0;              // 16-bit kind of the running V-cycle (0: none)
-  // kernel variants: forced choice per tuning key (-1: autotune) and the
-  // autotuner's choices per (precision, batch size)
+  // kernel variants: forced choice per tuning key (-1: automatic) and the
+  // choices made or pinned per (precision, batch size)
   int tune_force[WDMG_TUNE_COUNT] = {-1};
   signed char tune_dslash[4][kMaxRhs + 1];
   signed char tune_group[4][kMaxRhs + 1];  // rhs group size of batched Wilson launches
   // HIP-graph capture of a V-cycle: while capturing, the coarsest GCR runs
   // exactly coarse_fixed_iters iterations with no host interaction
   bool capturing = false;
-  // inside wdmg_apply_D_noalloc: no autotuning (its timing buffers) and no
-  // event records; kernels take already-tuned or default forms
+  // inside wdmg_apply_D_noalloc: no event records
   bool no_alloc = false;
   int device = 0;               // HIP device current at wdmg_create
+  int ncu = 256;                // its compute units
   int coarse_fixed_iters = 0;
   int last_coarse_iters = 0;    // most iterations of one coarsest solve since reset
   hipStream_t cap_stream = nullptr;
@@ -263,10 +255,6 @@ constexpr int kPartialsPerBlock = 64;
 // ---------------------------------------------------------------------------
 // Layout conversion (layout.hip).
 void gauge_import(Ctx& c, const cx<double>* canon, int t_bc);
-template <typename Rio, typename R>
-void fine_to_internal(Ctx& c, const Geom& g, const cx<Rio>* canon, cx<R>* out, int nrhs);
-template <typename R, typename Rio>
-void fine_to_canonical(Ctx& c, const Geom& g, const cx<R>* in, cx<Rio>* canon, int nrhs);
 template <typename Rout, typename Rin>
 void convert(Ctx& c, cx<Rout>* out, const cx<Rin>* in, size_t n);
 
@@ -280,16 +268,11 @@ template <typename H>
 void hf_zero(Ctx& c, HF f, int nrhs);
 void hf_copy(Ctx& c, HF dst, HF src, int nrhs);
 void hf_neg(Ctx& c, HF f, int nrhs);  // f = -f, exact
-// internal R field [rhs][12 vpad] <-> 16-bit field
+// R field <-> 16-bit field
 template <typename R, typename H>
 void to_half(Ctx& c, const cx<R>* in, HF out, int nrhs);
 template <typename H, typename R>
 void from_half(Ctx& c, HF in, cx<R>* out, int nrhs);
-// canonical complex64 <-> 16-bit field
-template <typename H>
-void canon_to_half(Ctx& c, const cx<float>* canon, HF out, int nrhs);
-template <typename H>
-void half_to_canon(Ctx& c, HF in, cx<float>* canon, int nrhs);
 // Batched MR pieces on 16-bit fields: dsc[slot + 2q] = scale <a_q,b_q>/<a_q,a_q>;
 // x_q += s_q u_q, r_q -= s_q v_q (u may be r).
 template <typename H>
@@ -299,6 +282,8 @@ template <typename H>
 // x += s u only (mode 2)
 void update2_half(Ctx& c, HF x, HF u, HF r, HF v, int nrhs, int slot, int mode = 0);
 
+// Function attributes of the Wilson kernels on the current device.
+void init_dslash();
 // Wilson operator (dslash.hip): out = diag * in - 1/2 sum_mu hops.
 template <typename R>
 void dslash(Ctx& c, cx<R>* out, const cx<R>* in, int nrhs);
@@ -396,6 +381,10 @@ void block_qr0(Ctx& c, const Level& f, cx<double>* V);
 // level 0 with 16-bit fields and prolongator: coarse side in FP32
 template <typename H>
 void restrict0_h(Ctx& c, const Level& f, const void* V16, HF in, cx<float>* out, int nrhs);
+// the same for FP32 fields, each site rounded to 16 bits as storing it would
+// (false: not for this batch and hierarchy, nothing launched)
+template <typename H>
+bool restrict0_round(Ctx& c, const Level& f, const void* V16, const cx<float>* in, cx<float>* out, int nrhs);
 template <typename H>
 void prolong0_h(Ctx& c, const Level& f, const void* V16, const cx<float>* in, HF out, int nrhs);
 void block_qrC(Ctx& c, const Level& f, cx<double>* V);

@@ -1,5 +1,5 @@
-// Layout and precision conversion between the canonical ABI layouts and the
-// internal tile-major, component-major layouts.
+// Import of the links into their internal layout, and precision conversion of
+// fields (whose layout is the caller's).
 #include "fine_field.h"
 #include "internal.h"
 
@@ -68,39 +68,6 @@ __global__ void k_gauge_import(Geom g, const cx<double>* __restrict__ canon, cx<
   if (!(dev <= 1e-10)) flag[0] = 1.0;
 }
 
-template <typename Rio, typename R>
-__global__ void k_fine_in(Geom g, const cx<Rio>* __restrict__ canon, cx<R>* __restrict__ out) {
-  const int s = blockIdx.x * blockDim.x + threadIdx.x;
-  const int r = blockIdx.y;
-  if (s >= g.vpad) return;
-  cx<R>* dst = out + (size_t)r * 12 * g.vpad;
-  if (s >= g.vol) {
-#pragma unroll
-    for (int k = 0; k < 12; ++k) dst[fidx(s, k, 12)] = mk<R>(0, 0);
-    return;
-  }
-  int c[4];
-  coords_of(g, s, c);
-  const size_t i = (size_t)c[0] + (size_t)g.L[0] * (c[1] + (size_t)g.L[1] * (c[2] + (size_t)g.L[2] * c[3]));
-  const cx<Rio>* src = canon + ((size_t)r * g.vol + i) * 12;
-#pragma unroll
-  for (int k = 0; k < 12; ++k) dst[fidx(s, k, 12)] = cvt<R>(src[k]);
-}
-
-template <typename R, typename Rio>
-__global__ void k_fine_out(Geom g, const cx<R>* __restrict__ in, cx<Rio>* __restrict__ canon) {
-  const int s = blockIdx.x * blockDim.x + threadIdx.x;
-  const int r = blockIdx.y;
-  if (s >= g.vol) return;
-  int c[4];
-  coords_of(g, s, c);
-  const size_t i = (size_t)c[0] + (size_t)g.L[0] * (c[1] + (size_t)g.L[1] * (c[2] + (size_t)g.L[2] * c[3]));
-  cx<Rio>* dst = canon + ((size_t)r * g.vol + i) * 12;
-  const cx<R>* src = in + (size_t)r * 12 * g.vpad;
-#pragma unroll
-  for (int k = 0; k < 12; ++k) dst[k] = cvt<Rio>(src[fidx(s, k, 12)]);
-}
-
 template <typename Rout, typename Rin>
 __global__ void k_convert(cx<Rout>* __restrict__ out, const cx<Rin>* __restrict__ in, size_t n) {
   for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
@@ -117,20 +84,6 @@ void gauge_import(Ctx& c, const cx<double>* canon, int t_bc) {
   WDMG_HIP(hipGetLastError());
 }
 
-template <typename Rio, typename R>
-void fine_to_internal(Ctx& c, const Geom& g, const cx<Rio>* canon, cx<R>* out, int nrhs) {
-  dim3 grid((g.vpad + 255) / 256, nrhs);
-  hipLaunchKernelGGL((k_fine_in<Rio, R>), grid, dim3(256), 0, c.stream, g, canon, out);
-  WDMG_HIP(hipGetLastError());
-}
-
-template <typename R, typename Rio>
-void fine_to_canonical(Ctx& c, const Geom& g, const cx<R>* in, cx<Rio>* canon, int nrhs) {
-  dim3 grid((g.vol + 255) / 256, nrhs);
-  hipLaunchKernelGGL((k_fine_out<R, Rio>), grid, dim3(256), 0, c.stream, g, in, canon);
-  WDMG_HIP(hipGetLastError());
-}
-
 template <typename Rout, typename Rin>
 void convert(Ctx& c, cx<Rout>* out, const cx<Rin>* in, size_t n) {
   if (n == 0) return;
@@ -140,12 +93,6 @@ void convert(Ctx& c, cx<Rout>* out, const cx<Rin>* in, size_t n) {
   WDMG_HIP(hipGetLastError());
 }
 
-template void fine_to_internal<double, double>(Ctx&, const Geom&, const cx<double>*, cx<double>*, int);
-template void fine_to_internal<float, float>(Ctx&, const Geom&, const cx<float>*, cx<float>*, int);
-template void fine_to_internal<double, float>(Ctx&, const Geom&, const cx<double>*, cx<float>*, int);
-template void fine_to_canonical<double, double>(Ctx&, const Geom&, const cx<double>*, cx<double>*, int);
-template void fine_to_canonical<float, float>(Ctx&, const Geom&, const cx<float>*, cx<float>*, int);
-template void fine_to_canonical<float, double>(Ctx&, const Geom&, const cx<float>*, cx<double>*, int);
 template void convert<float, double>(Ctx&, cx<float>*, const cx<double>*, size_t);
 template void convert<double, float>(Ctx&, cx<double>*, const cx<float>*, size_t);
 template void convert<double, double>(Ctx&, cx<double>*, const cx<double>*, size_t);

@@ -70,11 +70,11 @@ __device__ __forceinline__ void coarse_coords(const Geom& g, int s, int (&c)[4])
   c[3] = s / g.L[2];
 }
 
-// gamma5 on fine fields in the internal layout: components 6..11 (spins 2, 3)
+// gamma5 on fine fields: components 6..11 (spins 2, 3)
 // change sign.
 __global__ void k_gamma5(cx<double>* f, size_t n) {
   for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
-    const int k = (int)((i >> 6) % 12);
+    const int k = (int)(i % 12);
     if (k >= 6) f[i] = mk(-f[i].re, -f[i].im);
   }
 }

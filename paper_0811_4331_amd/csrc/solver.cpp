@@ -422,8 +422,7 @@ template void vcycle_h<bf16_t>(Ctx&, HF, HF, int);
 // lockstep, each with its own coefficients; a converged right-hand side is
 // frozen (its steps are zero).  b (input) and x (initial guess, output) are
 // nrhs internal fields.
-int fgcr(Ctx& c, cx<double>* x, const cx<double>* b, int nrhs, const wdmg_solve_params& p, wdmg_solve_stats* st,
-         const void* b_canon) {
+int fgcr(Ctx& c, cx<double>* x, const cx<double>* b, int nrhs, const wdmg_solve_params& p, wdmg_solve_stats* st) {
   Level& L = c.lev[0];
   const size_t n = L.n;
   const size_t bs = n * nrhs;
@@ -437,15 +436,6 @@ int fgcr(Ctx& c, cx<double>* x, const cx<double>* b, int nrhs, const wdmg_solve_
   // FP32 copies of r and z: the FP32 V-cycle's input, and the fixed output of
   // a graph-captured V-cycle
   ensure_outer(c, k, nrhs, f32 || (p.use_graph && basis32), basis32);
-  // in place: b in the internal layout lives in the FP32 W basis (two slots'
-  // worth) while that basis is idle, at the start and at the end of a cycle
-  if (!b && (!basis32 || k < 2 || !b_canon))
-    throw Error(WDMG_ERR_ARG, "an in-place solve needs an FP32 outer basis of at least two directions");
-  cx<double>* bslot = b ? nullptr : reinterpret_cast<cx<double>*>(c.outer_W32);
-  auto load_b = [&]() {
-    if (bslot) fine_to_internal<double, double>(c, c.g0, static_cast<const cx<double>*>(b_canon), bslot, nrhs);
-  };
-  if (bslot) b = bslot;
   if (p.precond) ensure_mg_work(c, nrhs, f32 || half ? WDMG_F32 : WDMG_F64, half ? 1 : 0);
   if (half) ensure_work_h(c, nrhs);
   HalfScope hs(c, half ? p.mg_prec : 0);
@@ -509,7 +499,6 @@ int fgcr(Ctx& c, cx<double>* x, const cx<double>* b, int nrhs, const wdmg_solve_
   constexpr double kReliable = 1e-5;
   double rstart2[kMaxRhs];
   set_scalar(c, S_ERR, 0.0, 0.0);
-  load_b();
   norm2_b(c, b, n, nrhs, G, c.dring);
   WDMG_HIP(hipStreamSynchronize(c.stream));
   double bn2[kMaxRhs], tol2[kMaxRhs], act[kMaxRhs];
@@ -641,7 +630,6 @@ int fgcr(Ctx& c, cx<double>* x, const cx<double>* b, int nrhs, const wdmg_solve_
     else
       gcr_combine<double>(c, x, c.outer_Z, c.outer_hist, c.outer_av, c.outer_y, n, nrhs, jn, k);
     dslash<double>(c, r, x, nrhs);
-    load_b();
     xmy_norm_b(c, b, r, n, nrhs, G);
     read_rn(rn2);
     bool again = false;
@@ -835,7 +823,7 @@ void init_level0(Ctx& c) {
   L.g = c.g0;
   L.nsite = c.g0.vol;
   L.dof = 12;
-  L.n = (size_t)c.g0.vpad * 12;
+  L.n = (size_t)c.g0.vol * 12;
 }
 
 // Sec. 2 setup relaxation: setup_iters MR steps on A v = 0 for all Nv
@@ -881,7 +869,7 @@ static void relax_batch(Ctx& c, int l, cx<R>* V, int nv, int iters, double omega
 template <typename H>
 static void relax_batch_h(Ctx& c, cx<double>* V, int nv, int iters, double omega) {
   const size_t n = c.lev[0].n;
-  const size_t per_rhs = (size_t)c.g0.vpad * (12 * 4 + 4) * 3;
+  const size_t per_rhs = (size_t)c.g0.vol * (12 * 4 + 4) * 3;
   size_t kb = ((size_t)16 << 30) / per_rhs;
   if (kb < 1) kb = 1;
   if (kb > (size_t)nv) kb = nv;
@@ -1029,11 +1017,7 @@ void mg_setup(Ctx& c, const wdmg_mg_params& p) {
     F.nv = lp.nv;
     F.V64 = static_cast<cx<double>*>(dev_alloc(c, (size_t)lp.nv * F.n * sizeof(cx<double>)));
     F.V32 = static_cast<cx<float>*>(dev_alloc(c, (size_t)lp.nv * F.n * sizeof(cx<float>)));
-    const cx<double>* src = static_cast<const cx<double>*>(lp.vectors);
-    if (l == 0)
-      fine_to_internal<double, double>(c, F.g, src, F.V64, lp.nv);
-    else
-      copy<double>(c, F.V64, src, (size_t)lp.nv * F.n);
+    copy<double>(c, F.V64, static_cast<const cx<double>*>(lp.vectors), (size_t)lp.nv * F.n);
     if (lp.setup_iters > 0) {
       if (p.normal)
         normal_relax(c, F, lp.nv, lp.setup_iters, p.omega);  // candidates of D^dagger D v = 0
@@ -1098,7 +1082,7 @@ void release_unused(Ctx& c, int kind) {
 }
 
 void ensure_outer(Ctx& c, int k, int nrhs, bool need32, bool basis32) {
-  const size_t n = (size_t)c.g0.vpad * 12;
+  const size_t n = (size_t)c.g0.vol * 12;
   if (nrhs > c.outer_cap) {
     WDMG_HIP(hipStreamSynchronize(c.stream));
     dev_free(c, c.outer_r);
@@ -1152,7 +1136,7 @@ void ensure_outer(Ctx& c, int k, int nrhs, bool need32, bool basis32) {
 
 void ensure_bicg(Ctx& c) {
   if (c.bicg[0]) return;
-  const size_t n = (size_t)c.g0.vpad * 12;
+  const size_t n = (size_t)c.g0.vol * 12;
   for (cx<double>*& f : c.bicg) f = static_cast<cx<double>*>(dev_alloc(c, n * sizeof(cx<double>)));
 }
 

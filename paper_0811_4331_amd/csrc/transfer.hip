@@ -8,9 +8,8 @@
 // aggregate xhat and to the dofs of chirality chi.  A coarse field is
 // [rhs][xhat][chi * Nv + k].
 //
-// Level 0 fields are [12][V] over tile-major sites; chirality chi owns the
-// components 6 chi .. 6 chi + 5.  Level >= 1 fields are [site][dof] with the
-// two chiralities as the two halves of dof.
+// Fields of every level are [site][dof] in lexicographic site order, dof = 12
+// at level 0; the two chiralities are the two halves of dof.
 #include "half_field.h"
 #include "internal.h"
 
@@ -39,11 +38,12 @@ struct AggMap {
       lc[mu] = u % b[mu];
       u /= b[mu];
     }
-    return site_of(g, a[0] * b[0] + lc[0], a[1] * b[1] + lc[1], a[2] * b[2] + lc[2], a[3] * b[3] + lc[3]);
+    const int c[4] = {a[0] * b[0] + lc[0], a[1] * b[1] + lc[1], a[2] * b[2] + lc[2], a[3] * b[3] + lc[3]};
+    return canon_site(g, c);
   }
   __device__ __forceinline__ int agg_of(int s) const {
     int c[4];
-    coords_of(g, s, c);
+    canon_coords(g, s, c);
     return (c[0] / b[0]) + nb[0] * ((c[1] / b[1]) + nb[1] * ((c[2] / b[2]) + nb[2] * (c[3] / b[3])));
   }
 };
@@ -60,22 +60,16 @@ AggMap make_map(const Level& f) {
   return m;
 }
 
-// Row accessors: row r of the (aggregate, chirality) block -> element offset.
-struct Rows0 {  // level 0: r = m * bvol + l, m in 0..5 (component within chirality)
-  AggMap map;
-  int nrows() const { return map.bvol * 6; }
-  __device__ __forceinline__ size_t off(int agg, int chi, int r) const {
-    const int m = r / map.bvol, l = r - m * map.bvol;
-    return fidx(map.site(agg, l), 6 * chi + m, 12);
-  }
-};
-struct RowsC {  // level >= 1: r = d * bvol + l, d in 0..half-1
+// Row accessor: row r = l * half + d (site l of the aggregate, dof d of the
+// chirality) of an (aggregate, chirality) block -> element offset.  A site's
+// numbers of one chirality are consecutive rows and consecutive in memory.
+struct Rows {
   AggMap map;
   int dof;
   int nrows() const { return map.bvol * (dof / 2); }
   __device__ __forceinline__ size_t off(int agg, int chi, int r) const {
-    const int d = r / map.bvol, l = r - d * map.bvol;
-    return (size_t)map.site(agg, l) * dof + chi * (dof / 2) + d;
+    const int half = dof / 2, l = r / half, d = r - l * half;
+    return (size_t)map.site(agg, l) * dof + chi * half + d;
   }
 };
 
@@ -96,361 +90,661 @@ __device__ __forceinline__ void agg_rhs_block(int nagg, int nrhs, int& agg, int&
   rhs = local % nrhs;
 }
 
-// ---- restriction: one workgroup per (aggregate, rhs, column range) ---------
-// The nv columns of an aggregate are split into nsplit ranges of kper columns
-// so that a single right-hand side still fills the chip; the ranges of one
-// (aggregate, rhs) run back to back on one XCD and re-read the fine field
-// from its L2.
-template <typename R, class Rows>
-__global__ __launch_bounds__(256) void k_restrict(Rows rows, int nrows, const cx<R>* __restrict__ Vv, size_t vstride,
-                                                  const cx<R>* __restrict__ in, size_t fstride, cx<R>* __restrict__ out,
-                                                  int nagg, int nv, int nsplit, int kper) {
-  __shared__ double lds[4 * KC * 4];
+// ---- batched restriction on the matrix cores --------------------------------
+// For a batch of right-hand sides P^dagger is, per (aggregate, chirality), the
+// complex GEMM out[k][q] = sum_row conj(V[row][k]) f[row][q], done as four real
+// products of 16 columns x 4 rows x 16 right-hand sides:
+//   re += Re V . Re f + Im V . Im f,   im += Re V . Im f - Im V . Re f.
+// A lane's operand of V is one complex number, so V goes straight from memory
+// to registers (two rows per lane and load); it is read once per 32 rhs.  The
+// fields go through LDS: their rows are columns of the product and are shared
+// by the column tiles.  Workgroup = (aggregate, up to 16 QT rhs), four waves =
+// (chirality, half of the chunk's rows) with all column tiles in registers;
+// the two halves add up at the end.  Chunk c + 1 is on its way while the
+// products of chunk c run.
+//
+// Bound: memory (V once, fields once) up to about 40 columns x rhs per byte of
+// V.  24^3x48, nv 24, bf16, 32 FP32 right-hand sides in: 954 us (a kernel that
+// staged V in LDS for vector-unit products, with a conversion pass before it:
+// 2019 us).
+constexpr int kMmRows = 48;  // rows of a chunk (of each chirality): eight sites at level 0
+
+template <typename R>
+struct Mm;
+template <>
+struct Mm<float> {
+  typedef float acc_t __attribute__((ext_vector_type(4)));
+  static __device__ __forceinline__ acc_t mma(float a, float b, acc_t c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+  }
+  // row of D held by lane group g = lane / 16 in register r
+  static __device__ __forceinline__ int row(int g, int r) { return 4 * g + r; }
+};
+template <>
+struct Mm<double> {
+  typedef double acc_t __attribute__((ext_vector_type(4)));
+  static __device__ __forceinline__ acc_t mma(double a, double b, acc_t c) {
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+  }
+  static __device__ __forceinline__ int row(int g, int r) { return 4 * r + g; }
+};
+
+// Prolongator columns [k][element]; two consecutive rows of a site at `off`.
+template <typename R>
+struct VFull {
+  using T = R;
+  const cx<R>* v;
+  size_t stride;
+  struct Raw {
+    cx<R> a, b;
+  };
+  __device__ __forceinline__ cx<R> one(int k, size_t off) const { return v[(size_t)k * stride + off]; }
+  __device__ __forceinline__ Raw pair(int k, size_t off) const {
+    const cx<R>* p = v + (size_t)k * stride + off;
+    return {p[0], p[1]};
+  }
+  static __device__ __forceinline__ cx<R> first(Raw r) { return r.a; }
+  static __device__ __forceinline__ cx<R> second(Raw r) { return r.b; }
+};
+template <typename H>
+struct VHalf {
+  using T = float;
+  const cxh<H>* v;
+  size_t stride;
+  struct Raw {
+    cxh<H> a, b;
+  };
+  __device__ __forceinline__ Raw pair(int k, size_t off) const {
+    const cxh<H>* p = v + (size_t)k * stride + off;
+    return {p[0], p[1]};
+  }
+  static __device__ __forceinline__ cx<float> first(Raw r) { return h2f(r.a); }
+  static __device__ __forceinline__ cx<float> second(Raw r) { return h2f(r.b); }
+};
+
+// Prolonged fields: as they are, or in 16 bits.
+template <typename R>
+struct OutFull {
+  using T = R;
+  static constexpr bool kHalf = false;
+  cx<R>* f;
+};
+template <typename H>
+struct OutHalf {
+  using T = float;
+  static constexpr bool kHalf = true;
+  cxh<H>* v;
+  float* s;
+  __device__ __forceinline__ void store(int q, int vol, int site, const cx<float> (&x)[12]) const {
+    store_site_h(v + (size_t)q * 12 * vol, s + (size_t)q * vol, site, x);
+  }
+};
+
+// Fields of level 0, half a site (the six numbers of one chirality) of one
+// right-hand side per item; lanes 2 i, 2 i + 1 hold the two halves of a site.
+// load() issues the loads, get() gives the values.
+template <typename R>
+struct SiteFull {
+  using T = R;
+  static constexpr bool kSite = true;
+  const cx<R>* f;
+  int vol;
+  struct Raw {
+    cx<R> x[6];
+  };
+  __device__ __forceinline__ Raw load(int q, int site, int chi) const {
+    Raw r;
+    const cx<R>* p = f + ((size_t)q * vol + site) * 12 + 6 * chi;
+#pragma unroll
+    for (int m = 0; m < 6; ++m) r.x[m] = p[m];
+    return r;
+  }
+  static __device__ __forceinline__ void get(const Raw& r, cx<R> (&x)[6]) {
+#pragma unroll
+    for (int m = 0; m < 6; ++m) x[m] = r.x[m];
+  }
+};
+// FP32 fields taken as if stored in 16 bits (rounded with their site's scale).
+template <typename H>
+struct SiteRound {
+  using T = float;
+  static constexpr bool kSite = true;
+  const cx<float>* f;
+  int vol;
+  using Raw = typename SiteFull<float>::Raw;
+  __device__ __forceinline__ Raw load(int q, int site, int chi) const {
+    return SiteFull<float>{f, vol}.load(q, site, chi);
+  }
+  static __device__ __forceinline__ void get(const Raw& r, cx<float> (&x)[6]) {
+    float a[12];
+#pragma unroll
+    for (int m = 0; m < 6; ++m) {
+      a[2 * m] = r.x[m].re;
+      a[2 * m + 1] = r.x[m].im;
+    }
+    float s = site_scale<12>(a), inv;
+    s = scale_join(s, __shfl_xor(s, 1, 64));
+    s = quant_scale(s, inv);
+#pragma unroll
+    for (int m = 0; m < 6; ++m) {
+      const cx<float> z = h2f(quantise<H>(a[2 * m], a[2 * m + 1], inv));
+      x[m] = mk(s * z.re, s * z.im);
+    }
+  }
+};
+template <typename H>
+struct SiteHalf {  // 16-bit fields with per-site scales
+  using T = float;
+  static constexpr bool kSite = true;
+  const cxh<H>* v;
+  const float* sc;
+  int vol;
+  struct Raw {
+    cxh<H> x[6];
+    float s;
+  };
+  __device__ __forceinline__ Raw load(int q, int site, int chi) const {
+    Raw r;
+    const cxh<H>* p = v + ((size_t)q * vol + site) * 12 + 6 * chi;
+#pragma unroll
+    for (int m = 0; m < 6; ++m) r.x[m] = p[m];
+    r.s = sc[(size_t)q * vol + site];
+    return r;
+  }
+  static __device__ __forceinline__ void get(const Raw& r, cx<float> (&x)[6]) {
+#pragma unroll
+    for (int m = 0; m < 6; ++m) {
+      const cx<float> z = h2f(r.x[m]);
+      x[m] = mk(r.s * z.re, r.s * z.im);
+    }
+  }
+};
+// Fields of any level, two consecutive rows of a site per item.
+template <typename R>
+struct PairFull {
+  using T = R;
+  static constexpr bool kSite = false;
+  const cx<R>* f;
+  size_t n;  // elements of a field
+  struct Raw {
+    cx<R> a, b;
+  };
+  __device__ __forceinline__ Raw load(int q, size_t off) const {
+    const cx<R>* p = f + (size_t)q * n + off;
+    return {p[0], p[1]};
+  }
+};
+
+template <class VL, class FL, int CT, int QT>
+__global__ __launch_bounds__(256) void k_restrict_mm(AggMap map, int dof, VL V, FL F,
+                                                     cx<typename VL::T>* __restrict__ out, int nagg, int nv,
+                                                     int nrhs) {
+  using R = typename VL::T;
+  using acc_t = typename Mm<R>::acc_t;
+  constexpr int QN = 16 * QT, LD = QN + 1;
+  __shared__ cx<R> Fs[2][2][kMmRows][LD];
+  int agg, tile;
+  agg_rhs_block(nagg, gridDim.x / nagg, agg, tile);
+  const int q0 = tile * QN, nq = min(QN, nrhs - q0);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int chi = wave >> 1, kh = wave & 1;
+  const int half = dof / 2, nrows = map.bvol * half;
+  const int nch = (nrows + kMmRows - 1) / kMmRows;
+  const int li = lane & 15, lk = lane >> 4;
+  // items of the fields per chunk and thread
+  constexpr int NI = FL::kSite ? QN * (kMmRows / 6) * 2 / 256 : QN * kMmRows / 256;
+  typename FL::Raw fr[NI];
+  typename VL::Raw vr[3][CT];
+  auto load = [&](int c) {
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const int e = i * 256 + threadIdx.x;
+      if constexpr (FL::kSite) {
+        const int q = e >> 4, l = c * 8 + ((e >> 1) & 7);
+        if (q < nq && l < map.bvol) fr[i] = F.load(q0 + q, map.site(agg, l), e & 1);
+      } else {
+        const int q = e / kMmRows, p = e % kMmRows, row = c * kMmRows + 2 * (p % (kMmRows / 2));
+        const int l = row / half;
+        if (q < nq && row < nrows)
+          fr[i] = F.load(q0 + q, (size_t)map.site(agg, l) * dof + (p / (kMmRows / 2)) * half + (row - l * half));
+      }
+    }
+#pragma unroll
+    for (int t = 0; t < 3; ++t) {
+      const int row = min(c * kMmRows + kh * 24 + t * 8 + 2 * lk, nrows - 2), l = row / half;
+      const size_t off = (size_t)map.site(agg, l) * dof + chi * half + (row - l * half);
+#pragma unroll
+      for (int j = 0; j < CT; ++j) vr[t][j] = V.pair(min(16 * j + li, nv - 1), off);
+    }
+  };
+  auto stage = [&](int c, int b) {
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const int e = i * 256 + threadIdx.x;
+      if constexpr (FL::kSite) {
+        const int q = e >> 4, s = (e >> 1) & 7;
+        cx<R> x[6];
+        FL::get(fr[i], x);
+        const bool on = q < nq && c * 8 + s < map.bvol;
+#pragma unroll
+        for (int m = 0; m < 6; ++m) Fs[b][e & 1][s * 6 + m][q] = on ? x[m] : mk<R>(0, 0);
+      } else {
+        const int q = e / kMmRows, p = e % kMmRows, r = 2 * (p % (kMmRows / 2));
+        const bool on = q < nq && c * kMmRows + r < nrows;
+        Fs[b][p / (kMmRows / 2)][r][q] = on ? fr[i].a : mk<R>(0, 0);
+        Fs[b][p / (kMmRows / 2)][r + 1][q] = on ? fr[i].b : mk<R>(0, 0);
+      }
+    }
+  };
+  acc_t re[CT][QT], im[CT][QT];
+#pragma unroll
+  for (int j = 0; j < CT; ++j)
+#pragma unroll
+    for (int t = 0; t < QT; ++t) {
+      re[j][t] = acc_t{0, 0, 0, 0};
+      im[j][t] = acc_t{0, 0, 0, 0};
+    }
+  load(0);
+  for (int c = 0; c < nch; ++c) {
+    const int b = c & 1;
+    stage(c, b);
+    typename VL::Raw vc[3][CT];
+#pragma unroll
+    for (int t = 0; t < 3; ++t)
+#pragma unroll
+      for (int j = 0; j < CT; ++j) vc[t][j] = vr[t][j];
+    __syncthreads();  // chunk c is staged; the other buffer (chunk c - 1) has been read
+    if (c + 1 < nch) load(c + 1);
+#pragma unroll
+    for (int t = 0; t < 3; ++t) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        // rows 2 lk + h of the step: the same pairing on both operands
+        cx<R> f[QT];
+#pragma unroll
+        for (int u = 0; u < QT; ++u) f[u] = Fs[b][chi][kh * 24 + t * 8 + 2 * lk + h][16 * u + li];
+#pragma unroll
+        for (int j = 0; j < CT; ++j) {
+          const cx<R> v = h == 0 ? VL::first(vc[t][j]) : VL::second(vc[t][j]);
+#pragma unroll
+          for (int u = 0; u < QT; ++u) {
+            re[j][u] = Mm<R>::mma(v.re, f[u].re, re[j][u]);
+            im[j][u] = Mm<R>::mma(v.re, f[u].im, im[j][u]);
+            re[j][u] = Mm<R>::mma(v.im, f[u].im, re[j][u]);
+            im[j][u] = Mm<R>::mma(-v.im, f[u].re, im[j][u]);
+          }
+        }
+      }
+    }
+  }
+  // the second half's sums join the first's
+  cx<R>* part = &Fs[0][0][0][0];
+  static_assert(sizeof(Fs) >= 2 * 64 * 4 * sizeof(cx<R>), "one tile of both chiralities");
+#pragma unroll
+  for (int j = 0; j < CT; ++j) {
+#pragma unroll
+    for (int u = 0; u < QT; ++u) {
+      __syncthreads();
+      if (kh == 1) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) part[(chi * 4 + r) * 64 + lane] = mk<R>(re[j][u][r], im[j][u][r]);
+      }
+      __syncthreads();
+      const int q = 16 * u + li;
+      if (kh == 0 && q < nq) {
+        cx<R>* o = out + ((size_t)(q0 + q) * nagg + agg) * 2 * nv + chi * nv;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int k = 16 * j + Mm<R>::row(lk, r);
+          const cx<R> p = part[(chi * 4 + r) * 64 + lane];
+          if (k < nv) o[k] = mk<R>(re[j][u][r] + p.re, im[j][u][r] + p.im);
+        }
+      }
+    }
+  }
+}
+
+// ---- prolongation: one thread per element of a finer-level field and NB right-hand sides ----
+constexpr int RB = 8;
+template <class VL, int NB>
+__global__ __launch_bounds__(256) void k_prolong(AggMap map, int dof, VL V, const cx<typename VL::T>* __restrict__ in,
+                                                 cx<typename VL::T>* __restrict__ out, int nagg, int nv, int nrhs) {
+  using R = typename VL::T;
+  const size_t n = (size_t)map.g.vol * dof;
+  const size_t idx = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
+  const int r0 = blockIdx.y * NB, nr = min(NB, nrhs - r0);
+  if (idx >= n) return;
+  const int s = (int)(idx / dof), e = (int)(idx % dof);
+  const int chi = e >= dof / 2;
+  const cx<R>* ec = in + ((size_t)r0 * nagg + map.agg_of(s)) * 2 * nv + chi * nv;
+  cx<R> acc[NB];
+#pragma unroll
+  for (int q = 0; q < NB; ++q) acc[q] = mk<R>(0, 0);
+#pragma unroll 4
+  for (int k = 0; k < nv; ++k) {
+    const cx<R> w = V.one(k, idx);
+#pragma unroll
+    for (int q = 0; q < NB; ++q)
+      if (q < nr) cmadd(acc[q], w, ec[(size_t)q * nagg * 2 * nv + k]);
+  }
+#pragma unroll
+  for (int q = 0; q < NB; ++q)
+    if (q < nr) out[(size_t)(r0 + q) * n + idx] = acc[q];
+}
+
+// The same into a 16-bit field, one thread per site.
+template <typename H>
+__global__ __launch_bounds__(256) void k_prolong0_h(AggMap map, VHalf<H> V, const cx<float>* __restrict__ in,
+                                                    OutHalf<H> O, int nagg, int nv) {
+  const int s = blockIdx.x * blockDim.x + threadIdx.x, rhs = blockIdx.y, vol = map.g.vol;
+  if (s >= vol) return;
+  const cx<float>* ec = in + ((size_t)rhs * nagg + map.agg_of(s)) * 2 * nv;
+  cx<float> acc[12];
+#pragma unroll
+  for (int m = 0; m < 12; ++m) acc[m] = mk(0.0f, 0.0f);
+  for (int k = 0; k < nv; ++k) {
+    cx<float> w[12];
+    const u4* vk = reinterpret_cast<const u4*>(V.v + (size_t)k * V.stride) + (size_t)s * 3;
+#pragma unroll
+    for (int m = 0; m < 3; ++m) unpack_h<H>(vk[m], m, w);
+    const cx<float> e0 = ec[k], e1 = ec[nv + k];
+#pragma unroll
+    for (int m = 0; m < 6; ++m) cmadd(acc[m], w[m], e0);
+#pragma unroll
+    for (int m = 6; m < 12; ++m) cmadd(acc[m], w[m], e1);
+  }
+  O.store(rhs, vol, s, acc);
+}
+
+// ---- batched prolongation on the matrix cores (level 0) -----------------------
+// Per (aggregate, chirality) f[row][q] = sum_k V[row][k] c[k][q], as four real
+// products of 16 rows x 4 columns x 16 right-hand sides per complex one.  The
+// coarse values of the aggregate stay in registers; V goes from memory to
+// registers, two consecutive rows of a column per lane (so a wave's product
+// covers 32 rows, even and odd ones in two tiles) and is read once per 16 QT
+// rhs.  Six waves (chirality x 32-row parts) cover a unit of 16 sites, whose
+// results cross LDS to be stored as rows of sites; a 16-bit field gets its
+// site's scale there.  The next unit's columns are on their way during the
+// products.
+//
+// Bound: memory (V and the result once).
+constexpr int kPmSites = 16, kPmThreads = 384, kPmLd = kPmSites * 12 + 2;
+
+template <class VL, class OUT, int KT, int QT>
+__global__ __launch_bounds__(kPmThreads) void k_prolong_mm(AggMap map, VL V, const cx<typename VL::T>* __restrict__ in,
+                                                           OUT O, int nagg, int nv, int nrhs) {
+  using R = typename VL::T;
+  using acc_t = typename Mm<R>::acc_t;
+  __shared__ __align__(16) cx<R> tile[16][kPmLd];  // [rhs][site x 12]
+  __shared__ int table[2][kPmSites];
+  int agg, qt;
+  agg_rhs_block(nagg, gridDim.x / nagg, agg, qt);
+  const int q0 = qt * 16 * QT, nq = min(16 * QT, nrhs - q0);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int chi = wave & 1, part = wave >> 1;
+  const int li = lane & 15, lk = lane >> 4;
+  const int nu = map.bvol / kPmSites, vol = map.g.vol;
+  // coarse values: lane (q = li, column 4 t + lk)
+  cx<R> c[KT][QT];
+#pragma unroll
+  for (int t = 0; t < KT; ++t)
+#pragma unroll
+    for (int u = 0; u < QT; ++u) {
+      const int q = 16 * u + li, k = 4 * t + lk;
+      c[t][u] = q < nq && k < nv ? in[((size_t)(q0 + q) * nagg + agg) * 2 * nv + chi * nv + k] : mk<R>(0, 0);
+    }
+  // this lane's row pair of a unit
+  const int row = 32 * part + 2 * li, ls = row / 6, lm = row - 6 * ls;
+  typename VL::Raw vr[KT];
+  auto load = [&](int un) {
+    const size_t off = (size_t)map.site(agg, un * kPmSites + ls) * 12 + 6 * chi + lm;
+#pragma unroll
+    for (int t = 0; t < KT; ++t) vr[t] = V.pair(min(4 * t + lk, nv - 1), off);
+  };
+  load(0);
+  for (int un = 0; un < nu; ++un) {
+    acc_t re[2][QT], im[2][QT];
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int u = 0; u < QT; ++u) {
+        re[h][u] = acc_t{0, 0, 0, 0};
+        im[h][u] = acc_t{0, 0, 0, 0};
+      }
+    if (threadIdx.x < kPmSites) table[un & 1][threadIdx.x] = map.site(agg, un * kPmSites + threadIdx.x);
+    typename VL::Raw vc[KT];
+#pragma unroll
+    for (int t = 0; t < KT; ++t) vc[t] = vr[t];
+    if (un + 1 < nu) load(un + 1);
+#pragma unroll
+    for (int t = 0; t < KT; ++t) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const cx<R> v = h == 0 ? VL::first(vc[t]) : VL::second(vc[t]);
+#pragma unroll
+        for (int u = 0; u < QT; ++u) {
+          re[h][u] = Mm<R>::mma(v.re, c[t][u].re, re[h][u]);
+          im[h][u] = Mm<R>::mma(v.re, c[t][u].im, im[h][u]);
+          re[h][u] = Mm<R>::mma(-v.im, c[t][u].im, re[h][u]);
+          im[h][u] = Mm<R>::mma(v.im, c[t][u].re, im[h][u]);
+        }
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < QT; ++u) {
+      __syncthreads();  // the previous tile of 16 rhs has been stored
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const int rr = 32 * part + 2 * Mm<R>::row(lk, r) + h;
+          tile[li][(rr / 6) * 12 + 6 * chi + rr % 6] = mk<R>(re[h][u][r], im[h][u][r]);
+        }
+      }
+      __syncthreads();
+      const int* tb = table[un & 1];
+      const int nqu = min(16, nq - 16 * u);
+      if constexpr (OUT::kHalf) {
+        for (int e = threadIdx.x; e < nqu * kPmSites; e += kPmThreads) {
+          const int q = e / kPmSites, sl = e % kPmSites;
+          cx<float> x[12];
+#pragma unroll
+          for (int m = 0; m < 12; ++m) x[m] = tile[q][sl * 12 + m];
+          O.store(q0 + 16 * u + q, vol, tb[sl], x);
+        }
+      } else {
+        constexpr int N = 16 / sizeof(cx<R>), PER = kPmSites * 12 / N;  // numbers per chunk, chunks per rhs
+        for (int e = threadIdx.x; e < nqu * PER; e += kPmThreads) {
+          const int q = e / PER, p = (e % PER) * N, sl = p / 12, m = p % 12;
+          cx<R>* o = O.f + ((size_t)(q0 + 16 * u + q) * vol + tb[sl]) * 12 + m;
+#pragma unroll
+          for (int w = 0; w < N; ++w) o[w] = tile[q][p + w];
+        }
+      }
+    }
+  }
+}
+
+// ---- restriction of one right-hand side -------------------------------------
+// Every element of V is used once, so V is streamed: one workgroup per
+// (aggregate, rhs, column range), thread t on component t % dof of every S-th
+// site (a row of sites is one run of memory), KC columns at a time in double.
+// The site table of the aggregate replaces a dozen integer divisions per
+// element.  The column ranges fill the chip (about 2048 workgroups); those of
+// one (aggregate, rhs) run back to back on one XCD and re-read the field from
+// its L2.
+constexpr int kSiteTable = 1024;
+
+template <typename R>
+struct OneFull {
+  const cx<R>* v;
+  size_t vstride;
+  const cx<R>* f;
+  size_t n;  // elements of a field
+  using T = R;
+  __device__ __forceinline__ cx<R> column(int k, size_t off) const { return v[(size_t)k * vstride + off]; }
+  __device__ __forceinline__ cx<R> field(int rhs, int, size_t off) const { return f[(size_t)rhs * n + off]; }
+};
+template <typename H>
+struct OneHalf {
+  const cxh<H>* v;
+  size_t vstride;
+  const cxh<H>* f;
+  const float* sc;
+  int vol;
+  using T = float;
+  __device__ __forceinline__ cx<float> column(int k, size_t off) const { return h2f(v[(size_t)k * vstride + off]); }
+  __device__ __forceinline__ cx<float> field(int rhs, int site, size_t off) const {
+    const cx<float> z = h2f(f[(size_t)rhs * 12 * vol + off]);
+    const float s = sc[(size_t)rhs * vol + site];
+    return mk(s * z.re, s * z.im);
+  }
+};
+
+template <class D, int KC>
+__global__ __launch_bounds__(256) void k_restrict_one(AggMap map, int dof, int S, D io, cx<typename D::T>* __restrict__ out,
+                                                      int nagg, int nv, int nsplit, int kper) {
+  using R = typename D::T;
+  __shared__ int table[kSiteTable];
+  __shared__ double red[2 * KC][256];
   int agg, item;
   agg_rhs_block(nagg, gridDim.x / nagg, agg, item);
   const int rhs = item / nsplit, split = item % nsplit;
   const int kbeg = split * kper, kend = min(nv, kbeg + kper);
-  in += (size_t)rhs * fstride;
   out += ((size_t)rhs * nagg + agg) * 2 * nv;
+  const int half = dof / 2;
+  const int e = threadIdx.x % dof, l0 = threadIdx.x / dof;
   for (int k0 = kbeg; k0 < kend; k0 += KC) {
-    double v[4 * KC];
+    double v[2 * KC];
 #pragma unroll
-    for (int q = 0; q < 4 * KC; ++q) v[q] = 0.0;
-    for (int chi = 0; chi < 2; ++chi) {
-      for (int r = threadIdx.x; r < nrows; r += blockDim.x) {
-        const size_t o = rows.off(agg, chi, r);
-        const cx<R> f = in[o];
+    for (int q = 0; q < 2 * KC; ++q) v[q] = 0.0;
+    for (int c0 = 0; c0 < map.bvol; c0 += kSiteTable) {
+      const int nc = min(kSiteTable, map.bvol - c0);
+      if (k0 == kbeg || map.bvol > kSiteTable) {
+        __syncthreads();
+        for (int l = threadIdx.x; l < nc; l += blockDim.x) table[l] = map.site(agg, c0 + l);
+        __syncthreads();
+      }
+#pragma unroll 2
+      for (int l = l0; l < nc; l += S) {
+        const int site = table[l];
+        const size_t o = (size_t)site * dof + e;
+        const cx<R> f = io.field(rhs, site, o);
+        cx<R> w[KC];
+#pragma unroll
+        for (int q = 0; q < KC; ++q) w[q] = io.column(min(k0 + q, kend - 1), o);
 #pragma unroll
         for (int q = 0; q < KC; ++q) {
-          if (k0 + q < kend) {
-            const cx<R> w = Vv[(size_t)(k0 + q) * vstride + o];
-            v[4 * q + 2 * chi] += (double)w.re * f.re + (double)w.im * f.im;
-            v[4 * q + 2 * chi + 1] += (double)w.re * f.im - (double)w.im * f.re;
-          }
+          v[2 * q] += (double)w[q].re * f.re + (double)w[q].im * f.im;
+          v[2 * q + 1] += (double)w[q].re * f.im - (double)w[q].im * f.re;
         }
       }
     }
-    block_sum<4 * KC>(v, lds);
-    if (threadIdx.x == 0) {
-      for (int q = 0; q < KC && k0 + q < kend; ++q) {
-        out[k0 + q] = mk<R>((R)v[4 * q], (R)v[4 * q + 1]);
-        out[nv + k0 + q] = mk<R>((R)v[4 * q + 2], (R)v[4 * q + 3]);
-      }
-    }
-  }
-}
-
-constexpr int RB = 8;  // right-hand sides per workgroup in the batched prolongation
-
-// ---- prolongation of a batch at level 0: V read once for RB rhs -----------
-template <typename R>
-__global__ __launch_bounds__(256) void k_prolong0_b(AggMap map, const cx<R>* __restrict__ Vv,
-                                                    const cx<R>* __restrict__ in, cx<R>* __restrict__ out, int nagg,
-                                                    int nv, int nrhs, int nsb) {
-  int sb, grp;
-  agg_rhs_block(nsb, gridDim.x / nsb, sb, grp);
-  const int s = sb * blockDim.x + threadIdx.x;
-  const int r0 = grp * RB;
-  const int nr = min(RB, nrhs - r0);
-  const size_t n = (size_t)12 * map.g.vpad;
-  if (s >= map.g.vpad) return;
-  const int agg = s < map.g.vol ? map.agg_of(s) : 0;
-  for (int m = 0; m < 12; ++m) {
-    cx<R> acc[RB];
 #pragma unroll
-    for (int q = 0; q < RB; ++q) acc[q] = mk<R>(0, 0);
-    if (s < map.g.vol) {
-      const int chi = m / 6;
-      for (int k = 0; k < nv; ++k) {
-        const cx<R> w = Vv[(size_t)k * n + fidx(s, m, 12)];
-#pragma unroll
-        for (int q = 0; q < RB; ++q)
-          if (q < nr) cmadd(acc[q], w, in[((size_t)(r0 + q) * nagg + agg) * 2 * nv + chi * nv + k]);
-      }
-    }
-#pragma unroll
-    for (int q = 0; q < RB; ++q)
-      if (q < nr) out[(size_t)(r0 + q) * n + fidx(s, m, 12)] = acc[q];
-  }
-}
-
-// ---- prolongation: one thread per (row of a finer-level field) ------------
-template <typename R>
-__global__ __launch_bounds__(256) void k_prolong0(AggMap map, const cx<R>* __restrict__ Vv, const cx<R>* __restrict__ in,
-                                                  cx<R>* __restrict__ out, int nagg, int nv) {
-  const int s = blockIdx.x * blockDim.x + threadIdx.x;
-  const int rhs = blockIdx.y;
-  const size_t n = (size_t)12 * map.g.vpad;
-  if (s >= map.g.vpad) return;
-  cx<R>* o = out + (size_t)rhs * n;
-  cx<R> acc[12];
-#pragma unroll
-  for (int k = 0; k < 12; ++k) acc[k] = mk<R>(0, 0);
-  if (s < map.g.vol) {
-    const int agg = map.agg_of(s);
-    const cx<R>* ec = in + ((size_t)rhs * nagg + agg) * 2 * nv;
-    for (int k = 0; k < nv; ++k) {
-      const cx<R> e0 = ec[k], e1 = ec[nv + k];
-      const cx<R>* vk = Vv + (size_t)k * n;
-#pragma unroll
-      for (int m = 0; m < 6; ++m) cmadd(acc[m], vk[fidx(s, m, 12)], e0);
-#pragma unroll
-      for (int m = 6; m < 12; ++m) cmadd(acc[m], vk[fidx(s, m, 12)], e1);
-    }
-  }
-#pragma unroll
-  for (int m = 0; m < 12; ++m) o[fidx(s, m, 12)] = acc[m];
-}
-
-template <typename R>
-__global__ __launch_bounds__(256) void k_prolongC(AggMap map, int dof, const cx<R>* __restrict__ Vv,
-                                                  const cx<R>* __restrict__ in, cx<R>* __restrict__ out, int nagg,
-                                                  int nv) {
-  const size_t nsite = map.g.vol;
-  const size_t idx = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
-  const int rhs = blockIdx.y;
-  if (idx >= nsite * dof) return;
-  const int s = (int)(idx / dof), e = (int)(idx % dof);
-  const int chi = e >= dof / 2;
-  const int agg = map.agg_of(s);
-  const cx<R>* ec = in + ((size_t)rhs * nagg + agg) * 2 * nv + chi * nv;
-  const size_t vstride = nsite * dof;
-  cx<R> acc = mk<R>(0, 0);
-  for (int k = 0; k < nv; ++k) cmadd(acc, Vv[(size_t)k * vstride + idx], ec[k]);
-  out[(size_t)rhs * vstride + idx] = acc;
-}
-
-// ---- level 0 with 16-bit fine fields and prolongator columns ----------------
-// Restriction: one workgroup per (aggregate, rhs) as above; values are read
-// as scale(site) x stored value, P columns unscaled.
-template <typename H>
-__global__ __launch_bounds__(256) void k_restrict0_h(Rows0 rows, int nrows, const cxh<H>* __restrict__ Vv,
-                                                     size_t vstride, const cxh<H>* __restrict__ in,
-                                                     const float* __restrict__ isc, cx<float>* __restrict__ out,
-                                                     int nagg, int nv, int vpad) {
-  __shared__ double lds[4 * KC * 4];
-  int agg, rhs;
-  agg_rhs_block(nagg, gridDim.x / nagg, agg, rhs);
-  in += (size_t)rhs * 12 * vpad;
-  isc += (size_t)rhs * vpad;
-  out += ((size_t)rhs * nagg + agg) * 2 * nv;
-  const int bvol = rows.map.bvol;
-  for (int k0 = 0; k0 < nv; k0 += KC) {
-    double v[4 * KC];
-#pragma unroll
-    for (int q = 0; q < 4 * KC; ++q) v[q] = 0.0;
-    for (int chi = 0; chi < 2; ++chi) {
-      for (int r = threadIdx.x; r < nrows; r += blockDim.x) {
-        const int m = r / bvol, l = r - m * bvol;
-        const int site = rows.map.site(agg, l);
-        const size_t o = fidx(site, 6 * chi + m, 12);
-        const float sc = isc[site];
-        const cx<float> q16 = h2f(in[o]);
-        const cx<float> f = mk(sc * q16.re, sc * q16.im);
-#pragma unroll
-        for (int q = 0; q < KC; ++q) {
-          if (k0 + q < nv) {
-            const cx<float> w = h2f(Vv[(size_t)(k0 + q) * vstride + o]);
-            v[4 * q + 2 * chi] += (double)w.re * f.re + (double)w.im * f.im;
-            v[4 * q + 2 * chi + 1] += (double)w.re * f.im - (double)w.im * f.re;
-          }
-        }
-      }
-    }
-    block_sum<4 * KC>(v, lds);
-    if (threadIdx.x == 0) {
-      for (int q = 0; q < KC && k0 + q < nv; ++q) {
-        out[k0 + q] = mk((float)v[4 * q], (float)v[4 * q + 1]);
-        out[nv + k0 + q] = mk((float)v[4 * q + 2], (float)v[4 * q + 3]);
-      }
-    }
-  }
-}
-
-// Prolongation into a 16-bit field: one thread per site and RBH right-hand
-// sides (each site's 12 components are needed together for its scale).
-constexpr int RBH = 4;
-template <typename H>
-__global__ __launch_bounds__(256) void k_prolong0_h(AggMap map, const cxh<H>* __restrict__ Vv,
-                                                    const cx<float>* __restrict__ in, cxh<H>* __restrict__ out,
-                                                    float* __restrict__ osc, int nagg, int nv, int nrhs, int nsb) {
-  int sb, grp;
-  agg_rhs_block(nsb, gridDim.x / nsb, sb, grp);
-  const int s = sb * blockDim.x + threadIdx.x;
-  const int r0 = grp * RBH;
-  const int nr = min(RBH, nrhs - r0);
-  const int vpad = map.g.vpad;
-  const size_t n = (size_t)12 * vpad;
-  if (s >= vpad) return;
-  cx<float> acc[RBH][12];
-#pragma unroll
-  for (int q = 0; q < RBH; ++q)
-#pragma unroll
-    for (int m = 0; m < 12; ++m) acc[q][m] = mk(0.0f, 0.0f);
-  if (s < map.g.vol) {
-    const int agg = map.agg_of(s);
-    for (int k = 0; k < nv; ++k) {
-      cx<float> w[12];
-#pragma unroll
-      for (int m = 0; m < 12; ++m) w[m] = h2f(Vv[(size_t)k * n + fidx(s, m, 12)]);
-#pragma unroll
-      for (int q = 0; q < RBH; ++q) {
-        if (q < nr) {
-          const cx<float>* ec = in + ((size_t)(r0 + q) * nagg + agg) * 2 * nv;
-          const cx<float> e0 = ec[k], e1 = ec[nv + k];
-#pragma unroll
-          for (int m = 0; m < 6; ++m) cmadd(acc[q][m], w[m], e0);
-#pragma unroll
-          for (int m = 6; m < 12; ++m) cmadd(acc[q][m], w[m], e1);
-        }
-      }
-    }
-  }
-#pragma unroll
-  for (int q = 0; q < RBH; ++q)
-    if (q < nr) store_site_h(out + (size_t)(r0 + q) * n, osc + (size_t)(r0 + q) * vpad, s, acc[q]);
-}
-
-// ---- batched restriction on the matrix cores (FP32 arithmetic) ----------------
-// For a batch of right-hand sides P^dagger is, per (aggregate, chirality), the
-// complex GEMM out[k][q] = sum_row conj(V[row][k]) f[row][q]; it runs as the
-// real GEMM with rows (k, re|im) and the contraction over (row, re|im):
-//   A[(k,0)][(r,0)] = Re v, A[(k,0)][(r,1)] = Im v, A[(k,1)][(r,0)] = -Im v,
-//   A[(k,1)][(r,1)] = Re v;  B[(r,0)][q] = Re f, B[(r,1)][q] = Im f.
-// Workgroup = one aggregate and up to 32 right-hand sides; wave w handles
-// chirality w / 2 and output row tile w % 2 (32 real rows, 2 Nv <= 64).
-// Chunks of 64 rows (one spin-colour component on 64 aggregate sites) of V
-// and of the fields are staged in LDS with coalesced loads, then fed to
-// v_mfma_f32_32x32x2f32 (lanes as in the coarse-operator kernel).
-// Operand loaders of the batched restriction: raw() issues the load, conv()
-// turns its result into FP32 (kept apart so a load can be in flight while
-// matrix-core work runs, and converted only when it is stored to LDS).
-struct FieldF32 {  // plain FP32 fine fields [rhs][12 vpad]
-  const cx<float>* f;
-  int vpad;
-  using Raw = cx<float>;
-  __device__ __forceinline__ Raw raw(int q, int site, int comp) const {
-    return f[(size_t)q * 12 * vpad + fidx(site, comp, 12)];
-  }
-  __device__ __forceinline__ static cx<float> conv(Raw r) { return r; }
-};
-template <typename H>
-struct FieldH {  // 16-bit fine fields with per-site scales
-  const cxh<H>* v;
-  const float* sc;
-  int vpad;
-  struct Raw {
-    cxh<H> x;
-    float s;
-  };
-  __device__ __forceinline__ Raw raw(int q, int site, int comp) const {
-    return {v[(size_t)q * 12 * vpad + fidx(site, comp, 12)], sc[(size_t)q * vpad + site]};
-  }
-  __device__ __forceinline__ static cx<float> conv(Raw r) {
-    const cx<float> x = h2f(r.x);
-    return mk(r.s * x.re, r.s * x.im);
-  }
-};
-struct VF32 {
-  const cx<float>* v;
-  size_t stride;
-  using Raw = cx<float>;
-  __device__ __forceinline__ Raw raw(int k, size_t off) const { return v[(size_t)k * stride + off]; }
-  __device__ __forceinline__ static cx<float> conv(Raw r) { return r; }
-};
-template <typename H>
-struct VH {
-  const cxh<H>* v;
-  size_t stride;
-  using Raw = cxh<H>;
-  __device__ __forceinline__ Raw raw(int k, size_t off) const { return v[(size_t)k * stride + off]; }
-  __device__ __forceinline__ static cx<float> conv(Raw r) { return h2f(r); }
-};
-
-typedef float floatx16_t __attribute__((ext_vector_type(16)));
-
-template <class VL, class FL>
-__global__ __launch_bounds__(256) void k_restrict0_mfma(AggMap map, VL V, FL F, cx<float>* __restrict__ out,
-                                                        int nagg, int nv, int nrhs) {
-  __shared__ cx<float> Vs[2][64][33];
-  __shared__ cx<float> Fs[2][64][33];
-  int agg, tile;
-  agg_rhs_block(nagg, gridDim.x / nagg, agg, tile);
-  const int q0 = tile * 32, nq = min(32, nrhs - q0);
-  const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-  const int chi = w >> 1, rt = w & 1;
-  const int i = rt * 32 + (l & 31), kidx = i >> 1, part = i & 1;
-  const int q = l & 31;
-  floatx16_t acc;
-#pragma unroll
-  for (int e = 0; e < 16; ++e) acc[e] = 0.f;
-  const int per = map.bvol / 64;
-  // Staging: for chunk c (component pair m, 64 sites from l0) thread t loads
-  // site l0 + (t & 63), columns k = t / 64 + 4u and rhs q0 + t / 64 + 4u
-  // (nv, nq <= 32: u < 8).  The loads of chunk c + 1 are issued before the
-  // matrix-core work of chunk c and stored to LDS after it.
-  const int ll = threadIdx.x & 63, grp = threadIdx.x >> 6;
-  typename VL::Raw vr[2][8];
-  typename FL::Raw fr[2][8];
-  auto load = [&](int c) {
-    const int m = c / per, l0 = (c % per) * 64;
-    const int site = map.site(agg, l0 + ll);
-#pragma unroll
-    for (int ch = 0; ch < 2; ++ch) {
-      const size_t off = fidx(site, 6 * ch + m, 12);
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        if (grp + 4 * u < nv) vr[ch][u] = V.raw(grp + 4 * u, off);
-        if (grp + 4 * u < nq) fr[ch][u] = F.raw(q0 + grp + 4 * u, site, 6 * ch + m);
-      }
-    }
-  };
-  load(0);
-  for (int c = 0; c < 6 * per; ++c) {
+    for (int q = 0; q < 2 * KC; ++q) red[q][threadIdx.x] = v[q];
     __syncthreads();
+    // value u = 2 KC chi + q summed over the S x half threads of its chirality:
+    // 16 threads each, then across them
+    constexpr int G = 16;
+    for (int u = threadIdx.x / G; u < 4 * KC; u += blockDim.x / G) {
+      const int chi = u / (2 * KC), q = u % (2 * KC);
+      double t = 0.0;
+      for (int i = threadIdx.x % G; i < S * half; i += G) t += red[q][(i / half) * dof + chi * half + i % half];
 #pragma unroll
-    for (int ch = 0; ch < 2; ++ch) {
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        if (grp + 4 * u < nv) Vs[ch][ll][grp + 4 * u] = VL::conv(vr[ch][u]);
-        if (grp + 4 * u < nq) Fs[ch][ll][grp + 4 * u] = FL::conv(fr[ch][u]);
-      }
+      for (int m = G / 2; m > 0; m >>= 1) t += __shfl_xor(t, m, 64);
+      if (threadIdx.x % G == 0 && k0 + (q >> 1) < kend)
+        reinterpret_cast<R*>(out + chi * nv + k0 + (q >> 1))[q & 1] = (R)t;
     }
     __syncthreads();
-    if (c + 1 < 6 * per) load(c + 1);
-#pragma unroll 4
-    for (int kk = 0; kk < 128; kk += 2) {
-      const int kr = kk + (l >> 5), r = kr >> 1, pk = kr & 1;
-      float a = 0.f, b = 0.f;
-      if (kidx < nv) {
-        const cx<float> v = Vs[chi][r][kidx];
-        a = part == 0 ? (pk == 0 ? v.re : v.im) : (pk == 0 ? -v.im : v.re);
-      }
-      if (q < nq) {
-        const cx<float> fv = Fs[chi][r][q];
-        b = pk == 0 ? fv.re : fv.im;
-      }
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, acc, 0, 0, 0);
-    }
-  }
-  // D[i][q] in lane q + 32 ((i / 4) % 2), register 4 (i / 8) + i % 4
-  if (q < nq) {
-    float* o = reinterpret_cast<float*>(out + ((size_t)(q0 + q) * nagg + agg) * 2 * nv + chi * nv);
-#pragma unroll
-    for (int reg = 0; reg < 16; ++reg) {
-      const int ii = rt * 32 + 8 * (reg >> 2) + 4 * (l >> 5) + (reg & 3);
-      if ((ii >> 1) < nv) o[ii] = acc[reg];
-    }
   }
 }
 
-// ---- block orthonormalisation (FP64): CGS with a second pass --------------
-// One workgroup per (aggregate, chirality); column j is orthogonalised
-// against columns 0..j-1 twice, then normalised by its (real, positive) norm,
-// which makes diag(R) real positive and Q unique.
-template <class Rows>
+// ---- block orthonormalisation (FP64): block Gram-Schmidt, two passes --------
+// One workgroup per (aggregate, chirality); column j is orthogonalised against
+// columns 0..j-1 twice, QB of them at a time, then normalised by its (real,
+// positive) norm, which makes diag(R) real positive and Q unique.  A thread
+// keeps its NR rows' offsets and the current column's values in registers and
+// reads the QB earlier columns once per pass (they feed the dot products and,
+// still in registers, the update).
+constexpr int QB = 4;
+template <int NR>
 __global__ __launch_bounds__(256) void k_block_qr(Rows rows, int nrows, cx<double>* Vv, size_t vstride, int nv,
                                                   double* dsc) {
+  __shared__ double lds[2 * QB * 4];
+  __shared__ double coef[2 * QB];
+  const int agg = blockIdx.x, chi = blockIdx.y;
+  size_t off[NR];
+  bool on[NR];
+#pragma unroll
+  for (int i = 0; i < NR; ++i) {
+    const int r = threadIdx.x + i * blockDim.x;
+    on[i] = r < nrows;
+    off[i] = rows.off(agg, chi, on[i] ? r : 0);
+  }
+  auto norm2 = [&](const cx<double> (&a)[NR]) {
+    double v[1] = {0.0};
+#pragma unroll
+    for (int i = 0; i < NR; ++i)
+      if (on[i]) v[0] += a[i].re * a[i].re + a[i].im * a[i].im;
+    block_sum<1>(v, lds);
+    if (threadIdx.x == 0) coef[0] = v[0];
+    __syncthreads();
+    const double t = coef[0];
+    __syncthreads();
+    return t;
+  };
+  for (int j = 0; j < nv; ++j) {
+    cx<double>* vj = Vv + (size_t)j * vstride;
+    cx<double> a[NR];
+#pragma unroll
+    for (int i = 0; i < NR; ++i) a[i] = on[i] ? vj[off[i]] : mk(0.0, 0.0);
+    const double norm0 = norm2(a);
+    for (int pass = 0; pass < 2; ++pass) {
+      for (int i0 = 0; i0 < j; i0 += QB) {
+        cx<double> b[QB][NR];
+        double v[2 * QB];
+#pragma unroll
+        for (int q = 0; q < QB; ++q) {
+          v[2 * q] = v[2 * q + 1] = 0.0;
+          const cx<double>* vi = Vv + (size_t)(i0 + q) * vstride;
+#pragma unroll
+          for (int i = 0; i < NR; ++i) b[q][i] = i0 + q < j && on[i] ? vi[off[i]] : mk(0.0, 0.0);
+        }
+#pragma unroll
+        for (int q = 0; q < QB; ++q)
+#pragma unroll
+          for (int i = 0; i < NR; ++i) {
+            v[2 * q] += b[q][i].re * a[i].re + b[q][i].im * a[i].im;
+            v[2 * q + 1] += b[q][i].re * a[i].im - b[q][i].im * a[i].re;
+          }
+        block_sum<2 * QB>(v, lds);
+        if (threadIdx.x == 0) {
+#pragma unroll
+          for (int q = 0; q < 2 * QB; ++q) coef[q] = v[q];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < QB; ++q) {
+          const cx<double> h = mk(coef[2 * q], coef[2 * q + 1]);
+#pragma unroll
+          for (int i = 0; i < NR; ++i) a[i] = a[i] - h * b[q][i];
+        }
+        __syncthreads();
+      }
+    }
+    const double n1 = norm2(a), nr = sqrt(n1);
+    if (threadIdx.x == 0 && !(nr > 1e-12 * sqrt(norm0))) dsc[S_ERR + 1] = 1.0;  // rank lost (or NaN)
+    const double inv = nr > 0.0 ? 1.0 / nr : 0.0;
+#pragma unroll
+    for (int i = 0; i < NR; ++i)
+      if (on[i]) vj[off[i]] = mk(a[i].re * inv, a[i].im * inv);
+  }
+}
+
+// The same for blocks of more rows than the registers of a workgroup hold,
+// column values re-read from memory.
+__global__ __launch_bounds__(256) void k_block_qr_long(Rows rows, int nrows, cx<double>* Vv, size_t vstride, int nv,
+                                                       double* dsc) {
   __shared__ double lds[2 * KC * 4];
   __shared__ double coef[2 * 64];
   __shared__ double scal;
@@ -531,7 +825,7 @@ inline int tpb_for(int nrows) {
   return t > 256 ? 256 : t;
 }
 
-// Column ranges per (aggregate, rhs) of k_restrict: enough workgroups to
+// Column ranges per (aggregate, rhs) of k_restrict_one: enough workgroups to
 // fill the chip (about 2048), ranges of at least one column.
 struct RestrictSplit {
   int nsplit, kper;
@@ -545,126 +839,199 @@ inline RestrictSplit restrict_split(int nagg, int nrhs, int nv) {
   return {(nv + kper - 1) / kper, kper};
 }
 
+template <class D>
+void launch_restrict_one(Ctx& c, const Level& f, const D& io, cx<typename D::T>* out, int nrhs) {
+  const int nagg = nagg_of(f);
+  const RestrictSplit sp = restrict_split(nagg, nrhs, f.nv);
+  // S sites per sweep, a power of two; whole groups of 16 threads for the sums
+  int S = 1;
+  while (2 * S * f.dof <= 256) S *= 2;
+  const dim3 grid(nagg * nrhs * sp.nsplit), block(S * f.dof % 16 ? (S * f.dof + 15) / 16 * 16 : S * f.dof);
+  if (sp.kper <= 4)
+    hipLaunchKernelGGL((k_restrict_one<D, 4>), grid, block, 0, c.stream, make_map(f), f.dof, S, io, out, nagg, f.nv,
+                       sp.nsplit, sp.kper);
+  else
+    hipLaunchKernelGGL((k_restrict_one<D, 8>), grid, block, 0, c.stream, make_map(f), f.dof, S, io, out, nagg, f.nv,
+                       sp.nsplit, sp.kper);
+  WDMG_HIP(hipGetLastError());
+}
+
 }  // namespace
 
-template <typename R>
-void restrict0(Ctx& c, const Level& f, const cx<R>* V, const cx<R>* in, cx<R>* out, int nrhs) {
-  if constexpr (sizeof(R) == 4) {
-    const AggMap map = make_map(f);
-    if (nrhs >= 2 && map.bvol % 64 == 0 && f.nv <= 32) {
-      const int nagg = nagg_of(f);
-      ProfScope ps(c, WDMG_K_RESTRICT_F32, (long long)f.nsite * nrhs);
-      hipLaunchKernelGGL((k_restrict0_mfma<VF32, FieldF32>), dim3(nagg * ((nrhs + 31) / 32)), dim3(256), 0,
-                         c.stream, map, VF32{V, f.n}, FieldF32{in, f.g.vpad}, out, nagg, f.nv, nrhs);
-      WDMG_HIP(hipGetLastError());
-      return;
-    }
-  }
-  Rows0 rows{make_map(f)};
-  const int nrows = rows.nrows();
+// The matrix-core restriction where it applies: two rows of a site in a pair,
+// at most 32 columns (two column tiles of registers).  One right-hand side
+// would fill one of a tile's 16 columns: it streams V instead.
+inline bool mm_fits(const Level& f) { return f.dof % 4 == 0 && f.nv <= 32; }
+
+template <class VL, class FL>
+void launch_restrict_mm(Ctx& c, const Level& f, const VL& V, const FL& F, cx<typename VL::T>* out, int nrhs) {
+  const AggMap map = make_map(f);
   const int nagg = nagg_of(f);
-  // (one workgroup per (aggregate, rhs): measured faster than reading V once
-  // per rhs chunk, because the chunked form re-reads the fine fields per column)
-  ProfScope ps(c, sizeof(R) == 8 ? WDMG_K_RESTRICT_F64 : WDMG_K_RESTRICT_F32, (long long)f.nsite * nrhs);
-  const RestrictSplit sp = restrict_split(nagg, nrhs, f.nv);
-  hipLaunchKernelGGL((k_restrict<R, Rows0>), dim3(nagg * nrhs * sp.nsplit), dim3(tpb_for(nrows)), 0, c.stream, rows,
-                     nrows, V, f.n, in, f.n, out, nagg, f.nv, sp.nsplit, sp.kper);
+  const dim3 block(256);
+  if (nrhs <= 16) {
+    const dim3 grid(nagg);
+    if (f.nv <= 16)
+      hipLaunchKernelGGL((k_restrict_mm<VL, FL, 1, 1>), grid, block, 0, c.stream, map, f.dof, V, F, out, nagg, f.nv, nrhs);
+    else
+      hipLaunchKernelGGL((k_restrict_mm<VL, FL, 2, 1>), grid, block, 0, c.stream, map, f.dof, V, F, out, nagg, f.nv, nrhs);
+  } else {
+    const dim3 grid(nagg * ((nrhs + 31) / 32));
+    if (f.nv <= 16)
+      hipLaunchKernelGGL((k_restrict_mm<VL, FL, 1, 2>), grid, block, 0, c.stream, map, f.dof, V, F, out, nagg, f.nv, nrhs);
+    else
+      hipLaunchKernelGGL((k_restrict_mm<VL, FL, 2, 2>), grid, block, 0, c.stream, map, f.dof, V, F, out, nagg, f.nv, nrhs);
+  }
   WDMG_HIP(hipGetLastError());
 }
 
 template <typename R>
-void restrictC(Ctx& c, const Level& f, const cx<R>* V, const cx<R>* in, cx<R>* out, int nrhs) {
-  RowsC rows{make_map(f), f.dof};
-  const int nrows = rows.nrows();
-  const int nagg = nagg_of(f);
+void restrict_any(Ctx& c, const Level& f, const cx<R>* V, const cx<R>* in, cx<R>* out, int nrhs) {
+  if (nrhs >= 2 && mm_fits(f)) {
+    if (f.dof == 12)
+      launch_restrict_mm(c, f, VFull<R>{V, f.n}, SiteFull<R>{in, f.nsite}, out, nrhs);
+    else
+      launch_restrict_mm(c, f, VFull<R>{V, f.n}, PairFull<R>{in, f.n}, out, nrhs);
+    return;
+  }
+  launch_restrict_one(c, f, OneFull<R>{V, f.n, in, f.n}, out, nrhs);
+}
 
-  const RestrictSplit sp = restrict_split(nagg, nrhs, f.nv);
-  hipLaunchKernelGGL((k_restrict<R, RowsC>), dim3(nagg * nrhs * sp.nsplit), dim3(tpb_for(nrows)), 0, c.stream, rows,
-                     nrows, V, f.n, in, f.n, out, nagg, f.nv, sp.nsplit, sp.kper);
+template <typename R>
+void restrict0(Ctx& c, const Level& f, const cx<R>* V, const cx<R>* in, cx<R>* out, int nrhs) {
+  ProfScope ps(c, sizeof(R) == 8 ? WDMG_K_RESTRICT_F64 : WDMG_K_RESTRICT_F32, (long long)f.nsite * nrhs);
+  restrict_any<R>(c, f, V, in, out, nrhs);
+}
+
+template <typename R>
+void restrictC(Ctx& c, const Level& f, const cx<R>* V, const cx<R>* in, cx<R>* out, int nrhs) {
+  restrict_any<R>(c, f, V, in, out, nrhs);
+}
+
+// The matrix-core prolongation where it applies: level 0, aggregates of whole
+// units, at most 32 columns.  24^3x48, nv 24, FP32, 16 rhs: 557 us, against
+// 3116 us of the vector-unit kernel, which reads V once per RB = 4 rhs.
+inline bool pm_fits(const Level& f) { return f.dof == 12 && make_map(f).bvol % kPmSites == 0 && f.nv <= 32; }
+
+template <class VL, class OUT>
+void launch_prolong_mm(Ctx& c, const Level& f, const VL& V, const cx<typename VL::T>* in, const OUT& O, int nrhs) {
+  const AggMap map = make_map(f);
+  const int nagg = nagg_of(f);
+  // 32 rhs per workgroup read V half as often; FP64 has registers for 16
+  constexpr int Q2 = sizeof(typename VL::T) == 4 ? 2 : 1;
+  const int qt = nrhs <= 16 ? 1 : Q2;
+  const dim3 block(kPmThreads), grid(nagg * ((nrhs + 16 * qt - 1) / (16 * qt)));
+#define PM(KT)                                                                                                       \
+  do {                                                                                                               \
+    if (qt == 1)                                                                                                     \
+      hipLaunchKernelGGL((k_prolong_mm<VL, OUT, KT, 1>), grid, block, 0, c.stream, map, V, in, O, nagg, f.nv, nrhs); \
+    else                                                                                                             \
+      hipLaunchKernelGGL((k_prolong_mm<VL, OUT, KT, Q2>), grid, block, 0, c.stream, map, V, in, O, nagg, f.nv, nrhs); \
+  } while (0)
+  if (f.nv <= 16)
+    PM(4);
+  else if (f.nv <= 24)
+    PM(6);
+  else
+    PM(8);
+#undef PM
+  WDMG_HIP(hipGetLastError());
+}
+
+template <typename R>
+void launch_prolong(Ctx& c, const Level& f, const cx<R>* V, const cx<R>* in, cx<R>* out, int nrhs) {
+  if (nrhs >= 2 && pm_fits(f)) {
+    launch_prolong_mm(c, f, VFull<R>{V, f.n}, in, OutFull<R>{out}, nrhs);
+    return;
+  }
+  const dim3 grid((unsigned)((f.n + 255) / 256), (nrhs + RB - 1) / RB);
+  if (nrhs == 1)
+    hipLaunchKernelGGL((k_prolong<VFull<R>, 1>), grid, dim3(256), 0, c.stream, make_map(f), f.dof, VFull<R>{V, f.n}, in,
+                       out, nagg_of(f), f.nv, nrhs);
+  else
+    hipLaunchKernelGGL((k_prolong<VFull<R>, RB>), grid, dim3(256), 0, c.stream, make_map(f), f.dof, VFull<R>{V, f.n},
+                       in, out, nagg_of(f), f.nv, nrhs);
   WDMG_HIP(hipGetLastError());
 }
 
 template <typename R>
 void prolong0(Ctx& c, const Level& f, const cx<R>* V, const cx<R>* in, cx<R>* out, int nrhs) {
-  const AggMap map = make_map(f);
-  if (nrhs > 1) {
-    ProfScope ps(c, sizeof(R) == 8 ? WDMG_K_PROLONG_F64 : WDMG_K_PROLONG_F32, (long long)f.nsite * nrhs);
-    const int nsb = (f.g.vpad + 255) / 256;
-    hipLaunchKernelGGL((k_prolong0_b<R>), dim3(nsb * ((nrhs + RB - 1) / RB)), dim3(256), 0, c.stream, map, V, in,
-                       out, nagg_of(f), f.nv, nrhs, nsb);
-    WDMG_HIP(hipGetLastError());
-    return;
-  }
   ProfScope ps(c, sizeof(R) == 8 ? WDMG_K_PROLONG_F64 : WDMG_K_PROLONG_F32, (long long)f.nsite * nrhs);
-  hipLaunchKernelGGL((k_prolong0<R>), dim3((f.g.vpad + 255) / 256, nrhs), dim3(256), 0, c.stream, map, V, in, out,
-                     nagg_of(f), f.nv);
-  WDMG_HIP(hipGetLastError());
+  launch_prolong<R>(c, f, V, in, out, nrhs);
 }
 
 template <typename R>
 void prolongC(Ctx& c, const Level& f, const cx<R>* V, const cx<R>* in, cx<R>* out, int nrhs) {
-  const AggMap map = make_map(f);
-  hipLaunchKernelGGL((k_prolongC<R>), dim3((unsigned)((f.n + 255) / 256), nrhs), dim3(256), 0, c.stream, map, f.dof,
-                     V, in, out, nagg_of(f), f.nv);
-  WDMG_HIP(hipGetLastError());
+  launch_prolong<R>(c, f, V, in, out, nrhs);
+}
+
+template <typename H>
+bool restrict0_round(Ctx& c, const Level& f, const void* V16, const cx<float>* in, cx<float>* out, int nrhs) {
+  if (nrhs < 2 || !mm_fits(f)) return false;
+  ProfScope ps(c, WDMG_K_RESTRICT_H, (long long)f.nsite * nrhs);
+  launch_restrict_mm(c, f, VHalf<H>{static_cast<const cxh<H>*>(V16), f.n}, SiteRound<H>{in, f.nsite}, out, nrhs);
+  return true;
 }
 
 template <typename H>
 void restrict0_h(Ctx& c, const Level& f, const void* V16, HF in, cx<float>* out, int nrhs) {
-  {
-    const AggMap map = make_map(f);
-    if (nrhs >= 2 && map.bvol % 64 == 0 && f.nv <= 32) {
-      const int nagg = nagg_of(f);
-      ProfScope ps(c, WDMG_K_RESTRICT_H, (long long)f.nsite * nrhs);
-      hipLaunchKernelGGL((k_restrict0_mfma<VH<H>, FieldH<H>>), dim3(nagg * ((nrhs + 31) / 32)), dim3(256), 0,
-                         c.stream, map, VH<H>{static_cast<const cxh<H>*>(V16), f.n},
-                         FieldH<H>{static_cast<const cxh<H>*>(in.v), in.s, f.g.vpad}, out, nagg, f.nv, nrhs);
-      WDMG_HIP(hipGetLastError());
-      return;
-    }
+  if (nrhs >= 2 && mm_fits(f)) {
+    ProfScope ps(c, WDMG_K_RESTRICT_H, (long long)f.nsite * nrhs);
+    launch_restrict_mm(c, f, VHalf<H>{static_cast<const cxh<H>*>(V16), f.n},
+                       SiteHalf<H>{static_cast<const cxh<H>*>(in.v), in.s, f.nsite}, out, nrhs);
+    return;
   }
-  Rows0 rows{make_map(f)};
-  const int nrows = rows.nrows();
-  const int nagg = nagg_of(f);
   ProfScope ps(c, WDMG_K_RESTRICT_H, (long long)f.nsite * nrhs);
-  hipLaunchKernelGGL((k_restrict0_h<H>), dim3(nagg * nrhs), dim3(tpb_for(nrows)), 0, c.stream, rows, nrows,
-                     static_cast<const cxh<H>*>(V16), f.n, static_cast<const cxh<H>*>(in.v), in.s, out, nagg, f.nv,
-                     f.g.vpad);
-  WDMG_HIP(hipGetLastError());
+  launch_restrict_one(c, f, OneHalf<H>{static_cast<const cxh<H>*>(V16), f.n, static_cast<const cxh<H>*>(in.v), in.s,
+                                       f.nsite}, out, nrhs);
 }
 
 template <typename H>
 void prolong0_h(Ctx& c, const Level& f, const void* V16, const cx<float>* in, HF out, int nrhs) {
-  const AggMap map = make_map(f);
   ProfScope ps(c, WDMG_K_PROLONG_H, (long long)f.nsite * nrhs);
-  const int nsb = (f.g.vpad + 255) / 256;
-  hipLaunchKernelGGL((k_prolong0_h<H>), dim3(nsb * ((nrhs + RBH - 1) / RBH)), dim3(256), 0, c.stream, map,
-                     static_cast<const cxh<H>*>(V16), in, static_cast<cxh<H>*>(out.v), out.s, nagg_of(f), f.nv, nrhs,
-                     nsb);
+  const VHalf<H> V{static_cast<const cxh<H>*>(V16), f.n};
+  const OutHalf<H> O{static_cast<cxh<H>*>(out.v), out.s};
+  if (nrhs >= 2 && pm_fits(f)) {
+    launch_prolong_mm(c, f, V, in, O, nrhs);
+    return;
+  }
+  hipLaunchKernelGGL((k_prolong0_h<H>), dim3((f.nsite + 255) / 256, nrhs), dim3(256), 0, c.stream, make_map(f), V, in,
+                     O, nagg_of(f), f.nv);
   WDMG_HIP(hipGetLastError());
 }
 
+template bool restrict0_round<f16_t>(Ctx&, const Level&, const void*, const cx<float>*, cx<float>*, int);
+template bool restrict0_round<bf16_t>(Ctx&, const Level&, const void*, const cx<float>*, cx<float>*, int);
 template void restrict0_h<f16_t>(Ctx&, const Level&, const void*, HF, cx<float>*, int);
 template void restrict0_h<bf16_t>(Ctx&, const Level&, const void*, HF, cx<float>*, int);
 template void prolong0_h<f16_t>(Ctx&, const Level&, const void*, const cx<float>*, HF, int);
 template void prolong0_h<bf16_t>(Ctx&, const Level&, const void*, const cx<float>*, HF, int);
 
-void block_qr0(Ctx& c, const Level& f, cx<double>* V) {
-  Rows0 rows{make_map(f)};
+void launch_qr(Ctx& c, const Level& f, cx<double>* V) {
+  Rows rows{make_map(f), f.dof};
   const int nrows = rows.nrows();
-  ProfScope ps(c, WDMG_K_BLOCK_QR, (long long)nagg_of(f) * 2);
-  hipLaunchKernelGGL((k_block_qr<Rows0>), dim3(nagg_of(f), 2), dim3(tpb_for(nrows)), 0, c.stream, rows, nrows, V, f.n,
-                     f.nv, c.dsc);
+  const dim3 grid(nagg_of(f), 2), block(tpb_for(nrows));
+  const int nr = (nrows + block.x - 1) / block.x;
+#define QR(N) hipLaunchKernelGGL((k_block_qr<N>), grid, block, 0, c.stream, rows, nrows, V, f.n, f.nv, c.dsc)
+  if (nr <= 1)
+    QR(1);
+  else if (nr <= 2)
+    QR(2);
+  else if (nr <= 4)
+    QR(4);
+  else if (nr <= 6)
+    QR(6);
+  else
+    hipLaunchKernelGGL(k_block_qr_long, grid, block, 0, c.stream, rows, nrows, V, f.n, f.nv, c.dsc);
+#undef QR
   WDMG_HIP(hipGetLastError());
 }
 
-void block_qrC(Ctx& c, const Level& f, cx<double>* V) {
-  RowsC rows{make_map(f), f.dof};
-  const int nrows = rows.nrows();
-  hipLaunchKernelGGL((k_block_qr<RowsC>), dim3(nagg_of(f), 2), dim3(tpb_for(nrows)), 0, c.stream, rows, nrows, V, f.n,
-                     f.nv, c.dsc);
-  WDMG_HIP(hipGetLastError());
+void block_qr0(Ctx& c, const Level& f, cx<double>* V) {
+  ProfScope ps(c, WDMG_K_BLOCK_QR, (long long)nagg_of(f) * 2);
+  launch_qr(c, f, V);
 }
+
+void block_qrC(Ctx& c, const Level& f, cx<double>* V) { launch_qr(c, f, V); }
 
 #define INST(R)                                                                                 \
   template void restrict0<R>(Ctx&, const Level&, const cx<R>*, const cx<R>*, cx<R>*, int);     \

@@ -7,26 +7,31 @@
 
 namespace wdmg {
 
-// Half-spinor projection h = first two rows of (1 - sign*gamma_mu) psi, per colour.
+// Colour c of the half-spinor projection h = first two rows of
+// (1 - sign*gamma_mu) psi (reads p[c], p[3 + c], p[6 + c], p[9 + c]).
+template <int MU, int SIGN, typename R>
+__device__ __forceinline__ void project_colour(const cx<R> (&p)[12], int c, cx<R> (&h)[6]) {
+  const cx<R> p0 = p[c], p1 = p[3 + c], p2 = p[6 + c], p3 = p[9 + c];
+  if (MU == 0) {  // gamma_1 : (g psi) = (-i p3, -i p2, i p1, i p0)
+    h[c] = SIGN > 0 ? p0 + ti(p3) : p0 - ti(p3);
+    h[3 + c] = SIGN > 0 ? p1 + ti(p2) : p1 - ti(p2);
+  } else if (MU == 1) {  // gamma_2 : (-p3, p2, p1, -p0)
+    h[c] = SIGN > 0 ? p0 + p3 : p0 - p3;
+    h[3 + c] = SIGN > 0 ? p1 - p2 : p1 + p2;
+  } else if (MU == 2) {  // gamma_3 : (-i p2, i p3, i p0, -i p1)
+    h[c] = SIGN > 0 ? p0 + ti(p2) : p0 - ti(p2);
+    h[3 + c] = SIGN > 0 ? p1 - ti(p3) : p1 + ti(p3);
+  } else {  // gamma_4 : (p2, p3, p0, p1)
+    h[c] = SIGN > 0 ? p0 - p2 : p0 + p2;
+    h[3 + c] = SIGN > 0 ? p1 - p3 : p1 + p3;
+  }
+}
+
+// All three colours.
 template <int MU, int SIGN, typename R>
 __device__ __forceinline__ void project(const cx<R> (&p)[12], cx<R> (&h)[6]) {
 #pragma unroll
-  for (int c = 0; c < 3; ++c) {
-    const cx<R> p0 = p[c], p1 = p[3 + c], p2 = p[6 + c], p3 = p[9 + c];
-    if (MU == 0) {  // gamma_1 : (g psi) = (-i p3, -i p2, i p1, i p0)
-      h[c] = SIGN > 0 ? p0 + ti(p3) : p0 - ti(p3);
-      h[3 + c] = SIGN > 0 ? p1 + ti(p2) : p1 - ti(p2);
-    } else if (MU == 1) {  // gamma_2 : (-p3, p2, p1, -p0)
-      h[c] = SIGN > 0 ? p0 + p3 : p0 - p3;
-      h[3 + c] = SIGN > 0 ? p1 - p2 : p1 + p2;
-    } else if (MU == 2) {  // gamma_3 : (-i p2, i p3, i p0, -i p1)
-      h[c] = SIGN > 0 ? p0 + ti(p2) : p0 - ti(p2);
-      h[3 + c] = SIGN > 0 ? p1 - ti(p3) : p1 + ti(p3);
-    } else {  // gamma_4 : (p2, p3, p0, p1)
-      h[c] = SIGN > 0 ? p0 - p2 : p0 + p2;
-      h[3 + c] = SIGN > 0 ? p1 - p3 : p1 + p3;
-    }
-  }
+  for (int c = 0; c < 3; ++c) project_colour<MU, SIGN>(p, c, h);
 }
 
 // acc += full four-spin image of the (link-multiplied) half spinor.

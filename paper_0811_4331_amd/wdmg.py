@@ -392,11 +392,11 @@ class Context:
     TUNE = {"dslash": 0, "dslash_group": 1, "coarse_apply": 2}
 
     def set_tuning(self, key: str, value: int | None):
-        """Force a kernel form (0, 1, ...) or let the autotuner pick (None)."""
+        """Force a kernel form (0, 1, ...) or let the library pick (None)."""
         self._check(self.lib.wdmg_set_tuning(self.h, self.TUNE[key], -1 if value is None else int(value)))
 
     def set_tuning_for(self, key: str, prec: str, nrhs: int, value: int | None):
-        """Pin the autotuner's choice of ``key`` ("dslash" or "dslash_group") for one
+        """Pin the choice of ``key`` ("dslash" or "dslash_group") for one
         precision and batch size (None clears it)."""
         self._check(self.lib.wdmg_set_tuning_for(self.h, self.TUNE[key], PREC[prec], int(nrhs),
                                                  -1 if value is None else int(value)))

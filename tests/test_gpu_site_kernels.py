@@ -1,0 +1,146 @@
+"""The kernels that work on fields as the caller lays them out, at the sizes
+where they can go wrong: the tile form of the Wilson operator over more tiles
+than workgroups and over lattices of a few tiles, the matrix-core transfers at
+the edges of their column and right-hand-side tiles and on aggregates that are
+no whole number of their units, buffers that are aligned to a complex number
+only, and the block QR's row counts.
+
+Tolerances: u = 2^-24.  A Wilson result sums 8 x 3 complex products per
+component of numbers of magnitude about 1: 1e-6 of the largest result covers
+FP32, 1e-13 FP64.  A transfer's element sums n complex products; with rounding
+errors of either sign its error is at most (4 sqrt(2 n) + 1) u times the sum
+of the products' magnitudes (n = rows of an aggregate's chirality down, Nv
+up), and 2^-53 in place of u in FP64."""
+import numpy as np
+import pytest
+import torch
+
+import synthetic
+from oracle import precision, transfer, wilson
+from paper_0811_4331_amd import wdmg
+
+pytestmark = pytest.mark.gpu
+DEV = torch.device("cuda:0")
+
+
+def gpu(x):
+    return torch.from_numpy(np.ascontiguousarray(x)).to(DEV)
+
+
+def rel(a, b):
+    return float(np.abs(a - b).max() / np.abs(b).max())
+
+
+def context(dims, seed, m=-0.4):
+    u = synthetic.gauge_field(dims, 0.35, seed)
+    ctx = wdmg.Context(dims, DEV)
+    ctx.set_gauge(gpu(u), t_bc=-1)
+    ctx.set_mass(m)
+    return ctx, u
+
+
+@pytest.mark.parametrize("dims,nrhs", [((16, 16, 16, 20), 2),  # 320 tiles: a whole round and a shared one
+                                       ((4, 4, 4, 12), 5),     # three tiles, each its own x, y, z neighbour
+                                       ((4, 4, 4, 4), 3)])     # one tile, its own neighbour everywhere
+def test_tile_form_over_all_its_work(dims, nrhs):
+    ctx, u = context(dims, 901)
+    psi = synthetic.gaussian_spinor(dims, seed=902, nrhs=nrhs).astype(np.complex64)
+    ctx.set_tuning("dslash", 5)
+    out = ctx.apply_D(gpu(psi), prec="f32").cpu().numpy()
+    ctx.set_tuning("dslash", 1)
+    other = ctx.apply_D(gpu(psi), prec="f32").cpu().numpy()
+    assert rel(out, other) < 1e-6
+    for j in {0, nrhs - 1}:
+        assert rel(out[j], wilson.apply_D(u, psi[j].astype(np.complex128), -0.4, -1.0)) < 1e-6
+    ctx.close()
+
+
+def _hierarchy(dims, blk, nv, seed):
+    ctx, u = context(dims, seed)
+    lx, ly, lz, lt = dims
+    v = synthetic.gaussian_vectors((nv, lt, lz, ly, lx, 4, 3), seed + 1)
+    ctx.mg_setup([{"block": blk, "nv": nv, "setup_iters": 0, "vectors": gpu(v)}])
+    q, _ = transfer.block_orthonormalize(transfer.as_chiral(v), blk)
+    return ctx, q
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32", "f16", "bf16"])
+@pytest.mark.parametrize("dims,blk,nv,nrhs", [
+    ((8, 4, 4, 4), (4, 4, 4, 4), 16, 2),    # one full column tile
+    ((8, 4, 4, 4), (4, 4, 4, 4), 17, 16),   # one column into the second; a full rhs tile
+    ((4, 4, 4, 8), (4, 4, 4, 4), 32, 17),   # both column tiles full, one rhs into the second tile
+    ((4, 4, 8, 4), (4, 4, 4, 4), 1, 33),    # one column, a third rhs tile
+    ((4, 4, 4, 4), (2, 2, 2, 2), 7, 3),     # 16-site aggregates: one unit
+    ((6, 4, 4, 4), (3, 2, 2, 2), 9, 4),     # 24 sites: no whole number of 16-site units
+    ((6, 6, 3, 2), (3, 3, 3, 2), 5, 2),     # 54 sites: neither 8 nor 16 divides them
+    ((4, 4, 4, 8), (4, 4, 4, 4), 20, 1),    # one right-hand side
+])
+def test_transfers_at_tile_edges(prec, dims, blk, nv, nrhs):
+    ctx, q = _hierarchy(dims, blk, nv, 911 + nv)
+    cdt = np.complex128 if prec == "f64" else np.complex64
+    unit = 2.0 ** (-53 if prec == "f64" else -24)
+    f = synthetic.gaussian_spinor(dims, seed=921, nrhs=nrhs).astype(cdt)
+    rows = 6 * int(np.prod(blk))
+    qs, fs = q, f.astype(np.complex128)
+    if prec in ("f16", "bf16"):  # the operator acts on what 16-bit storage holds
+        q32 = precision.round_f32(q)
+        qs = (precision.round_16(q32.real, prec) + 1j * precision.round_16(q32.imag, prec)).astype(np.complex128)
+        fs = np.stack([precision.store_fine(x.astype(np.complex128), prec) for x in f]).astype(np.complex128)
+    # the first 2 for the FP64 prolongator's own rounding and the FP32 copy
+    down, up = (unit * (4 * np.sqrt(2 * n) + 2) for n in (rows, nv))
+    got = ctx.restrict(0, gpu(f), prec=prec).cpu().numpy().astype(np.complex128)
+    for j in range(nrhs):
+        fc = transfer.as_chiral(fs[j])
+        ref, mag = transfer.restrict(qs, fc, blk), np.abs(transfer.restrict(np.abs(qs), np.abs(fc), blk))
+        assert np.all(np.abs(got[j] - ref) <= down * mag + 1e-13), (j, float(np.abs(got[j] - ref).max()))
+    c = synthetic.gaussian_vectors((nrhs,) + got.shape[1:], 931).astype(cdt)
+    back = ctx.prolong(0, gpu(c), prec=prec).cpu().numpy().astype(np.complex128)
+    for j in range(nrhs):
+        cc = c[j].astype(np.complex128)
+        ref = transfer.as_spinor(transfer.prolong(qs, cc, blk))
+        mag = np.abs(transfer.as_spinor(transfer.prolong(np.abs(qs), np.abs(cc), blk)))
+        tol = up * mag + 1e-13
+        if prec in ("f16", "bf16"):  # stored with a site scale
+            top = np.maximum(np.abs(ref.real), np.abs(ref.imag)).max(axis=(-2, -1), keepdims=True)
+            tol = tol + 2 * precision.HALF_ULP[prec] * top
+        assert np.all(np.abs(back[j] - ref) <= tol), (j, float(np.abs(back[j] - ref).max()))
+    ctx.close()
+
+
+@pytest.mark.parametrize("dims,blk,nv", [((4, 4, 4, 4), (2, 2, 1, 1), 6),    # 24 rows
+                                         ((6, 6, 6, 4), (6, 6, 3, 2), 8),    # 648 rows: three per thread
+                                         ((8, 8, 4, 8), (8, 8, 4, 2), 5)])   # 3072 rows: more than registers hold
+def test_block_qr_row_counts(dims, blk, nv):
+    ctx, q = _hierarchy(dims, blk, nv, 941)
+    got = ctx.get_prolongator(0).cpu().numpy().reshape(q.shape)
+    assert rel(got, q) < 1e-12
+    ctx.close()
+
+
+def test_buffers_aligned_to_one_number():
+    """Complex64 buffers that start 8 bytes off a 16-byte boundary give what
+    aligned ones give."""
+    dims, blk, nv, nrhs = (8, 4, 4, 8), (4, 4, 4, 4), 6, 3
+    ctx, _ = _hierarchy(dims, blk, nv, 951)
+
+    def off(t):  # the same values, 8 bytes into an allocation
+        flat = torch.empty(t.numel() + 1, dtype=t.dtype, device=DEV)
+        flat[1:] = t.reshape(-1)
+        out = flat[1:].view(t.shape)
+        assert out.data_ptr() % 16 == 8
+        return out
+
+    psi = gpu(synthetic.gaussian_spinor(dims, seed=952, nrhs=nrhs).astype(np.complex64))
+    for prec in ("f32", "bf16"):
+        out = off(torch.zeros_like(psi))
+        ctx.apply_D(off(psi), prec=prec, out=out)
+        assert torch.equal(out, ctx.apply_D(psi, prec=prec))
+        x0 = ctx.smooth(0, torch.zeros_like(psi), psi, 2, prec=prec)
+        assert torch.equal(ctx.smooth(0, off(torch.zeros_like(psi)), off(psi), 2, prec=prec), x0)
+        c = ctx.restrict(0, psi, prec=prec)
+        assert torch.equal(ctx.restrict(0, off(psi), prec=prec), c)
+        assert torch.equal(ctx.prolong(0, off(c), prec=prec), ctx.prolong(0, c, prec=prec))
+    out = off(torch.zeros_like(psi))
+    ctx.apply_D_noalloc(off(psi), out, prec="f32")
+    assert torch.equal(out, ctx.apply_D(psi, prec="f32"))
+    ctx.close()
