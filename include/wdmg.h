@@ -303,13 +303,8 @@ int wdmg_solve_bicgstab(wdmg_ctx* ctx, void* x, const void* b, int nrhs, double 
  *                     one-wave-per-direction form below FP64 (links are loaded
  *                     once per group; a value above the batch size means the
  *                     whole batch).  FP64 and the tile form ignore it.
- *   WDMG_TUNE_COARSE_APPLY: the batched coarsest-level operator (nrhs >= 2)
- *                     on the FP64 matrix cores; 0 waves split over
- *                     directions with operands read straight from memory,
- *                     1 operator block and neighbour rows staged through
- *                     LDS one direction at a time, the next one loading
- *                     during the products (needs 2Nv % 8 == 0 and at most
- *                     16 waves for 16 rhs x 16 rows tiles, else form 0).
+ *   WDMG_TUNE_COARSE_APPLY: 0 or 1, kept for callers that set it; the
+ *                     batched coarsest-level operator has one form.
  *                     AUTO means form 1 where it applies (not timed);
  *                     wdmg_get_tuning reports only a forced value. */
 enum {

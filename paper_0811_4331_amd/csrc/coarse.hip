@@ -302,15 +302,13 @@ __device__ __forceinline__ void block_row_madd(const cx<R>* __restrict__ blk, in
 
 template <typename R>
 __global__ __launch_bounds__(576) void k_coarse_apply(Geom g, int n2, const cx<R>* __restrict__ Dc,
-                                                      const cx<R>* __restrict__ in, cx<R>* __restrict__ out,
-                                                      cx<R>* __restrict__ copy) {
+                                                      const cx<R>* __restrict__ in, cx<R>* __restrict__ out) {
   __shared__ cx<R> part[9][64];
   const int s = blockIdx.x, rhs = blockIdx.y;
   const int d = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const size_t nsite = g.vol;
   in += (size_t)rhs * nsite * n2;
   out += (size_t)rhs * nsite * n2;
-  if (copy && d == 8 && lane < n2) copy[(size_t)rhs * nsite * n2 + (size_t)s * n2 + lane] = in[(size_t)s * n2 + lane];
   int nb = s;
   if (d < 8) {
     int c[4];
@@ -331,52 +329,6 @@ __global__ __launch_bounds__(576) void k_coarse_apply(Geom g, int n2, const cx<R
   }
 }
 
-// ---- batched application on the matrix cores ---------------------------------
-// For a block of right-hand sides the coarse operator at one site is a
-// complex GEMM, y = [X | Y_{+x} | ... | Y_{-t}] [c(x); c(x+x); ...; c(x-t)],
-// (2Nv x 9*2Nv) x (9*2Nv x nrhs).  It runs as the equivalent real GEMM with
-// re/im-interleaved rows and columns: the complex entry a of row i, column j
-// becomes the 2x2 block [[Re a, -Im a], [Im a, Re a]], and the right-hand
-// sides enter as (Re, Im) row pairs.  The flop count equals the complex one.
-// One workgroup per (site, rhs tile); wave t owns a tile of real rows; the
-// right-hand-side operand of one direction is staged in LDS at a time.
-typedef double doublex4 __attribute__((ext_vector_type(4)));
-typedef float floatx16 __attribute__((ext_vector_type(16)));
-
-// real-row r, real-col k of the complex block stored column-major (col j, row i)
-template <typename R>
-__device__ __forceinline__ R real_entry(const cx<R>* __restrict__ blk, int n2, int r, int k) {
-  const int i = r >> 1, j = k >> 1;
-  if (i >= n2) return (R)0;
-  const cx<R> a = blk[(size_t)j * n2 + i];
-  const int pr = r & 1, pk = k & 1;
-  return pr == 0 ? (pk == 0 ? a.re : -a.im) : (pk == 0 ? a.im : a.re);
-}
-
-// Operands are read straight from memory into the MFMA lane layout (no LDS
-// staging): wave w owns real-row tile w % nrt and the directions
-// d = w / nrt, w / nrt + ng, ... (ng direction groups), so the nine blocks of
-// a site stream in parallel; the groups' partial products are added through
-// LDS in group order.  The right-hand sides of a tile are the columns of the
-// B operand.
-//
-// FP64: v_mfma_f64_16x16x4f64; tile = 16 real rows x 16 rhs.
-// Operand lanes: A[i][k] at lane i + 16k, B[k][j] at lane j + 16k;
-// result D[i][j] in lane j + 16 (i % 4), register i / 4.
-__host__ __device__ inline int mfma64_row_tiles(int n2) { return (2 * n2 + 15) / 16; }
-__host__ __device__ inline int mfma64_groups(int n2) {
-  const int g = 16 / mfma64_row_tiles(n2);
-  return g < 9 ? g : 9;
-}
-constexpr int kMfma64Lds = 4096;  // doubles of LDS for the group partials
-
-// All right-hand sides of the batch (up to kMaxRhs = 4 tiles of 16) are
-// done by one workgroup, so each operand chunk of A is loaded once and
-// multiplied into every tile's accumulator.  NT >= ceil(nrhs / 16) tiles are
-// held in registers; instantiating the smallest NT keeps the unused
-// accumulators out of the register budget.
-constexpr int kMaxTiles = kMaxRhs / 16;
-
 // Coarse vector layouts: element (rhs q, site, row) of nrhs vectors.
 struct RhsMajor {  // [rhs][site][row], the canonical coarse layout
   size_t fs;       // site count x rows
@@ -390,87 +342,6 @@ struct RhsFast {  // [site][row][rhs]: the rhs of one row are adjacent
     return ((size_t)site * n2 + row) * nrhs + q;
   }
 };
-
-template <int NT, class Lay>
-__device__ __forceinline__ void apply_site_mfma64(const Geom& g, int n2, int nrhs, int s,
-                                                  const cx<double>* __restrict__ Dc, const cx<double>* in,
-                                                  cx<double>* out, double* lds, Lay lay) {
-  const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int nrt = mfma64_row_tiles(n2), ng = mfma64_groups(n2);
-  const int rt = w % nrt, grp = w / nrt;
-  const int ntile = (nrhs + 15) / 16;
-  const int kr = 2 * n2;
-  const int r = rt * 16 + (l & 15), i = r >> 1, pr = r & 1;
-  const bool rowok = i < n2;
-  const int kl = l >> 4;
-  int c[4];
-  coords_of(g, s, c);
-  doublex4 acc[NT];
-#pragma unroll
-  for (int t = 0; t < NT; ++t) acc[t] = doublex4{0.0, 0.0, 0.0, 0.0};
-  // MFMA steps whose operands are loaded together (fewer when more tiles
-  // hold accumulators, to stay within the register budget)
-  constexpr int KC = NT == 1 ? 8 : 4;
-  for (int d = grp; d < 9; d += ng) {
-    const int nb = d == 8 ? s : ((d & 1) ? nbr_bwd(g, s, c, d >> 1) : nbr_fwd(g, s, c, d >> 1));
-    const double* blk = reinterpret_cast<const double*>(Dc + ((size_t)s * 9 + d) * n2 * n2);
-    for (int t0 = 0; 4 * t0 < kr; t0 += KC) {
-      double av[KC];
-#pragma unroll
-      for (int t = 0; t < KC; ++t) {
-        const int k = 4 * (t0 + t) + kl, j = k >> 1, pk = k & 1;
-        av[t] = 0.0;
-        if (k < kr && rowok) {
-          const double a = blk[2 * ((size_t)j * n2 + i) + (pr ^ pk)];
-          av[t] = (pr == 0 && pk == 1) ? -a : a;
-        }
-      }
-#pragma unroll
-      for (int tt = 0; tt < NT; ++tt) {
-        if (tt >= ntile) break;
-        const int q = tt * 16 + (l & 15);
-        const bool qok = q < nrhs;
-        double bv[KC];
-#pragma unroll
-        for (int t = 0; t < KC; ++t) {
-          const int k = 4 * (t0 + t) + kl, j = k >> 1, pk = k & 1;
-          bv[t] = (qok && k < kr) ? reinterpret_cast<const double*>(in + lay.at(q, nb, j, n2))[pk] : 0.0;
-        }
-#pragma unroll
-        for (int t = 0; t < KC; ++t)
-          if (4 * (t0 + t) < kr) acc[tt] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[t], bv[t], acc[tt], 0, 0, 0);
-      }
-    }
-  }
-  // groups 1.. hand their partial tiles to group 0, one rhs tile at a time
-#pragma unroll
-  for (int tt = 0; tt < NT; ++tt) {
-    if (tt >= ntile) break;
-    if (grp > 0 && grp < ng) {
-      double* dst = lds + ((size_t)((grp - 1) * nrt + rt) * 64 + l) * 4;
-#pragma unroll
-      for (int reg = 0; reg < 4; ++reg) dst[reg] = acc[tt][reg];
-    }
-    __syncthreads();
-    if (grp == 0) {
-      doublex4 a = acc[tt];
-      for (int gg = 1; gg < ng; ++gg) {
-        const double* src = lds + ((size_t)((gg - 1) * nrt + rt) * 64 + l) * 4;
-#pragma unroll
-        for (int reg = 0; reg < 4; ++reg) a[reg] += src[reg];
-      }
-      const int q = tt * 16 + (l & 15);
-      if (q < nrhs) {
-#pragma unroll
-        for (int reg = 0; reg < 4; ++reg) {
-          const int rr = rt * 16 + 4 * reg + (l >> 4);
-          if ((rr >> 1) < n2) reinterpret_cast<double*>(out + lay.at(q, s, rr >> 1, n2))[rr & 1] = a[reg];
-        }
-      }
-    }
-    __syncthreads();
-  }
-}
 
 // One right-hand side on the vector units: wave d (of nine) applies block d
 // of site s with lane = row; the nine partial rows are added in order.
@@ -511,84 +382,21 @@ __device__ __forceinline__ void copy_site(int n2, size_t fs, int s, int q0, int 
   }
 }
 
-template <int NT>
-__global__ __launch_bounds__(1024) void k_coarse_apply_mfma64(Geom g, int n2, int nrhs,
-                                                              const cx<double>* __restrict__ Dc,
-                                                              const cx<double>* __restrict__ in,
-                                                              cx<double>* __restrict__ out,
-                                                              cx<double>* __restrict__ copy) {
-  __shared__ double lds[kMfma64Lds];
-  const int s = blockIdx.x;
-  if (copy) copy_site(n2, (size_t)g.vol * n2, s, 0, nrhs, in, copy);
-  apply_site_mfma64<NT>(g, n2, nrhs, s, Dc, in, out, lds, RhsMajor{(size_t)g.vol * n2});
-}
-
-// FP32: v_mfma_f32_32x32x2f32; tile = 32 real rows x 32 rhs.
-// Operand lanes: A[i][k] at lane i + 32k, B[k][j] at lane j + 32k; result
-// D[i][j] in lane j + 32 ((i / 4) % 2), register 4 (i / 8) + i % 4.
-__global__ __launch_bounds__(256) void k_coarse_apply_mfma32(Geom g, int n2, int nrhs,
-                                                             const cx<float>* __restrict__ Dc,
-                                                             const cx<float>* __restrict__ in,
-                                                             cx<float>* __restrict__ out,
-                                                             cx<float>* __restrict__ copy) {
-  const int s = blockIdx.x, q0 = blockIdx.y * 32;
-  const int wave = threadIdx.x >> 6, l = threadIdx.x & 63;
-  const size_t fs = (size_t)g.vol * n2;
-  if (copy) copy_site(n2, fs, s, q0, min(32, nrhs - q0), in, copy);
-  const int kr = 2 * n2;
-  const int r = wave * 32 + (l & 31), i = r >> 1, pr = r & 1;
-  const bool rowok = i < n2;
-  const int q = q0 + (l & 31);
-  const bool qok = q < nrhs;
-  const int kl = l >> 5;
-  int c[4];
-  coords_of(g, s, c);
-  floatx16 acc;
-#pragma unroll
-  for (int e = 0; e < 16; ++e) acc[e] = 0.f;
-  constexpr int KC = 16;  // MFMA steps loaded together
-  for (int d = 0; d < 9; ++d) {
-    const int nb = d == 8 ? s : ((d & 1) ? nbr_bwd(g, s, c, d >> 1) : nbr_fwd(g, s, c, d >> 1));
-    const float* blk = reinterpret_cast<const float*>(Dc + ((size_t)s * 9 + d) * n2 * n2);
-    const float* v = reinterpret_cast<const float*>(in + (size_t)(qok ? q : 0) * fs + (size_t)nb * n2);
-    for (int t0 = 0; 2 * t0 < kr; t0 += KC) {
-      float av[KC], bv[KC];
-#pragma unroll
-      for (int t = 0; t < KC; ++t) {
-        const int k = 2 * (t0 + t) + kl, j = k >> 1, pk = k & 1;
-        av[t] = 0.f;
-        bv[t] = 0.f;
-        if (k < kr) {
-          if (rowok) {
-            const float a = blk[2 * ((size_t)j * n2 + i) + (pr ^ pk)];
-            av[t] = (pr == 0 && pk == 1) ? -a : a;
-          }
-          if (qok) bv[t] = v[2 * j + pk];
-        }
-      }
-#pragma unroll
-      for (int t = 0; t < KC; ++t)
-        if (2 * (t0 + t) < kr) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av[t], bv[t], acc, 0, 0, 0);
-    }
-  }
-  if (qok) {
-    float* o = reinterpret_cast<float*>(out + (size_t)q * fs + (size_t)s * n2);
-#pragma unroll
-    for (int reg = 0; reg < 16; ++reg) {
-      const int rr = wave * 32 + 8 * (reg >> 2) + 4 * (l >> 5) + (reg & 3);
-      if ((rr >> 1) < n2) o[rr] = acc[reg];
-    }
-  }
-}
-
 // ---- 16-bit blocks ---------------------------------------------------------------
+// Stored [column / 4][row][column % 4] (the padding of the last columns holds
+// zeros): four consecutive columns of a row, re and im alternating, are one
+// 16-byte load and a matrix-core operand as they stand, and the lanes of
+// consecutive rows read one run of memory.
+__host__ __device__ inline int h16_chunks(int n2) { return (n2 + 3) / 4; }
+
 // One workgroup per block: scale = largest magnitude of the block's real
 // components (after rounding to FP32), stored = fl16(fl32(value * fl32(1/scale))).
 template <typename H>
 __global__ __launch_bounds__(256) void k_dc_to_half(const cx<double>* __restrict__ Dc, cxh<H>* __restrict__ Dh,
-                                                    float* __restrict__ scales, int nn) {
+                                                    float* __restrict__ scales, int n2) {
   __shared__ float red[4];
   const size_t b = blockIdx.x;
+  const int nn = n2 * n2, np = h16_chunks(n2) * n2 * 4;
   const cx<double>* src = Dc + b * nn;
   float m = 0.0f;
   bool nan = false;
@@ -610,25 +418,26 @@ __global__ __launch_bounds__(256) void k_dc_to_half(const cx<double>* __restrict
   float inv;
   const float sc = quant_scale(mm, inv);
   if (threadIdx.x == 0) scales[b] = sc;
-  for (int i = threadIdx.x; i < nn; i += blockDim.x) {
-    const cx<float> a = cvt<float>(src[i]);
-    Dh[b * nn + i] = quantise<H>(a.re, a.im, inv);
+  for (int i = threadIdx.x; i < np; i += blockDim.x) {
+    const int row = (i >> 2) % n2, col = (i >> 2) / n2 * 4 + (i & 3);
+    const cx<float> a = col < n2 ? cvt<float>(src[(size_t)col * n2 + row]) : mk(0.0f, 0.0f);
+    Dh[b * np + i] = col < n2 ? quantise<H>(a.re, a.im, inv) : f2h<H>(0.0f, 0.0f);
   }
 }
 
-// One right-hand side on the vector units (as k_coarse_apply), 16-bit blocks.
+// One right-hand side on the vector units (as k_coarse_apply), 16-bit blocks,
+// the vector in FP32.
 template <typename H>
 __global__ __launch_bounds__(576) void k_coarse_apply_h(Geom g, int n2, const cxh<H>* __restrict__ Dc,
                                                         const float* __restrict__ Dcs,
                                                         const cx<float>* __restrict__ in,
-                                                        cx<float>* __restrict__ out, cx<float>* __restrict__ copy) {
+                                                        cx<float>* __restrict__ out) {
   __shared__ cx<float> part[9][64];
   const int s = blockIdx.x, rhs = blockIdx.y;
   const int d = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const size_t nsite = g.vol;
   in += (size_t)rhs * nsite * n2;
   out += (size_t)rhs * nsite * n2;
-  if (copy && d == 8 && lane < n2) copy[(size_t)rhs * nsite * n2 + (size_t)s * n2 + lane] = in[(size_t)s * n2 + lane];
   int nb = s;
   if (d < 8) {
     int c[4];
@@ -637,9 +446,19 @@ __global__ __launch_bounds__(576) void k_coarse_apply_h(Geom g, int n2, const cx
   }
   cx<float> acc = mk(0.0f, 0.0f);
   if (lane < n2) {
-    const cxh<H>* blk = Dc + ((size_t)s * 9 + d) * n2 * n2 + lane;
+    const u4* blk = reinterpret_cast<const u4*>(Dc) + ((size_t)s * 9 + d) * h16_chunks(n2) * n2 + lane;
     const cx<float>* v = in + (size_t)nb * n2;
-    for (int j = 0; j < n2; ++j) cmadd(acc, h2f(blk[(size_t)j * n2]), v[j]);
+#pragma unroll 4
+    for (int j = 0; j < n2; j += 4) {
+      union {
+        u4 q;
+        cxh<H> v[4];
+      } x;
+      x.q = blk[(size_t)(j >> 2) * n2];
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (j + e < n2) cmadd(acc, h2f(x.v[e]), v[j + e]);
+    }
     const float sc = Dcs[(size_t)s * 9 + d];
     acc = mk(sc * acc.re, sc * acc.im);
   }
@@ -653,163 +472,230 @@ __global__ __launch_bounds__(576) void k_coarse_apply_h(Geom g, int n2, const cx
   }
 }
 
-// A batch on the matrix cores with 16-bit operands (v_mfma_f32_32x32x8 f16 or
-// bf16, FP32 accumulation).  Same real-GEMM form and tiling as the FP32
-// kernel.  Per direction, each right-hand-side column of the staged operand
-// is rounded to 16 bits: in FP16 after scaling it into [-1, 1] by its largest
-// magnitude (the format's range is narrow), in BF16 as it is (BF16 has the
-// range of FP32, so a scale would change no relative rounding error); the
-// product of that direction is accumulated from zero and added to the result
-// times the block scale (and the FP16 column scale).  Operand lanes: A[i][k] at lane
-// i + 32 (k / 4), element k % 4; B[k][j] at lane j + 32 (k / 4), element
-// k % 4; result as for the FP32 kernel.
-typedef _Float16 half4_t __attribute__((ext_vector_type(4)));
-typedef short short4_t __attribute__((ext_vector_type(4)));
+// ---- batched application on the matrix cores ---------------------------------
+// For a batch the coarse operator at one site is, per direction, a complex GEMM
+// of the (n2 x n2) block with the neighbour's n2 x nrhs values.  One workgroup
+// per site and 16 NT right-hand sides; its W waves share the nine directions,
+// every wave holding all RT = ceil(n2 / 16) row tiles, so a block entry is
+// loaded once, straight from memory into the operand's lanes, and no operand
+// passes through LDS.  The waves' sums meet in LDS at the end, in wave order.
+// Many sites: W = 3 (three directions per wave keep loads in flight while
+// products run).  Few sites: W = 9, one direction per wave.
+//
+// FP64 / FP32 (v_mfma 16x16x4): four real products per complex one; a lane
+// group supplies columns 4 g + u of a block of 16 in step u for both operands,
+// so a lane's values of one right-hand side are contiguous.
+// 16 bits (v_mfma 16x16x32): a block row's (re, im) pairs are the operand as
+// stored; the values enter twice, as (re, -im) for the real and (im, re) for
+// the imaginary part.  They are rounded to 16 bits per column and direction:
+// in FP16 after scaling the column into [-1, 1] by its largest magnitude (the
+// format's range is narrow), in BF16 as they are (it has FP32's range); the
+// direction's product is accumulated from zero and added times the block (and
+// FP16 column) scale.
+//
+// Bound: memory (the blocks once).  2592 sites, nv 24: BF16 44 us for 2 and 98
+// for 32 rhs (215 MB of blocks; a kernel with both operands staged in LDS, 134
+// and 170), FP32 95 and 162 (715 and 835), FP64 173 and 296 (808 and 1249).
+template <typename R>
+struct Mma;
+template <>
+struct Mma<double> {
+  typedef double acc_t __attribute__((ext_vector_type(4)));
+  static __device__ __forceinline__ acc_t mma(double a, double b, acc_t c) {
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+  }
+  static __device__ __forceinline__ int row(int g, int r) { return 4 * r + g; }  // of D, lane group g, register r
+};
+template <>
+struct Mma<float> {
+  typedef float acc_t __attribute__((ext_vector_type(4)));
+  static __device__ __forceinline__ acc_t mma(float a, float b, acc_t c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+  }
+  static __device__ __forceinline__ int row(int g, int r) { return 4 * g + r; }
+};
 
+template <typename R>
+struct BlocksFull {
+  using T = R;
+  static constexpr bool kHalf = false;
+  const cx<R>* Dc;
+};
 template <typename H>
-__device__ __forceinline__ floatx16 mfma_32x32x8(const float (&a)[4], const float (&b)[4], floatx16 acc);
-template <>
-__device__ __forceinline__ floatx16 mfma_32x32x8<f16_t>(const float (&a)[4], const float (&b)[4], floatx16 acc) {
-  half4_t x, y;
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    x[e] = (_Float16)a[e];
-    y[e] = (_Float16)b[e];
-  }
-  return __builtin_amdgcn_mfma_f32_32x32x8f16(x, y, acc, 0, 0, 0);
-}
-template <>
-__device__ __forceinline__ floatx16 mfma_32x32x8<bf16_t>(const float (&a)[4], const float (&b)[4], floatx16 acc) {
-  short4_t x, y;
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    x[e] = __builtin_bit_cast(short, (__bf16)a[e]);
-    y[e] = __builtin_bit_cast(short, (__bf16)b[e]);
-  }
-  return __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(x, y, acc, 0, 0, 0);
+struct BlocksHalf {
+  using T = float;
+  using Half = H;
+  static constexpr bool kHalf = true;
+  const cxh<H>* Dc;
+  const float* scale;
+};
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+template <typename H>
+__device__ __forceinline__ Mma<float>::acc_t mma32(u4 a, u4 b, Mma<float>::acc_t c) {
+  if constexpr (std::is_same<H, bf16_t>::value)
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0,
+                                                   0);
+  else
+    return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0,
+                                                  0);
 }
 
-// Per-thread staging of one direction (workgroup of 64 ceil(2 n2 / 32)
-// threads, n2 <= 64): the block's 16-byte chunks, n2^2 / 4 <= 4 per thread,
-// and the batch's rhs rows, 32 n2 <= 8 per thread.
-constexpr int kH16Chunks = 4, kH16Rows = 8;
-template <typename H, int CB = kH16Rows>  // CB: rhs rows staged per thread (>= 32 n2 / threads for the batch)
-__global__ __launch_bounds__(256) void k_coarse_apply_mfma16(Geom g, int n2, int nrhs, const cxh<H>* __restrict__ Dc,
-                                                             const float* __restrict__ Dcs,
-                                                             const cx<float>* __restrict__ in,
-                                                             cx<float>* __restrict__ out,
-                                                             cx<float>* __restrict__ copy) {
-  __shared__ float Bs[128][33];
-  __shared__ float Bsc[32], Binv[32];
-  extern __shared__ __align__(16) char dyn16[];
-  cxh<H>* As16 = reinterpret_cast<cxh<H>*>(dyn16);
-  const int s = blockIdx.x, q0 = blockIdx.y * 32;
-  const int wave = threadIdx.x >> 6, l = threadIdx.x & 63;
-  const size_t nsite = g.vol, fs = nsite * n2;
-  const int kr = 2 * n2;
+template <class B, class Lay, int RT, int NT, int W>
+__global__ __launch_bounds__(64 * W) void k_coarse_mm(Geom g, int n2, int nrhs, B blocks,
+                                                      Lay lay, const cx<typename B::T>* __restrict__ in,
+                                                      cx<typename B::T>* __restrict__ out,
+                                                      cx<typename B::T>* __restrict__ copy) {
+  using R = typename B::T;
+  using acc_t = typename Mma<R>::acc_t;
+  __shared__ acc_t part[W][NT][2][64];
+  // the right-hand-side tiles of a site run back to back on one XCD (blocks are
+  // dealt to the eight XCDs in turn), each XCD on a contiguous range of sites
+  const int ntile = (nrhs + 16 * NT - 1) / (16 * NT), per = (g.vol + 7) / 8;
+  const int s = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3) / ntile;
+  const int q0 = (int)(blockIdx.x >> 3) % ntile * 16 * NT;
+  if (s >= g.vol || (int)(blockIdx.x >> 3) >= per * ntile) return;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int li = lane & 15, lk = lane >> 4;
   int c[4];
   coords_of(g, s, c);
-  floatx16 acc;
+  acc_t re[RT][NT], im[RT][NT];
 #pragma unroll
-  for (int e = 0; e < 16; ++e) acc[e] = 0.f;
-  // rhs columns beyond the batch stay zero for every direction
-  const int nq = nrhs - q0 < 32 ? nrhs - q0 : 32;
-  for (int w = threadIdx.x; w < (32 - nq) * kr; w += blockDim.x) Bs[w % kr][nq + w / kr] = 0.f;
-  const int nthr = blockDim.x;
-  const int nch = n2 * n2 / 4;  // 16-byte chunks of a block (n2 even)
-  typedef float f2v __attribute__((ext_vector_type(2)));
-  typedef unsigned int u4v __attribute__((ext_vector_type(4)));
-  u4v ra[kH16Chunks];
-  f2v rb[CB];
-  float fsc = 0.f;  // block scale of the fetched direction
-  // Direction d + 1 is fetched into registers (every load issued before any
-  // use) while the matrix cores work on direction d from LDS.
-  auto fetch = [&](int d) {
+  for (int i = 0; i < RT; ++i)
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      re[i][t] = acc_t{0, 0, 0, 0};
+      im[i][t] = acc_t{0, 0, 0, 0};
+    }
+  for (int d = wave; d < 9; d += W) {
     const int nb = d == 8 ? s : ((d & 1) ? nbr_bwd(g, s, c, d >> 1) : nbr_fwd(g, s, c, d >> 1));
-    const u4v* blk = reinterpret_cast<const u4v*>(Dc + ((size_t)s * 9 + d) * n2 * n2);
+    // four consecutive columns of the neighbour's values of rhs 16 t + li
+    auto values = [&](int t, int col, cx<R> (&b)[4]) {
+      const int q = q0 + 16 * t + li;
 #pragma unroll
-    for (int u = 0; u < kH16Chunks; ++u) {
-      const int e = threadIdx.x + u * nthr;
-      if (e < nch) ra[u] = blk[e];
-    }
+      for (int u = 0; u < 4; ++u) {
+        const cx<R> x = in[lay.at(min(q, nrhs - 1), nb, min(col + u, n2 - 1), n2)];
+        if (copy && d == 8 && q < nrhs && col + u < n2) copy[lay.at(q, s, col + u, n2)] = x;
+        b[u] = q < nrhs && col + u < n2 ? x : mk<R>(0, 0);
+      }
+    };
+    if constexpr (!B::kHalf) {
+      const cx<R>* blk = blocks.Dc + ((size_t)s * 9 + d) * n2 * n2;
+#pragma unroll 1
+      for (int kb = 0; kb < RT; ++kb) {
+        const int col = 16 * kb + 4 * lk;
+        cx<R> b[NT][4], a[4][RT];
 #pragma unroll
-    for (int u = 0; u < CB; ++u) {
-      const int w = threadIdx.x + u * nthr;
-      if (w < nq * n2)
-        rb[u] = *reinterpret_cast<const f2v*>(in + (size_t)(q0 + w / n2) * fs + (size_t)nb * n2 + w % n2);
-    }
-    fsc = Dcs[(size_t)s * 9 + d];
-  };
-  auto stage = [&](int d) {
+        for (int u = 0; u < 4; ++u)
 #pragma unroll
-    for (int u = 0; u < kH16Chunks; ++u) {
-      const int e = threadIdx.x + u * nthr;
-      if (e < nch) reinterpret_cast<u4v*>(As16)[e] = ra[u];
-    }
+          for (int i = 0; i < RT; ++i) a[u][i] = blk[(size_t)min(col + u, n2 - 1) * n2 + min(16 * i + li, n2 - 1)];
 #pragma unroll
-    for (int u = 0; u < CB; ++u) {
-      const int w = threadIdx.x + u * nthr;
-      if (w < nq * n2) {
-        const int q = w / n2, j = w % n2;
-        Bs[2 * j][q] = rb[u].x;
-        Bs[2 * j + 1][q] = rb[u].y;
-        if (d == 8 && copy) copy[(size_t)(q0 + q) * fs + (size_t)s * n2 + j] = mk(rb[u].x, rb[u].y);
+        for (int t = 0; t < NT; ++t) values(t, col, b[t]);
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+          for (int i = 0; i < RT; ++i)
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+              re[i][t] = Mma<R>::mma(a[u][i].re, b[t][u].re, re[i][t]);
+              im[i][t] = Mma<R>::mma(a[u][i].re, b[t][u].im, im[i][t]);
+              re[i][t] = Mma<R>::mma(-a[u][i].im, b[t][u].im, re[i][t]);
+              im[i][t] = Mma<R>::mma(a[u][i].im, b[t][u].re, im[i][t]);
+            }
+      }
+    } else {
+      using H = typename B::Half;
+      const int nch = h16_chunks(n2);
+      const u4* blk = reinterpret_cast<const u4*>(blocks.Dc) + ((size_t)s * 9 + d) * nch * n2;
+      u4 a[RT][RT];
+#pragma unroll
+      for (int kb = 0; kb < RT; ++kb)
+#pragma unroll
+        for (int i = 0; i < RT; ++i) a[kb][i] = blk[(size_t)min(4 * kb + lk, nch - 1) * n2 + min(16 * i + li, n2 - 1)];
+      const float f = blocks.scale[(size_t)s * 9 + d];
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        cx<float> b[RT][4];
+#pragma unroll
+        for (int kb = 0; kb < RT; ++kb) values(t, 16 * kb + 4 * lk, b[kb]);
+        float fs16 = f, inv = 1.0f;
+        if constexpr (!std::is_same<H, bf16_t>::value) {
+          // largest magnitude of the column: this lane's values, then the four lane groups
+          float m = 0.0f;
+#pragma unroll
+          for (int kb = 0; kb < RT; ++kb)
+#pragma unroll
+            for (int u = 0; u < 4; ++u) m = fmaxf(m, fmaxf(fabsf(b[kb][u].re), fabsf(b[kb][u].im)));
+          m = fmaxf(m, __shfl_xor(m, 16, 64));
+          m = fmaxf(m, __shfl_xor(m, 32, 64));
+          fs16 = f * quant_scale(m, inv);
+        }
+        acc_t tr[RT], ti_[RT];
+#pragma unroll
+        for (int i = 0; i < RT; ++i) {
+          tr[i] = acc_t{0, 0, 0, 0};
+          ti_[i] = acc_t{0, 0, 0, 0};
+        }
+#pragma unroll
+        for (int kb = 0; kb < RT; ++kb) {
+          u4 b1, b2;  // (re, -im) and (im, re) of four columns
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            float br = b[kb][u].re, bi = b[kb][u].im;
+            if constexpr (!std::is_same<H, bf16_t>::value) {
+              br *= inv;
+              bi *= inv;
+            }
+            const unsigned w = __builtin_bit_cast(unsigned, f2h<H>(br, bi));
+            b1[u] = w ^ 0x80000000u;
+            b2[u] = (w << 16) | (w >> 16);
+          }
+#pragma unroll
+          for (int i = 0; i < RT; ++i) {
+            tr[i] = mma32<H>(a[kb][i], b1, tr[i]);
+            ti_[i] = mma32<H>(a[kb][i], b2, ti_[i]);
+          }
+        }
+        // FP16 result columns belong to right-hand side li, as the scale does
+#pragma unroll
+        for (int i = 0; i < RT; ++i)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            re[i][t][r] += fs16 * tr[i][r];
+            im[i][t][r] += fs16 * ti_[i][r];
+          }
       }
     }
-  };
-  fetch(0);
-  for (int d = 0; d < 9; ++d) {
-    __syncthreads();  // every wave is done with the previous direction's operands
-    stage(d);
-    const float fd = fsc;
-    if (d + 1 < 9) fetch(d + 1);
+  }
+  // row tile i summed over the waves by wave i % W
+#pragma unroll
+  for (int i = 0; i < RT; ++i) {
+    if (i > 0) __syncthreads();
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      part[wave][t][0][lane] = re[i][t];
+      part[wave][t][1][lane] = im[i][t];
+    }
     __syncthreads();
-    float binv = 1.0f, bsc = 1.0f;
-    if constexpr (sizeof(H) == 2 && !std::is_same<H, bf16_t>::value) {
-      if (threadIdx.x < 32) {
-        float m = 0.0f;
-        for (int k = 0; k < kr; ++k) m = fmaxf(m, fabsf(Bs[k][threadIdx.x]));
-        float inv;
-        Bsc[threadIdx.x] = quant_scale(m, inv);
-        Binv[threadIdx.x] = inv;
-      }
-      __syncthreads();
-      binv = Binv[l & 31];
-      bsc = Bsc[l & 31];
-    }
-    const int r = wave * 32 + (l & 31), i = r >> 1, pr = r & 1;
-    floatx16 t;
+    if (wave == i % W) {
 #pragma unroll
-    for (int e = 0; e < 16; ++e) t[e] = 0.f;
-    for (int k0 = 0; k0 < kr; k0 += 8) {
-      float a[4], b[4];
+      for (int t = 0; t < NT; ++t) {
+        acc_t sr = part[0][t][0][lane], si = part[0][t][1][lane];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int k = k0 + 4 * (l >> 5) + e;
-        a[e] = 0.f;
-        b[e] = 0.f;
-        if (k < kr) {
-          b[e] = Bs[k][l & 31] * binv;
-          if (i < n2) {
-            const cx<float> z = h2f(As16[(size_t)(k >> 1) * n2 + i]);
-            const int pk = k & 1;
-            a[e] = pr == 0 ? (pk == 0 ? z.re : -z.im) : (pk == 0 ? z.im : z.re);
+        for (int w = 1; w < W; ++w) {
+          sr += part[w][t][0][lane];
+          si += part[w][t][1][lane];
+        }
+        const int q = q0 + 16 * t + li;
+        if (q < nrhs) {
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int row = 16 * i + Mma<R>::row(lk, r);
+            if (row < n2) out[lay.at(q, s, row, n2)] = mk<R>(sr[r], si[r]);
           }
         }
       }
-      t = mfma_32x32x8<H>(a, b, t);
-    }
-    const float f = fd * bsc;
-#pragma unroll
-    for (int e = 0; e < 16; ++e) acc[e] += f * t[e];
-  }
-  const int q = q0 + (l & 31);
-  if (q < nrhs) {
-    float* o = reinterpret_cast<float*>(out + (size_t)q * fs + (size_t)s * n2);
-#pragma unroll
-    for (int reg = 0; reg < 16; ++reg) {
-      const int r = wave * 32 + 8 * (reg >> 2) + 4 * (l >> 5) + (reg & 3);
-      if ((r >> 1) < n2) o[r] = acc[reg];
     }
   }
 }
@@ -871,7 +757,7 @@ __global__ __launch_bounds__(1024) void k_cgcr_apply(Geom g, int n2, int nrhs, i
                                                     double* part) {
   extern __shared__ __align__(16) char dyn1[];
   double* acc = reinterpret_cast<double*>(dyn1);  // [nrhs][vals]
-  __shared__ double lds[kMfma64Lds];
+  __shared__ double lds[2 * 9 * 64];
   const int q0 = 0, nq = nrhs;
   const int wave = threadIdx.x >> 6, nw = blockDim.x >> 6, lane = threadIdx.x & 63;
   const size_t fs = (size_t)g.vol * n2, bs = (size_t)nrhs * fs;
@@ -1022,6 +908,9 @@ __global__ __launch_bounds__(256) void k_cgcr_update(size_t n, int nrhs, int j, 
 // ---- the same solve for a batch of rhs in the rhs-fast layout ---------------
 // Vectors of the batch are stored [site][row][rhs] for the whole solve, so the
 // matrix-core operand of one row and 16 rhs is one contiguous 256-byte run.
+// K1 is the batched operator above: 113 us at 2304 sites, nv 24, 16 rhs (135 us
+// for a kernel that staged both operands in LDS), 12.7 us (14.4) at 162 sites,
+// nv 16.
 // Threads of a workgroup form a (rows x nrhs) grid, thread t handling rhs
 // t % nrhs at positions (site, row) t / nrhs, t / nrhs + R, ... of the
 // workgroup's chunk; sums over those positions meet in LDS, per rhs.
@@ -1099,173 +988,6 @@ __global__ __launch_bounds__(256) void k_cgcrT_out(size_t npos, int nrhs, const 
   const size_t p = e / nrhs;
   const int q = (int)(e % nrhs);
   x[(size_t)q * npos + p] = xT[e];
-}
-
-// K1 (rhs-fast): w_j = D_c r and z_j = r at one site per workgroup.
-template <int NT>
-__global__ __launch_bounds__(1024) void k_cgcrT_apply(Geom g, int n2, int nrhs, const cx<double>* __restrict__ Dc,
-                                                     const cx<double>* __restrict__ r, cx<double>* __restrict__ w,
-                                                     cx<double>* __restrict__ z) {
-  __shared__ double lds[kMfma64Lds];
-  const int s = blockIdx.x;
-  const size_t o = (size_t)s * n2 * nrhs;
-  for (int e = threadIdx.x; e < n2 * nrhs; e += blockDim.x) z[o + e] = r[o + e];
-  apply_site_mfma64<NT>(g, n2, nrhs, s, Dc, r, w, lds, RhsFast{nrhs});
-}
-
-// K1 (rhs-fast) with both operands staged through LDS: one workgroup per
-// site, split into ng direction groups of nrt x ntile waves; wave (rt, tt) of
-// group g owns real rows 16 rt.. and rhs 16 tt.. of w for the directions
-// g, g + ng, ...  Each group fetches the block of its next direction and the
-// neighbour's n2 x nrhs rows (contiguous in the rhs-fast layout) into
-// registers with 16-byte loads while the matrix cores work on its current
-// direction from LDS, so the product loop issues no global loads.  The
-// groups' partial tiles are added through LDS at the end (one group: none).
-// Block columns are padded to ldc = 8 (mod 16) complex so the two columns one
-// MFMA operand fetch touches fall in disjoint bank halves.  Needs n2 % 8 == 0.
-// Staging registers hold complex numbers as a clang vector of two doubles: an
-// array of HIP's double2 class is not promoted to registers (it lands in
-// scratch memory, whose stores wait for the loads and serialise the prefetch).
-typedef double dbl2 __attribute__((ext_vector_type(2)));
-constexpr int kStageA = 8;  // most complex of a block staged per thread (n2 <= 64)
-constexpr int kStageB = 2;  // complex of the rhs rows staged per thread
-__host__ __device__ inline int cgcr_ldc(int n2) {
-  int l = n2;
-  while ((l & 15) != 8) ++l;
-  return l;
-}
-// LDS of one direction group's operands, and of the whole workgroup
-__host__ __device__ inline size_t cgcr_group_bytes(int n2, int nrhs) {
-  return ((size_t)n2 * cgcr_ldc(n2) + (size_t)n2 * nrhs) * 16;
-}
-__host__ __device__ inline size_t cgcr_lds_bytes(int n2, int nrhs, int ng) {
-  const size_t waves = (size_t)mfma64_row_tiles(n2) * ((nrhs + 15) / 16);
-  const size_t ops = ng * cgcr_group_bytes(n2, nrhs), part = (ng - 1) * waves * 64 * 4 * sizeof(double);
-  return ops > part ? ops : part;
-}
-// (the smaller stagings keep to 80 registers so that two 12-wave workgroups
-// share a compute unit)
-template <int SA>  // complex of the block staged per thread (n2^2 <= SA x group threads)
-__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(SA <= 4 ? 6 : 4))) void k_cgcrT_apply_lds(
-    Geom g, int n2, int nrhs, int ng, const cx<double>* __restrict__ Dc, const cx<double>* __restrict__ r,
-    cx<double>* __restrict__ w, cx<double>* __restrict__ z) {
-  extern __shared__ __align__(16) char dyn4[];
-  const int ldc = cgcr_ldc(n2), nrt = mfma64_row_tiles(n2);
-  const int wg = nrt * ((nrhs + 15) / 16);  // waves per group
-  const int nthr = 64 * wg;                 // threads per group
-  const int l = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int grp = wave / wg, wv = wave % wg, tid = threadIdx.x - grp * nthr;
-  const int rt = wv % nrt, tt = wv / nrt;
-  dbl2* al = reinterpret_cast<dbl2*>(dyn4 + grp * cgcr_group_bytes(n2, nrhs));  // [n2 cols][ldc]
-  dbl2* bl = al + (size_t)n2 * ldc;                                              // [n2 rows][nrhs]
-  const int s = blockIdx.x;
-  const int nblk = n2 * n2, nb2 = n2 * nrhs;
-  const size_t o = (size_t)s * nb2;
-  for (int e = threadIdx.x; e < nb2; e += blockDim.x) z[o + e] = r[o + e];
-  int c[4];
-  coords_of(g, s, c);
-  // staging slots: block element e = tid + u nthr (column-major) goes to
-  // column e / n2, row e % n2; loads past the end re-read the last element
-  dbl2 sa[SA], sb[kStageB];
-  auto fetch = [&](int d) {
-    const int nb = d == 8 ? s : ((d & 1) ? nbr_bwd(g, s, c, d >> 1) : nbr_fwd(g, s, c, d >> 1));
-    const dbl2* blk = reinterpret_cast<const dbl2*>(Dc + ((size_t)s * 9 + d) * nblk);
-    const dbl2* rows = reinterpret_cast<const dbl2*>(r + (size_t)nb * nb2);
-#pragma unroll
-    for (int u = 0; u < SA; ++u) sa[u] = blk[min(tid + u * nthr, nblk - 1)];
-#pragma unroll
-    for (int u = 0; u < kStageB; ++u) sb[u] = rows[min(tid + u * nthr, nb2 - 1)];
-  };
-  auto stage = [&]() {
-#pragma unroll
-    for (int u = 0; u < SA; ++u) {
-      const int e = tid + u * nthr, col = e / n2;
-      if (e < nblk) al[col * ldc + (e - col * n2)] = sa[u];
-    }
-#pragma unroll
-    for (int u = 0; u < kStageB; ++u)
-      if (tid + u * nthr < nb2) bl[tid + u * nthr] = sb[u];
-  };
-  // lane roles of the 16x16x4 product: A row rr, B column q, k = 4 t + kl
-  const int rr = rt * 16 + (l & 15), kl = l >> 4;
-  const int i = min(rr >> 1, n2 - 1), pr = rr & 1, pk = kl & 1, jl = kl >> 1;
-  const int q = tt * 16 + (l & 15), qc = min(q, nrhs - 1);
-  // real entry (rr, k) of the complex block: Re or Im of element (i, j), the
-  // sign bit flipped for row pr = 0, column pk = 1 (-Im)
-  const unsigned long long sgn = (pr == 0 && pk == 1) ? 0x8000000000000000ull : 0ull;
-  const double* pa = reinterpret_cast<const double*>(al) + 2 * (jl * ldc + i) + (pr ^ pk);
-  const double* pb = reinterpret_cast<const double*>(bl) + 2 * (jl * nrhs + qc) + pk;
-  const int sa4 = 4 * ldc, sb4 = 4 * nrhs;  // doubles per step of t (j += 2)
-  const int nk = n2 / 2;
-  doublex4 acc = doublex4{0.0, 0.0, 0.0, 0.0};
-  const int rounds = (9 + ng - 1) / ng;
-  if (grp < 9) {
-    fetch(grp);
-    stage();
-  }
-  __syncthreads();
-  for (int k = 0; k < rounds; ++k) {
-    const int d = grp + k * ng, dn = d + ng;
-    if (dn < 9) fetch(dn);
-    if (d < 9) {
-      for (int t = 0; t < nk; t += 4) {
-        double av[4], bv[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          av[u] = __longlong_as_double(__double_as_longlong(pa[(t + u) * sa4]) ^ sgn);
-          bv[u] = pb[(t + u) * sb4];
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av[u], bv[u], acc, 0, 0, 0);
-      }
-    }
-    if (k + 1 < rounds) {
-      __syncthreads();  // every wave of the group is done with direction d
-      if (dn < 9) stage();
-      __syncthreads();
-    }
-  }
-  if (ng > 1) {  // groups 1.. hand their tiles to group 0 (in group order)
-    double* part = reinterpret_cast<double*>(dyn4);
-    __syncthreads();
-    if (grp > 0) {
-      double* dst = part + ((size_t)((grp - 1) * wg + wv) * 64 + l) * 4;
-#pragma unroll
-      for (int reg = 0; reg < 4; ++reg) dst[reg] = acc[reg];
-    }
-    __syncthreads();
-    if (grp == 0) {
-      for (int gg = 1; gg < ng; ++gg) {
-        const double* src = part + ((size_t)((gg - 1) * wg + wv) * 64 + l) * 4;
-#pragma unroll
-        for (int reg = 0; reg < 4; ++reg) acc[reg] += src[reg];
-      }
-    }
-  }
-  if (grp == 0 && q < nrhs) {
-#pragma unroll
-    for (int reg = 0; reg < 4; ++reg) {
-      const int row = rt * 16 + 4 * reg + (l >> 4);
-      if ((row >> 1) < n2) reinterpret_cast<double*>(w + ((size_t)s * n2 + (row >> 1)) * nrhs + q)[row & 1] = acc[reg];
-    }
-  }
-}
-
-// The staged K1 needs n2 % 8 == 0 and a group's block and waves within the
-// staging registers.  Direction groups: one when the grid has several sites
-// per compute unit (workgroups then overlap each other's loads), else the
-// most of 3, 2 that fit 16 waves and the LDS limit.
-constexpr int kCgcrStagedMinSites = 1024;
-constexpr size_t kCgcrStagedLds = 128 * 1024;
-inline int cgcr_staged_groups(int n2, int nrhs, long long nsite) {
-  const int wg = mfma64_row_tiles(n2) * ((nrhs + 15) / 16);
-  if (n2 % 8 != 0 || n2 > 64 || wg > 16 || n2 * n2 > kStageA * 64 * wg || n2 * nrhs > kStageB * 64 * wg ||
-      cgcr_lds_bytes(n2, nrhs, 1) > kCgcrStagedLds)
-    return 0;
-  if (nsite < kCgcrStagedMinSites)
-    for (int ng = 3; ng >= 2; --ng)
-      if (ng * wg <= 16 && cgcr_lds_bytes(n2, nrhs, ng) <= kCgcrStagedLds) return ng;
-  return 1;
 }
 
 // Dots (rhs-fast): partial c_i = <W_i, w>, d_i = <W_i, r> (i < j) and
@@ -1385,6 +1107,50 @@ __global__ __launch_bounds__(256) void k_cgcrT_combine(size_t npos, int nrhs, in
   }
 }
 
+template <int RT, int NT, int W, class B, class Lay>
+void launch_coarse_mm(Ctx& c, const Level& cl, const B& blocks, const Lay& lay, const cx<typename B::T>* in,
+                      cx<typename B::T>* out, cx<typename B::T>* copy, int nrhs) {
+  hipLaunchKernelGGL((k_coarse_mm<B, Lay, RT, NT, W>), dim3(8 * ((cl.nsite + 7) / 8) * ((nrhs + 16 * NT - 1) / (16 * NT))),
+                     dim3(64 * W), 0, c.stream, cl.g, cl.dof, nrhs, blocks, lay, in, out, copy);
+}
+
+// out = D_c in for a batch, and copy = in where given (dof <= 64).
+template <class B, class Lay>
+void coarse_mm(Ctx& c, const Level& cl, const B& blocks, const Lay& lay, const cx<typename B::T>* in,
+               cx<typename B::T>* out, cx<typename B::T>* copy, int nrhs) {
+  // Two tiles of right-hand sides per workgroup halve the reads of the blocks
+  // but leave half the workgroups: they pay where FP32 accumulators leave room
+  // for them and the sites alone fill the chip (nv 24, 32 rhs, 2592 sites: BF16
+  // 98 us against 114 with one tile, FP32 162 against 167, FP64 339 against
+  // 296; 256 sites, nv 20: BF16 13.0 against 12.5).  Nine waves per workgroup
+  // pay where a workgroup has a compute unit to itself (256 sites, nv 20, 16
+  // rhs: FP32 14.0 against 16.2, FP64 22.9 against 24.9; at 32 rhs FP32 25.1
+  // against 24.3).
+  const bool two = sizeof(typename B::T) == 4 && nrhs > 16 && cl.nsite >= 4 * c.ncu;
+  const bool nine = (long long)cl.nsite * ((nrhs + 15) / 16) <= c.ncu;
+#define MM(RT)                                                                    \
+  do {                                                                            \
+    if (nine) {                                                                   \
+      launch_coarse_mm<RT, 1, 9>(c, cl, blocks, lay, in, out, copy, nrhs);        \
+    } else {                                                                      \
+      if constexpr (sizeof(typename B::T) == 4)                                   \
+        if (two) {                                                                \
+          launch_coarse_mm<RT, 2, 3>(c, cl, blocks, lay, in, out, copy, nrhs);    \
+          break;                                                                  \
+        }                                                                         \
+      launch_coarse_mm<RT, 1, 3>(c, cl, blocks, lay, in, out, copy, nrhs);        \
+    }                                                                             \
+  } while (0)
+  switch ((cl.dof + 15) / 16) {
+    case 1: MM(1); break;
+    case 2: MM(2); break;
+    case 3: MM(3); break;
+    default: MM(4); break;
+  }
+#undef MM
+  WDMG_HIP(hipGetLastError());
+}
+
 template <typename R>
 __global__ void k_coarse_shift(cx<R>* Dc, int nsite, int n2, double dm) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -1424,35 +1190,16 @@ void coarse_buildC(Ctx& c, const Level& f, Level& cl) {
 }
 
 template <typename R>
-void coarse_apply(Ctx& c, const Level& cl, const cx<R>* Dc, cx<R>* out, const cx<R>* in, int nrhs, cx<R>* copy) {
-  const int n2 = cl.dof;
-  if (nrhs >= kMfmaMinRhs && n2 <= 64) {
-    // matrix-core path for a batch of right-hand sides
-    if constexpr (sizeof(R) == 8) {
-      ProfScope ps(c, WDMG_K_DC_MFMA_F64, (long long)cl.nsite * nrhs);
-      const int waves = mfma64_row_tiles(n2) * mfma64_groups(n2);
-      const dim3 grid(cl.nsite), block(64 * waves);
-      switch ((nrhs + 15) / 16) {
-        case 1: hipLaunchKernelGGL(k_coarse_apply_mfma64<1>, grid, block, 0, c.stream, cl.g, n2, nrhs, Dc, in, out, copy); break;
-        case 2: hipLaunchKernelGGL(k_coarse_apply_mfma64<2>, grid, block, 0, c.stream, cl.g, n2, nrhs, Dc, in, out, copy); break;
-        case 3: hipLaunchKernelGGL(k_coarse_apply_mfma64<3>, grid, block, 0, c.stream, cl.g, n2, nrhs, Dc, in, out, copy); break;
-        default: hipLaunchKernelGGL(k_coarse_apply_mfma64<kMaxTiles>, grid, block, 0, c.stream, cl.g, n2, nrhs, Dc, in, out, copy); break;
-      }
-    } else {
-      ProfScope ps(c, WDMG_K_DC_MFMA_F32, (long long)cl.nsite * nrhs);
-      const int waves = (2 * n2 + 31) / 32;
-      hipLaunchKernelGGL(k_coarse_apply_mfma32, dim3(cl.nsite, (nrhs + 31) / 32), dim3(64 * waves), 0, c.stream,
-                         cl.g, n2, nrhs, Dc, in, out, copy);
-    }
-    WDMG_HIP(hipGetLastError());
-    c.n_Dc[cl.l] += nrhs;
+void coarse_apply(Ctx& c, const Level& cl, const cx<R>* Dc, cx<R>* out, const cx<R>* in, int nrhs) {
+  c.n_Dc[cl.l] += nrhs;
+  if (nrhs >= kMfmaMinRhs && cl.dof <= 64) {
+    ProfScope ps(c, sizeof(R) == 8 ? WDMG_K_DC_MFMA_F64 : WDMG_K_DC_MFMA_F32, (long long)cl.nsite * nrhs);
+    coarse_mm(c, cl, BlocksFull<R>{Dc}, RhsMajor{(size_t)cl.nsite * cl.dof}, in, out, nullptr, nrhs);
     return;
   }
   ProfScope ps(c, sizeof(R) == 8 ? WDMG_K_DC_F64 : WDMG_K_DC_F32, (long long)cl.nsite * nrhs);
-  hipLaunchKernelGGL((k_coarse_apply<R>), dim3(cl.nsite, nrhs), dim3(576), 0, c.stream, cl.g, cl.dof, Dc, in, out,
-                     copy);
+  hipLaunchKernelGGL((k_coarse_apply<R>), dim3(cl.nsite, nrhs), dim3(576), 0, c.stream, cl.g, cl.dof, Dc, in, out);
   WDMG_HIP(hipGetLastError());
-  c.n_Dc[cl.l] += nrhs;
 }
 
 void coarse_shift(Ctx& c, Level& cl, double dm) {
@@ -1469,7 +1216,7 @@ void coarse_shift(Ctx& c, Level& cl, double dm) {
 
 void ensure_dc16(Ctx& c, Level& cl, int kind) {
   const int n2 = cl.dof;
-  const size_t nblk = (size_t)cl.nsite * 9, nn = (size_t)n2 * n2;
+  const size_t nblk = (size_t)cl.nsite * 9, nn = (size_t)h16_chunks(n2) * n2 * 4;
   if (cl.dc16_kind != kind) {
     if (!cl.Dc64) throw Error(WDMG_ERR_ARG, "FP64 coarse blocks released by wdmg_release_unused");
     if (!cl.Dc16) {
@@ -1478,54 +1225,36 @@ void ensure_dc16(Ctx& c, Level& cl, int kind) {
     }
     if (kind == WDMG_F16)
       hipLaunchKernelGGL((k_dc_to_half<f16_t>), dim3((unsigned)nblk), dim3(256), 0, c.stream, cl.Dc64,
-                         static_cast<cxh<f16_t>*>(cl.Dc16), cl.Dc16s, (int)nn);
+                         static_cast<cxh<f16_t>*>(cl.Dc16), cl.Dc16s, n2);
     else
       hipLaunchKernelGGL((k_dc_to_half<bf16_t>), dim3((unsigned)nblk), dim3(256), 0, c.stream, cl.Dc64,
-                         static_cast<cxh<bf16_t>*>(cl.Dc16), cl.Dc16s, (int)nn);
+                         static_cast<cxh<bf16_t>*>(cl.Dc16), cl.Dc16s, n2);
     WDMG_HIP(hipGetLastError());
     cl.dc16_kind = kind;
   }
 }
 
-void coarse_apply_h(Ctx& c, Level& cl, int kind, cx<float>* out, const cx<float>* in, int nrhs, cx<float>* copy) {
-  const int n2 = cl.dof;
-  const size_t nn = (size_t)n2 * n2;
-  ensure_dc16(c, cl, kind);
-  if (nrhs >= kMfmaMinRhs && n2 <= 64) {
+template <typename H>
+void coarse_apply_16(Ctx& c, Level& cl, cx<float>* out, const cx<float>* in, int nrhs) {
+  const cxh<H>* d16 = static_cast<const cxh<H>*>(cl.Dc16);
+  if (nrhs >= kMfmaMinRhs && cl.dof <= 64) {
     ProfScope ps(c, WDMG_K_DC_MFMA_H, (long long)cl.nsite * nrhs);
-    const int waves = (2 * n2 + 31) / 32;
-    const size_t lds = nn * 4;
-    // small batches stage at most two rhs rows per thread (fewer registers)
-    const bool few = (nrhs < 32 ? nrhs : 32) * n2 <= 2 * 64 * waves;
-    const dim3 grid(cl.nsite, (nrhs + 31) / 32), block(64 * waves);
-    if (kind == WDMG_F16) {
-      const auto* d16 = static_cast<const cxh<f16_t>*>(cl.Dc16);
-      if (few)
-        hipLaunchKernelGGL((k_coarse_apply_mfma16<f16_t, 2>), grid, block, lds, c.stream, cl.g, n2, nrhs, d16,
-                           cl.Dc16s, in, out, copy);
-      else
-        hipLaunchKernelGGL((k_coarse_apply_mfma16<f16_t>), grid, block, lds, c.stream, cl.g, n2, nrhs, d16, cl.Dc16s,
-                           in, out, copy);
-    } else {
-      const auto* d16 = static_cast<const cxh<bf16_t>*>(cl.Dc16);
-      if (few)
-        hipLaunchKernelGGL((k_coarse_apply_mfma16<bf16_t, 2>), grid, block, lds, c.stream, cl.g, n2, nrhs, d16,
-                           cl.Dc16s, in, out, copy);
-      else
-        hipLaunchKernelGGL((k_coarse_apply_mfma16<bf16_t>), grid, block, lds, c.stream, cl.g, n2, nrhs, d16,
-                           cl.Dc16s, in, out, copy);
-    }
-  } else {
-    ProfScope ps(c, WDMG_K_DC_H, (long long)cl.nsite * nrhs);
-    if (kind == WDMG_F16)
-      hipLaunchKernelGGL((k_coarse_apply_h<f16_t>), dim3(cl.nsite, nrhs), dim3(576), 0, c.stream, cl.g, n2,
-                         static_cast<const cxh<f16_t>*>(cl.Dc16), cl.Dc16s, in, out, copy);
-    else
-      hipLaunchKernelGGL((k_coarse_apply_h<bf16_t>), dim3(cl.nsite, nrhs), dim3(576), 0, c.stream, cl.g, n2,
-                         static_cast<const cxh<bf16_t>*>(cl.Dc16), cl.Dc16s, in, out, copy);
+    coarse_mm(c, cl, BlocksHalf<H>{d16, cl.Dc16s}, RhsMajor{(size_t)cl.nsite * cl.dof}, in, out, nullptr, nrhs);
+    return;
   }
+  ProfScope ps(c, WDMG_K_DC_H, (long long)cl.nsite * nrhs);
+  hipLaunchKernelGGL((k_coarse_apply_h<H>), dim3(cl.nsite, nrhs), dim3(576), 0, c.stream, cl.g, cl.dof, d16, cl.Dc16s,
+                     in, out);
   WDMG_HIP(hipGetLastError());
+}
+
+void coarse_apply_h(Ctx& c, Level& cl, int kind, cx<float>* out, const cx<float>* in, int nrhs) {
+  ensure_dc16(c, cl, kind);
   c.n_Dc[cl.l] += nrhs;
+  if (kind == WDMG_F16)
+    coarse_apply_16<f16_t>(c, cl, out, in, nrhs);
+  else
+    coarse_apply_16<bf16_t>(c, cl, out, in, nrhs);
 }
 
 void coarsest_gcr(Ctx& c, Level& L, cx<double>* x, const cx<double>* b, int nrhs, double tol, int k, int maxit) {
@@ -1534,19 +1263,12 @@ void coarsest_gcr(Ctx& c, Level& L, cx<double>* x, const cx<double>* b, int nrhs
   double* gb = c.dsc + gcr_base(L.l);
   CgcrState S{gb + G_H, gb + G_NRM, gb + G_A, gb + G_RN, gb + G_ACT, gb + G_TOL};
   const int g1 = L.nsite < kCgcrG1 ? L.nsite : kCgcrG1;
-  const int waves = mfma64_row_tiles(n2) * mfma64_groups(n2);
-  const int form = c.tune_force[WDMG_TUNE_COARSE_APPLY];
-  const int sgroups = nrhs >= 2 && form != 0 ? cgcr_staged_groups(n2, nrhs, L.nsite) : 0;
   if (nrhs == 1 && (size_t)(4 * k + 4) * sizeof(double) > 96 * 1024)
     throw Error(WDMG_ERR_ARG, "coarse_restart too long (LDS)");
   static bool lds_attr = false;
-  if (!lds_attr) {  // the single-rhs K1 keeps 4 j + 4 partial sums in LDS, the staged one a block
+  if (!lds_attr) {  // the single-rhs K1 keeps 4 j + 4 partial sums in LDS
     WDMG_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_cgcr_apply),
                                  hipFuncAttributeMaxDynamicSharedMemorySize, 96 * 1024));
-    for (const void* f : {reinterpret_cast<const void*>(&k_cgcrT_apply_lds<2>),
-                          reinterpret_cast<const void*>(&k_cgcrT_apply_lds<4>),
-                          reinterpret_cast<const void*>(&k_cgcrT_apply_lds<kStageA>)})
-      WDMG_HIP(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kCgcrStagedLds));
     lds_attr = true;
   }
   // a batch keeps its vectors rhs-fast for the whole solve (x in L.xT)
@@ -1594,32 +1316,7 @@ void coarsest_gcr(Ctx& c, Level& L, cx<double>* x, const cx<double>* b, int nrhs
     if (fast) {
       {
         ProfScope ps(c, WDMG_K_COARSE_GCR, (long long)L.nsite * nrhs);
-        const dim3 grid(L.nsite);
-        if (sgroups) {
-          const int nthr = 64 * mfma64_row_tiles(n2) * ((nrhs + 15) / 16);
-          const size_t lb = cgcr_lds_bytes(n2, nrhs, sgroups);
-          const dim3 block(nthr * sgroups);
-          if (n2 * n2 <= 2 * nthr)
-            hipLaunchKernelGGL(k_cgcrT_apply_lds<2>, grid, block, lb, c.stream, L.g, n2, nrhs, sgroups, L.Dc64, r, w,
-                               z);
-          else if (n2 * n2 <= 4 * nthr)
-            hipLaunchKernelGGL(k_cgcrT_apply_lds<4>, grid, block, lb, c.stream, L.g, n2, nrhs, sgroups, L.Dc64, r, w,
-                               z);
-          else
-            hipLaunchKernelGGL(k_cgcrT_apply_lds<kStageA>, grid, block, lb, c.stream, L.g, n2, nrhs, sgroups, L.Dc64,
-                               r, w, z);
-        } else {
-          const dim3 block(64 * waves);
-          switch ((nrhs + 15) / 16) {
-            case 1: hipLaunchKernelGGL(k_cgcrT_apply<1>, grid, block, 0, c.stream, L.g, n2, nrhs, L.Dc64, r, w, z); break;
-            case 2: hipLaunchKernelGGL(k_cgcrT_apply<2>, grid, block, 0, c.stream, L.g, n2, nrhs, L.Dc64, r, w, z); break;
-            case 3: hipLaunchKernelGGL(k_cgcrT_apply<3>, grid, block, 0, c.stream, L.g, n2, nrhs, L.Dc64, r, w, z); break;
-            default:
-              hipLaunchKernelGGL(k_cgcrT_apply<kMaxTiles>, grid, block, 0, c.stream, L.g, n2, nrhs, L.Dc64, r, w, z);
-              break;
-          }
-        }
-        WDMG_HIP(hipGetLastError());
+        coarse_mm(c, L, BlocksFull<double>{L.Dc64}, RhsFast{nrhs}, r, w, z, nrhs);  // also z = r
       }
       hipLaunchKernelGGL(k_cgcrT_dots, dim3(g1f), dim3(256), 0, c.stream, npos, nrhs, j, vals, L.basisW, w, r,
                          L.cpart);
@@ -1675,9 +1372,7 @@ size_t coarsest_gcr_partials(int nrhs, int k) {
 size_t coarsest_gcr_history(int nrhs, int k) { return (size_t)nrhs * k * (2 * (size_t)k + 4); }
 size_t coarsest_gcr_partials3(int nrhs) { return (size_t)nrhs * (kCgcrG3T > kCgcrG3 ? kCgcrG3T : kCgcrG3); }
 
-template void coarse_apply<double>(Ctx&, const Level&, const cx<double>*, cx<double>*, const cx<double>*, int,
-                                   cx<double>*);
-template void coarse_apply<float>(Ctx&, const Level&, const cx<float>*, cx<float>*, const cx<float>*, int,
-                                  cx<float>*);
+template void coarse_apply<double>(Ctx&, const Level&, const cx<double>*, cx<double>*, const cx<double>*, int);
+template void coarse_apply<float>(Ctx&, const Level&, const cx<float>*, cx<float>*, const cx<float>*, int);
 
 }  // namespace wdmg

@@ -392,10 +392,9 @@ void block_qrC(Ctx& c, const Level& f, cx<double>* V);
 // Coarse operator (coarse.hip).
 void coarse_build0(Ctx& c, const Level& f, Level& cl);
 void coarse_buildC(Ctx& c, const Level& f, Level& cl);
-// out = D_c in; when copy is given, copy = in as well (one pass).
+// out = D_c in.
 template <typename R>
-void coarse_apply(Ctx& c, const Level& cl, const cx<R>* Dc, cx<R>* out, const cx<R>* in, int nrhs,
-                  cx<R>* copy = nullptr);
+void coarse_apply(Ctx& c, const Level& cl, const cx<R>* Dc, cx<R>* out, const cx<R>* in, int nrhs);
 void coarse_shift(Ctx& c, Level& cl, double dm);
 // The 16-bit blocks of kind (WDMG_F16 / WDMG_BF16) of coarse level cl, made
 // from its FP64 blocks unless already current.
@@ -416,7 +415,6 @@ size_t coarsest_gcr_partials3(int nrhs);
 size_t coarsest_gcr_history(int nrhs, int k);
 // out = D_c in with the blocks stored in 16-bit (one scale per block), FP32
 // vectors; the 16-bit blocks are made from the FP64 ones on first use.
-void coarse_apply_h(Ctx& c, Level& cl, int kind, cx<float>* out, const cx<float>* in, int nrhs,
-                    cx<float>* copy = nullptr);
+void coarse_apply_h(Ctx& c, Level& cl, int kind, cx<float>* out, const cx<float>* in, int nrhs);
 
 }  // namespace wdmg

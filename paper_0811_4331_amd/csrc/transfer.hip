@@ -909,7 +909,7 @@ void restrictC(Ctx& c, const Level& f, const cx<R>* V, const cx<R>* in, cx<R>* o
 
 // The matrix-core prolongation where it applies: level 0, aggregates of whole
 // units, at most 32 columns.  24^3x48, nv 24, FP32, 16 rhs: 557 us, against
-// 3116 us of the vector-unit kernel, which reads V once per RB = 4 rhs.
+// 3116 us of the vector-unit kernel, which reads V once per RB rhs.
 inline bool pm_fits(const Level& f) { return f.dof == 12 && make_map(f).bvol % kPmSites == 0 && f.nv <= 32; }
 
 template <class VL, class OUT>

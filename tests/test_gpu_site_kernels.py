@@ -144,3 +144,33 @@ def test_buffers_aligned_to_one_number():
     ctx.apply_D_noalloc(off(psi), out, prec="f32")
     assert torch.equal(out, ctx.apply_D(psi, prec="f32"))
     ctx.close()
+
+
+@pytest.mark.parametrize("dims,blk,nv,nrhs", [
+    ((4, 4, 4, 4), (2, 2, 2, 2), 1, 2),       # two rows; the sites are each other's neighbours
+    ((8, 8, 4, 8), (4, 4, 4, 4), 8, 16),      # one whole row tile, one whole tile of right-hand sides
+    ((8, 8, 8, 8), (4, 4, 4, 4), 9, 17),      # one row, one column and one right-hand side over
+    ((8, 8, 8, 16), (4, 4, 4, 4), 32, 33),    # the most rows
+    ((16, 16, 16, 16), (2, 2, 2, 4), 5, 35),  # sites enough for two tiles per workgroup, the last one ragged
+    ((8, 12, 12, 20), (2, 2, 2, 2), 3, 16),   # 720 sites: three waves, one tile
+])
+def test_batched_coarse_operator_at_tile_edges(dims, blk, nv, nrhs):
+    """A batch on the matrix cores against one right-hand side at a time on the
+    vector units.  Both sum 9 x 2 Nv <= 576 complex products: 2e-6 (1e-13 in
+    FP64) of the largest result covers either order.  With 16-bit blocks the
+    batch also rounds its vectors, by at most one half unit of the column's
+    largest number each: errors of random sign, under 16 half units of the
+    largest result."""
+    ctx, _ = context(dims, 931)
+    lx, ly, lz, lt = dims
+    v = synthetic.gaussian_vectors((nv, lt, lz, ly, lx, 4, 3), 930)
+    ctx.mg_setup([{"block": blk, "nv": nv, "setup_iters": 0, "vectors": gpu(v)}])
+    c = synthetic.gaussian_vectors((nrhs,) + tuple(ctx.coarse_shape(1)), 932)
+    for prec, tol in (("f64", 1e-13), ("f32", 2e-6), ("bf16", 16 * precision.HALF_ULP["bf16"]),
+                      ("f16", 16 * precision.HALF_ULP["f16"])):
+        v = gpu(c if prec == "f64" else c.astype(np.complex64))
+        out = ctx.apply_Dc(1, v, prec=prec).cpu().numpy()
+        for j in range(nrhs):
+            one = ctx.apply_Dc(1, v[j], prec=prec).cpu().numpy()
+            assert rel(out[j], one) < tol, (prec, j)
+    ctx.close()
