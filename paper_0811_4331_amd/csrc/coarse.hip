@@ -283,7 +283,8 @@ __global__ __launch_bounds__(256) void k_coarse_build(Side side, AggGeom a, cons
 // One workgroup of nine waves per (coarse site, rhs); wave d applies block d
 // (lane = row), and the nine partial rows are summed in a fixed order.
 // acc += sum_j blk[j n2] v[j]: one row of a column-major block times a
-// vector, in column order, with the loads of 8 columns issued together.
+// vector, in column order, with the loads of 8 columns issued together (20 at
+// a time is slower, 256 sites, nv 20, FP64: 11.6 against 10.6 us).
 template <typename R>
 __device__ __forceinline__ void block_row_madd(const cx<R>* __restrict__ blk, int n2, const cx<R>* v, cx<R>& acc) {
   int jj = 0;
@@ -345,17 +346,18 @@ struct RhsFast {  // [site][row][rhs]: the rhs of one row are adjacent
 
 // One right-hand side on the vector units: wave d (of nine) applies block d
 // of site s with lane = row; the nine partial rows are added in order.
-// Needs blockDim.x >= 576; ends with a block barrier.
+// Needs blockDim.x >= 576; ends with a block barrier, the result also in `res`.
 __device__ __forceinline__ void apply_site_valu1(const Geom& g, int n2, int s, const cx<double>* __restrict__ Dc,
-                                                 const cx<double>* in, cx<double>* out, double* lds) {
+                                                 const cx<double>* in, cx<double>* out, double* lds, cx<double>* res) {
   const int d = threadIdx.x >> 6, lane = threadIdx.x & 63;
   cx<double> acc = mk(0.0, 0.0);
   if (d < 9 && lane < n2) {
-    int nb = s;
-    if (d < 8) {
-      int c[4];
-      coords_of(g, s, c);
-      nb = (d & 1) ? nbr_bwd(g, s, c, d >> 1) : nbr_fwd(g, s, c, d >> 1);
+    int nb = s, c[4];
+    coords_of(g, s, c);
+#pragma unroll
+    for (int mu = 0; mu < 4; ++mu) {
+      if (d == 2 * mu) nb = nbr_fwd(g, s, c, mu);
+      if (d == 2 * mu + 1) nb = nbr_bwd(g, s, c, mu);
     }
     block_row_madd(Dc + ((size_t)s * 9 + d) * n2 * n2 + lane, n2, in + (size_t)nb * n2, acc);
   }
@@ -369,17 +371,9 @@ __device__ __forceinline__ void apply_site_valu1(const Geom& g, int n2, int s, c
 #pragma unroll
     for (int dd = 0; dd < 8; ++dd) t = t + mk(lds[2 * (dd * 64 + lane)], lds[2 * (dd * 64 + lane) + 1]);
     out[(size_t)s * n2 + lane] = t;
+    res[lane] = t;
   }
   __syncthreads();
-}
-
-// copy = in on site s for the right-hand sides [q0, q0 + nq) (all threads of the block)
-template <typename R>
-__device__ __forceinline__ void copy_site(int n2, size_t fs, int s, int q0, int nq, const cx<R>* in, cx<R>* copy) {
-  for (int w = threadIdx.x; w < nq * n2; w += blockDim.x) {
-    const int q = q0 + w / n2, j = w % n2;
-    copy[(size_t)q * fs + (size_t)s * n2 + j] = in[(size_t)q * fs + (size_t)s * n2 + j];
-  }
 }
 
 // ---- 16-bit blocks ---------------------------------------------------------------
@@ -716,6 +710,10 @@ __global__ __launch_bounds__(64 * W) void k_coarse_mm(Geom g, int n2, int nrhs, 
 // later, so it never waits for the GPU inside the solve.
 constexpr int kCgcrG1 = 4096;  // workgroups of K1 (one coarse site each up to this many sites)
 constexpr int kCgcrG3 = 64;   // chunks per rhs of K3
+// Most K1 workgroups whose partials K3 adds up by itself (256 sites, nv 20, 10
+// iterations: 6.7 us against 9.6 and a launch with K2 on its own; the partials of
+// 4096 workgroups would be 50 MB of reads).
+constexpr int kCgcrFusedG1 = 512;
 
 struct CgcrState {  // per-rhs device scalars of one solve (inside the level's scalar block)
   double* h;    // [rhs][2 kMaxKrylov]
@@ -727,10 +725,10 @@ struct CgcrState {  // per-rhs device scalars of one solve (inside the level's s
 };
 
 // x = 0, r = b, tol2 = tol^2 |b|^2, active = |b| > 0 (one workgroup per rhs)
-__global__ __launch_bounds__(256) void k_cgcr_init(const cx<double>* __restrict__ b, cx<double>* __restrict__ x,
+__global__ __launch_bounds__(1024) void k_cgcr_init(const cx<double>* __restrict__ b, cx<double>* __restrict__ x,
                                                    cx<double>* __restrict__ r, size_t n, double tol, CgcrState S,
                                                    double* err) {
-  __shared__ double red[4];
+  __shared__ double red[16];
   const int q = blockIdx.x;
   const size_t o = (size_t)q * n;
   double v[1] = {0.0};
@@ -750,47 +748,45 @@ __global__ __launch_bounds__(256) void k_cgcr_init(const cx<double>* __restrict_
 }
 
 // K1 of a single rhs: grid-stride over sites, nine waves (one per block of
-// the stencil), then the dot products of w_j with the basis and r.
-__global__ __launch_bounds__(1024) void k_cgcr_apply(Geom g, int n2, int nrhs, int j, int vals,
+// the stencil), then the dot products of w_j with the basis and r: wave t
+// takes basis vectors t, t + 9, ... and the norms come last.  w_j stays in LDS
+// for them, and a wave's first basis vector and r are on their way during the
+// product (256 sites, nv 20, ten iterations: 13.1 us, 10.6 of them the product
+// with its 59 MB of blocks; 13.6 us with w_j read back from memory).
+__global__ __launch_bounds__(576) void k_cgcr_apply(Geom g, int n2, int j, int vals,
                                                     const cx<double>* __restrict__ Dc, const cx<double>* r,
                                                     const cx<double>* Wb, cx<double>* w, cx<double>* z,
                                                     double* part) {
   extern __shared__ __align__(16) char dyn1[];
-  double* acc = reinterpret_cast<double*>(dyn1);  // [nrhs][vals]
+  double* acc = reinterpret_cast<double*>(dyn1);  // [vals]
   __shared__ double lds[2 * 9 * 64];
-  const int q0 = 0, nq = nrhs;
+  __shared__ cx<double> ws[64];
   const int wave = threadIdx.x >> 6, nw = blockDim.x >> 6, lane = threadIdx.x & 63;
-  const size_t fs = (size_t)g.vol * n2, bs = (size_t)nrhs * fs;
-  for (int t = threadIdx.x; t < nq * vals; t += blockDim.x) acc[t] = 0.0;
+  const size_t bs = (size_t)g.vol * n2;
+  const bool on = lane < n2;
+  for (int t = threadIdx.x; t < vals; t += blockDim.x) acc[t] = 0.0;
   for (int s = blockIdx.x; s < g.vol; s += gridDim.x) {
-    copy_site(n2, fs, s, q0, nq, r, z);
+    const size_t o = (size_t)s * n2 + lane;
+    const cx<double> rv = on ? r[o] : mk(0.0, 0.0);
+    cx<double> u = on && wave < j ? Wb[(size_t)wave * bs + o] : mk(0.0, 0.0);
+    if (wave == 8 && on) z[o] = rv;
     // ends with a block barrier: w_j of site s is then complete
-    apply_site_valu1(g, n2, s, Dc, r, w, lds);
-    // Dot-product tasks (rhs qq, basis vector i < j) and (qq, the four
-    // norms) spread over the waves; a task keeps its wave for every site of
-    // the loop, so each accumulator has a single writer.
-    const int per = j + 1;
-    for (int t = wave; t < nq * per; t += nw) {
-      const int qq = t / per, i = t % per;
-      const size_t o = (size_t)(q0 + qq) * fs + (size_t)s * n2 + lane;
-      cx<double> wv = mk(0.0, 0.0), rv = mk(0.0, 0.0);
-      if (lane < n2) {
-        wv = w[o];
-        rv = r[o];
-      }
-      double* aq = acc + qq * vals;
+    apply_site_valu1(g, n2, s, Dc, r, w, lds, ws);
+    const cx<double> wv = on ? ws[lane] : mk(0.0, 0.0);
+    // a basis vector keeps its wave for every site of the loop, so each
+    // accumulator has a single writer
+    for (int i = wave; i <= j; i += nw) {
       if (i < j) {
-        cx<double> u = mk(0.0, 0.0);
-        if (lane < n2) u = Wb[(size_t)i * bs + o];
+        if (i != wave) u = on ? Wb[(size_t)i * bs + o] : mk(0.0, 0.0);
         const double c_re = wave_sum(u.re * wv.re + u.im * wv.im);
         const double c_im = wave_sum(u.re * wv.im - u.im * wv.re);
         const double d_re = wave_sum(u.re * rv.re + u.im * rv.im);
         const double d_im = wave_sum(u.re * rv.im - u.im * rv.re);
         if (lane == 0) {
-          aq[2 * i] += c_re;
-          aq[2 * i + 1] += c_im;
-          aq[2 * j + 2 * i] += d_re;
-          aq[2 * j + 2 * i + 1] += d_im;
+          acc[2 * i] += c_re;
+          acc[2 * i + 1] += c_im;
+          acc[2 * j + 2 * i] += d_re;
+          acc[2 * j + 2 * i + 1] += d_im;
         }
       } else {
         const double ww = wave_sum(wv.re * wv.re + wv.im * wv.im);
@@ -798,98 +794,169 @@ __global__ __launch_bounds__(1024) void k_cgcr_apply(Geom g, int n2, int nrhs, i
         const double wr_im = wave_sum(wv.re * rv.im - wv.im * rv.re);
         const double rr = wave_sum(rv.re * rv.re + rv.im * rv.im);
         if (lane == 0) {
-          aq[4 * j] += ww;
-          aq[4 * j + 1] += wr_re;
-          aq[4 * j + 2] += wr_im;
-          aq[4 * j + 3] += rr;
+          acc[4 * j] += ww;
+          acc[4 * j + 1] += wr_re;
+          acc[4 * j + 2] += wr_im;
+          acc[4 * j + 3] += rr;
         }
       }
     }
     __syncthreads();
   }
-  for (int t = threadIdx.x; t < nq * vals; t += blockDim.x) {
-    const int qq = t / vals, v = t % vals;
-    part[((size_t)(q0 + qq) * gridDim.x + blockIdx.x) * vals + v] = acc[t];
-  }
+  for (int t = threadIdx.x; t < vals; t += blockDim.x) part[(size_t)blockIdx.x * vals + t] = acc[t];
 }
 
-// K2: one workgroup per rhs.  vals = 4 j + 4 partial values per K1 workgroup;
-// p3: K3's g3 partial |w_{j-1}|^2 per rhs (j > 0).
-// hist (batched solves, else null): per rhs and iteration j, the h_i of
-// iteration j at [2 i], a_j at [2 kmax]; stride 2 kmax + 4 doubles per j.
-__global__ __launch_bounds__(1024) void k_cgcr_coef(int j, int vals, int g1, const double* __restrict__ part,
-                                                   const double* __restrict__ p3, int g3, int kmax, CgcrState S,
-                                                   double* host_act, double* err, double* hist) {
-  extern __shared__ __align__(16) char dyn2[];
-  double* tot = reinterpret_cast<double*>(dyn2);  // [vals + 1]
-  const int q = blockIdx.x;
-  const int wave = threadIdx.x >> 6, nw = blockDim.x >> 6, lane = threadIdx.x & 63;
-  for (int v = wave; v <= vals; v += nw) {
+// K2 on T threads for rhs q.  vals = 4 j + 4 partial values per K1 workgroup;
+// p3: K3's g3 partial |w_{j-1}|^2 per rhs (j > 0).  On return h_i is in
+// hs[2 i] for every thread, and lane 0 of wave 0 has the rest.
+struct CgcrCoef {
+  cx<double> a;
+  double rr;
+  bool on, bad;
+};
+template <int T>
+__device__ __forceinline__ CgcrCoef cgcr_coef(int q, int j, int vals, int g1, const double* __restrict__ part,
+                                              const double* __restrict__ p3, int g3, int kmax, const CgcrState& S,
+                                              double* tot, double* hs) {
+  __shared__ double sub[T];  // [groups][vals]
+  const int wave = threadIdx.x >> 6, nw = T / 64, lane = threadIdx.x & 63;
+  // thread (group, value) sums every groups-th partial of its value, so that
+  // a sweep of the threads reads one run of memory; vals <= 4 kMaxKrylov <= T
+  const int groups = T / vals, v0 = threadIdx.x % vals, g0 = threadIdx.x / vals;
+  double n3 = 0.0;
+  if (wave == nw - 1 && j > 0)
+    for (int b = lane; b < g3; b += 64) n3 += p3[(size_t)q * g3 + b];
+  if (g0 < groups) {
+    const double* p = part + (size_t)q * g1 * vals + v0;
     double s = 0.0;
-    if (v < vals) {
-      for (int b = lane; b < g1; b += 64) s += part[((size_t)q * g1 + b) * vals + v];
-    } else if (j > 0) {
-      for (int b = lane; b < g3; b += 64) s += p3[(size_t)q * g3 + b];
-    }
+#pragma unroll 8
+    for (int b = g0; b < g1; b += groups) s += p[(size_t)b * vals];
+    sub[g0 * vals + v0] = s;
+  }
+  __syncthreads();
+  for (int v = wave; v < vals; v += nw) {
+    double s = 0.0;
+    for (int b = lane; b < groups; b += 64) s += sub[b * vals + v];
     s = wave_sum(s);
     if (lane == 0) tot[v] = s;
   }
+  if (wave == nw - 1) {
+    n3 = wave_sum(n3);
+    if (lane == 0) tot[vals] = n3;
+  }
   __syncthreads();
-  if (threadIdx.x != 0) return;
-  double* nrm = S.nrm + (size_t)q * kmax;
-  double* h = S.h + (size_t)q * 2 * kmax;
-  if (j > 0) nrm[j - 1] = tot[vals];
-  double ww = tot[4 * j], wr_re = tot[4 * j + 1], wr_im = tot[4 * j + 2];
-  const double rr = tot[4 * j + 3];
-  for (int i = 0; i < j; ++i) {
-    const double ni = nrm[i];
-    const double cr = tot[2 * i], ci = tot[2 * i + 1];
-    const double hr = ni > 0.0 ? cr / ni : 0.0, hi = ni > 0.0 ? ci / ni : 0.0;
-    h[2 * i] = hr;
-    h[2 * i + 1] = hi;
-    if (hist) {
-      hist[((size_t)q * kmax + j) * (2 * kmax + 4) + 2 * i] = hr;
-      hist[((size_t)q * kmax + j) * (2 * kmax + 4) + 2 * i + 1] = hi;
+  CgcrCoef c;
+  c.rr = tot[4 * j + 3];
+  double ww = 0.0, wr_re = 0.0, wr_im = 0.0;
+  if (wave == 0) {
+    const double* nrm = S.nrm + (size_t)q * kmax;
+    for (int i = lane; i < j; i += 64) {
+      const double ni = i == j - 1 ? tot[vals] : nrm[i];
+      const double cr = tot[2 * i], ci = tot[2 * i + 1];
+      const double hr = ni > 0.0 ? cr / ni : 0.0, hi = ni > 0.0 ? ci / ni : 0.0;
+      hs[2 * i] = hr;
+      hs[2 * i + 1] = hi;
+      ww += hr * cr + hi * ci;  // |c_i|^2 / |W_i|^2
+      const double dr = tot[2 * j + 2 * i], di = tot[2 * j + 2 * i + 1];
+      wr_re += hr * dr + hi * di;  // conj(h_i) d_i
+      wr_im += hr * di - hi * dr;
     }
-    ww -= hr * cr + hi * ci;  // |c_i|^2 / |W_i|^2
-    const double dr = tot[2 * j + 2 * i], di = tot[2 * j + 2 * i + 1];
-    wr_re -= hr * dr + hi * di;  // conj(h_i) d_i
-    wr_im -= hr * di - hi * dr;
+    ww = tot[4 * j] - wave_sum(ww);
+    wr_re = tot[4 * j + 1] - wave_sum(wr_re);
+    wr_im = tot[4 * j + 2] - wave_sum(wr_im);
+    if (lane == 0) {
+      sub[0] = ww;
+      sub[1] = wr_re;
+      sub[2] = wr_im;
+    }
   }
-  S.rn[q] = rr;
-  if (!isfinite(rr) || !isfinite(ww)) err[0] = 1.0;
-  const bool on = S.act[q] != 0.0 && rr > S.tol2[q];
-  const bool ok = on && ww > 1e-28 * tot[4 * j];
-  S.act[q] = on ? 1.0 : 0.0;
-  S.a[2 * q] = ok ? wr_re / ww : 0.0;
-  S.a[2 * q + 1] = ok ? wr_im / ww : 0.0;
-  if (hist) {
-    hist[((size_t)q * kmax + j) * (2 * kmax + 4) + 2 * kmax] = S.a[2 * q];
-    hist[((size_t)q * kmax + j) * (2 * kmax + 4) + 2 * kmax + 1] = S.a[2 * q + 1];
-  }
-  if (host_act) host_act[q] = on ? 1.0 : 0.0;
+  __syncthreads();
+  ww = sub[0];
+  c.bad = !isfinite(c.rr) || !isfinite(ww);
+  c.on = S.act[q] != 0.0 && c.rr > S.tol2[q];
+  const bool ok = c.on && ww > 1e-28 * tot[4 * j];
+  c.a = ok ? mk(sub[1] / ww, sub[2] / ww) : mk(0.0, 0.0);
+  return c;
 }
 
-// K3: blocks (kCgcrG3 chunks, rhs).
-__global__ __launch_bounds__(256) void k_cgcr_update(size_t n, int nrhs, int j, int kmax, const cx<double>* Wb,
-                                                     const cx<double>* Zb, cx<double>* w, cx<double>* z,
-                                                     cx<double>* x, cx<double>* r, CgcrState S, double* p3) {
-  __shared__ double red[4];
+// What K2 leaves for the host and for later iterations (one thread).
+__device__ __forceinline__ void cgcr_record(int q, int j, int kmax, const CgcrCoef& c, double n3, const CgcrState& S,
+                                            double* host_act, double* err) {
+  if (j > 0) S.nrm[(size_t)q * kmax + j - 1] = n3;
+  S.rn[q] = c.rr;
+  if (c.bad) err[0] = 1.0;
+  S.act[q] = c.on ? 1.0 : 0.0;
+  S.a[2 * q] = c.a.re;
+  S.a[2 * q + 1] = c.a.im;
+  if (host_act) host_act[q] = c.on ? 1.0 : 0.0;
+}
+
+// K2 of its own, one workgroup per rhs.
+// hist (batched solves, else null): per rhs and iteration j, the h_i of
+// iteration j at [2 i], a_j at [2 kmax]; stride 2 kmax + 4 doubles per j.
+__global__ __launch_bounds__(1024) void k_cgcr_coef(int j, int vals, int g1, const double* __restrict__ part,
+                                                    const double* __restrict__ p3, int g3, int kmax, CgcrState S,
+                                                    double* host_act, double* err, double* hist) {
+  extern __shared__ __align__(16) char dyn2[];
+  double* tot = reinterpret_cast<double*>(dyn2);  // [vals + 1]
   __shared__ double hs[2 * kMaxKrylov];
+  const int q = blockIdx.x;
+  const CgcrCoef c = cgcr_coef<1024>(q, j, vals, g1, part, p3, g3, kmax, S, tot, hs);
+  double* h = S.h + (size_t)q * 2 * kmax;
+  double* hj = hist ? hist + ((size_t)q * kmax + j) * (2 * kmax + 4) : nullptr;
+  if (threadIdx.x < 2 * j) {
+    h[threadIdx.x] = hs[threadIdx.x];
+    if (hist) hj[threadIdx.x] = hs[threadIdx.x];
+  }
+  if (threadIdx.x != 0) return;
+  if (hist) {
+    hj[2 * kmax] = c.a.re;
+    hj[2 * kmax + 1] = c.a.im;
+  }
+  cgcr_record(q, j, kmax, c, tot[vals], S, host_act, err);
+}
+
+// K3: blocks (kCgcrG3 chunks, rhs); p3 and p3n: the partial |w|^2 of the
+// iteration before and of this one.  COEF (one rhs): every workgroup does K2
+// for itself first, in the same order, and the first records it -- worth a
+// launch as long as the partials are few (see kCgcrFusedG1).  The others may
+// read act before or after it is recorded: recorded, it only holds what they
+// find themselves.
+constexpr int kCgcrK3 = 512;
+template <bool COEF>
+__global__ __launch_bounds__(kCgcrK3) void k_cgcr_update(size_t n, int nrhs, int j, int kmax, const cx<double>* Wb,
+                                                         const cx<double>* Zb, cx<double>* w, cx<double>* z,
+                                                         cx<double>* x, cx<double>* r, CgcrState S, double* p3n,
+                                                         int vals, int g1, const double* __restrict__ part,
+                                                         const double* p3, double* host_act, double* err) {
+  __shared__ double red[kCgcrK3 / 64];
+  __shared__ double hs[2 * kMaxKrylov];
+  __shared__ double tot[4 * kMaxKrylov + 1];
   const int q = blockIdx.y;
-  if (S.act[q] == 0.0) {
-    if (threadIdx.x == 0) p3[(size_t)q * kCgcrG3 + blockIdx.x] = 0.0;
+  cx<double> a;
+  bool on;
+  if constexpr (COEF) {
+    const CgcrCoef c = cgcr_coef<kCgcrK3>(q, j, vals, g1, part, p3, kCgcrG3, kmax, S, tot, hs);
+    a = c.a;
+    on = c.on;
+    if (blockIdx.x == 0 && threadIdx.x == 0) cgcr_record(q, j, kmax, c, tot[vals], S, host_act, err);
+  } else {
+    on = S.act[q] != 0.0;
+    a = mk(S.a[2 * q], S.a[2 * q + 1]);
+    const double* h = S.h + (size_t)q * 2 * kmax;
+    for (int t = threadIdx.x; t < 2 * j; t += blockDim.x) hs[t] = h[t];
+    __syncthreads();
+  }
+  if (!on) {
+    if (threadIdx.x == 0) p3n[(size_t)q * kCgcrG3 + blockIdx.x] = 0.0;
     return;
   }
-  const double* h = S.h + (size_t)q * 2 * kmax;
-  for (int t = threadIdx.x; t < 2 * j; t += blockDim.x) hs[t] = h[t];
-  __syncthreads();
-  const cx<double> a = mk(S.a[2 * q], S.a[2 * q + 1]);
   const size_t bs = (size_t)nrhs * n, o = (size_t)q * n;
   const size_t cs = (n + kCgcrG3 - 1) / kCgcrG3, e0 = blockIdx.x * cs, e1 = e0 + cs < n ? e0 + cs : n;
   double v[1] = {0.0};
   for (size_t e = e0 + threadIdx.x; e < e1; e += blockDim.x) {
     cx<double> wv = w[o + e], zv = z[o + e];
+#pragma unroll 4
     for (int i = 0; i < j; ++i) {
       const cx<double> hi = mk(hs[2 * i], hs[2 * i + 1]);
       wv = wv - hi * Wb[(size_t)i * bs + o + e];
@@ -902,7 +969,7 @@ __global__ __launch_bounds__(256) void k_cgcr_update(size_t n, int nrhs, int j, 
     v[0] += wv.re * wv.re + wv.im * wv.im;
   }
   block_sum<1>(v, red);
-  if (threadIdx.x == 0) p3[(size_t)q * kCgcrG3 + blockIdx.x] = v[0];
+  if (threadIdx.x == 0) p3n[(size_t)q * kCgcrG3 + blockIdx.x] = v[0];
 }
 
 // ---- the same solve for a batch of rhs in the rhs-fast layout ---------------
@@ -1284,7 +1351,7 @@ void coarsest_gcr(Ctx& c, Level& L, cx<double>* x, const cx<double>* b, int nrhs
     hipLaunchKernelGGL(k_cgcrT_init_fin, dim3(nrhs), dim3(64), 0, c.stream, nrhs, kCgcrG3T, L.cpart3, tol, S,
                        c.dsc + S_ERR);
   } else {
-    hipLaunchKernelGGL(k_cgcr_init, dim3(nrhs), dim3(256), 0, c.stream, b, x, r, n, tol, S, c.dsc + S_ERR);
+    hipLaunchKernelGGL(k_cgcr_init, dim3(nrhs), dim3(1024), 0, c.stream, b, x, r, n, tol, S, c.dsc + S_ERR);
   }
   WDMG_HIP(hipGetLastError());
   // The active flags of iteration it land in pinned memory and are inspected
@@ -1339,18 +1406,30 @@ void coarsest_gcr(Ctx& c, Level& L, cx<double>* x, const cx<double>* b, int nrhs
     }
     {
       ProfScope ps(c, WDMG_K_COARSE_GCR, (long long)L.nsite * nrhs);
-      hipLaunchKernelGGL(k_cgcr_apply, dim3(g1), dim3(576), (size_t)vals * sizeof(double), c.stream, L.g, n2, nrhs,
-                         j, vals, L.Dc64, r, L.basisW, w, z, L.cpart);
+      hipLaunchKernelGGL(k_cgcr_apply, dim3(g1), dim3(576), (size_t)vals * sizeof(double), c.stream, L.g, n2, j, vals,
+                         L.Dc64, r, L.basisW, w, z, L.cpart);
       WDMG_HIP(hipGetLastError());
     }
-    hipLaunchKernelGGL(k_cgcr_coef, dim3(nrhs), dim3(1024), (size_t)(vals + 1) * sizeof(double), c.stream, j, vals,
-                       g1, L.cpart, L.cpart3, kCgcrG3, k, S,
-                       c.capturing ? nullptr : c.dring + (size_t)(it % kRing) * kMaxRhs, c.dsc + S_ERR, nullptr);
-    WDMG_HIP(hipGetLastError());
-    if (!c.capturing) WDMG_HIP(hipEventRecord(c.ring_ev[it % kRing], c.stream));
-    hipLaunchKernelGGL(k_cgcr_update, dim3(kCgcrG3, nrhs), dim3(256), 0, c.stream, n, nrhs, j, k, L.basisW,
-                       L.basisZ, w, z, x, r, S, L.cpart3);
-    WDMG_HIP(hipGetLastError());
+    double* host_act = c.capturing ? nullptr : c.dring + (size_t)(it % kRing) * kMaxRhs;
+    double* err = c.dsc + S_ERR;
+    // the partial |w|^2 of an iteration are read while the next one's are written
+    double* p3 = L.cpart3 + (size_t)(it & 1) * kCgcrG3;
+    double* p3n = L.cpart3 + (size_t)(~it & 1) * kCgcrG3;
+    const dim3 grid(kCgcrG3, nrhs), block(kCgcrK3);
+    if (g1 <= kCgcrFusedG1) {
+      hipLaunchKernelGGL(k_cgcr_update<true>, grid, block, 0, c.stream, n, nrhs, j, k, L.basisW, L.basisZ, w, z, x, r,
+                         S, p3n, vals, g1, L.cpart, p3, host_act, err);
+      WDMG_HIP(hipGetLastError());
+      if (!c.capturing) WDMG_HIP(hipEventRecord(c.ring_ev[it % kRing], c.stream));
+    } else {
+      hipLaunchKernelGGL(k_cgcr_coef, dim3(nrhs), dim3(1024), (size_t)(vals + 1) * sizeof(double), c.stream, j, vals,
+                         g1, L.cpart, p3, kCgcrG3, k, S, host_act, err, nullptr);
+      WDMG_HIP(hipGetLastError());
+      if (!c.capturing) WDMG_HIP(hipEventRecord(c.ring_ev[it % kRing], c.stream));
+      hipLaunchKernelGGL(k_cgcr_update<false>, grid, block, 0, c.stream, n, nrhs, j, k, L.basisW, L.basisZ, w, z, x, r,
+                         S, p3n, vals, g1, L.cpart, p3, host_act, err);
+      WDMG_HIP(hipGetLastError());
+    }
     c.n_Dc[L.l] += nrhs;
     if (!c.capturing && it >= lag && done_at(it - lag)) {
       ++it;
