@@ -59,6 +59,11 @@ __constant__ int c_off[2][kMaxOff] = {{0, 1, -1, 0, 0, 1, -1, 1, -1}, {0, 0, 0, 
 enum { S_RHO = 0, S_ALPHA, S_OMEGA, S_BETA, S_PQ, S_RR, S_FLAG, S_MR, S_TOTAL = S_MR + 64 };
 // Workgroups of one reduction per rhs, and rhs of one reduction launch.
 constexpr int kMaxDotGroups = 128, kMaxDotRhs = 64;
+// Most workgroups of an operator launch that also leaves the sums of an MR
+// step: every wavefront of the update adds them up, 16 per lane (64^2 sites of
+// 16 dof are 1024 workgroups; beyond that the sums take a launch of their own
+// with at most kMaxDotGroups).
+constexpr int kMaxMrGroups = 1024;
 
 __device__ __forceinline__ C neg(C a) { return mk(-a.re, -a.im); }
 __device__ __forceinline__ C cdiv(C a, C b) {
@@ -74,14 +79,32 @@ inline unsigned blocks_for(size_t n, int bs) { return (unsigned)((n + bs - 1) / 
 // thread per site and rhs.  Spin projections of the 2d gamma matrices:
 //   (1 - sigma_1) c = (h, -h),   h = c0 - c1;   (1 + sigma_1) c = (h, h),    h = c0 + c1;
 //   (1 - sigma_2) c = (h, -i h), h = c0 + i c1; (1 + sigma_2) c = (h, i h),  h = c0 - i c1.
-template <bool G5>
+// With DOTS (grid y = rhs) the launch also leaves each workgroup's share of
+// <p, p> and <p, q>, p = out, q = dr, for the MR step that follows.
+__device__ __forceinline__ void leave_mr_sums(C pq, double pp, double* part, int rhs) {
+  __shared__ double lds[3 * 16];
+  double v[3] = {pp, pq.re, pq.im};
+  wdmg::block_sum<3>(v, lds);
+  if (threadIdx.x == 0) {
+    double* p = part + ((size_t)rhs * gridDim.x + blockIdx.x) * 4;
+    p[0] = v[0];
+    p[1] = 0.0;
+    p[2] = v[1];
+    p[3] = v[2];
+  }
+}
+
+template <bool G5, bool DOTS>
 __global__ void __launch_bounds__(256) k_wilson(C* __restrict__ out, const C* __restrict__ in,
                                                 const C* __restrict__ U, int lx, int lt, double diag,
-                                                double tbc, int nrhs) {
+                                                double tbc, int nrhs, const C* __restrict__ dr,
+                                                double* __restrict__ part) {
   const int vol = lx * lt;
   const size_t gid = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (gid >= (size_t)vol * nrhs) return;
-  const int r = (int)(gid / vol), s = (int)(gid - (size_t)r * vol);
+  const bool live = gid < (DOTS ? (size_t)vol : (size_t)vol * nrhs);
+  if (!DOTS && !live) return;
+  const int r = DOTS ? (int)blockIdx.y : (int)(gid / vol);
+  const int s = !live ? 0 : DOTS ? (int)gid : (int)(gid - (size_t)r * vol);
   const int x = s % lx, t = s / lx;
   const C* f = in + (size_t)r * vol * 2;
   auto ld = [&](int site, C& c0, C& c1) {
@@ -133,8 +156,21 @@ __global__ void __launch_bounds__(256) k_wilson(C* __restrict__ out, const C* __
   C o1 = diag * c1 - 0.5 * acc1;
   if (G5) o1 = neg(o1);
   C* g = out + (size_t)r * vol * 2;
-  g[2 * s] = o0;
-  g[2 * s + 1] = o1;
+  if (live) {
+    g[2 * s] = o0;
+    g[2 * s + 1] = o1;
+  }
+  if constexpr (DOTS) {
+    C pq = mk(0.0, 0.0);
+    double pp = 0.0;
+    if (live) {
+      const C* q = dr + (size_t)r * vol * 2;
+      cmaddc(pq, o0, q[2 * s]);
+      cmaddc(pq, o1, q[2 * s + 1]);
+      pp = o0.re * o0.re + o0.im * o0.im + o1.re * o1.re + o1.im * o1.im;
+    }
+    leave_mr_sums(pq, pp, part, r);
+  }
 }
 
 // Coarse stencil: out(s)[i] = sum_o sum_j B[o][s][i][j] in(s + d_o)[j], one
@@ -162,33 +198,53 @@ __global__ void __launch_bounds__(256) k_stencil(C* __restrict__ out, const C* _
 // The same stencil for N = 8, 16 or 32 dof per site: 64 / N rows of one
 // site per wavefront, lane (row, j) multiplying B[o](s)[i][j] by in(s + d_o)[j],
 // so that a wavefront reads 64 consecutive block entries per offset; the
-// N lanes of a row are summed with cross-lane adds.
-template <int N>
-__global__ void __launch_bounds__(256) k_stencil_w(C* __restrict__ out, const C* __restrict__ in,
-                                                   const C* __restrict__ B, int lx, int lt, int S, int nrhs) {
-  static_assert(N >= 8 && N <= 64 && (N & (N - 1)) == 0, "N must be a power of two in 8..64");
+// N lanes of a row are summed with cross-lane adds.  The few wavefronts of a
+// small lattice leave nothing to hide a load behind, so all 2 S loads are
+// issued before the first product: 32^2 sites, N = 16, S = 5, 5.5 us (one
+// offset at a time, 9.8 us).  With `b` the result is b - A in; DOTS as for
+// k_wilson.
+constexpr int kStencilThreads = 1024;  // few workgroups, hence few partial sums
+template <int N, int S, bool DOTS>
+__global__ void __launch_bounds__(kStencilThreads) k_stencil_w(C* __restrict__ out, const C* __restrict__ in,
+                                                   const C* __restrict__ B, int lx, int lt, int nrhs,
+                                                   const C* __restrict__ b, const C* __restrict__ dr,
+                                                   double* __restrict__ part) {
+  constexpr int off[2][kMaxOff] = {{0, 1, -1, 0, 0, 1, -1, 1, -1}, {0, 0, 0, 1, -1, 1, 1, -1, -1}};
   constexpr int R = 64 / N;  // rows per wavefront
   constexpr int W = N / R;   // wavefronts per site
   const int vol = lx * lt;
   const size_t wave = ((size_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
   const int lane = threadIdx.x & 63;
-  if (wave >= (size_t)nrhs * vol * W) return;
+  const bool live = wave < (size_t)vol * W * (DOTS ? 1 : nrhs);
+  if (!DOTS && !live) return;
   const int grp = (int)(wave % W);
-  const size_t rest = wave / W;
-  const int s = (int)(rest % vol), r = (int)(rest / vol);
+  const size_t rest = live ? wave / W : 0;
+  const int s = (int)(rest % vol), r = DOTS ? (int)blockIdx.y : (int)(rest / vol);
   const int i = grp * R + lane / N, j = lane % N;
   const int x = s % lx, t = s / lx;
-  C acc = mk(0.0, 0.0);
-  for (int o = 0; o < S; ++o) {
-    const int xn = (x + c_off[0][o] + lx) % lx, tn = (t + c_off[1][o] + lt) % lt;
-    cmadd(acc, B[(((size_t)o * vol + s) * N + i) * N + j], in[((size_t)r * vol + tn * lx + xn) * N + j]);
-  }
+  const int xs[3] = {x == 0 ? lx - 1 : x - 1, x, x + 1 == lx ? 0 : x + 1};
+  const int ts[3] = {t == 0 ? lt - 1 : t - 1, t, t + 1 == lt ? 0 : t + 1};
+  C m[S], v[S];
 #pragma unroll
-  for (int h = N / 2; h > 0; h >>= 1) {
-    acc.re += __shfl_xor(acc.re, h, 64);
-    acc.im += __shfl_xor(acc.im, h, 64);
+  for (int o = 0; o < S; ++o) {
+    m[o] = B[(((size_t)o * vol + s) * N + i) * N + j];
+    v[o] = in[((size_t)r * vol + ts[1 + off[1][o]] * lx + xs[1 + off[0][o]]) * N + j];
   }
-  if (j == 0) out[((size_t)r * vol + s) * N + i] = acc;
+  C acc = mk(0.0, 0.0);
+#pragma unroll
+  for (int o = 0; o < S; ++o) cmadd(acc, m[o], v[o]);
+  acc = mk(wdmg::group_sum<N>(acc.re), wdmg::group_sum<N>(acc.im));
+  const size_t e = ((size_t)r * vol + s) * N + i;
+  if (live && j == N - 1) out[e] = b ? b[e] - acc : acc;
+  if constexpr (DOTS) {
+    C pq = mk(0.0, 0.0);
+    double pp = 0.0;
+    if (live && j == N - 1) {
+      cmaddc(pq, acc, dr[e]);
+      pp = acc.re * acc.re + acc.im * acc.im;
+    }
+    leave_mr_sums(pq, pp, part, r);
+  }
 }
 
 // Restriction P^dagger: out(sc, chi, k) = sum_{s in aggregate} sum_i conj(Q_k(s)_{chi,i}) in(s)_{chi,i}
@@ -238,6 +294,7 @@ __global__ void __launch_bounds__(256) k_restrict_w(C* __restrict__ out, const C
   const C* q = Q + (((size_t)k * vol + s) * g + chi) * n;
   const C* f = in + (((size_t)r * vol + s) * g + chi) * n;
   C acc = mk(0.0, 0.0);
+#pragma unroll 8
   for (int i = 0; i < n; ++i) cmaddc(acc, q[i], (g5 && chi * n + i == 1) ? neg(f[i]) : f[i]);
 #pragma unroll
   for (int h = A / 2; h > 0; h >>= 1) {
@@ -262,6 +319,7 @@ __global__ void __launch_bounds__(256) k_prolong(C* __restrict__ out, const C* _
   const int sc = (t / bt) * lxc + x / bx;
   C acc = mk(0.0, 0.0);
   const C* c = in + (((size_t)r * volc + sc) * g + chi) * nv;
+#pragma unroll 8
   for (int k = 0; k < nv; ++k) cmadd(acc, Q[(((size_t)k * vol + s) * g + chi) * n + i], c[k]);
   out[gid] = acc;
 }
@@ -438,20 +496,29 @@ __global__ void __launch_bounds__(256) k_gj_elim(C* __restrict__ M, const C* __r
   M[i * ld + j] = M[i * ld + j] - f * M[k * ld + j];
 }
 
-// Coarsest solve out = M^-1 in, the inverse being the right half of the
-// reduced [I | M^-1]; one wavefront per (rhs, row).
+// The inverse, the right half of the reduced [I | M^-1], in rows of its own:
+// read where it is, its rows start 32 n bytes apart and use some of the memory
+// channels only.
+__global__ void __launch_bounds__(256) k_dense_inv(C* __restrict__ inv, const C* __restrict__ M, int n) {
+  const size_t gid = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (gid < (size_t)n * n) inv[gid] = M[gid / n * 2 * n + n + gid % n];
+}
+
+// Coarsest solve out = M^-1 in; one workgroup per (rhs, row): with a wavefront
+// per row the matrix is read by one wavefront per SIMD, 16 loads deep (n =
+// 1024: 14.6 against 10.7 us).
 __global__ void __launch_bounds__(256) k_dense_apply(C* __restrict__ out, const C* __restrict__ M,
-                                                     const C* __restrict__ in, int n, int nrhs) {
-  const size_t wave = ((size_t)blockIdx.x * blockDim.x + threadIdx.x) / 64;
-  const int lane = threadIdx.x & 63;
-  if (wave >= (size_t)n * nrhs) return;
-  const int row = (int)(wave % n), r = (int)(wave / n);
-  const C* m = M + (size_t)row * 2 * n + n;
+                                                     const C* __restrict__ in, int n) {
+  __shared__ double lds[2 * 4];
+  const int row = blockIdx.x, r = blockIdx.y;
+  const C* m = M + (size_t)row * n;
   const C* v = in + (size_t)r * n;
   C acc = mk(0.0, 0.0);
-  for (int j = lane; j < n; j += 64) cmadd(acc, m[j], v[j]);
-  const double re = wdmg::wave_sum(acc.re), im = wdmg::wave_sum(acc.im);
-  if (lane == 0) out[(size_t)r * n + row] = mk(re, im);
+#pragma unroll 4
+  for (int j = threadIdx.x; j < n; j += 256) cmadd(acc, m[j], v[j]);
+  double t[2] = {acc.re, acc.im};
+  wdmg::block_sum<2>(t, lds);
+  if (threadIdx.x == 0) out[(size_t)r * n + row] = mk(t[0], t[1]);
 }
 
 // ---------------------------------------------------------------------------
@@ -469,9 +536,7 @@ enum {
 // The coefficient logic of the solvers, from the summed dot products.
 template <int MODE>
 __device__ void finish_dots(C d0, C d1, int rhs, C* sc, double omega) {
-  if (MODE == M_MR) {
-    sc[S_MR + rhs] = d0.re == 0.0 ? mk(0.0, 0.0) : (omega / d0.re) * d1;
-  } else if (MODE == M_NORM) {
+  if (MODE == M_NORM) {
     sc[S_RR] = mk(d0.re, 0.0);
   } else if (MODE == M_RHO) {
     if (is_zero(d0)) {
@@ -545,21 +610,38 @@ __global__ void __launch_bounds__(64) k_finish(const double* __restrict__ part, 
 }
 
 // The MR step (and the minimal-residual step after a prolongation) in one
-// launch: every wavefront sums the partials of <p,p> and <p,r> of its rhs,
-// c = omega <p,r> / <p,p> (0 when <p,p> = 0), then x += c dx, r -= c dr.
-// Needs n % 64 == 0, so that a wavefront never spans two right-hand sides.
-__global__ void __launch_bounds__(256) k_update_mr(C* __restrict__ x, C* r, const C* dx, const C* __restrict__ dr,
-                                                   const double* __restrict__ part, int G, double omega, size_t n,
-                                                   int nrhs) {
-  const size_t gid = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if ((gid & ~(size_t)63) >= n * nrhs) return;  // whole wavefronts
-  const int rhs = (int)(gid / n);
-  double t[4];
-  sum_partials(part, rhs, G, t);
-  const C c = t[0] == 0.0 ? mk(0.0, 0.0) : (omega / t[0]) * mk(t[2], t[3]);
-  const C d = dx[gid];
-  x[gid] = x[gid] + c * d;
-  r[gid] = r[gid] - c * dr[gid];
+// launch: every wavefront sums the partials of <p,p> and <p,r> of its rhs
+// (grid y), c = omega <p,r> / <p,p> (0 when <p,p> = 0), then x += c dx,
+// r = rin - c dr.  FIRST: the step from x = 0, x is written only.
+template <bool FIRST>
+__global__ void __launch_bounds__(256) k_update_mr(C* __restrict__ x, C* r, const C* rin, const C* dx,
+                                                   const C* __restrict__ dr, const double* __restrict__ part, int G,
+                                                   double omega, size_t n) {
+  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const size_t gid = blockIdx.y * n + i;
+  const bool live = i < n;
+  // on their way while the partials are added
+  C d = mk(0.0, 0.0), rv = d, xv = d, p = d;
+  if (live) {
+    d = dx[gid];
+    rv = rin[gid];
+    p = dr[gid];
+    if (!FIRST) xv = x[gid];
+  }
+  double t[3] = {0.0, 0.0, 0.0};
+  const double* q = part + (size_t)blockIdx.y * G * 4;
+#pragma unroll 4
+  for (int k = threadIdx.x & 63; k < G; k += 64) {
+    t[0] += q[4 * k];
+    t[1] += q[4 * k + 2];
+    t[2] += q[4 * k + 3];
+  }
+#pragma unroll
+  for (int k = 0; k < 3; ++k) t[k] = wdmg::wave_sum(t[k]);
+  const C c = t[0] == 0.0 ? mk(0.0, 0.0) : (omega / t[0]) * mk(t[1], t[2]);
+  if (!live) return;
+  x[gid] = FIRST ? c * d : xv + c * d;
+  r[gid] = rv - c * p;
 }
 
 // x += c dx; r -= c dr with c = coefficient slot `slot + rhs` (fields of n elements).
@@ -643,7 +725,7 @@ struct Lev2 {
   C* B = nullptr;                      // stencil of this level (l >= 1)
   int S = 0;
   C *X = nullptr, *R = nullptr, *T = nullptr, *Y = nullptr, *Bv = nullptr;  // cycle work
-  C *E = nullptr, *Rs = nullptr, *T2 = nullptr;  // repeated coarse cycles
+  C *E = nullptr, *Rs = nullptr;  // repeated coarse cycles
 };
 
 struct wdmg_2d_ctx {
@@ -670,8 +752,7 @@ struct wdmg_2d_ctx {
   double omega = 0.8;
   int nu_pre = 2, nu_post = 2, use_alpha = 1, coarse_cycles = 1;
   int blocking = 0;              // 0 chirality kept; 1 spin blocked, R = P^dagger gamma5; 2 spin blocked, R = P^dagger
-  C* Maug = nullptr;             // coarsest [M^-1 reduced | ...]: [nc][2 nc]
-  C* gjcol = nullptr;
+  C* Minv = nullptr;             // inverse of the coarsest operator: [nc][nc]
   int nc = 0;
   // counters
   long long wilson = 0;
@@ -716,7 +797,7 @@ void drop_hierarchy(Ctx& c) {
   release(c, c.hier);
   c.lev.clear();
   c.setup = false;
-  c.Maug = c.gjcol = nullptr;
+  c.Minv = nullptr;
   c.nc = 0;
 }
 
@@ -766,9 +847,11 @@ void launch_check() {
 void wilson(Ctx& c, C* out, const C* in, int nrhs, bool dagger) {
   const size_t n = (size_t)c.lx * c.lt * nrhs;
   if (dagger)
-    k_wilson<true><<<blocks_for(n, 256), 256, 0, c.stream>>>(out, in, c.U, c.lx, c.lt, 2.0 + c.m, c.t_bc, nrhs);
+    k_wilson<true, false><<<blocks_for(n, 256), 256, 0, c.stream>>>(out, in, c.U, c.lx, c.lt, 2.0 + c.m, c.t_bc, nrhs,
+                                                                    nullptr, nullptr);
   else
-    k_wilson<false><<<blocks_for(n, 256), 256, 0, c.stream>>>(out, in, c.U, c.lx, c.lt, 2.0 + c.m, c.t_bc, nrhs);
+    k_wilson<false, false><<<blocks_for(n, 256), 256, 0, c.stream>>>(out, in, c.U, c.lx, c.lt, 2.0 + c.m, c.t_bc,
+                                                                     nrhs, nullptr, nullptr);
   launch_check();
   c.wilson += nrhs;
   c.flops += 8.0 * 18.0 * (double)n;
@@ -780,30 +863,64 @@ void normal0(Ctx& c, C* out, const C* in, int nrhs) {
   wilson(c, out, t, nrhs, true);
 }
 
-// out = A_l in.
-void apply_level(Ctx& c, int l, C* out, const C* in, int nrhs) {
+template <int N, bool DOTS>
+void launch_stencil_w(Ctx& c, const Lev2& L, C* out, const C* in, const C* b, const C* dr, int nrhs) {
+  const size_t lanes = (size_t)L.vol * N * N;
+  const dim3 grid = DOTS ? dim3(blocks_for(lanes, kStencilThreads), nrhs) : dim3(blocks_for(lanes * nrhs, kStencilThreads));
+  if (L.S == 5)
+    k_stencil_w<N, 5, DOTS><<<grid, kStencilThreads, 0, c.stream>>>(out, in, L.B, L.lx, L.lt, nrhs, b, dr, c.part);
+  else
+    k_stencil_w<N, 9, DOTS><<<grid, kStencilThreads, 0, c.stream>>>(out, in, L.B, L.lx, L.lt, nrhs, b, dr, c.part);
+}
+
+// whole wavefronts per site: 8, 16 or 32 dof and a stencil of 5 or 9 offsets
+bool wave_stencil(const Lev2& L) {
+  const int N = L.g * L.n;
+  return (N == 8 || N == 16 || N == 32) && (L.S == 5 || L.S == 9);
+}
+
+template <bool DOTS>
+void stencil_w(Ctx& c, const Lev2& L, C* out, const C* in, const C* b, const C* dr, int nrhs) {
+  const int N = L.g * L.n;
+  if (N == 8)
+    launch_stencil_w<8, DOTS>(c, L, out, in, b, dr, nrhs);
+  else if (N == 16)
+    launch_stencil_w<16, DOTS>(c, L, out, in, b, dr, nrhs);
+  else
+    launch_stencil_w<32, DOTS>(c, L, out, in, b, dr, nrhs);
+}
+
+void count_stencil(Ctx& c, int l, int nrhs) {
+  const Lev2& L = c.lev[l];
+  const int N = L.g * L.n;
+  c.capp[l] += nrhs;
+  c.flops += 8.0 * L.S * (double)L.vol * N * N * nrhs;
+}
+
+// out = A_l in, or b - A_l in.
+void apply_level(Ctx& c, int l, C* out, const C* in, int nrhs, const C* b = nullptr) {
+  const Lev2& L = c.lev[l];
+  const bool fused = l > 0 && wave_stencil(L);
   if (l == 0) {
     if (c.normal)
       normal0(c, out, in, nrhs);
     else
       wilson(c, out, in, nrhs, false);
-    return;
+  } else {
+    const int N = L.g * L.n;
+    if (fused)
+      stencil_w<false>(c, L, out, in, b, nullptr, nrhs);
+    else
+      k_stencil<<<blocks_for((size_t)nrhs * L.vol * N, 256), 256, 0, c.stream>>>(out, in, L.B, L.lx, L.lt, N, L.S,
+                                                                                 nrhs);
+    launch_check();
+    count_stencil(c, l, nrhs);
   }
-  const Lev2& L = c.lev[l];
-  const int N = L.g * L.n;
-  const size_t tot = (size_t)nrhs * L.vol * N;
-  const size_t lanes = tot * N;
-  if (N == 8)
-    k_stencil_w<8><<<blocks_for(lanes, 256), 256, 0, c.stream>>>(out, in, L.B, L.lx, L.lt, L.S, nrhs);
-  else if (N == 16)
-    k_stencil_w<16><<<blocks_for(lanes, 256), 256, 0, c.stream>>>(out, in, L.B, L.lx, L.lt, L.S, nrhs);
-  else if (N == 32)
-    k_stencil_w<32><<<blocks_for(lanes, 256), 256, 0, c.stream>>>(out, in, L.B, L.lx, L.lt, L.S, nrhs);
-  else
-    k_stencil<<<blocks_for(tot, 256), 256, 0, c.stream>>>(out, in, L.B, L.lx, L.lt, N, L.S, nrhs);
-  launch_check();
-  c.capp[l] += nrhs;
-  c.flops += 8.0 * L.S * (double)L.vol * N * N * nrhs;
+  if (b && !fused) {
+    const size_t n = L.nf * nrhs;
+    k_xmy<<<blocks_for(n, 256), 256, 0, c.stream>>>(out, b, out, n);
+    launch_check();
+  }
 }
 
 // P^dagger (or P^dagger gamma5 at the fine level of the spin-blocked control with blocking = 1)
@@ -846,18 +963,45 @@ void dots(Ctx& c, const C* a0, const C* b0, const C* a1, const C* b1, size_t n, 
   launch_check();
 }
 
-// One MR step's coefficient and update: c = omega <p,r>/<p,p> per rhs, then
-// x += c dx, r -= c dr (dx = r, dr = p for the smoother; the prolonged
-// correction and its image for the minimal-residual step).
-void mr_update(Ctx& c, C* x, C* r, const C* dx, const C* dr, const C* p, size_t n, int nrhs, double omega) {
-  const int G = dot_groups(n);
-  k_dots<M_MR><<<dim3(G, nrhs), 256, 0, c.stream>>>(p, p, p, r, n, c.part);
-  if (n % 64 == 0) {
-    k_update_mr<<<blocks_for(n * nrhs, 256), 256, 0, c.stream>>>(x, r, dx, dr, c.part, G, omega, n, nrhs);
-  } else {
-    k_finish<M_MR><<<nrhs, 64, 0, c.stream>>>(c.part, G, c.sc, omega);
-    k_update<<<blocks_for(n * nrhs, 256), 256, 0, c.stream>>>(x, r, dx, dr, c.sc, S_MR, n, nrhs);
+// p = A_l in, and the partial sums of <p,p> and <p,r> per rhs: by the same
+// launch where its workgroups are few enough to be added by the update (128^2:
+// one launch of 3.7 us less per MR step), else by one of their own.  Returns
+// the number of partials.
+int apply_mr(Ctx& c, int l, C* p, const C* in, const C* r, int nrhs) {
+  const Lev2& L = c.lev[l];
+  const int N = L.g * L.n;
+  const size_t G = l == 0 ? blocks_for((size_t)L.vol, 256) : blocks_for((size_t)L.vol * N * N, kStencilThreads);
+  if (G <= (size_t)kMaxMrGroups && nrhs <= kMaxDotRhs && (l == 0 ? !c.normal : wave_stencil(L))) {
+    if (l == 0) {
+      k_wilson<false, true><<<dim3((unsigned)G, nrhs), 256, 0, c.stream>>>(p, in, c.U, c.lx, c.lt, 2.0 + c.m, c.t_bc,
+                                                                           nrhs, r, c.part);
+      c.wilson += nrhs;
+      c.flops += 8.0 * 18.0 * (double)L.vol * nrhs;
+    } else {
+      stencil_w<true>(c, L, p, in, nullptr, r, nrhs);
+      count_stencil(c, l, nrhs);
+    }
+    launch_check();
+    return (int)G;
   }
+  apply_level(c, l, p, in, nrhs);
+  const int g = dot_groups(L.nf);
+  k_dots<M_MR><<<dim3(g, nrhs), 256, 0, c.stream>>>(p, p, p, r, L.nf, c.part);
+  launch_check();
+  return g;
+}
+
+// The update of an MR step, from G partials per rhs: c = omega <p,r>/<p,p>,
+// x += c dx, r -= c dr (dx = r, dr = p for the smoother; the prolonged
+// correction and its image for the minimal-residual step).  With r0 the step
+// starts from x = 0 with residual r0.
+void mr_update(Ctx& c, C* x, C* r, const C* dx, const C* dr, int G, size_t n, int nrhs, double omega,
+               const C* r0 = nullptr) {
+  const dim3 grid(blocks_for(n, 256), nrhs);
+  if (r0)
+    k_update_mr<true><<<grid, 256, 0, c.stream>>>(x, r, r0, dx, dr, c.part, G, omega, n);
+  else
+    k_update_mr<false><<<grid, 256, 0, c.stream>>>(x, r, r, dx, dr, c.part, G, omega, n);
   launch_check();
 }
 
@@ -893,19 +1037,25 @@ void vcycle(Ctx& c, int l, C* x, const C* r) {
   const int nl = (int)c.lev.size();
   int blk[2];
   blk_pair(c, l, blk);
-  Q2_HIP(hipMemcpyAsync(L.R, r, L.nf * sizeof(C), hipMemcpyDeviceToDevice, c.stream));
-  Q2_HIP(hipMemsetAsync(x, 0, L.nf * sizeof(C), c.stream));
   auto mr_steps = [&](int k) {
     for (int i = 0; i < k; ++i) {
-      apply_level(c, l, L.T, L.R, 1);
-      mr_update(c, x, L.R, L.R, L.T, L.T, L.nf, 1, c.omega);
+      const int G = apply_mr(c, l, L.T, L.R, L.R, 1);
+      mr_update(c, x, L.R, L.R, L.T, G, L.nf, 1, c.omega);
     }
   };
-  mr_steps(c.nu_pre);
+  if (c.nu_pre > 0) {  // the first step reads r and writes x and L.R
+    const int G = apply_mr(c, l, L.T, r, r, 1);
+    mr_update(c, x, L.R, r, L.T, G, L.nf, 1, c.omega, r);
+    mr_steps(c.nu_pre - 1);
+  } else {
+    Q2_HIP(hipMemcpyAsync(L.R, r, L.nf * sizeof(C), hipMemcpyDeviceToDevice, c.stream));
+    Q2_HIP(hipMemsetAsync(x, 0, L.nf * sizeof(C), c.stream));
+  }
   Lev2& Cc = c.lev[l + 1];
   restrict_to(c, l, Cc.Bv, L.R, 1, blk);
+  const C* e = Cc.X;
   if (l + 1 == nl - 1) {
-    k_dense_apply<<<blocks_for((size_t)c.nc * 64, 256), 256, 0, c.stream>>>(Cc.X, c.Maug, Cc.Bv, c.nc, 1);
+    k_dense_apply<<<dim3(c.nc, 1), 256, 0, c.stream>>>(Cc.X, c.Minv, Cc.Bv, c.nc);
     launch_check();
     c.capp[l + 1] += 1;
     c.flops += 8.0 * (double)c.nc * c.nc;
@@ -913,26 +1063,21 @@ void vcycle(Ctx& c, int l, C* x, const C* r) {
     vcycle(c, l + 1, Cc.X, Cc.Bv);
   } else {
     // e <- e + M_{l+1} (r_c - A_{l+1} e) from e = 0, coarse_cycles times
-    Q2_HIP(hipMemsetAsync(Cc.E, 0, Cc.nf * sizeof(C), c.stream));
-    for (int it = 0; it < c.coarse_cycles; ++it) {
-      const C* res = Cc.Bv;
-      if (it > 0) {
-        apply_level(c, l + 1, Cc.T2, Cc.E, 1);
-        k_xmy<<<blocks_for(Cc.nf, 256), 256, 0, c.stream>>>(Cc.Rs, Cc.Bv, Cc.T2, Cc.nf);
-        launch_check();
-        res = Cc.Rs;
-      }
-      vcycle(c, l + 1, Cc.X, res);
+    vcycle(c, l + 1, Cc.E, Cc.Bv);
+    for (int it = 1; it < c.coarse_cycles; ++it) {
+      apply_level(c, l + 1, Cc.Rs, Cc.E, 1, Cc.Bv);
+      vcycle(c, l + 1, Cc.X, Cc.Rs);
       k_add<<<blocks_for(Cc.nf, 256), 256, 0, c.stream>>>(Cc.E, Cc.X, Cc.nf);
       launch_check();
     }
-    Q2_HIP(hipMemcpyAsync(Cc.X, Cc.E, Cc.nf * sizeof(C), hipMemcpyDeviceToDevice, c.stream));
+    e = Cc.E;
   }
-  prolong_from(c, l, L.Y, Cc.X, 1, blk);
-  apply_level(c, l, L.T, L.Y, 1);
-  if (c.use_alpha)
-    mr_update(c, x, L.R, L.Y, L.T, L.T, L.nf, 1, 1.0);
-  else {
+  prolong_from(c, l, L.Y, e, 1, blk);
+  if (c.use_alpha) {
+    const int G = apply_mr(c, l, L.T, L.Y, L.R, 1);
+    mr_update(c, x, L.R, L.Y, L.T, G, L.nf, 1, 1.0);
+  } else {
+    apply_level(c, l, L.T, L.Y, 1);
     k_set<<<1, 1, 0, c.stream>>>(c.sc, S_MR, 1.0);
     launch_check();
     update(c, x, L.R, L.Y, L.T, L.nf, 1);
@@ -1010,8 +1155,8 @@ void mg_setup(Ctx& c, const wdmg_2d_mg_params& p) {
         k_neg<<<blocks_for(nv * L.nf, 256), 256, 0, c.stream>>>(R, T, nv * L.nf);
         launch_check();
         for (int it = 0; it < p.setup_iters; ++it) {
-          apply_level(c, l, T, R, nv);
-          mr_update(c, L.Q, R, R, T, T, L.nf, nv, c.omega);
+          const int G = apply_mr(c, l, T, R, R, nv);
+          mr_update(c, L.Q, R, R, T, G, L.nf, nv, c.omega);
         }
       }
       Q2_HIP(hipMemsetAsync(c.status, 0, sizeof(int), c.stream));
@@ -1059,15 +1204,17 @@ void mg_setup(Ctx& c, const wdmg_2d_mg_params& p) {
     const int N = Cc.g * Cc.n;
     const int n = Cc.vol * N;
     c.nc = n;
-    c.Maug = calloc_fields(c, (size_t)n * 2 * n, c.hier);
-    c.gjcol = calloc_fields(c, (size_t)n, c.hier);
-    k_dense_aug<<<blocks_for((size_t)n * 2 * n, 256), 256, 0, c.stream>>>(c.Maug, Cc.B, Cc.lx, Cc.lt, N, Cc.S);
+    C* M = calloc_fields(c, (size_t)n * 2 * n, scratch.bufs);
+    C* col = calloc_fields(c, (size_t)n, scratch.bufs);
+    c.Minv = calloc_fields(c, (size_t)n * n, c.hier);
+    k_dense_aug<<<blocks_for((size_t)n * 2 * n, 256), 256, 0, c.stream>>>(M, Cc.B, Cc.lx, Cc.lt, N, Cc.S);
     launch_check();
     Q2_HIP(hipMemsetAsync(c.status, 0, sizeof(int), c.stream));
     for (int k = 0; k < n; ++k) {
-      k_gj_pivot<<<1, 1024, 0, c.stream>>>(c.Maug, c.gjcol, n, k, c.status);
-      k_gj_elim<<<blocks_for((size_t)n * (2 * (size_t)n - k), 256), 256, 0, c.stream>>>(c.Maug, c.gjcol, n, k);
+      k_gj_pivot<<<1, 1024, 0, c.stream>>>(M, col, n, k, c.status);
+      k_gj_elim<<<blocks_for((size_t)n * (2 * (size_t)n - k), 256), 256, 0, c.stream>>>(M, col, n, k);
     }
+    k_dense_inv<<<blocks_for((size_t)n * n, 256), 256, 0, c.stream>>>(c.Minv, M, n);
     launch_check();
     int st = 0;
     Q2_HIP(hipMemcpyAsync(&st, c.status, sizeof(int), hipMemcpyDeviceToHost, c.stream));
@@ -1082,7 +1229,6 @@ void mg_setup(Ctx& c, const wdmg_2d_mg_params& p) {
     L.Bv = calloc_fields(c, L.nf, c.hier);
     L.E = calloc_fields(c, L.nf, c.hier);
     L.Rs = calloc_fields(c, L.nf, c.hier);
-    L.T2 = calloc_fields(c, L.nf, c.hier);
   }
   if (c.tmp_fields > 1) free_tmp(c);  // the probes' D^dagger D work field
   ensure_tmp(c, 1);
@@ -1246,7 +1392,7 @@ int wdmg_2d_create(wdmg_2d_ctx** out, const int dims[2], const wdmg_alloc* alloc
     cc.U = calloc_fields(cc, (size_t)cc.lx * cc.lt * 2, cc.bufs);
     cc.sc = calloc_fields(cc, S_TOTAL, cc.bufs);
     cc.status = static_cast<int*>(dalloc(cc, 256, cc.bufs));
-    cc.part = static_cast<double*>(dalloc(cc, (size_t)kMaxDotRhs * kMaxDotGroups * 4 * sizeof(double), cc.bufs));
+    cc.part = static_cast<double*>(dalloc(cc, (size_t)kMaxDotRhs * kMaxMrGroups * 4 * sizeof(double), cc.bufs));
 
     Q2_HIP(hipHostMalloc(reinterpret_cast<void**>(&cc.hsc), S_TOTAL * sizeof(C), hipHostMallocDefault));
     Q2_HIP(hipMemsetAsync(cc.sc, 0, S_TOTAL * sizeof(C), cc.stream));

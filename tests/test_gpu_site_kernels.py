@@ -174,3 +174,34 @@ def test_batched_coarse_operator_at_tile_edges(dims, blk, nv, nrhs):
             one = ctx.apply_Dc(1, v[j], prec=prec).cpu().numpy()
             assert rel(out[j], one) < tol, (prec, j)
     ctx.close()
+
+
+@pytest.mark.parametrize("dims,nvs,cycles", [
+    ((20, 28), [3], 1),       # 6 dof per site: the general stencil, its sums in a launch of their own
+    ((24, 40), [4], 1),       # 8 dof; fields of 1920 numbers end inside a workgroup
+    ((24, 40), [16], 1),      # 32 dof
+    ((48, 48), [8, 4], 3),    # repeated coarse cycles
+    ((272, 272), [8, 4], 2),  # 68^2 sites of 16 dof: more workgroups than the update adds up
+])
+def test_2d_cycles_with_the_sums_in_the_operator(dims, nvs, cycles):
+    """The multigrid cycle of the 2d workload where its MR steps take another
+    path; the true residual, recomputed by the oracle in FP64, is what counts
+    (cond(D) times rounding is far below the 1e-10 asked for)."""
+    from oracle import qed2d as O
+    from paper_0811_4331_amd import qed2d
+    u = synthetic.u1_gauge_field(dims, 6.0, seed=941)
+    m = 0.05
+    b = synthetic.gaussian_spinor_2d(dims, seed=942)
+    lx, lt = dims
+    vecs, n = [], 1
+    for k, nv in enumerate(nvs):
+        vecs.append(gpu(synthetic.gaussian_vectors((nv, lt, lx, 2, n), 943 + k)))
+        lt, lx, n = lt // 4, lx // 4, nv
+    c = qed2d.Context2d(dims, "cuda:0")
+    c.set_gauge(gpu(u), -1)
+    c.set_mass(m)
+    c.mg_setup(nvs, vecs, setup_iters=20, coarse_cycles=cycles)
+    x, st = c.solve(gpu(b), method="mg-bicgstab", tol=1e-10, maxit=500)
+    res = np.linalg.norm(b - O.apply_D(u, x.cpu().numpy(), m, -1.0)) / np.linalg.norm(b)
+    assert st["converged"] and res <= 1e-10, (st, res)
+    c.close()
