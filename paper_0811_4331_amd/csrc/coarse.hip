@@ -469,12 +469,16 @@ __global__ __launch_bounds__(576) void k_coarse_apply_h(Geom g, int n2, const cx
 // ---- batched application on the matrix cores ---------------------------------
 // For a batch the coarse operator at one site is, per direction, a complex GEMM
 // of the (n2 x n2) block with the neighbour's n2 x nrhs values.  One workgroup
-// per site and 16 NT right-hand sides; its W waves share the nine directions,
+// per site and 16 right-hand sides; its W waves share the nine directions,
 // every wave holding all RT = ceil(n2 / 16) row tiles, so a block entry is
 // loaded once, straight from memory into the operand's lanes, and no operand
 // passes through LDS.  The waves' sums meet in LDS at the end, in wave order.
 // Many sites: W = 3 (three directions per wave keep loads in flight while
-// products run).  Few sites: W = 9, one direction per wave.
+// products run).  Few sites: W = 9, one direction per wave.  The tiles of
+// right-hand sides of a site follow each other on one XCD, whose L2 then holds
+// its blocks: two tiles in one workgroup are slower (BF16, 32 rhs: 89 us
+// against 87.7), and a wave per row tile, which loads the vectors once per
+// wave, far slower (218 us).
 //
 // FP64 / FP32 (v_mfma 16x16x4): four real products per complex one; a lane
 // group supplies columns 4 g + u of a block of 16 in step u for both operands,
@@ -487,9 +491,11 @@ __global__ __launch_bounds__(576) void k_coarse_apply_h(Geom g, int n2, const cx
 // direction's product is accumulated from zero and added times the block (and
 // FP16 column) scale.
 //
-// Bound: memory (the blocks once).  2592 sites, nv 24: BF16 44 us for 2 and 98
-// for 32 rhs (215 MB of blocks; a kernel with both operands staged in LDS, 134
-// and 170), FP32 95 and 162 (715 and 835), FP64 173 and 296 (808 and 1249).
+// Bound: the blocks (215 MB in 16 bits, 430 in FP32, 860 in FP64 at 2592
+// sites, nv 24) and the loads of the vectors, nine per value.  BF16 42 us for 2
+// right-hand sides, 53 for 16, 87 for 32 (a kernel with both operands staged in
+// LDS: 134, 159, 170), FP32 91, 101, 155 (715, 724, 835), FP64 173, 198, 296
+// (808, 924, 1249).
 template <typename R>
 struct Mma;
 template <>
@@ -536,42 +542,52 @@ __device__ __forceinline__ Mma<float>::acc_t mma32(u4 a, u4 b, Mma<float>::acc_t
                                                   0);
 }
 
-template <class B, class Lay, int RT, int NT, int W>
+template <class B, class Lay, int RT, int W>
 __global__ __launch_bounds__(64 * W) void k_coarse_mm(Geom g, int n2, int nrhs, B blocks,
                                                       Lay lay, const cx<typename B::T>* __restrict__ in,
                                                       cx<typename B::T>* __restrict__ out,
                                                       cx<typename B::T>* __restrict__ copy) {
   using R = typename B::T;
   using acc_t = typename Mma<R>::acc_t;
-  __shared__ acc_t part[W][NT][2][64];
+  __shared__ acc_t part[W][2][64];
   // the right-hand-side tiles of a site run back to back on one XCD (blocks are
   // dealt to the eight XCDs in turn), each XCD on a contiguous range of sites
-  const int ntile = (nrhs + 16 * NT - 1) / (16 * NT), per = (g.vol + 7) / 8;
+  const int ntile = (nrhs + 15) / 16, per = (g.vol + 7) / 8;
   const int s = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3) / ntile;
-  const int q0 = (int)(blockIdx.x >> 3) % ntile * 16 * NT;
+  const int q0 = (int)(blockIdx.x >> 3) % ntile * 16;
   if (s >= g.vol || (int)(blockIdx.x >> 3) >= per * ntile) return;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int li = lane & 15, lk = lane >> 4;
+  const int li = lane & 15, lk = lane >> 4, q = q0 + li;
   int c[4];
   coords_of(g, s, c);
-  acc_t re[RT][NT], im[RT][NT];
+  acc_t re[RT], im[RT];
 #pragma unroll
-  for (int i = 0; i < RT; ++i)
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      re[i][t] = acc_t{0, 0, 0, 0};
-      im[i][t] = acc_t{0, 0, 0, 0};
-    }
+  for (int i = 0; i < RT; ++i) {
+    re[i] = acc_t{0, 0, 0, 0};
+    im[i] = acc_t{0, 0, 0, 0};
+  }
   for (int d = wave; d < 9; d += W) {
     const int nb = d == 8 ? s : ((d & 1) ? nbr_bwd(g, s, c, d >> 1) : nbr_fwd(g, s, c, d >> 1));
-    // four consecutive columns of the neighbour's values of rhs 16 t + li
-    auto values = [&](int t, int col, cx<R> (&b)[4]) {
-      const int q = q0 + 16 * t + li;
+    // four consecutive columns of the neighbour's values of rhs q
+    auto values = [&](int col, cx<R> (&b)[4]) {
+      const int qc = min(q, nrhs - 1);
+      if constexpr (sizeof(R) == 4 && std::is_same<Lay, RhsMajor>::value) {
+        // two numbers a load (n2 is even); it is the count of loads that bounds FP32 vectors
+        typedef float f4 __attribute__((ext_vector_type(4), aligned(8)));
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const cx<R> x = in[lay.at(min(q, nrhs - 1), nb, min(col + u, n2 - 1), n2)];
-        if (copy && d == 8 && q < nrhs && col + u < n2) copy[lay.at(q, s, col + u, n2)] = x;
-        b[u] = q < nrhs && col + u < n2 ? x : mk<R>(0, 0);
+        for (int u = 0; u < 4; u += 2) {
+          const f4 x = *reinterpret_cast<const f4*>(in + lay.at(qc, nb, min(col + u, n2 - 2), n2));
+          const bool on = q < nrhs && col + u < n2;
+          b[u] = on ? mk(x.x, x.y) : mk(0.0f, 0.0f);
+          b[u + 1] = on ? mk(x.z, x.w) : mk(0.0f, 0.0f);
+        }
+      } else {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const cx<R> x = in[lay.at(qc, nb, min(col + u, n2 - 1), n2)];
+          if (copy && d == 8 && q < nrhs && col + u < n2) copy[lay.at(q, s, col + u, n2)] = x;
+          b[u] = q < nrhs && col + u < n2 ? x : mk<R>(0, 0);
+        }
       }
     };
     if constexpr (!B::kHalf) {
@@ -579,24 +595,21 @@ __global__ __launch_bounds__(64 * W) void k_coarse_mm(Geom g, int n2, int nrhs, 
 #pragma unroll 1
       for (int kb = 0; kb < RT; ++kb) {
         const int col = 16 * kb + 4 * lk;
-        cx<R> b[NT][4], a[4][RT];
+        cx<R> b[4], a[4][RT];
 #pragma unroll
         for (int u = 0; u < 4; ++u)
 #pragma unroll
           for (int i = 0; i < RT; ++i) a[u][i] = blk[(size_t)min(col + u, n2 - 1) * n2 + min(16 * i + li, n2 - 1)];
-#pragma unroll
-        for (int t = 0; t < NT; ++t) values(t, col, b[t]);
+        values(col, b);
 #pragma unroll
         for (int u = 0; u < 4; ++u)
 #pragma unroll
-          for (int i = 0; i < RT; ++i)
-#pragma unroll
-            for (int t = 0; t < NT; ++t) {
-              re[i][t] = Mma<R>::mma(a[u][i].re, b[t][u].re, re[i][t]);
-              im[i][t] = Mma<R>::mma(a[u][i].re, b[t][u].im, im[i][t]);
-              re[i][t] = Mma<R>::mma(-a[u][i].im, b[t][u].im, re[i][t]);
-              im[i][t] = Mma<R>::mma(a[u][i].im, b[t][u].re, im[i][t]);
-            }
+          for (int i = 0; i < RT; ++i) {
+            re[i] = Mma<R>::mma(a[u][i].re, b[u].re, re[i]);
+            im[i] = Mma<R>::mma(a[u][i].re, b[u].im, im[i]);
+            re[i] = Mma<R>::mma(-a[u][i].im, b[u].im, re[i]);
+            im[i] = Mma<R>::mma(a[u][i].im, b[u].re, im[i]);
+          }
       }
     } else {
       using H = typename B::Half;
@@ -608,86 +621,83 @@ __global__ __launch_bounds__(64 * W) void k_coarse_mm(Geom g, int n2, int nrhs, 
 #pragma unroll
         for (int i = 0; i < RT; ++i) a[kb][i] = blk[(size_t)min(4 * kb + lk, nch - 1) * n2 + min(16 * i + li, n2 - 1)];
       const float f = blocks.scale[(size_t)s * 9 + d];
+      cx<float> b[RT][4];
 #pragma unroll
-      for (int t = 0; t < NT; ++t) {
-        cx<float> b[RT][4];
+      for (int kb = 0; kb < RT; ++kb) values(16 * kb + 4 * lk, b[kb]);
+      float fs16 = f, inv = 1.0f;
+      if constexpr (!std::is_same<H, bf16_t>::value) {
+        // largest magnitude of the column: this lane's values, then the four lane groups
+        float m = 0.0f;
 #pragma unroll
-        for (int kb = 0; kb < RT; ++kb) values(t, 16 * kb + 4 * lk, b[kb]);
-        float fs16 = f, inv = 1.0f;
-        if constexpr (!std::is_same<H, bf16_t>::value) {
-          // largest magnitude of the column: this lane's values, then the four lane groups
-          float m = 0.0f;
+        for (int kb = 0; kb < RT; ++kb)
 #pragma unroll
-          for (int kb = 0; kb < RT; ++kb)
+          for (int u = 0; u < 4; ++u) m = fmaxf(m, fmaxf(fabsf(b[kb][u].re), fabsf(b[kb][u].im)));
+        m = fmaxf(m, __shfl_xor(m, 16, 64));
+        m = fmaxf(m, __shfl_xor(m, 32, 64));
+        fs16 = f * quant_scale(m, inv);
+      }
+      acc_t tr[RT], ti_[RT];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) m = fmaxf(m, fmaxf(fabsf(b[kb][u].re), fabsf(b[kb][u].im)));
-          m = fmaxf(m, __shfl_xor(m, 16, 64));
-          m = fmaxf(m, __shfl_xor(m, 32, 64));
-          fs16 = f * quant_scale(m, inv);
+      for (int i = 0; i < RT; ++i) {
+        tr[i] = acc_t{0, 0, 0, 0};
+        ti_[i] = acc_t{0, 0, 0, 0};
+      }
+#pragma unroll
+      for (int kb = 0; kb < RT; ++kb) {
+        u4 b1, b2;  // (re, -im) and (im, re) of four columns
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          float br = b[kb][u].re, bi = b[kb][u].im;
+          if constexpr (!std::is_same<H, bf16_t>::value) {
+            br *= inv;
+            bi *= inv;
+          }
+          const unsigned w = __builtin_bit_cast(unsigned, f2h<H>(br, bi));
+          b1[u] = w ^ 0x80000000u;
+          b2[u] = (w << 16) | (w >> 16);
         }
-        acc_t tr[RT], ti_[RT];
 #pragma unroll
         for (int i = 0; i < RT; ++i) {
-          tr[i] = acc_t{0, 0, 0, 0};
-          ti_[i] = acc_t{0, 0, 0, 0};
+          tr[i] = mma32<H>(a[kb][i], b1, tr[i]);
+          ti_[i] = mma32<H>(a[kb][i], b2, ti_[i]);
         }
-#pragma unroll
-        for (int kb = 0; kb < RT; ++kb) {
-          u4 b1, b2;  // (re, -im) and (im, re) of four columns
-#pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            float br = b[kb][u].re, bi = b[kb][u].im;
-            if constexpr (!std::is_same<H, bf16_t>::value) {
-              br *= inv;
-              bi *= inv;
-            }
-            const unsigned w = __builtin_bit_cast(unsigned, f2h<H>(br, bi));
-            b1[u] = w ^ 0x80000000u;
-            b2[u] = (w << 16) | (w >> 16);
-          }
-#pragma unroll
-          for (int i = 0; i < RT; ++i) {
-            tr[i] = mma32<H>(a[kb][i], b1, tr[i]);
-            ti_[i] = mma32<H>(a[kb][i], b2, ti_[i]);
-          }
-        }
-        // FP16 result columns belong to right-hand side li, as the scale does
-#pragma unroll
-        for (int i = 0; i < RT; ++i)
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            re[i][t][r] += fs16 * tr[i][r];
-            im[i][t][r] += fs16 * ti_[i][r];
-          }
       }
+      // FP16 result columns belong to right-hand side li, as the scale does
+#pragma unroll
+      for (int i = 0; i < RT; ++i)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          re[i][r] += fs16 * tr[i][r];
+          im[i][r] += fs16 * ti_[i][r];
+        }
     }
   }
   // row tile i summed over the waves by wave i % W
 #pragma unroll
   for (int i = 0; i < RT; ++i) {
     if (i > 0) __syncthreads();
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      part[wave][t][0][lane] = re[i][t];
-      part[wave][t][1][lane] = im[i][t];
-    }
+    part[wave][0][lane] = re[i];
+    part[wave][1][lane] = im[i];
     __syncthreads();
-    if (wave == i % W) {
+    if (wave == i % W && q < nrhs) {
+      acc_t sr = part[0][0][lane], si = part[0][1][lane];
 #pragma unroll
-      for (int t = 0; t < NT; ++t) {
-        acc_t sr = part[0][t][0][lane], si = part[0][t][1][lane];
+      for (int w = 1; w < W; ++w) {
+        sr += part[w][0][lane];
+        si += part[w][1][lane];
+      }
+      if constexpr (sizeof(R) == 4 && std::is_same<Lay, RhsMajor>::value) {
+        typedef float f4 __attribute__((ext_vector_type(4), aligned(8)));
 #pragma unroll
-        for (int w = 1; w < W; ++w) {
-          sr += part[w][t][0][lane];
-          si += part[w][t][1][lane];
+        for (int r = 0; r < 4; r += 2) {
+          const int row = 16 * i + Mma<R>::row(lk, r);
+          if (row < n2) *reinterpret_cast<f4*>(out + lay.at(q, s, row, n2)) = f4{sr[r], si[r], sr[r + 1], si[r + 1]};
         }
-        const int q = q0 + 16 * t + li;
-        if (q < nrhs) {
+      } else {
 #pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const int row = 16 * i + Mma<R>::row(lk, r);
-            if (row < n2) out[lay.at(q, s, row, n2)] = mk<R>(sr[r], si[r]);
-          }
+        for (int r = 0; r < 4; ++r) {
+          const int row = 16 * i + Mma<R>::row(lk, r);
+          if (row < n2) out[lay.at(q, s, row, n2)] = mk<R>(sr[r], si[r]);
         }
       }
     }
@@ -1174,39 +1184,27 @@ __global__ __launch_bounds__(256) void k_cgcrT_combine(size_t npos, int nrhs, in
   }
 }
 
-template <int RT, int NT, int W, class B, class Lay>
+template <int RT, int W, class B, class Lay>
 void launch_coarse_mm(Ctx& c, const Level& cl, const B& blocks, const Lay& lay, const cx<typename B::T>* in,
                       cx<typename B::T>* out, cx<typename B::T>* copy, int nrhs) {
-  hipLaunchKernelGGL((k_coarse_mm<B, Lay, RT, NT, W>), dim3(8 * ((cl.nsite + 7) / 8) * ((nrhs + 16 * NT - 1) / (16 * NT))),
-                     dim3(64 * W), 0, c.stream, cl.g, cl.dof, nrhs, blocks, lay, in, out, copy);
+  hipLaunchKernelGGL((k_coarse_mm<B, Lay, RT, W>), dim3(8 * ((cl.nsite + 7) / 8) * ((nrhs + 15) / 16)), dim3(64 * W),
+                     0, c.stream, cl.g, cl.dof, nrhs, blocks, lay, in, out, copy);
 }
 
 // out = D_c in for a batch, and copy = in where given (dof <= 64).
 template <class B, class Lay>
 void coarse_mm(Ctx& c, const Level& cl, const B& blocks, const Lay& lay, const cx<typename B::T>* in,
                cx<typename B::T>* out, cx<typename B::T>* copy, int nrhs) {
-  // Two tiles of right-hand sides per workgroup halve the reads of the blocks
-  // but leave half the workgroups: they pay where FP32 accumulators leave room
-  // for them and the sites alone fill the chip (nv 24, 32 rhs, 2592 sites: BF16
-  // 98 us against 114 with one tile, FP32 162 against 167, FP64 339 against
-  // 296; 256 sites, nv 20: BF16 13.0 against 12.5).  Nine waves per workgroup
-  // pay where a workgroup has a compute unit to itself (256 sites, nv 20, 16
-  // rhs: FP32 14.0 against 16.2, FP64 22.9 against 24.9; at 32 rhs FP32 25.1
-  // against 24.3).
-  const bool two = sizeof(typename B::T) == 4 && nrhs > 16 && cl.nsite >= 4 * c.ncu;
+  // Nine waves per workgroup pay where a workgroup has a compute unit to itself
+  // (256 sites, nv 20, 16 rhs: FP32 14.0 us against 16.2, FP64 22.9 against
+  // 24.9; at 32 rhs FP32 25.1 against 24.3).
   const bool nine = (long long)cl.nsite * ((nrhs + 15) / 16) <= c.ncu;
-#define MM(RT)                                                                    \
-  do {                                                                            \
-    if (nine) {                                                                   \
-      launch_coarse_mm<RT, 1, 9>(c, cl, blocks, lay, in, out, copy, nrhs);        \
-    } else {                                                                      \
-      if constexpr (sizeof(typename B::T) == 4)                                   \
-        if (two) {                                                                \
-          launch_coarse_mm<RT, 2, 3>(c, cl, blocks, lay, in, out, copy, nrhs);    \
-          break;                                                                  \
-        }                                                                         \
-      launch_coarse_mm<RT, 1, 3>(c, cl, blocks, lay, in, out, copy, nrhs);        \
-    }                                                                             \
+#define MM(RT)                                                             \
+  do {                                                                     \
+    if (nine)                                                              \
+      launch_coarse_mm<RT, 9>(c, cl, blocks, lay, in, out, copy, nrhs);    \
+    else                                                                   \
+      launch_coarse_mm<RT, 3>(c, cl, blocks, lay, in, out, copy, nrhs);    \
   } while (0)
   switch ((cl.dof + 15) / 16) {
     case 1: MM(1); break;
