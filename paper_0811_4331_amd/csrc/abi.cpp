@@ -209,24 +209,27 @@ void prolong_impl(Ctx& c, int level, void* fout, const void* cin, int nrhs) {
 template <typename R>
 void smooth_impl(Ctx& c, int level, void* x, const void* b, int nrhs, int iters) {
   // Right-hand sides are smoothed together, kSmoothRhs at a time (16^4, FP32,
-  // 8 rhs, 4 steps: 411 us, 1004 us one by one; more would only grow the
+  // 8 rhs, 4 steps: 379 us, 1004 us one by one; more would only grow the
   // buffers).  16-bit coarse blocks take one at a time: their batched kernel
   // rounds the vectors as well.
-  constexpr int kSmoothRhs = 16;
+  constexpr int kSmoothRhs = 8;
   const size_t n = c.lev[level].n;
   const int most = level > 0 && c.vc_half ? 1 : std::min(nrhs, kSmoothRhs);
-  ensure_io(c, 2 * most * n * sizeof(cx<R>));
-  cx<R>* r = static_cast<cx<R>*>(c.io_a);
-  cx<R>* p = static_cast<cx<R>*>(c.io_b);
+  ensure_io(c, 3 * most * n * sizeof(cx<R>));
+  cx<R>* a = static_cast<cx<R>*>(c.io_a);
+  cx<R>* q = static_cast<cx<R>*>(c.io_b);
+  const size_t f = most * n;
+  cx<R>* ring[kMrRing] = {a, a + f, a + 2 * f, q};
+  cx<R>* p = q + f;
   const double omega = c.have_mg ? c.mg.omega : 0.8;
   for (int k = 0; k < nrhs; k += most) {
     const int m = std::min(most, nrhs - k);
     cx<R>* xk = static_cast<cx<R>*>(x) + (size_t)k * n;
-    cx<R>* xi = field_out<R>(xk, r + most * n);
+    cx<R>* xi = field_out<R>(xk, q + 2 * f);
     field_in<R>(c, xk, xi, m * n);
-    apply_op<R>(c, level, r, xi, m);
-    xmy<R>(c, field_in<R>(c, static_cast<const cx<R>*>(b) + (size_t)k * n, p + most * n, m * n), r, m * n);
-    mr<R>(c, level, xi, r, p, m, iters, omega);
+    apply_op<R>(c, level, a, xi, m);
+    xmy<R>(c, field_in<R>(c, static_cast<const cx<R>*>(b) + (size_t)k * n, p, m * n), a, m * n);
+    mr_ring<R>(c, level, xi, ring, p, m, iters, omega);
     field_done<R>(c, xk, xi, m * n);
   }
 }

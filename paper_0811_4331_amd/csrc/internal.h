@@ -34,6 +34,7 @@ Geom make_geom(const int L[4], const int B[4]);
 // kernels directly; the host reads back only residual norms.
 constexpr int kMaxRhs = 64;     // right-hand sides solved together
 constexpr int kMaxKrylov = 128;  // GCR restart length limit
+constexpr int kMrRing = 4;       // MR steps whose updates of x are made together
 
 enum ScalarSlot {
   S_ERR = 0,        // NaN / rank / SU(3) flags (as doubles)
@@ -43,7 +44,7 @@ enum ScalarSlot {
   S_RNORM = 64,     // residual norm^2 per level (real)
   S_GCR = 128,      // unused (kept for layout stability)
   S_GCR_STRIDE = 512,
-  S_BATCH = S_GCR + 4 * S_GCR_STRIDE,  // batched step sizes: 2 per rhs
+  S_BATCH = S_GCR + 4 * S_GCR_STRIDE,  // batched step sizes: 2 per rhs, of up to kMrRing MR steps
   // Batched GCR state, one block per level (0..3) and one for the outer solve
   // (index 4): h [rhs][2*kMaxKrylov], nrm [rhs][kMaxKrylov], a [rhs][2],
   // rnorm^2 [rhs], active [rhs], target rnorm^2 [rhs].
@@ -54,7 +55,7 @@ enum ScalarSlot {
   G_ACT = G_RN + kMaxRhs,
   G_TOL = G_ACT + kMaxRhs,
   G_STRIDE = G_TOL + kMaxRhs,
-  S_G = S_BATCH + 2 * kMaxRhs,
+  S_G = S_BATCH + 2 * kMaxRhs * kMrRing,
   S_TOTAL = S_G + 5 * G_STRIDE
 };
 inline int gcr_base(int slot_level) { return S_G + slot_level * G_STRIDE; }
@@ -322,6 +323,13 @@ void step_alpha_batch(Ctx& c, const cx<R>* a, const cx<R>* b, size_t n, size_t s
 template <typename R>
 void update2_batch(Ctx& c, cx<R>* x, const cx<R>* u, cx<R>* r, const cx<R>* v, size_t n, size_t stride, int nb,
                    int slot, int mode = 0);
+// MR steps with the updates of x put off: rn = r - s p (step sizes at `slot`),
+// and x += sum_i s_i r_i over m <= kMrRing steps, s_i at S_BATCH + 2 kMaxRhs i.
+// With p the last step's update of the residual is part of it: r_0 = r_{m-1} - s_{m-1} p.
+template <typename R>
+void mr_residual(Ctx& c, cx<R>* rn, const cx<R>* r, const cx<R>* p, size_t n, int nb, int slot);
+template <typename R>
+void mr_solution(Ctx& c, cx<R>* x, cx<R>* const (&r)[kMrRing], const cx<R>* p, size_t n, int nb, int m);
 // Batched GCR over nb right-hand sides.  Fields of one rhs are n long and
 // consecutive (batch stride n); basis vector i of all rhs is W + i*nb*n.
 // State in the block gcr_base(g): h, nrm, a, rnorm^2, active (see ScalarSlot).

@@ -269,6 +269,28 @@ void mr(Ctx& c, int l, cx<R>* x, cx<R>* r, cx<R>* p, int nrhs, int iters, double
   }
 }
 
+// The same steps from x with residual ring[0], the updates of x made kMrRing at
+// a time: the residuals in between stay in the ring (overwritten, as is p).
+// The last residual is not formed.
+template <typename R>
+void mr_ring(Ctx& c, int l, cx<R>* x, cx<R>* const (&ring)[kMrRing], cx<R>* p, int nrhs, int iters, double omega) {
+  const size_t n = c.lev[l].n;
+  for (int it = 0; it < iters; ++it) {
+    const int k = it % kMrRing, slot = S_BATCH + 2 * kMaxRhs * k;
+    if (l == 0) {
+      dslash_mr<R>(c, p, ring[k], nrhs, omega, slot);
+    } else {
+      apply_op<R>(c, l, p, ring[k], nrhs);
+      step_alpha_batch<R>(c, p, ring[k], n, n, nrhs, omega, slot);
+    }
+    const bool last = it == iters - 1;
+    if (last || k == kMrRing - 1)
+      mr_solution<R>(c, x, ring, last ? nullptr : p, n, nrhs, k + 1);
+    else
+      mr_residual<R>(c, ring[k + 1], ring[k], p, n, nrhs, slot);
+  }
+}
+
 // ---------------------------------------------------------------------------
 // Coarsest solve: GCR(restart) on D_c in FP64 to relative tolerance tol_c,
 // for nrhs right-hand sides together (each with its own coefficients).
@@ -352,6 +374,7 @@ void vcycle(Ctx& c, int l, cx<R>* x, const cx<R>* b, int nrhs) {
   template void restrict_to<R>(Ctx&, int, const cx<R>*, cx<R>*, int);         \
   template void prolong_from<R>(Ctx&, int, const cx<R>*, cx<R>*, int);        \
   template void mr<R>(Ctx&, int, cx<R>*, cx<R>*, cx<R>*, int, int, double, const cx<R>*, bool); \
+  template void mr_ring<R>(Ctx&, int, cx<R>*, cx<R>* const (&)[kMrRing], cx<R>*, int, int, double); \
   template void ensure_work<R>(Ctx&, int, int);
 INST(double)
 INST(float)
@@ -834,11 +857,14 @@ static void relax_batch(Ctx& c, int l, cx<R>* V, int nv, int iters, double omega
   Level& F = c.lev[l];
   const size_t n = F.n;
   const size_t field = n * sizeof(cx<R>);
-  size_t kb = ((size_t)16 << 30) / (2 * field);
+  constexpr size_t budget = (size_t)16 << 30;
+  size_t kb = budget / (2 * field);
   if (kb < 1) kb = 1;
   if (kb > (size_t)nv) kb = nv;
   if (kb > (size_t)kMaxRhs) kb = kMaxRhs;
-  cx<R>* Rb = static_cast<cx<R>*>(dev_alloc(c, kb * field));
+  // the residuals of kMrRing steps where they fit the budget for the same batch
+  const bool fits = (kMrRing + 1) * kb * field <= budget;
+  cx<R>* Rb = static_cast<cx<R>*>(dev_alloc(c, (fits ? kMrRing : 1) * kb * field));
   cx<R>* Pb = static_cast<cx<R>*>(dev_alloc(c, kb * field));
   if (l == 0) dots_buffer(c, (int)kb);
   for (int k0 = 0; k0 < nv; k0 += (int)kb) {
@@ -847,14 +873,12 @@ static void relax_batch(Ctx& c, int l, cx<R>* V, int nv, int iters, double omega
     // r = 0 - A x
     apply_op<R>(c, l, Rb, X, nb);
     neg<R>(c, Rb, (size_t)nb * n);
-    for (int it = 0; it < iters; ++it) {
-      if (l == 0) {
-        dslash_mr<R>(c, Pb, Rb, nb, omega, S_BATCH);
-      } else {
-        apply_op<R>(c, l, Pb, Rb, nb);
-        step_alpha_batch<R>(c, Pb, Rb, n, n, nb, omega, S_BATCH);
-      }
-      update2_batch<R>(c, X, Rb, Rb, Pb, n, n, nb, S_BATCH);
+    if (fits) {
+      cx<R>* ring[kMrRing];
+      for (int k = 0; k < kMrRing; ++k) ring[k] = Rb + k * kb * n;
+      mr_ring<R>(c, l, X, ring, Pb, nb, iters, omega);
+    } else {
+      mr<R>(c, l, X, Rb, Pb, nb, iters, omega, nullptr, true);
     }
   }
   WDMG_HIP(hipStreamSynchronize(c.stream));

@@ -18,6 +18,8 @@ template <typename R>
 void mr(Ctx& c, int l, cx<R>* x, cx<R>* r, cx<R>* p, int nrhs, int iters, double omega, const cx<R>* b0 = nullptr,
         bool last_x_only = false);
 template <typename R>
+void mr_ring(Ctx& c, int l, cx<R>* x, cx<R>* const (&ring)[kMrRing], cx<R>* p, int nrhs, int iters, double omega);
+template <typename R>
 void vcycle(Ctx& c, int l, cx<R>* x, const cx<R>* b, int nrhs);
 void coarsest_solve(Ctx& c, cx<double>* x, const cx<double>* b, int nrhs);
 // 16-bit fine level (x, r, p and b are 16-bit fields of nrhs right-hand sides)
