@@ -215,10 +215,35 @@ struct StencilSide {
 };
 
 // ---- the build kernel ---------------------------------------------------------
+// Matrix-core operations on tiles of 16 x 16, four terms at a time; operand
+// lanes: A[i][k] at lane i + 16 k, B[k][j] at lane j + 16 k.
+template <typename R>
+struct Mma;
+template <>
+struct Mma<double> {
+  typedef double acc_t __attribute__((ext_vector_type(4)));
+  static __device__ __forceinline__ acc_t mma(double a, double b, acc_t c) {
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+  }
+  static __device__ __forceinline__ int row(int g, int r) { return 4 * r + g; }  // of D, lane group g, register r
+};
+template <>
+struct Mma<float> {
+  typedef float acc_t __attribute__((ext_vector_type(4)));
+  static __device__ __forceinline__ acc_t mma(float a, float b, acc_t c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+  }
+  static __device__ __forceinline__ int row(int g, int r) { return 4 * g + r; }
+};
+
+// The block is the product of the conjugated columns (n2 rows, chirality by
+// chirality) with the hopped ones, summed over the sites: a complex GEMM on
+// the FP64 matrix cores, at most 16 tiles, tile t on wave t % 4.
 template <class Side>
-__global__ __launch_bounds__(256) void k_coarse_build(Side side, AggGeom a, const cx<double>* __restrict__ Vv,
+__global__ __launch_bounds__(256, 2) void k_coarse_build(Side side, AggGeom a, const cx<double>* __restrict__ Vv,
                                                       size_t vstride, int nv, int dof, int cs, int cc_max,
                                                       cx<double>* __restrict__ Dc) {
+  using M = Mma<double>;
   extern __shared__ cx<double> sm[];
   __shared__ int sites[8];
   __shared__ int crd[8][4];
@@ -227,13 +252,18 @@ __global__ __launch_bounds__(256) void k_coarse_build(Side side, AggGeom a, cons
   cx<double>* Vt = sm;                          // [cs][dof][nv]
   cx<double>* T = sm + (size_t)cs * dof * nv;   // [cs][dof][cc_max]
   const int nsites = nsites_of_block(a, d);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, li = lane & 15, lk = lane >> 4;
+  const int rt = (nv + 15) / 16;  // row tiles of a chirality
   cx<double>* out = Dc + ((size_t)agg * 9 + d) * n2 * n2;
   for (int col0 = 0; col0 < n2; col0 += cc_max) {
     const int ncc = min(cc_max, n2 - col0);
-    const int nent = n2 * ncc;
-    cx<double> acc[16];
+    const int ntile = 2 * rt * ((ncc + 15) / 16);
+    M::acc_t re[4], im[4];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) acc[i] = mk(0.0, 0.0);
+    for (int i = 0; i < 4; ++i) {
+      re[i] = M::acc_t{0, 0, 0, 0};
+      im[i] = M::acc_t{0, 0, 0, 0};
+    }
     for (int i0 = 0; i0 < nsites; i0 += cs) {
       const int ncs = min(cs, nsites - i0);
       if (threadIdx.x < ncs) {
@@ -245,35 +275,41 @@ __global__ __launch_bounds__(256) void k_coarse_build(Side side, AggGeom a, cons
       }
       __syncthreads();
       for (int w = threadIdx.x; w < ncs * dof * nv; w += blockDim.x) {
-        const int k = w % nv, e = (w / nv) % dof, q = w / (nv * dof);
-        Vt[w] = Vv[(size_t)k * vstride + side.off(a.g.vol, sites[q], e)];
+        const int e = w % dof, k = (w / dof) % nv, q = w / (nv * dof);
+        Vt[((size_t)q * dof + e) * nv + k] = Vv[(size_t)k * vstride + side.off(a.g.vol, sites[q], e)];
       }
       side.columns(a, d, sites, crd, ncs, col0, ncc, cc_max, nv, Vv, vstride, T);
       __syncthreads();
+      const int nk = ncs * half;  // terms of a chirality in this chunk
 #pragma unroll
-      for (int slot = 0; slot < 16; ++slot) {
-        const int ent = threadIdx.x + slot * 256;
-        if (ent < nent) {
-          const int row = ent % n2, cc = ent / n2;
-          const int chi = row / nv, k = row % nv;
-          cx<double> s = acc[slot];
-          for (int q = 0; q < ncs; ++q) {
-            for (int m = 0; m < half; ++m) {
-              const int e = chi * half + m;
-              cmaddc(s, Vt[((size_t)q * dof + e) * nv + k], T[((size_t)q * dof + e) * cc_max + cc]);
-            }
-          }
-          acc[slot] = s;
+      for (int i = 0; i < 4; ++i) {
+        const int tile = wave + 4 * i;
+        if (tile >= ntile) break;
+        const int chi = tile & 1, k = 16 * ((tile >> 1) % rt) + li, cc = 16 * ((tile >> 1) / rt) + li;
+        const cx<double>* va = Vt + min(k, nv - 1);
+        const cx<double>* tb = T + min(cc, ncc - 1);
+        for (int r0 = 0; r0 < nk; r0 += 4) {
+          const int r = min(r0 + lk, nk - 1);
+          const size_t row = (size_t)(r / half) * dof + chi * half + r % half;
+          cx<double> v = va[row * nv], t = tb[row * cc_max];
+          if (r0 + lk >= nk) v = t = mk(0.0, 0.0);
+          re[i] = M::mma(v.re, t.re, re[i]);
+          im[i] = M::mma(v.re, t.im, im[i]);
+          re[i] = M::mma(v.im, t.im, re[i]);
+          im[i] = M::mma(-v.im, t.re, im[i]);
         }
       }
       __syncthreads();
     }
 #pragma unroll
-    for (int slot = 0; slot < 16; ++slot) {
-      const int ent = threadIdx.x + slot * 256;
-      if (ent < nent) {
-        const int row = ent % n2, cc = ent / n2;
-        out[(size_t)(col0 + cc) * n2 + row] = acc[slot];
+    for (int i = 0; i < 4; ++i) {
+      const int tile = wave + 4 * i;
+      if (tile >= ntile) break;
+      const int chi = tile & 1, k0 = 16 * ((tile >> 1) % rt), cc = 16 * ((tile >> 1) / rt) + li;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int k = k0 + M::row(lk, r);
+        if (k < nv && cc < ncc) out[(size_t)(col0 + cc) * n2 + chi * nv + k] = mk(re[i][r], im[i][r]);
       }
     }
   }
@@ -496,25 +532,6 @@ __global__ __launch_bounds__(576) void k_coarse_apply_h(Geom g, int n2, const cx
 // right-hand sides, 53 for 16, 87 for 32 (a kernel with both operands staged in
 // LDS: 134, 159, 170), FP32 91, 101, 155 (715, 724, 835), FP64 173, 198, 296
 // (808, 924, 1249).
-template <typename R>
-struct Mma;
-template <>
-struct Mma<double> {
-  typedef double acc_t __attribute__((ext_vector_type(4)));
-  static __device__ __forceinline__ acc_t mma(double a, double b, acc_t c) {
-    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-  }
-  static __device__ __forceinline__ int row(int g, int r) { return 4 * r + g; }  // of D, lane group g, register r
-};
-template <>
-struct Mma<float> {
-  typedef float acc_t __attribute__((ext_vector_type(4)));
-  static __device__ __forceinline__ acc_t mma(float a, float b, acc_t c) {
-    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-  }
-  static __device__ __forceinline__ int row(int g, int r) { return 4 * g + r; }
-};
-
 template <typename R>
 struct BlocksFull {
   using T = R;
