@@ -774,11 +774,14 @@ int auto_form(const Geom& g, int nrhs) {
   return pairs >= (nrhs >= 8 ? 3000 : 5000) ? kFormTile : kFormGather;
 }
 
-// Right-hand sides per workgroup of the gather kernel: as many as leave about
-// four workgroups per compute unit (8^4, 32 rhs: 13 us at 2, 32 us at 16;
-// 16^4, 8 rhs: 34 us at 8, 47 us at 1), at most 16, groups of equal size.
-inline int gather_group(int nsb, int nrhs, int forced) {
-  long long n = forced > 0 ? forced : (long long)nsb * nrhs / 1024;
+// Right-hand sides per workgroup of the gather kernel, at most 16, in groups of
+// equal size.  Two site blocks per compute unit are enough workgroups: then the
+// whole batch shares its links and offsets (12x20x10x18, 675 blocks, 5 rhs:
+// 20.8 us in one group, 24.1 in two).  With fewer blocks, as many as leave
+// about four workgroups per compute unit (8^4, 32 rhs: 13 us at 2, 32 us at
+// 16).
+inline int gather_group(const Ctx& c, int nsb, int nrhs, int forced) {
+  long long n = forced > 0 ? forced : nsb >= 2 * c.ncu ? 16 : (long long)nsb * nrhs / (4 * c.ncu);
   if (forced <= 0 && n > 16) n = 16;
   if (n < 1) n = 1;
   if (n > nrhs) n = nrhs;
@@ -807,7 +810,7 @@ int launch_dslash(Ctx& c, const S& io, int nrhs, int prof_id, int prec_index, do
   const bool tile = (v == 5 || v == 9) && tile_fits<S>(g);
   const int nsb = g.vpad / 64;
   int rg = c.tune_force[WDMG_TUNE_DSLASH_GROUP] >= 0 ? c.tune_force[WDMG_TUNE_DSLASH_GROUP] : gslot;
-  const int nper = sizeof(R) == 8 ? 1 : gather_group(nsb, nrhs, rg);
+  const int nper = sizeof(R) == 8 ? 1 : gather_group(c, nsb, nrhs, rg);
   if (rg < 0) gslot = (signed char)(nper < kMaxRhs ? nper : kMaxRhs);
   const int tneg = c.t_bc < 0 ? 1 : 0;
   const R diag = (R)(4.0 + c.mass);
