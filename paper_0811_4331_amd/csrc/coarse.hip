@@ -516,7 +516,7 @@ __global__ __launch_bounds__(576) void k_coarse_apply_h(Geom g, int n2, const cx
 // products run).  Few sites: W = 9, one direction per wave.  The tiles of
 // right-hand sides of a site follow each other on one XCD, whose L2 then holds
 // its blocks: two tiles in one workgroup are slower (BF16, 32 rhs: 89 us
-// against 87.7), and a wave per row tile, which loads the vectors once per
+// against 88, before the directions were unrolled), and a wave per row tile, which loads the vectors once per
 // wave, far slower (218 us).
 //
 // FP64 / FP32 (v_mfma 16x16x4): four real products per complex one; a lane
@@ -531,8 +531,8 @@ __global__ __launch_bounds__(576) void k_coarse_apply_h(Geom g, int n2, const cx
 // FP16 column) scale.
 //
 // Bound: the blocks (215 MB in 16 bits, 430 in FP32, 860 in FP64 at 2592
-// sites, nv 24) and the loads of the vectors, nine per value.  BF16 42 us for 2
-// right-hand sides, 53 for 16, 87 for 32 (a kernel with both operands staged in
+// sites, nv 24) and the loads of the vectors, nine per value.  BF16 35 us for 2
+// right-hand sides, 44 for 16, 73 for 32 (a kernel with both operands staged in
 // LDS: 134, 159, 170), FP32 91, 101, 155 (715, 724, 835), FP64 173, 198, 296
 // (808, 924, 1249).
 template <typename R>
@@ -586,7 +586,7 @@ __global__ __launch_bounds__(64 * W) void k_coarse_mm(Geom g, int n2, int nrhs, 
     re[i] = acc_t{0, 0, 0, 0};
     im[i] = acc_t{0, 0, 0, 0};
   }
-  for (int d = wave; d < 9; d += W) {
+  auto direction = [&](int d) __attribute__((always_inline)) {
     const int nb = d == 8 ? s : ((d & 1) ? nbr_bwd(g, s, c, d >> 1) : nbr_fwd(g, s, c, d >> 1));
     // four consecutive columns of the neighbour's values of rhs q
     auto values = [&](int col, cx<R> (&b)[4]) {
@@ -691,6 +691,16 @@ __global__ __launch_bounds__(64 * W) void k_coarse_mm(Geom g, int n2, int nrhs, 
           im[i][r] += fs16 * ti_[i][r];
         }
     }
+  };
+  // Unrolled, the next direction's loads go out before this one's products: in
+  // 16 bits 44 against 53 us (2592 sites, nv 24, 16 rhs); in FP64 its registers
+  // cost more than that brings (218 against 198 us).
+  if constexpr (B::kHalf) {
+#pragma unroll
+    for (int k = 0; k < 9 / W; ++k) direction(wave + k * W);
+  } else {
+#pragma unroll 1
+    for (int d = wave; d < 9; d += W) direction(d);
   }
   // row tile i summed over the waves by wave i % W
 #pragma unroll
