@@ -103,10 +103,12 @@ __device__ __forceinline__ void agg_rhs_block(int nagg, int nrhs, int& agg, int&
 // the two halves add up at the end.  Chunk c + 1 is on its way while the
 // products of chunk c run.
 //
-// Bound: memory (V once, fields once) up to about 40 columns x rhs per byte of
-// V.  24^3x48, nv 24, bf16, 32 FP32 right-hand sides in: 954 us (a kernel that
-// staged V in LDS for vector-unit products, with a conversion pass before it:
-// 2019 us).
+// Bound: the matrix cores (FP32 products, 1.0 of 1.7 M cycles at nv 24, whose
+// columns fill 24 of 32) and the vector units around them.  24^3x48, nv 24,
+// bf16, 32 FP32 right-hand sides in: 783 us, 950 us before the site table (a
+// kernel that staged V in LDS for vector-unit products, with a conversion pass
+// before it: 2019 us).
+constexpr int kMmTable = 512;  // sites of an aggregate whose indices are kept in LDS
 constexpr int kMmRows = 48;  // rows of a chunk (of each chirality): eight sites at level 0
 
 template <typename R>
@@ -283,12 +285,18 @@ __global__ __launch_bounds__(256) void k_restrict_mm(AggMap map, int dof, VL V, 
   using acc_t = typename Mm<R>::acc_t;
   constexpr int QN = 16 * QT, LD = QN + 1;
   __shared__ cx<R> Fs[2][2][kMmRows][LD];
+  __shared__ int table[kMmTable];
   int agg, tile;
   agg_rhs_block(nagg, gridDim.x / nagg, agg, tile);
+  // a site's index takes a dozen divisions, five times per thread and chunk
+  const bool tab = map.bvol <= kMmTable;
+  for (int l = threadIdx.x; tab && l < map.bvol; l += 256) table[l] = map.site(agg, l);
+  __syncthreads();
+  auto site = [&](int l) { return tab ? table[l] : map.site(agg, l); };
   const int q0 = tile * QN, nq = min(QN, nrhs - q0);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int chi = wave >> 1, kh = wave & 1;
-  const int half = dof / 2, nrows = map.bvol * half;
+  const int half = FL::kSite ? 6 : dof / 2, nrows = map.bvol * half;
   const int nch = (nrows + kMmRows - 1) / kMmRows;
   const int li = lane & 15, lk = lane >> 4;
   // items of the fields per chunk and thread
@@ -301,18 +309,18 @@ __global__ __launch_bounds__(256) void k_restrict_mm(AggMap map, int dof, VL V, 
       const int e = i * 256 + threadIdx.x;
       if constexpr (FL::kSite) {
         const int q = e >> 4, l = c * 8 + ((e >> 1) & 7);
-        if (q < nq && l < map.bvol) fr[i] = F.load(q0 + q, map.site(agg, l), e & 1);
+        if (q < nq && l < map.bvol) fr[i] = F.load(q0 + q, site(l), e & 1);
       } else {
         const int q = e / kMmRows, p = e % kMmRows, row = c * kMmRows + 2 * (p % (kMmRows / 2));
         const int l = row / half;
         if (q < nq && row < nrows)
-          fr[i] = F.load(q0 + q, (size_t)map.site(agg, l) * dof + (p / (kMmRows / 2)) * half + (row - l * half));
+          fr[i] = F.load(q0 + q, (size_t)site(l) * dof + (p / (kMmRows / 2)) * half + (row - l * half));
       }
     }
 #pragma unroll
     for (int t = 0; t < 3; ++t) {
       const int row = min(c * kMmRows + kh * 24 + t * 8 + 2 * lk, nrows - 2), l = row / half;
-      const size_t off = (size_t)map.site(agg, l) * dof + chi * half + (row - l * half);
+      const size_t off = (size_t)site(l) * dof + chi * half + (row - l * half);
 #pragma unroll
       for (int j = 0; j < CT; ++j) vr[t][j] = V.pair(min(16 * j + li, nv - 1), off);
     }
