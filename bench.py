@@ -647,9 +647,9 @@ def cpu_baseline_oracle(torch, dev, wdmg, synthetic):
 def kernel_family_names(kernel):
     """Substrings of the HIP kernel names (demangled or mangled) of one profiled kernel id."""
     fam, prec = kernel.split("_", 1)
-    io = {"f64": ["FullIO<double>", "FullIOIdE"], "f32": ["FullIO<float>", "FullIOIfE"],
-          "f16": ["HalfIO<_Float16>", "HalfIOIDF16_E"], "bf16": ["HalfIO<__bf16>", "HalfIOIDF16bE"]}[prec]
-    return ["k_dslash"], io
+    io = {"f64": ["Full<double>", "FullIdE"], "f32": ["Full<float>", "FullIfE"],
+          "f16": ["Half<_Float16>", "HalfIDF16_E"], "bf16": ["Half<__bf16>", "HalfIDF16bE"]}[prec]
+    return ["k_wilson_"], io
 
 
 def traffic_entry(fetch_csv, write_csv, bench_json, kernel, command):
