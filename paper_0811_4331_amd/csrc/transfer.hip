@@ -441,27 +441,37 @@ __global__ __launch_bounds__(256) void k_prolong(AggMap map, int dof, VL V, cons
 }
 
 // The same into a 16-bit field, one thread per site.
-template <typename H>
+template <typename H, int NB>
 __global__ __launch_bounds__(256) void k_prolong0_h(AggMap map, VHalf<H> V, const cx<float>* __restrict__ in,
-                                                    OutHalf<H> O, int nagg, int nv) {
-  const int s = blockIdx.x * blockDim.x + threadIdx.x, rhs = blockIdx.y, vol = map.g.vol;
+                                                    OutHalf<H> O, int nagg, int nv, int nrhs) {
+  const int s = blockIdx.x * blockDim.x + threadIdx.x, r0 = blockIdx.y * NB, vol = map.g.vol;
   if (s >= vol) return;
-  const cx<float>* ec = in + ((size_t)rhs * nagg + map.agg_of(s)) * 2 * nv;
-  cx<float> acc[12];
+  const cx<float>* ec = in + ((size_t)r0 * nagg + map.agg_of(s)) * 2 * nv;
+  cx<float> acc[NB][12];
 #pragma unroll
-  for (int m = 0; m < 12; ++m) acc[m] = mk(0.0f, 0.0f);
+  for (int q = 0; q < NB; ++q)
+#pragma unroll
+    for (int m = 0; m < 12; ++m) acc[q][m] = mk(0.0f, 0.0f);
+#pragma unroll 2
   for (int k = 0; k < nv; ++k) {
     cx<float> w[12];
     const u4* vk = reinterpret_cast<const u4*>(V.v + (size_t)k * V.stride) + (size_t)s * 3;
 #pragma unroll
     for (int m = 0; m < 3; ++m) unpack_h<H>(vk[m], m, w);
-    const cx<float> e0 = ec[k], e1 = ec[nv + k];
 #pragma unroll
-    for (int m = 0; m < 6; ++m) cmadd(acc[m], w[m], e0);
+    for (int q = 0; q < NB; ++q) {
+      if (r0 + q >= nrhs) break;
+      const cx<float>* e = ec + (size_t)q * nagg * 2 * nv;
+      const cx<float> e0 = e[k], e1 = e[nv + k];
 #pragma unroll
-    for (int m = 6; m < 12; ++m) cmadd(acc[m], w[m], e1);
+      for (int m = 0; m < 6; ++m) cmadd(acc[q][m], w[m], e0);
+#pragma unroll
+      for (int m = 6; m < 12; ++m) cmadd(acc[q][m], w[m], e1);
+    }
   }
-  O.store(rhs, vol, s, acc);
+#pragma unroll
+  for (int q = 0; q < NB; ++q)
+    if (r0 + q < nrhs) O.store(r0 + q, vol, s, acc[q]);
 }
 
 // ---- batched prolongation on the matrix cores (level 0) -----------------------
@@ -480,18 +490,21 @@ constexpr int kPmSites = 16, kPmThreads = 384, kPmLd = kPmSites * 12 + 2;
 
 template <class VL, class OUT, int KT, int QT>
 __global__ __launch_bounds__(kPmThreads) void k_prolong_mm(AggMap map, VL V, const cx<typename VL::T>* __restrict__ in,
-                                                           OUT O, int nagg, int nv, int nrhs) {
+                                                           OUT O, int nagg, int nv, int nrhs, int nsplit) {
   using R = typename VL::T;
   using acc_t = typename Mm<R>::acc_t;
   __shared__ __align__(16) cx<R> tile[16][kPmLd];  // [rhs][site x 12]
   __shared__ int table[2][kPmSites];
   int agg, qt;
   agg_rhs_block(nagg, gridDim.x / nagg, agg, qt);
+  const int split = qt % nsplit;
+  qt /= nsplit;
   const int q0 = qt * 16 * QT, nq = min(16 * QT, nrhs - q0);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int chi = wave & 1, part = wave >> 1;
   const int li = lane & 15, lk = lane >> 4;
   const int nu = map.bvol / kPmSites, vol = map.g.vol;
+  const int u0 = split * nu / nsplit, u1 = (split + 1) * nu / nsplit;  // this workgroup's units
   // coarse values: lane (q = li, column 4 t + lk)
   cx<R> c[KT][QT];
 #pragma unroll
@@ -509,8 +522,8 @@ __global__ __launch_bounds__(kPmThreads) void k_prolong_mm(AggMap map, VL V, con
 #pragma unroll
     for (int t = 0; t < KT; ++t) vr[t] = V.pair(min(4 * t + lk, nv - 1), off);
   };
-  load(0);
-  for (int un = 0; un < nu; ++un) {
+  load(u0);
+  for (int un = u0; un < u1; ++un) {
     acc_t re[2][QT], im[2][QT];
 #pragma unroll
     for (int h = 0; h < 2; ++h)
@@ -523,7 +536,7 @@ __global__ __launch_bounds__(kPmThreads) void k_prolong_mm(AggMap map, VL V, con
     typename VL::Raw vc[KT];
 #pragma unroll
     for (int t = 0; t < KT; ++t) vc[t] = vr[t];
-    if (un + 1 < nu) load(un + 1);
+    if (un + 1 < u1) load(un + 1);
 #pragma unroll
     for (int t = 0; t < KT; ++t) {
 #pragma unroll
@@ -916,9 +929,16 @@ void restrictC(Ctx& c, const Level& f, const cx<R>* V, const cx<R>* in, cx<R>* o
 }
 
 // The matrix-core prolongation where it applies: level 0, aggregates of whole
-// units, at most 32 columns.  24^3x48, nv 24, FP32, 16 rhs: 557 us, against
-// 3116 us of the vector-unit kernel, which reads V once per RB rhs.
-inline bool pm_fits(const Level& f) { return f.dof == 12 && make_map(f).bvol % kPmSites == 0 && f.nv <= 32; }
+// units, at most 32 columns, and a batch that fills enough of a tile's 16
+// columns: from 6 right-hand sides in FP64, 3 in FP32, 9 in 16 bits (vector
+// units / matrix cores, us, 24^3x48, nv 20: FP64 4 rhs 789 / 965, 6 rhs 1089 /
+// 1005, 16 rhs 2752 / 1233; FP32 2 rhs 411 / 380, 16 rhs 2151 / 506; BF16 4 rhs
+// 321 / 515, 8 rhs 605 / 618, 16 rhs 1162 / 820; 16^4: FP32 2 rhs 36 / 42, 3 rhs
+// 46 / 43).
+enum { kPmMinF64 = 6, kPmMinF32 = 3, kPmMinHalf = 9 };
+inline bool pm_fits(const Level& f, int nrhs, int least) {
+  return nrhs >= least && f.dof == 12 && make_map(f).bvol % kPmSites == 0 && f.nv <= 32;
+}
 
 template <class VL, class OUT>
 void launch_prolong_mm(Ctx& c, const Level& f, const VL& V, const cx<typename VL::T>* in, const OUT& O, int nrhs) {
@@ -927,13 +947,21 @@ void launch_prolong_mm(Ctx& c, const Level& f, const VL& V, const cx<typename VL
   // 32 rhs per workgroup read V half as often; FP64 has registers for 16
   constexpr int Q2 = sizeof(typename VL::T) == 4 ? 2 : 1;
   const int qt = nrhs <= 16 ? 1 : Q2;
-  const dim3 block(kPmThreads), grid(nagg * ((nrhs + 16 * qt - 1) / (16 * qt)));
-#define PM(KT)                                                                                                       \
-  do {                                                                                                               \
-    if (qt == 1)                                                                                                     \
-      hipLaunchKernelGGL((k_prolong_mm<VL, OUT, KT, 1>), grid, block, 0, c.stream, map, V, in, O, nagg, f.nv, nrhs); \
-    else                                                                                                             \
-      hipLaunchKernelGGL((k_prolong_mm<VL, OUT, KT, Q2>), grid, block, 0, c.stream, map, V, in, O, nagg, f.nv, nrhs); \
+  const int ntile = (nrhs + 16 * qt - 1) / (16 * qt);
+  // an aggregate's units go over several workgroups where the aggregates do not
+  // fill the chip (32 aggregates, nv 20, FP32, 16 rhs: 45 us unsplit, 11 us in
+  // 16; 256 of them: 50 us unsplit, 58 us in 4)
+  const int nu = map.bvol / kPmSites, want = (c.ncu + nagg * ntile - 1) / (nagg * ntile);
+  const int nsplit = want < nu ? want : nu;
+  const dim3 block(kPmThreads), grid(nagg * ntile * nsplit);
+#define PM(KT)                                                                                                 \
+  do {                                                                                                         \
+    if (qt == 1)                                                                                               \
+      hipLaunchKernelGGL((k_prolong_mm<VL, OUT, KT, 1>), grid, block, 0, c.stream, map, V, in, O, nagg, f.nv,  \
+                         nrhs, nsplit);                                                                        \
+    else                                                                                                       \
+      hipLaunchKernelGGL((k_prolong_mm<VL, OUT, KT, Q2>), grid, block, 0, c.stream, map, V, in, O, nagg, f.nv, \
+                         nrhs, nsplit);                                                                        \
   } while (0)
   if (f.nv <= 16)
     PM(4);
@@ -947,7 +975,7 @@ void launch_prolong_mm(Ctx& c, const Level& f, const VL& V, const cx<typename VL
 
 template <typename R>
 void launch_prolong(Ctx& c, const Level& f, const cx<R>* V, const cx<R>* in, cx<R>* out, int nrhs) {
-  if (nrhs >= 2 && pm_fits(f)) {
+  if (pm_fits(f, nrhs, sizeof(R) == 8 ? kPmMinF64 : kPmMinF32)) {
     launch_prolong_mm(c, f, VFull<R>{V, f.n}, in, OutFull<R>{out}, nrhs);
     return;
   }
@@ -998,12 +1026,20 @@ void prolong0_h(Ctx& c, const Level& f, const void* V16, const cx<float>* in, HF
   ProfScope ps(c, WDMG_K_PROLONG_H, (long long)f.nsite * nrhs);
   const VHalf<H> V{static_cast<const cxh<H>*>(V16), f.n};
   const OutHalf<H> O{static_cast<cxh<H>*>(out.v), out.s};
-  if (nrhs >= 2 && pm_fits(f)) {
+  if (pm_fits(f, nrhs, kPmMinHalf)) {
     launch_prolong_mm(c, f, V, in, O, nrhs);
     return;
   }
-  hipLaunchKernelGGL((k_prolong0_h<H>), dim3((f.nsite + 255) / 256, nrhs), dim3(256), 0, c.stream, make_map(f), V, in,
-                     O, nagg_of(f), f.nv);
+  // four right-hand sides per thread read V once for them; where that leaves
+  // fewer than four workgroups per compute unit, one (8x8x8x16, 8 rhs: 14 us
+  // against 24; 16^4, 8 rhs: 56 us at four, 66 at one)
+  const int nblk = (f.nsite + 255) / 256;
+  if ((long long)nblk * nrhs <= 4 * c.ncu)
+    hipLaunchKernelGGL((k_prolong0_h<H, 1>), dim3(nblk, nrhs), dim3(256), 0, c.stream, make_map(f), V, in, O,
+                       nagg_of(f), f.nv, nrhs);
+  else
+    hipLaunchKernelGGL((k_prolong0_h<H, 4>), dim3(nblk, (nrhs + 3) / 4), dim3(256), 0, c.stream, make_map(f), V, in, O,
+                       nagg_of(f), f.nv, nrhs);
   WDMG_HIP(hipGetLastError());
 }
 
