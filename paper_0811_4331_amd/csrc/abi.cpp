@@ -123,8 +123,7 @@ template <typename H>
 void apply_D_half(Ctx& c, void* out, const void* in, int nrhs) {
   ensure_ioh(c, nrhs);
   to_half<float, H>(c, static_cast<const cx<float>*>(in), c.ioh[0], nrhs);
-  dslash_h<H>(c, c.ioh[1], c.ioh[0], nrhs);
-  from_half<H, float>(c, c.ioh[1], static_cast<cx<float>*>(out), nrhs);
+  dslash_h_f32<H>(c, static_cast<cx<float>*>(out), c.ioh[0], nrhs);
 }
 
 template <typename H>

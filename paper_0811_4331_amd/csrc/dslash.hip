@@ -28,6 +28,7 @@ namespace {
 template <typename R>
 struct Full {
   using T = R;
+  static constexpr bool kDots = true;
   static constexpr bool kHalf = false;
   static constexpr int NC = 12 * 2 * sizeof(R) / 16;  // stored chunks per site
   const u4* in;
@@ -39,6 +40,7 @@ struct Full {
 template <typename H>
 struct Half {
   using T = float;
+  static constexpr bool kDots = true;
   static constexpr bool kHalf = true;
   static constexpr int NC = 3;
   const u4* in;
@@ -78,11 +80,35 @@ __device__ __forceinline__ void load_numbers(const Half<H>*, const unsigned* v, 
     p[2 * k + 1] = z.im;
   }
 }
+// Half's result as FP32 numbers, each what 16-bit storage would have held: for
+// callers with FP32 fields (24^3x48, BF16, 1 rhs: 98 us with a pass that reads
+// the stored result back, XX us so).
+template <typename H>
+struct HalfOut32 : Half<H> {
+  static constexpr bool kDots = false;
+  cx<float>* f32;
+};
+
+// N / 2 numbers of a site from the first on, in 16 bits with the site's scale
+// so = 1 / inv, which the site's first thread stores.
 template <typename H, int N>
-__device__ __forceinline__ void store_numbers(const Half<H>*, unsigned* v, const float (&a)[N], float inv) {
+__device__ __forceinline__ void store_numbers(const Half<H>& io, int r, int vol, int site, int first,
+                                              const float (&a)[N], float so, float inv) {
+  if (first == 0) io.osc[(size_t)r * vol + site] = so;
+  unsigned* v = reinterpret_cast<unsigned*>(io.out) + ((size_t)r * vol + site) * 12 + first;
 #pragma unroll
   for (int k = 0; k < N / 2; ++k)
     v[k] = __builtin_bit_cast(unsigned, quantise<H>(a[2 * k], a[2 * k + 1], inv));
+}
+template <typename H, int N>
+__device__ __forceinline__ void store_numbers(const HalfOut32<H>& io, int r, int vol, int site, int first,
+                                              const float (&a)[N], float so, float inv) {
+  cx<float>* v = io.f32 + ((size_t)r * vol + site) * 12 + first;
+#pragma unroll
+  for (int k = 0; k < N / 2; ++k) {
+    const cx<float> z = h2f(quantise<H>(a[2 * k], a[2 * k + 1], inv));
+    v[k] = mk(so * z.re, so * z.im);
+  }
 }
 
 // U h (SIGN > 0) or U^+ h of the two colour vectors of a half spinor.
@@ -409,8 +435,7 @@ __global__ __launch_bounds__(256) void k_wilson_gather(Geom g, S io, R diag, int
       if (live) {
         float inv;
         const float so = quant_scale(m, inv);
-        if (q == 0) io.osc[(size_t)r * g.vol + site] = so;
-        store_numbers(&io, reinterpret_cast<unsigned*>(io.out + r * fs) + ((size_t)site * 12 + 3 * q), a, inv);
+        store_numbers(io, r, g.vol, site, 3 * q, a, so, inv);
         if constexpr (DOTS) {
           mr_dots(a, p, 6, d);
           d[0] *= (double)sc;
@@ -722,8 +747,7 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(2,
       m = scale_join(m, __shfl_xor(m, 1, 64));
       float inv;
       const float so = quant_scale(m, inv);
-      if (h == 0) io.osc[(size_t)r * g.vol + oown] = so;
-      store_numbers(&io, reinterpret_cast<unsigned*>(o) + ((size_t)oown * 12 + 6 * h), a, inv);
+      store_numbers(io, r, g.vol, oown, 6 * h, a, so, inv);
       if constexpr (DOTS) mr_dots(a, p, 12, d);
     }
     if constexpr (DOTS) {
@@ -791,9 +815,11 @@ inline int gather_group(const Ctx& c, int nsb, int nrhs, int forced) {
 
 template <class S>
 void allow_tile_lds() {
-  for (const void* f : {reinterpret_cast<const void*>(&k_wilson_tile<S, false>),
-                        reinterpret_cast<const void*>(&k_wilson_tile<S, true>)})
+  auto allow = [](const void* f) {
     WDMG_HIP(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kTileLds));
+  };
+  allow(reinterpret_cast<const void*>(&k_wilson_tile<S, false>));
+  if constexpr (S::kDots) allow(reinterpret_cast<const void*>(&k_wilson_tile<S, true>));
 }
 
 // Runs the operator; with `dots` the launch also writes the MR partial sums,
@@ -812,6 +838,7 @@ int launch_dslash(Ctx& c, const S& io, int nrhs, int prof_id, int prec_index, do
   int rg = c.tune_force[WDMG_TUNE_DSLASH_GROUP] >= 0 ? c.tune_force[WDMG_TUNE_DSLASH_GROUP] : gslot;
   const int nper = sizeof(R) == 8 ? 1 : gather_group(c, nsb, nrhs, rg);
   if (rg < 0) gslot = (signed char)(nper < kMaxRhs ? nper : kMaxRhs);
+  const bool with_dots = dots != nullptr;
   const int tneg = c.t_bc < 0 ? 1 : 0;
   const R diag = (R)(4.0 + c.mass);
   ProfScope ps(c, prof_id, (long long)g.vol * nrhs);
@@ -820,22 +847,15 @@ int launch_dslash(Ctx& c, const S& io, int nrhs, int prof_id, int prec_index, do
     if (tile) {
       const int nt = g.vol / 256, nx = nt % 8 == 0 ? 8 : 1;
       const dim3 grid(c.ncu / 8 * 8), block(kTileThreads);
-      if (dots)
-        hipLaunchKernelGGL((k_wilson_tile<S, true>), grid, block, kTileLds, c.stream, g, io, diag, tneg, nt, nrhs, nx,
-                           dots);
-      else
-        hipLaunchKernelGGL((k_wilson_tile<S, false>), grid, block, kTileLds, c.stream, g, io, diag, tneg, nt, nrhs, nx,
-                           dots);
+      const auto k = with_dots ? &k_wilson_tile<S, S::kDots> : &k_wilson_tile<S, false>;
+      hipLaunchKernelGGL(k, grid, block, kTileLds, c.stream, g, io, diag, tneg, nt, nrhs, nx, dots);
       WDMG_HIP(hipGetLastError());
       return nt;
     }
   }
   const dim3 grid((unsigned)((long long)nsb * ((nrhs + nper - 1) / nper))), block(256);
-  if (dots)
-    hipLaunchKernelGGL((k_wilson_gather<S, true>), grid, block, 0, c.stream, g, io, diag, tneg, nsb, nrhs, nper, dots);
-  else
-    hipLaunchKernelGGL((k_wilson_gather<S, false>), grid, block, 0, c.stream, g, io, diag, tneg, nsb, nrhs, nper,
-                       dots);
+  const auto k = with_dots ? &k_wilson_gather<S, S::kDots, R> : &k_wilson_gather<S, false, R>;
+  hipLaunchKernelGGL(k, grid, block, 0, c.stream, g, io, diag, tneg, nsb, nrhs, nper, dots);
   WDMG_HIP(hipGetLastError());
   return nsb;
 }
@@ -869,6 +889,8 @@ void init_dslash() {
   allow_tile_lds<Full<float>>();
   allow_tile_lds<Half<f16_t>>();
   allow_tile_lds<Half<bf16_t>>();
+  allow_tile_lds<HalfOut32<f16_t>>();
+  allow_tile_lds<HalfOut32<bf16_t>>();
 }
 
 template <typename R>
@@ -905,6 +927,13 @@ void dslash_mr(Ctx& c, cx<R>* out, const cx<R>* in, int nrhs, double scale, int 
 }
 
 template <typename H>
+void dslash_h_f32(Ctx& c, cx<float>* out, HF in, int nrhs) {
+  HalfOut32<H> io;
+  static_cast<Half<H>&>(io) = half_io<H>(c, in, in);
+  io.f32 = out;
+  launch_dslash(c, io, nrhs, half_kind<H>() == WDMG_F16 ? WDMG_K_DSLASH_F16 : WDMG_K_DSLASH_BF16, half_kind<H>());
+}
+template <typename H>
 void dslash_h_mr(Ctx& c, HF out, HF in, int nrhs, double scale, int slot) {
   double* d = dots_buffer(c, nrhs);
   const int nparts = launch_dslash(c, half_io<H>(c, out, in), nrhs,
@@ -917,6 +946,8 @@ template void dslash<double>(Ctx&, cx<double>*, const cx<double>*, int);
 template void dslash<float>(Ctx&, cx<float>*, const cx<float>*, int);
 template void dslash_h<f16_t>(Ctx&, HF, HF, int);
 template void dslash_h<bf16_t>(Ctx&, HF, HF, int);
+template void dslash_h_f32<f16_t>(Ctx&, cx<float>*, HF, int);
+template void dslash_h_f32<bf16_t>(Ctx&, cx<float>*, HF, int);
 template void dslash_mr<double>(Ctx&, cx<double>*, const cx<double>*, int, double, int);
 template void dslash_mr<float>(Ctx&, cx<float>*, const cx<float>*, int, double, int);
 template void dslash_h_mr<f16_t>(Ctx&, HF, HF, int, double, int);

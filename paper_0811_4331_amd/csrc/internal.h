@@ -291,6 +291,9 @@ void dslash(Ctx& c, cx<R>* out, const cx<R>* in, int nrhs);
 // The same on 16-bit fields and links, FP32 arithmetic.
 template <typename H>
 void dslash_h(Ctx& c, HF out, HF in, int nrhs);
+// The same with the stored result as FP32 numbers.
+template <typename H>
+void dslash_h_f32(Ctx& c, cx<float>* out, HF in, int nrhs);
 // Fused MR step (Sec. 3): out = D in, and for every rhs q
 // dsc[slot + 2q] = scale <out_q, in_q> / <out_q, out_q> (0 if the norm is 0),
 // from partial sums the operator launch writes per wave.
