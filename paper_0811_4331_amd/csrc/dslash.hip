@@ -82,7 +82,7 @@ __device__ __forceinline__ void load_numbers(const Half<H>*, const unsigned* v, 
 }
 // Half's result as FP32 numbers, each what 16-bit storage would have held: for
 // callers with FP32 fields (24^3x48, BF16, 1 rhs: 98 us with a pass that reads
-// the stored result back, XX us so).
+// the stored result back, 72 us so).
 template <typename H>
 struct HalfOut32 : Half<H> {
   static constexpr bool kDots = false;
