@@ -205,3 +205,35 @@ def test_2d_cycles_with_the_sums_in_the_operator(dims, nvs, cycles):
     res = np.linalg.norm(b - O.apply_D(u, x.cpu().numpy(), m, -1.0)) / np.linalg.norm(b)
     assert st["converged"] and res <= 1e-10, (st, res)
     c.close()
+
+
+@pytest.mark.parametrize("prec,nrhs", [("f16", 5), ("bf16", 8), ("f64", 3)])
+def test_prolongation_shared_by_right_hand_sides(prec, nrhs):
+    """Batches below the matrix cores' on a lattice large enough for several
+    right-hand sides per thread: the same products in the same order as one at
+    a time, so equal numbers."""
+    ctx, _ = context((16, 16, 16, 16), 951)
+    v = synthetic.gaussian_vectors((3, 16, 16, 16, 16, 4, 3), 952)
+    ctx.mg_setup([{"block": (4, 4, 4, 4), "nv": 3, "setup_iters": 0, "vectors": gpu(v)}])
+    c = synthetic.gaussian_vectors((nrhs,) + tuple(ctx.coarse_shape(1)), 953)
+    c = gpu(c if prec == "f64" else c.astype(np.complex64))
+    out = ctx.prolong(0, c, prec=prec)
+    for j in range(nrhs):
+        assert torch.equal(out[j], ctx.prolong(0, c[j].contiguous(), prec=prec)), j
+    ctx.close()
+
+
+@pytest.mark.parametrize("dims", [(8, 8, 8, 16), (4, 4, 8, 8)])  # 1024 and 64 coarse sites
+def test_coarsest_solve_of_one_right_hand_side(dims):
+    """The coefficients in a launch of their own (many sites) or in the update:
+    the cycle's solve to a true residual of 1e-10, recomputed by the oracle."""
+    ctx, u = context(dims, 961, -0.3)
+    lx, ly, lz, lt = dims
+    v = synthetic.gaussian_vectors((4, lt, lz, ly, lx, 4, 3), 962)
+    ctx.mg_setup([{"block": (2, 2, 2, 2), "nv": 4, "setup_iters": 20, "vectors": gpu(v)}], coarse_tol=1e-3)
+    b = synthetic.gaussian_spinor(dims, seed=963)
+    x, st = ctx.solve(gpu(b), tol=1e-10, restart=20, maxit=300)
+    st = st[0] if isinstance(st, list) else st
+    r = b.reshape(x.shape) - wilson.apply_D(u, x.cpu().numpy(), -0.3, -1.0)
+    assert st["converged"] and np.linalg.norm(r) <= 1e-10 * np.linalg.norm(b), st
+    ctx.close()
