@@ -103,6 +103,10 @@ __device__ __forceinline__ void agg_rhs_block(int nagg, int nrhs, int& agg, int&
 // the two halves add up at the end.  Chunk c + 1 is on its way while the
 // products of chunk c run.
 //
+// A is the type of products and sums: FP32 for FP32 and 16-bit operands at
+// level 0 on aggregates of whole 64 sites, FP64 on all others (see
+// launch_restrict_mm).
+//
 // Bound: the matrix cores (FP32 products, 1.0 of 1.7 M cycles at nv 24, whose
 // columns fill 24 of 32) and the vector units around them.  24^3x48, nv 24,
 // bf16, 32 FP32 right-hand sides in: 783 us, 950 us before the site table (a
@@ -277,14 +281,14 @@ struct PairFull {
   }
 };
 
-template <class VL, class FL, int CT, int QT>
+template <class VL, class FL, typename A, int CT, int QT>
 __global__ __launch_bounds__(256) void k_restrict_mm(AggMap map, int dof, VL V, FL F,
                                                      cx<typename VL::T>* __restrict__ out, int nagg, int nv,
                                                      int nrhs) {
   using R = typename VL::T;
-  using acc_t = typename Mm<R>::acc_t;
+  using acc_t = typename Mm<A>::acc_t;
   constexpr int QN = 16 * QT, LD = QN + 1;
-  __shared__ cx<R> Fs[2][2][kMmRows][LD];
+  __shared__ __align__(16) cx<R> Fs[2][2][kMmRows][LD];
   __shared__ int table[kMmTable];
   int agg, tile;
   agg_rhs_block(nagg, gridDim.x / nagg, agg, tile);
@@ -368,26 +372,26 @@ __global__ __launch_bounds__(256) void k_restrict_mm(AggMap map, int dof, VL V, 
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
         // rows 2 lk + h of the step: the same pairing on both operands
-        cx<R> f[QT];
+        cx<A> f[QT];
 #pragma unroll
-        for (int u = 0; u < QT; ++u) f[u] = Fs[b][chi][kh * 24 + t * 8 + 2 * lk + h][16 * u + li];
+        for (int u = 0; u < QT; ++u) f[u] = cvt<A>(Fs[b][chi][kh * 24 + t * 8 + 2 * lk + h][16 * u + li]);
 #pragma unroll
         for (int j = 0; j < CT; ++j) {
-          const cx<R> v = h == 0 ? VL::first(vc[t][j]) : VL::second(vc[t][j]);
+          const cx<A> v = cvt<A>(h == 0 ? VL::first(vc[t][j]) : VL::second(vc[t][j]));
 #pragma unroll
           for (int u = 0; u < QT; ++u) {
-            re[j][u] = Mm<R>::mma(v.re, f[u].re, re[j][u]);
-            im[j][u] = Mm<R>::mma(v.re, f[u].im, im[j][u]);
-            re[j][u] = Mm<R>::mma(v.im, f[u].im, re[j][u]);
-            im[j][u] = Mm<R>::mma(-v.im, f[u].re, im[j][u]);
+            re[j][u] = Mm<A>::mma(v.re, f[u].re, re[j][u]);
+            im[j][u] = Mm<A>::mma(v.re, f[u].im, im[j][u]);
+            re[j][u] = Mm<A>::mma(v.im, f[u].im, re[j][u]);
+            im[j][u] = Mm<A>::mma(-v.im, f[u].re, im[j][u]);
           }
         }
       }
     }
   }
   // the second half's sums join the first's
-  cx<R>* part = &Fs[0][0][0][0];
-  static_assert(sizeof(Fs) >= 2 * 64 * 4 * sizeof(cx<R>), "one tile of both chiralities");
+  cx<A>* part = reinterpret_cast<cx<A>*>(&Fs[0][0][0][0]);
+  static_assert(sizeof(Fs) >= 2 * 64 * 4 * sizeof(cx<A>), "one tile of both chiralities");
 #pragma unroll
   for (int j = 0; j < CT; ++j) {
 #pragma unroll
@@ -395,7 +399,7 @@ __global__ __launch_bounds__(256) void k_restrict_mm(AggMap map, int dof, VL V, 
       __syncthreads();
       if (kh == 1) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) part[(chi * 4 + r) * 64 + lane] = mk<R>(re[j][u][r], im[j][u][r]);
+        for (int r = 0; r < 4; ++r) part[(chi * 4 + r) * 64 + lane] = mk<A>(re[j][u][r], im[j][u][r]);
       }
       __syncthreads();
       const int q = 16 * u + li;
@@ -403,9 +407,9 @@ __global__ __launch_bounds__(256) void k_restrict_mm(AggMap map, int dof, VL V, 
         cx<R>* o = out + ((size_t)(q0 + q) * nagg + agg) * 2 * nv + chi * nv;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          const int k = 16 * j + Mm<R>::row(lk, r);
-          const cx<R> p = part[(chi * 4 + r) * 64 + lane];
-          if (k < nv) o[k] = mk<R>(re[j][u][r] + p.re, im[j][u][r] + p.im);
+          const int k = 16 * j + Mm<A>::row(lk, r);
+          const cx<A> p = part[(chi * 4 + r) * 64 + lane];
+          if (k < nv) o[k] = mk<R>((R)(re[j][u][r] + p.re), (R)(im[j][u][r] + p.im));
         }
       }
     }
@@ -884,25 +888,44 @@ void launch_restrict_one(Ctx& c, const Level& f, const D& io, cx<typename D::T>*
 // would fill one of a tile's 16 columns: it streams V instead.
 inline bool mm_fits(const Level& f) { return f.dof % 4 == 0 && f.nv <= 32; }
 
-template <class VL, class FL>
-void launch_restrict_mm(Ctx& c, const Level& f, const VL& V, const FL& F, cx<typename VL::T>* out, int nrhs) {
+template <typename A, class VL, class FL>
+void launch_restrict_sums(Ctx& c, const Level& f, const VL& V, const FL& F, cx<typename VL::T>* out, int nrhs) {
   const AggMap map = make_map(f);
   const int nagg = nagg_of(f);
   const dim3 block(256);
+#define RM(CT, QT)                                                                                                  \
+  hipLaunchKernelGGL((k_restrict_mm<VL, FL, A, CT, QT>), grid, block, 0, c.stream, map, f.dof, V, F, out, nagg, f.nv, \
+                     nrhs)
   if (nrhs <= 16) {
     const dim3 grid(nagg);
     if (f.nv <= 16)
-      hipLaunchKernelGGL((k_restrict_mm<VL, FL, 1, 1>), grid, block, 0, c.stream, map, f.dof, V, F, out, nagg, f.nv, nrhs);
+      RM(1, 1);
     else
-      hipLaunchKernelGGL((k_restrict_mm<VL, FL, 2, 1>), grid, block, 0, c.stream, map, f.dof, V, F, out, nagg, f.nv, nrhs);
+      RM(2, 1);
   } else {
     const dim3 grid(nagg * ((nrhs + 31) / 32));
     if (f.nv <= 16)
-      hipLaunchKernelGGL((k_restrict_mm<VL, FL, 1, 2>), grid, block, 0, c.stream, map, f.dof, V, F, out, nagg, f.nv, nrhs);
+      RM(1, 2);
     else
-      hipLaunchKernelGGL((k_restrict_mm<VL, FL, 2, 2>), grid, block, 0, c.stream, map, f.dof, V, F, out, nagg, f.nv, nrhs);
+      RM(2, 2);
   }
+#undef RM
   WDMG_HIP(hipGetLastError());
+}
+
+// Sums of FP32 and 16-bit operands: in FP32 at level 0 on aggregates of whole
+// 64 sites (the 4^4 ones of every production hierarchy: 24^3x48, nv 24, bf16,
+// 32 rhs 783 us), in FP64 on smaller or odd aggregates and on the coarse
+// levels, as a single right-hand side sums everywhere.  FP64 products run at
+// half the FP32 rate: 2592 sites of 48 numbers, nv 16, 16 rhs 20 us (17 with
+// FP32 sums, 160 with FP64 sums on the vector units); 24^4, 3^4 aggregates, nv
+// 20, FP32, 32 rhs 692 us (430, 11500).
+template <class VL, class FL>
+void launch_restrict_mm(Ctx& c, const Level& f, const VL& V, const FL& F, cx<typename VL::T>* out, int nrhs) {
+  if (sizeof(typename VL::T) == 4 && f.l == 0 && make_map(f).bvol % 64 == 0)
+    launch_restrict_sums<typename VL::T>(c, f, V, F, out, nrhs);
+  else
+    launch_restrict_sums<double>(c, f, V, F, out, nrhs);
 }
 
 template <typename R>
