@@ -194,22 +194,26 @@ int wdmg_set_gauge(wdmg_ctx* ctx, const void* U, int t_bc);
 int wdmg_set_mass(wdmg_ctx* ctx, double m);
 
 /* Sec. 1: out = D in for nrhs fine fields.  in, out: device, canonical fine
- * layout, out != in.  prec WDMG_F64 (complex128 I/O) or WDMG_F32, WDMG_F16,
+ * layout, out != in (they may overlap, which costs a copy of `in` through a
+ * library buffer; here as in wdmg_apply_D_noalloc, wdmg_roundtrip,
+ * wdmg_restrict and wdmg_prolong).  prec WDMG_F64 (complex128 I/O) or WDMG_F32, WDMG_F16,
  * WDMG_BF16 (complex64 I/O; the 16-bit paths store `in`, the links and the
  * result in 16 bits as described for WDMG_F16 and compute in FP32). */
 int wdmg_apply_D(wdmg_ctx* ctx, void* out, const void* in, int nrhs, int prec);
 
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid allocation): the same
- * out = D in as wdmg_apply_D.  Fields that are not aligned to 16 bytes go
- * through a 64 MiB device array that the library holds on every GPU it runs
- * on until the process ends; the limit below holds for all.  prec WDMG_F64 or WDMG_F32 only; at most
+ * out = D in as wdmg_apply_D.  Fields that are not aligned to 16 bytes,
+ * or overlap, go through a 64 MiB device array that the library holds on every
+ * GPU it runs on until the process ends; the limit below holds for all.
+ * prec WDMG_F64 or WDMG_F32 only; at most
  * 2 x 12 x padded sites x nrhs x (16 or 8) bytes <= 64 MiB (a 16^4 lattice
  * takes 2 FP64 or 5 FP32 right-hand sides), else WDMG_ERR_ARG before
  * anything is launched.  Makes no hipMalloc/hipFree or other allocating call,
- * and the call is not timed by wdmg_profile.  All calls on one GPU share its array (which keeps the last
- * call's contents; nothing in it needs to start at zero), so calls that
- * overlap on one GPU, from any context or stream, race. */
+ * and the call is not timed by wdmg_profile.  All calls on one GPU share its
+ * array (which keeps the last call's contents; nothing in it needs to start at
+ * zero), so calls that overlap in time on one GPU, from any context or stream,
+ * race. */
 int wdmg_apply_D_noalloc(wdmg_ctx* ctx, void* out, const void* in, int nrhs, int prec);
 
 /* Storage conversion of fine fields (the layout and precision conversion in
@@ -247,7 +251,7 @@ int wdmg_get_prolongator(wdmg_ctx* ctx, int level, void* V_out);
 /* Sec. 2: out = D_c in on coarse level l >= 1 (nrhs fields).  Canonical
  * coarse layout; prec WDMG_F64 (complex128) or WDMG_F32, WDMG_F16, WDMG_BF16
  * (complex64 vectors; the 16-bit kinds use 16-bit blocks with one scale per
- * block). */
+ * block).  out and in must not overlap. */
 int wdmg_apply_Dc(wdmg_ctx* ctx, int level, void* out, const void* in, int nrhs, int prec);
 
 /* Sec. 3 (normal equations): out = (D^dagger D)_c in = P^dagger D^dagger D P in

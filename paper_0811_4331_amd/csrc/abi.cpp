@@ -88,8 +88,13 @@ void ensure_ioh(Ctx& c, int nrhs) {
 }
 
 // Caller fields are in the layout the kernels work on.  One that is not aligned
-// to the 16 bytes in which they move sites goes through a library buffer.
+// to the 16 bytes in which they move sites goes through a library buffer, and so
+// does an input that shares memory with the output.
 bool aligned(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
+bool shares(const void* p, size_t np, const void* q, size_t nq) {
+  const uintptr_t a = reinterpret_cast<uintptr_t>(p), b = reinterpret_cast<uintptr_t>(q);
+  return a < b + nq && b < a + np;
+}
 
 // n complex numbers of R copied as pairs of FP32 words, for any 8-byte aligned pointer.
 template <typename R>
@@ -98,8 +103,8 @@ void copy_words(Ctx& c, void* dst, const void* src, size_t n) {
 }
 // `p` itself, or its copy in `stage`
 template <typename R>
-const cx<R>* field_in(Ctx& c, const void* p, void* stage, size_t n) {
-  if (aligned(p)) return static_cast<const cx<R>*>(p);
+const cx<R>* field_in(Ctx& c, const void* p, void* stage, size_t n, bool shared = false) {
+  if (aligned(p) && !shared) return static_cast<const cx<R>*>(p);
   copy_words<R>(c, stage, p, n);
   return static_cast<const cx<R>*>(stage);
 }
@@ -115,9 +120,10 @@ void field_done(Ctx& c, void* p, const void* stage, size_t n) {
 size_t fine_n(const Ctx& c) { return (size_t)c.g0.vol * 12; }
 
 // io_a / io_b when one of the pointers needs them
-void ensure_stage(Ctx& c, const void* p, const void* q, size_t bytes) {
-  if (!aligned(p) || !aligned(q)) ensure_io(c, bytes);
+void ensure_stage(Ctx& c, const void* p, const void* q, size_t bytes, bool shared) {
+  if (!aligned(p) || !aligned(q) || shared) ensure_io(c, bytes);
 }
+size_t coarse_n(const Ctx& c, int level) { return c.lev[level + 1].n; }
 
 template <typename H>
 void apply_D_half(Ctx& c, void* out, const void* in, int nrhs) {
@@ -136,7 +142,9 @@ void roundtrip_half(Ctx& c, void* out, const void* in, int nrhs) {
 template <typename H>
 void restrict_half(Ctx& c, void* cout, const void* fin, int nrhs) {
   const void* V = v16(c, c.lev[0], half_kind<H>());
-  if (restrict0_round<H>(c, c.lev[0], V, static_cast<const cx<float>*>(fin), static_cast<cx<float>*>(cout), nrhs))
+  const size_t cn = coarse_n(c, 0) * nrhs, fn = fine_n(c) * nrhs;
+  if (!shares(cout, cn * sizeof(cx<float>), fin, fn * sizeof(cx<float>)) &&
+      restrict0_round<H>(c, c.lev[0], V, static_cast<const cx<float>*>(fin), static_cast<cx<float>*>(cout), nrhs))
     return;
   ensure_ioh(c, nrhs);
   to_half<float, H>(c, static_cast<const cx<float>*>(fin), c.ioh[0], nrhs);
@@ -178,9 +186,10 @@ void need_nrhs(int nrhs) {
 template <typename R>
 void apply_D_impl(Ctx& c, void* out, const void* in, int nrhs) {
   const size_t n = fine_n(c) * nrhs;
-  ensure_stage(c, in, out, n * sizeof(cx<R>));
+  const bool shared = shares(out, n * sizeof(cx<R>), in, n * sizeof(cx<R>));
+  ensure_stage(c, in, out, n * sizeof(cx<R>), shared);
   cx<R>* o = field_out<R>(out, c.io_b);
-  dslash<R>(c, o, field_in<R>(c, in, c.io_a, n), nrhs);
+  dslash<R>(c, o, field_in<R>(c, in, c.io_a, n, shared), nrhs);
   field_done<R>(c, out, o, n);
 }
 
@@ -197,12 +206,27 @@ const cx<R>* dc_of(const Level& L) {
 
 template <typename R>
 void restrict_impl(Ctx& c, int level, void* cout, const void* fin, int nrhs) {
-  restrict_to<R>(c, level, static_cast<const cx<R>*>(fin), static_cast<cx<R>*>(cout), nrhs);
+  const cx<R>* f = static_cast<const cx<R>*>(fin);
+  const size_t n = c.lev[level].n * nrhs;
+  if (shares(cout, coarse_n(c, level) * nrhs * sizeof(cx<R>), fin, n * sizeof(cx<R>))) {
+    ensure_io(c, n * sizeof(cx<R>));
+    copy_words<R>(c, c.io_a, fin, n);
+    f = static_cast<const cx<R>*>(c.io_a);
+  }
+  restrict_to<R>(c, level, f, static_cast<cx<R>*>(cout), nrhs);
 }
 
 template <typename R>
 void prolong_impl(Ctx& c, int level, void* fout, const void* cin, int nrhs) {
-  prolong_from<R>(c, level, static_cast<const cx<R>*>(cin), static_cast<cx<R>*>(fout), nrhs);
+  cx<R>* f = static_cast<cx<R>*>(fout);
+  const size_t n = c.lev[level].n * nrhs;
+  const bool shared = shares(fout, n * sizeof(cx<R>), cin, coarse_n(c, level) * nrhs * sizeof(cx<R>));
+  if (shared) {
+    ensure_io(c, n * sizeof(cx<R>));
+    f = static_cast<cx<R>*>(c.io_a);
+  }
+  prolong_from<R>(c, level, static_cast<const cx<R>*>(cin), f, nrhs);
+  if (shared) copy_words<R>(c, fout, f, n);
 }
 
 template <typename R>
@@ -210,10 +234,12 @@ void smooth_impl(Ctx& c, int level, void* x, const void* b, int nrhs, int iters)
   // Right-hand sides are smoothed together, kSmoothRhs at a time (16^4, FP32,
   // 8 rhs, 4 steps: 379 us, 1004 us one by one; more would only grow the
   // buffers).  16-bit coarse blocks take one at a time: their batched kernel
-  // rounds the vectors as well.
+  // rounds the vectors as well.  So do x and b that overlap without being the
+  // same buffer: a right-hand side there may be an earlier one's solution.
   constexpr int kSmoothRhs = 8;
   const size_t n = c.lev[level].n;
-  const int most = level > 0 && c.vc_half ? 1 : std::min(nrhs, kSmoothRhs);
+  const bool shared = x != b && shares(x, n * nrhs * sizeof(cx<R>), b, n * nrhs * sizeof(cx<R>));
+  const int most = (level > 0 && c.vc_half) || shared ? 1 : std::min(nrhs, kSmoothRhs);
   ensure_io(c, 3 * most * n * sizeof(cx<R>));
   cx<R>* a = static_cast<cx<R>*>(c.io_a);
   cx<R>* q = static_cast<cx<R>*>(c.io_b);
@@ -467,7 +493,7 @@ int wdmg_apply_D_noalloc(wdmg_ctx* c, void* out, const void* in, int nrhs, int p
     if (2 * field > kNoAllocScratchBytes)
       throw Error(WDMG_ERR_ARG, "wdmg_apply_D_noalloc: " + std::to_string(2 * field) +
                                     " bytes of scratch needed, the maximum is 64 MiB");
-    // used for fields that are not aligned to 16 bytes only; `field` is a
+    // used for fields that are not aligned to 16 bytes or overlap; `field` is a
     // multiple of 64 sites x 12 x 8 bytes, so both halves are 256-byte aligned
     unsigned char* base = static_cast<unsigned char*>(g_scratch[dev]);
     c->no_alloc = true;
@@ -475,14 +501,15 @@ int wdmg_apply_D_noalloc(wdmg_ctx* c, void* out, const void* in, int nrhs, int p
       Ctx& c;
       ~Restore() { c.no_alloc = false; }
     } restore{*c};
-    const size_t n = fine_n(*c) * nrhs;
+    const size_t n = fine_n(*c) * nrhs, bytes = n * (prec == WDMG_F64 ? 16 : 8);
+    const bool shared = shares(out, bytes, in, bytes);
     if (prec == WDMG_F64) {
       cx<double>* o = field_out<double>(out, base + field);
-      dslash<double>(*c, o, field_in<double>(*c, in, base, n), nrhs);
+      dslash<double>(*c, o, field_in<double>(*c, in, base, n, shared), nrhs);
       field_done<double>(*c, out, o, n);
     } else {
       cx<float>* o = field_out<float>(out, base + field);
-      dslash<float>(*c, o, field_in<float>(*c, in, base, n), nrhs);
+      dslash<float>(*c, o, field_in<float>(*c, in, base, n, shared), nrhs);
       field_done<float>(*c, out, o, n);
     }
     return WDMG_OK;
@@ -496,11 +523,14 @@ int wdmg_roundtrip(wdmg_ctx* c, void* out, const void* in, int nrhs, int prec) {
     need_nrhs(nrhs);
     need_prec(prec);
     if (out == in) throw Error(WDMG_ERR_ARG, "out must differ from in");
-    const size_t n = fine_n(*c) * nrhs;
-    if (prec == WDMG_F64) {
-      copy_words<double>(*c, out, in, n);
-    } else if (prec == WDMG_F32) {
-      copy_words<float>(*c, out, in, n);
+    const size_t n = fine_n(*c) * nrhs, bytes = n * (prec == WDMG_F64 ? 16 : 8);
+    if (!is_half(prec)) {
+      if (shares(out, bytes, in, bytes)) {
+        ensure_io(*c, bytes);
+        copy_words<float>(*c, c->io_a, in, bytes / sizeof(cx<float>));
+        in = c->io_a;
+      }
+      copy_words<float>(*c, out, in, bytes / sizeof(cx<float>));
     } else if (prec == WDMG_F16) {
       roundtrip_half<f16_t>(*c, out, in, nrhs);
     } else {
