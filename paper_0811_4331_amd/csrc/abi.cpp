@@ -80,10 +80,8 @@ bool is_half(int prec) { return prec == WDMG_F16 || prec == WDMG_BF16; }
 void ensure_ioh(Ctx& c, int nrhs) {
   if (nrhs <= c.ioh_cap) return;
   WDMG_HIP(hipStreamSynchronize(c.stream));
-  for (HF& f : c.ioh) {
-    hf_free(c, f);
-    f = hf_alloc(c, nrhs);
-  }
+  c.ioh_cap = 0;
+  for (HF& f : c.ioh) hf_renew(c, f, nrhs);
   c.ioh_cap = nrhs;
 }
 
@@ -263,8 +261,8 @@ void smooth_impl(Ctx& c, int level, void* x, const void* b, int nrhs, int iters)
 void ensure_solve_x(Ctx& c, int nrhs) {
   if (nrhs <= c.sol_cap) return;
   WDMG_HIP(hipStreamSynchronize(c.stream));
-  dev_free(c, c.sol_x);
-  c.sol_x = static_cast<cx<double>*>(dev_alloc(c, (size_t)nrhs * fine_n(c) * sizeof(cx<double>)));
+  c.sol_cap = 0;
+  dev_renew(c, c.sol_x, (size_t)nrhs * fine_n(c) * sizeof(cx<double>));
   c.sol_cap = nrhs;
 }
 
@@ -273,8 +271,8 @@ const cx<double>* solve_b(Ctx& c, const void* b, int nrhs) {
   const size_t n = fine_n(c) * nrhs;
   if (!aligned(b) && nrhs > c.sol_bcap) {
     WDMG_HIP(hipStreamSynchronize(c.stream));
-    dev_free(c, c.sol_b);
-    c.sol_b = static_cast<cx<double>*>(dev_alloc(c, n * sizeof(cx<double>)));
+    c.sol_bcap = 0;
+    dev_renew(c, c.sol_b, n * sizeof(cx<double>));
     c.sol_bcap = nrhs;
   }
   return field_in<double>(c, b, c.sol_b, n);
@@ -413,10 +411,8 @@ int wdmg_set_gauge(wdmg_ctx* c, const void* U, int t_bc) {
     if (t_bc != 1 && t_bc != -1) throw Error(WDMG_ERR_ARG, "t_bc must be +1 or -1");
     if (c->have_mg) free_hierarchy(*c);
     const size_t n = (size_t)c->g0.vpad * kLinkComp;
-    if (!c->U64) {
-      c->U64 = static_cast<cx<double>*>(dev_alloc(*c, n * sizeof(cx<double>)));
-      c->U32 = static_cast<cx<float>*>(dev_alloc(*c, n * sizeof(cx<float>)));
-    }
+    if (!c->U64) c->U64 = static_cast<cx<double>*>(dev_alloc(*c, n * sizeof(cx<double>)));
+    if (!c->U32) c->U32 = static_cast<cx<float>*>(dev_alloc(*c, n * sizeof(cx<float>)));
     set_scalar(*c, S_ERR + 2, 0.0, 0.0);
     c->u16_kind = 0;
     gauge_import(*c, static_cast<const cx<double>*>(U), t_bc);

@@ -1314,10 +1314,8 @@ void ensure_dc16(Ctx& c, Level& cl, int kind) {
   const size_t nblk = (size_t)cl.nsite * 9, nn = (size_t)h16_chunks(n2) * n2 * 4;
   if (cl.dc16_kind != kind) {
     if (!cl.Dc64) throw Error(WDMG_ERR_ARG, "FP64 coarse blocks released by wdmg_release_unused");
-    if (!cl.Dc16) {
-      cl.Dc16 = dev_alloc(c, nblk * nn * 4);
-      cl.Dc16s = static_cast<float*>(dev_alloc(c, nblk * sizeof(float)));
-    }
+    if (!cl.Dc16) cl.Dc16 = dev_alloc(c, nblk * nn * 4);
+    if (!cl.Dc16s) cl.Dc16s = static_cast<float*>(dev_alloc(c, nblk * sizeof(float)));
     if (kind == WDMG_F16)
       hipLaunchKernelGGL((k_dc_to_half<f16_t>), dim3((unsigned)nblk), dim3(256), 0, c.stream, cl.Dc64,
                          static_cast<cxh<f16_t>*>(cl.Dc16), cl.Dc16s, n2);

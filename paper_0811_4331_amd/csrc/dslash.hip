@@ -910,8 +910,8 @@ double* dots_buffer(Ctx& c, int nrhs) {
   if (need > c.dots_cap) {
     if (c.capturing) throw Error(WDMG_ERR_ARG, "MR partial-sum buffer too small inside a graph capture");
     WDMG_HIP(hipStreamSynchronize(c.stream));
-    dev_free(c, c.dots);
-    c.dots = static_cast<double*>(dev_alloc(c, need * sizeof(double)));
+    c.dots_cap = 0;
+    dev_renew(c, c.dots, need * sizeof(double));
     c.dots_cap = need;
   }
   return c.dots;

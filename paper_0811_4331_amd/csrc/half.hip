@@ -103,12 +103,11 @@ const void* v16(Ctx& c, Level& L, int kind) {
   return L.V16;
 }
 
-HF hf_alloc(Ctx& c, int nrhs) {
-  HF f;
+void hf_renew(Ctx& c, HF& f, int nrhs) {
   const size_t vol = c.g0.vol;
-  f.v = dev_alloc(c, (size_t)nrhs * 12 * vol * 4);
-  f.s = static_cast<float*>(dev_alloc(c, (size_t)nrhs * vol * sizeof(float)));
-  return f;
+  hf_free(c, f);
+  dev_renew(c, f.v, (size_t)nrhs * 12 * vol * 4);
+  dev_renew(c, f.s, (size_t)nrhs * vol * sizeof(float));
 }
 
 void hf_free(Ctx& c, HF& f) {

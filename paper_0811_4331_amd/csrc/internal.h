@@ -247,6 +247,14 @@ void prof_collect(Ctx& c);
 
 void* dev_alloc(Ctx& c, size_t bytes);
 void dev_free(Ctx& c, void* p);
+// Replaces the buffer at p; p is null if the allocation fails.  Callers set
+// the capacity that stands for the buffer to 0 first.
+template <typename T>
+void dev_renew(Ctx& c, T*& p, size_t bytes) {
+  dev_free(c, p);
+  p = nullptr;
+  p = static_cast<T*>(dev_alloc(c, bytes));
+}
 void ensure_io(Ctx& c, size_t bytes);
 
 constexpr int kReduceThreads = 256;
@@ -263,7 +271,7 @@ void convert(Ctx& c, cx<Rout>* out, const cx<Rin>* in, size_t n);
 // from their FP32 copies.
 const void* u16(Ctx& c, int kind);
 const void* v16(Ctx& c, Level& L, int kind);
-HF hf_alloc(Ctx& c, int nrhs);
+void hf_renew(Ctx& c, HF& f, int nrhs);  // as dev_renew
 void hf_free(Ctx& c, HF& f);
 template <typename H>
 void hf_zero(Ctx& c, HF f, int nrhs);

@@ -56,13 +56,29 @@ void dev_free(Ctx& c, void* p) {
     (void)hipFree(p);
 }
 
+namespace {
+// Device memory of one call, given back when it ends or fails.
+struct Scratch {
+  Ctx& c;
+  std::vector<void*> bufs;
+  void* get(size_t bytes) {
+    bufs.reserve(bufs.size() + 1);
+    bufs.push_back(dev_alloc(c, bytes));
+    return bufs.back();
+  }
+  ~Scratch() {
+    (void)hipStreamSynchronize(c.stream);
+    for (void* p : bufs) dev_free(c, p);
+  }
+};
+}  // namespace
+
 void ensure_io(Ctx& c, size_t bytes) {
   if (bytes <= c.io_bytes) return;
   WDMG_HIP(hipStreamSynchronize(c.stream));
-  dev_free(c, c.io_a);
-  dev_free(c, c.io_b);
-  c.io_a = dev_alloc(c, bytes);
-  c.io_b = dev_alloc(c, bytes);
+  c.io_bytes = 0;
+  dev_renew(c, c.io_a, bytes);
+  dev_renew(c, c.io_b, bytes);
   c.io_bytes = bytes;
 }
 
@@ -198,15 +214,13 @@ void ensure_work(Ctx& c, int l, int nrhs) {
   int& cap = sizeof(R) == 8 ? L.cap64 : L.cap32;
   if (nrhs <= cap) return;
   WDMG_HIP(hipStreamSynchronize(c.stream));
+  cap = 0;
   for (int i = 0; i < kWork; ++i) {
     if (l == 0 && (i == 0 || i > 4)) continue;  // the fine level uses work fields 1..4 only
-    if constexpr (sizeof(R) == 8) {
-      dev_free(c, L.w64[i]);
-      L.w64[i] = static_cast<cx<double>*>(dev_alloc(c, (size_t)nrhs * L.n * sizeof(cx<double>)));
-    } else {
-      dev_free(c, L.w32[i]);
-      L.w32[i] = static_cast<cx<float>*>(dev_alloc(c, (size_t)nrhs * L.n * sizeof(cx<float>)));
-    }
+    if constexpr (sizeof(R) == 8)
+      dev_renew(c, L.w64[i], (size_t)nrhs * L.n * sizeof(cx<double>));
+    else
+      dev_renew(c, L.w32[i], (size_t)nrhs * L.n * sizeof(cx<float>));
   }
   cap = nrhs;
 }
@@ -215,19 +229,14 @@ void ensure_coarsest_basis(Ctx& c, int nrhs) {
   Level& L = c.lev[c.nlevels - 1];
   if (nrhs <= L.capB) return;
   WDMG_HIP(hipStreamSynchronize(c.stream));
-  dev_free(c, L.basisZ);
-  dev_free(c, L.basisW);
-  dev_free(c, L.xT);
+  L.capB = 0;
   const size_t sz = (size_t)c.mg.coarse_restart * nrhs * L.n * sizeof(cx<double>);
-  L.basisZ = static_cast<cx<double>*>(dev_alloc(c, sz));
-  L.basisW = static_cast<cx<double>*>(dev_alloc(c, sz));
-  L.xT = static_cast<cx<double>*>(dev_alloc(c, (size_t)nrhs * L.n * sizeof(cx<double>)));
-  dev_free(c, L.cpart);
-  dev_free(c, L.cpart3);
-  dev_free(c, L.chist);
-  L.cpart = static_cast<double*>(dev_alloc(c, coarsest_gcr_partials(nrhs, c.mg.coarse_restart) * sizeof(double)));
-  L.cpart3 = static_cast<double*>(dev_alloc(c, coarsest_gcr_partials3(nrhs) * sizeof(double)));
-  L.chist = static_cast<double*>(dev_alloc(c, coarsest_gcr_history(nrhs, c.mg.coarse_restart) * sizeof(double)));
+  dev_renew(c, L.basisZ, sz);
+  dev_renew(c, L.basisW, sz);
+  dev_renew(c, L.xT, (size_t)nrhs * L.n * sizeof(cx<double>));
+  dev_renew(c, L.cpart, coarsest_gcr_partials(nrhs, c.mg.coarse_restart) * sizeof(double));
+  dev_renew(c, L.cpart3, coarsest_gcr_partials3(nrhs) * sizeof(double));
+  dev_renew(c, L.chist, coarsest_gcr_history(nrhs, c.mg.coarse_restart) * sizeof(double));
   L.capB = nrhs;
 }
 
@@ -388,10 +397,8 @@ void ensure_work_h(Ctx& c, int nrhs) {
   Level& L = c.lev[0];
   if (nrhs <= L.caph) return;
   WDMG_HIP(hipStreamSynchronize(c.stream));
-  for (HF& f : L.wh) {
-    hf_free(c, f);
-    f = hf_alloc(c, nrhs);
-  }
+  L.caph = 0;
+  for (HF& f : L.wh) hf_renew(c, f, nrhs);
   L.caph = nrhs;
 }
 
@@ -467,8 +474,8 @@ int fgcr(Ctx& c, cx<double>* x, const cx<double>* b, int nrhs, const wdmg_solve_
     if (!c.cap_stream) WDMG_HIP(hipStreamCreateWithFlags(&c.cap_stream, hipStreamNonBlocking));
     if (!basis32 && nrhs > c.outer_zf_cap) {
       WDMG_HIP(hipStreamSynchronize(c.stream));
-      dev_free(c, c.outer_zf);
-      c.outer_zf = static_cast<cx<double>*>(dev_alloc(c, (size_t)nrhs * n * sizeof(cx<double>)));
+      c.outer_zf_cap = 0;
+      dev_renew(c, c.outer_zf, (size_t)nrhs * n * sizeof(cx<double>));
       c.outer_zf_cap = nrhs;
     }
   }
@@ -864,8 +871,9 @@ static void relax_batch(Ctx& c, int l, cx<R>* V, int nv, int iters, double omega
   if (kb > (size_t)kMaxRhs) kb = kMaxRhs;
   // the residuals of kMrRing steps where they fit the budget for the same batch
   const bool fits = (kMrRing + 1) * kb * field <= budget;
-  cx<R>* Rb = static_cast<cx<R>*>(dev_alloc(c, (fits ? kMrRing : 1) * kb * field));
-  cx<R>* Pb = static_cast<cx<R>*>(dev_alloc(c, kb * field));
+  Scratch tmp{c};
+  cx<R>* Rb = static_cast<cx<R>*>(tmp.get((fits ? kMrRing : 1) * kb * field));
+  cx<R>* Pb = static_cast<cx<R>*>(tmp.get(kb * field));
   if (l == 0) dots_buffer(c, (int)kb);
   for (int k0 = 0; k0 < nv; k0 += (int)kb) {
     const int nb = (nv - k0) < (int)kb ? (nv - k0) : (int)kb;
@@ -881,9 +889,6 @@ static void relax_batch(Ctx& c, int l, cx<R>* V, int nv, int iters, double omega
       mr<R>(c, l, X, Rb, Pb, nb, iters, omega, nullptr, true);
     }
   }
-  WDMG_HIP(hipStreamSynchronize(c.stream));
-  dev_free(c, Rb);
-  dev_free(c, Pb);
 }
 
 // The same relaxation at level 0 with the candidates, residuals and A r in
@@ -898,7 +903,12 @@ static void relax_batch_h(Ctx& c, cx<double>* V, int nv, int iters, double omega
   if (kb < 1) kb = 1;
   if (kb > (size_t)nv) kb = nv;
   if (kb > (size_t)kMaxRhs) kb = kMaxRhs;
-  HF X = hf_alloc(c, (int)kb), Rb = hf_alloc(c, (int)kb), Pb = hf_alloc(c, (int)kb);
+  Scratch tmp{c};
+  HF X, Rb, Pb;
+  for (HF* f : {&X, &Rb, &Pb}) {
+    f->v = tmp.get(kb * 12 * c.g0.vol * 4);
+    f->s = static_cast<float*>(tmp.get(kb * c.g0.vol * sizeof(float)));
+  }
   dots_buffer(c, (int)kb);
   for (int k0 = 0; k0 < nv; k0 += (int)kb) {
     const int nb = (nv - k0) < (int)kb ? (nv - k0) : (int)kb;
@@ -912,10 +922,6 @@ static void relax_batch_h(Ctx& c, cx<double>* V, int nv, int iters, double omega
     }
     from_half<H, double>(c, X, V + (size_t)k0 * n, nb);
   }
-  WDMG_HIP(hipStreamSynchronize(c.stream));
-  hf_free(c, X);
-  hf_free(c, Rb);
-  hf_free(c, Pb);
 }
 
 static void relax(Ctx& c, int l, const wdmg_level_params& lp, double omega) {
@@ -955,8 +961,9 @@ static void adapt_candidates(Ctx& c, int l, int iters) {
   ensure_work<double>(c, l, 1);
   ensure_work<double>(c, l + 1, 1);
   ensure_coarsest_basis(c, 1);
-  cx<double>* ax = static_cast<cx<double>*>(dev_alloc(c, F.n * sizeof(cx<double>)));
-  cx<double>* mx = static_cast<cx<double>*>(dev_alloc(c, F.n * sizeof(cx<double>)));
+  Scratch tmp{c};
+  cx<double>* ax = static_cast<cx<double>*>(tmp.get(F.n * sizeof(cx<double>)));
+  cx<double>* mx = static_cast<cx<double>*>(tmp.get(F.n * sizeof(cx<double>)));
   for (int k = 1; k < nv; ++k) {
     F.nv = k;
     if (l == 0)
@@ -978,9 +985,6 @@ static void adapt_candidates(Ctx& c, int l, int iters) {
     }
     check_flags(c);
   }
-  WDMG_HIP(hipStreamSynchronize(c.stream));
-  dev_free(c, ax);
-  dev_free(c, mx);
   F.nv = nv;
   C.dof = 2 * nv;
   C.n = (size_t)C.nsite * C.dof;
@@ -1109,59 +1113,54 @@ void ensure_outer(Ctx& c, int k, int nrhs, bool need32, bool basis32) {
   const size_t n = (size_t)c.g0.vol * 12;
   if (nrhs > c.outer_cap) {
     WDMG_HIP(hipStreamSynchronize(c.stream));
-    dev_free(c, c.outer_r);
-    c.outer_r = static_cast<cx<double>*>(dev_alloc(c, (size_t)nrhs * n * sizeof(cx<double>)));
+    c.outer_cap = 0;
+    dev_renew(c, c.outer_r, (size_t)nrhs * n * sizeof(cx<double>));
     c.outer_cap = nrhs;
   }
   if (!basis32 && (k > c.outer_k || nrhs > c.outer_capB)) {
     WDMG_HIP(hipStreamSynchronize(c.stream));
-    dev_free(c, c.outer_Z);
-    dev_free(c, c.outer_W);
     const int kk = k > c.outer_k ? k : c.outer_k;
     const int cc = nrhs > c.outer_capB ? nrhs : c.outer_capB;
-    c.outer_Z = static_cast<cx<double>*>(dev_alloc(c, (size_t)kk * cc * n * sizeof(cx<double>)));
-    c.outer_W = static_cast<cx<double>*>(dev_alloc(c, (size_t)kk * cc * n * sizeof(cx<double>)));
+    c.outer_k = c.outer_capB = 0;
+    dev_renew(c, c.outer_Z, (size_t)kk * cc * n * sizeof(cx<double>));
+    dev_renew(c, c.outer_W, (size_t)kk * cc * n * sizeof(cx<double>));
     c.outer_k = kk;
     c.outer_capB = cc;
   }
   if (k > c.outer_histk || nrhs > c.outer_histcap) {
     WDMG_HIP(hipStreamSynchronize(c.stream));
-    dev_free(c, c.outer_hist);
-    dev_free(c, c.outer_av);
-    dev_free(c, c.outer_y);
     const int kk = k > c.outer_histk ? k : c.outer_histk;
     const int cc = nrhs > c.outer_histcap ? nrhs : c.outer_histcap;
-    c.outer_hist = static_cast<cx<double>*>(dev_alloc(c, (size_t)cc * kk * kk * sizeof(cx<double>)));
-    c.outer_av = static_cast<cx<double>*>(dev_alloc(c, (size_t)cc * kk * sizeof(cx<double>)));
-    c.outer_y = static_cast<cx<double>*>(dev_alloc(c, (size_t)cc * kk * sizeof(cx<double>)));
+    c.outer_histk = c.outer_histcap = 0;
+    dev_renew(c, c.outer_hist, (size_t)cc * kk * kk * sizeof(cx<double>));
+    dev_renew(c, c.outer_av, (size_t)cc * kk * sizeof(cx<double>));
+    dev_renew(c, c.outer_y, (size_t)cc * kk * sizeof(cx<double>));
     c.outer_histk = kk;
     c.outer_histcap = cc;
   }
   if (basis32 && (k > c.outer_k32 || nrhs > c.outer_capB32)) {
     WDMG_HIP(hipStreamSynchronize(c.stream));
-    dev_free(c, c.outer_Z32);
-    dev_free(c, c.outer_W32);
     const int kk = k > c.outer_k32 ? k : c.outer_k32;
     const int cc = nrhs > c.outer_capB32 ? nrhs : c.outer_capB32;
-    c.outer_Z32 = static_cast<cx<float>*>(dev_alloc(c, (size_t)kk * cc * n * sizeof(cx<float>)));
-    c.outer_W32 = static_cast<cx<float>*>(dev_alloc(c, (size_t)kk * cc * n * sizeof(cx<float>)));
+    c.outer_k32 = c.outer_capB32 = 0;
+    dev_renew(c, c.outer_Z32, (size_t)kk * cc * n * sizeof(cx<float>));
+    dev_renew(c, c.outer_W32, (size_t)kk * cc * n * sizeof(cx<float>));
     c.outer_k32 = kk;
     c.outer_capB32 = cc;
   }
   if (need32 && nrhs > c.outer_cap32) {
     WDMG_HIP(hipStreamSynchronize(c.stream));
-    dev_free(c, c.outer_r32);
-    dev_free(c, c.outer_z32);
-    c.outer_r32 = static_cast<cx<float>*>(dev_alloc(c, (size_t)nrhs * n * sizeof(cx<float>)));
-    c.outer_z32 = static_cast<cx<float>*>(dev_alloc(c, (size_t)nrhs * n * sizeof(cx<float>)));
+    c.outer_cap32 = 0;
+    dev_renew(c, c.outer_r32, (size_t)nrhs * n * sizeof(cx<float>));
+    dev_renew(c, c.outer_z32, (size_t)nrhs * n * sizeof(cx<float>));
     c.outer_cap32 = nrhs;
   }
 }
 
 void ensure_bicg(Ctx& c) {
-  if (c.bicg[0]) return;
   const size_t n = (size_t)c.g0.vol * 12;
-  for (cx<double>*& f : c.bicg) f = static_cast<cx<double>*>(dev_alloc(c, n * sizeof(cx<double>)));
+  for (cx<double>*& f : c.bicg)
+    if (!f) f = static_cast<cx<double>*>(dev_alloc(c, n * sizeof(cx<double>)));
 }
 
 }  // namespace wdmg
