@@ -119,7 +119,7 @@ size_t fine_n(const Ctx& c) { return (size_t)c.g0.vol * 12; }
 
 // io_a / io_b when one of the pointers needs them
 void ensure_stage(Ctx& c, const void* p, const void* q, size_t bytes, bool shared) {
-  if (!aligned(p) || !aligned(q) || shared) ensure_io(c, bytes);
+  if (!aligned(p) || !aligned(q) || shared) ensure_io(c, bytes, bytes);
 }
 size_t coarse_n(const Ctx& c, int level) { return c.lev[level + 1].n; }
 
@@ -162,7 +162,7 @@ void prolong_half(Ctx& c, void* fout, const void* cin, int nrhs) {
 template <typename H>
 void smooth_half0(Ctx& c, void* x, const void* b, int nrhs, int iters) {
   const size_t n = c.lev[0].n * nrhs;
-  ensure_io(c, 2 * n * sizeof(cx<float>));
+  ensure_io(c, (aligned(x) ? 1 : 2) * n * sizeof(cx<float>), 0);
   ensure_ioh(c, nrhs);
   cx<float>* ri = static_cast<cx<float>*>(c.io_a);
   const cx<float>* xi = field_in<float>(c, x, ri + n, n);
@@ -207,7 +207,7 @@ void restrict_impl(Ctx& c, int level, void* cout, const void* fin, int nrhs) {
   const cx<R>* f = static_cast<const cx<R>*>(fin);
   const size_t n = c.lev[level].n * nrhs;
   if (shares(cout, coarse_n(c, level) * nrhs * sizeof(cx<R>), fin, n * sizeof(cx<R>))) {
-    ensure_io(c, n * sizeof(cx<R>));
+    ensure_io(c, n * sizeof(cx<R>), 0);
     copy_words<R>(c, c.io_a, fin, n);
     f = static_cast<const cx<R>*>(c.io_a);
   }
@@ -220,7 +220,7 @@ void prolong_impl(Ctx& c, int level, void* fout, const void* cin, int nrhs) {
   const size_t n = c.lev[level].n * nrhs;
   const bool shared = shares(fout, n * sizeof(cx<R>), cin, coarse_n(c, level) * nrhs * sizeof(cx<R>));
   if (shared) {
-    ensure_io(c, n * sizeof(cx<R>));
+    ensure_io(c, n * sizeof(cx<R>), 0);
     f = static_cast<cx<R>*>(c.io_a);
   }
   prolong_from<R>(c, level, static_cast<const cx<R>*>(cin), f, nrhs);
@@ -231,28 +231,39 @@ template <typename R>
 void smooth_impl(Ctx& c, int level, void* x, const void* b, int nrhs, int iters) {
   // Right-hand sides are smoothed together, kSmoothRhs at a time (16^4, FP32,
   // 8 rhs, 4 steps: 379 us, 1004 us one by one; more would only grow the
-  // buffers).  16-bit coarse blocks take one at a time: their batched kernel
+  // buffers, which the context keeps: at most kSmoothBytes, 8 FP64 fields of
+  // 32^4).  Without the memory for that, one at a time in the two fields of
+  // plain steps.  16-bit coarse blocks take one at a time: their batched kernel
   // rounds the vectors as well.  So do x and b that overlap without being the
   // same buffer: a right-hand side there may be an earlier one's solution.
   constexpr int kSmoothRhs = 8;
-  const size_t n = c.lev[level].n;
-  const bool shared = x != b && shares(x, n * nrhs * sizeof(cx<R>), b, n * nrhs * sizeof(cx<R>));
-  const int most = (level > 0 && c.vc_half) || shared ? 1 : std::min(nrhs, kSmoothRhs);
-  ensure_io(c, 3 * most * n * sizeof(cx<R>));
+  constexpr size_t kSmoothBytes = (size_t)8 << 30;
+  const size_t n = c.lev[level].n, field = n * sizeof(cx<R>);
+  const bool shared = x != b && shares(x, nrhs * field, b, nrhs * field);
+  const int stage = aligned(x) ? 0 : 1;  // a field for x (a field is a multiple of 16 bytes long)
+  size_t most = (level > 0 && c.vc_half) || shared ? 1 : std::min(nrhs, kSmoothRhs);
+  most = std::min(most, kSmoothBytes / ((kMrRing + 1 + stage) * field));
+  const bool ring = most > 0 && try_io(c, (kMrRing - 1) * most * field, (2 + stage) * most * field);
+  if (!ring) {
+    most = 1;
+    ensure_io(c, field, (1 + stage) * field);
+  }
   cx<R>* a = static_cast<cx<R>*>(c.io_a);
-  cx<R>* q = static_cast<cx<R>*>(c.io_b);
   const size_t f = most * n;
-  cx<R>* ring[kMrRing] = {a, a + f, a + 2 * f, q};
-  cx<R>* p = q + f;
+  cx<R>* q = static_cast<cx<R>*>(c.io_b) + (ring ? f : 0);
+  cx<R>* const r[kMrRing] = {a, a + f, a + 2 * f, static_cast<cx<R>*>(c.io_b)};
   const double omega = c.have_mg ? c.mg.omega : 0.8;
-  for (int k = 0; k < nrhs; k += most) {
-    const int m = std::min(most, nrhs - k);
+  for (int k = 0; k < nrhs; k += (int)most) {
+    const int m = std::min((int)most, nrhs - k);
     cx<R>* xk = static_cast<cx<R>*>(x) + (size_t)k * n;
-    cx<R>* xi = field_out<R>(xk, q + 2 * f);
+    cx<R>* xi = field_out<R>(xk, q + f);
     field_in<R>(c, xk, xi, m * n);
     apply_op<R>(c, level, a, xi, m);
-    xmy<R>(c, field_in<R>(c, static_cast<const cx<R>*>(b) + (size_t)k * n, p, m * n), a, m * n);
-    mr_ring<R>(c, level, xi, ring, p, m, iters, omega);
+    xmy<R>(c, field_in<R>(c, static_cast<const cx<R>*>(b) + (size_t)k * n, q, m * n), a, m * n);
+    if (ring)
+      mr_ring<R>(c, level, xi, r, q, m, iters, omega);
+    else
+      mr<R>(c, level, xi, a, q, m, iters, omega, nullptr, true);
     field_done<R>(c, xk, xi, m * n);
   }
 }
@@ -522,7 +533,7 @@ int wdmg_roundtrip(wdmg_ctx* c, void* out, const void* in, int nrhs, int prec) {
     const size_t n = fine_n(*c) * nrhs, bytes = n * (prec == WDMG_F64 ? 16 : 8);
     if (!is_half(prec)) {
       if (shares(out, bytes, in, bytes)) {
-        ensure_io(*c, bytes);
+        ensure_io(*c, bytes, 0);
         copy_words<float>(*c, c->io_a, in, bytes / sizeof(cx<float>));
         in = c->io_a;
       }

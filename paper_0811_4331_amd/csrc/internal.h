@@ -191,7 +191,7 @@ struct Ctx {
   // scratch fine / coarse fields for canonical <-> internal conversion
   void* io_a = nullptr;
   void* io_b = nullptr;
-  size_t io_bytes = 0;
+  size_t io_abytes = 0, io_bbytes = 0;
   HF ioh[3];                    // 16-bit scratch fine fields
   int ioh_cap = 0;
 
@@ -255,7 +255,8 @@ void dev_renew(Ctx& c, T*& p, size_t bytes) {
   p = nullptr;
   p = static_cast<T*>(dev_alloc(c, bytes));
 }
-void ensure_io(Ctx& c, size_t bytes);
+void ensure_io(Ctx& c, size_t a, size_t b);  // io_a of a bytes and io_b of b
+bool try_io(Ctx& c, size_t a, size_t b);     // false where there is no memory for them
 
 constexpr int kReduceThreads = 256;
 constexpr int kMaxReduceBlocks = 1024;

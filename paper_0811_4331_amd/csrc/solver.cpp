@@ -63,8 +63,16 @@ struct Scratch {
   std::vector<void*> bufs;
   void* get(size_t bytes) {
     bufs.reserve(bufs.size() + 1);
-    bufs.push_back(dev_alloc(c, bytes));
+    bufs.push_back(dev_alloc(c, bytes));  // throws before the vector changes
     return bufs.back();
+  }
+  void* try_get(size_t bytes) {  // null where there is no memory for it
+    try {
+      return get(bytes);
+    } catch (const Error& e) {
+      if (e.code != WDMG_ERR_OOM) throw;
+      return nullptr;
+    }
   }
   ~Scratch() {
     (void)hipStreamSynchronize(c.stream);
@@ -73,13 +81,29 @@ struct Scratch {
 };
 }  // namespace
 
-void ensure_io(Ctx& c, size_t bytes) {
-  if (bytes <= c.io_bytes) return;
-  WDMG_HIP(hipStreamSynchronize(c.stream));
-  c.io_bytes = 0;
-  dev_renew(c, c.io_a, bytes);
-  dev_renew(c, c.io_b, bytes);
-  c.io_bytes = bytes;
+void ensure_io(Ctx& c, size_t a, size_t b) {
+  if (a > c.io_abytes) {
+    WDMG_HIP(hipStreamSynchronize(c.stream));
+    c.io_abytes = 0;
+    dev_renew(c, c.io_a, a);
+    c.io_abytes = a;
+  }
+  if (b > c.io_bbytes) {
+    WDMG_HIP(hipStreamSynchronize(c.stream));
+    c.io_bbytes = 0;
+    dev_renew(c, c.io_b, b);
+    c.io_bbytes = b;
+  }
+}
+
+bool try_io(Ctx& c, size_t a, size_t b) {
+  try {
+    ensure_io(c, a, b);
+    return true;
+  } catch (const Error& e) {
+    if (e.code != WDMG_ERR_OOM) throw;
+    return false;
+  }
 }
 
 ProfScope::ProfScope(Ctx& ctx, int id, long long units) : c(ctx) {
@@ -869,11 +893,15 @@ static void relax_batch(Ctx& c, int l, cx<R>* V, int nv, int iters, double omega
   if (kb < 1) kb = 1;
   if (kb > (size_t)nv) kb = nv;
   if (kb > (size_t)kMaxRhs) kb = kMaxRhs;
-  // the residuals of kMrRing steps where they fit the budget for the same batch
-  const bool fits = (kMrRing + 1) * kb * field <= budget;
+  // the residuals of kMrRing steps where they fit the budget for the same batch,
+  // and the memory there is
   Scratch tmp{c};
-  cx<R>* Rb = static_cast<cx<R>*>(tmp.get((fits ? kMrRing : 1) * kb * field));
-  cx<R>* Pb = static_cast<cx<R>*>(tmp.get(kb * field));
+  cx<R>* Rb = nullptr;
+  if ((kMrRing + 1) * kb * field <= budget)
+    Rb = static_cast<cx<R>*>(tmp.try_get((kMrRing + 1) * kb * field));
+  const bool fits = Rb != nullptr;
+  if (!fits) Rb = static_cast<cx<R>*>(tmp.get(kb * field));
+  cx<R>* Pb = fits ? Rb + kMrRing * kb * n : static_cast<cx<R>*>(tmp.get(kb * field));
   if (l == 0) dots_buffer(c, (int)kb);
   for (int k0 = 0; k0 < nv; k0 += (int)kb) {
     const int nb = (nv - k0) < (int)kb ? (nv - k0) : (int)kb;

@@ -18,14 +18,17 @@ def gpu(x):
 
 
 class Memory:
-    """Device memory that ends after `left` more allocations (None: never)."""
+    """Device memory that ends after `left` more allocations (None: never) and
+    has no piece of more than `most` bytes (None: any)."""
 
     def __init__(self, monkeypatch):
-        self.left = None
+        self.left = self.most = None
         self.alloc = torch.cuda.caching_allocator_alloc
         monkeypatch.setattr(torch.cuda, "caching_allocator_alloc", self)
 
     def __call__(self, size, *rest):
+        if self.most is not None and size > self.most:
+            raise RuntimeError("no piece of this size left for the test")
         if self.left is not None:
             if self.left == 0:
                 raise RuntimeError("no memory left for the test")
@@ -126,3 +129,48 @@ def test_out_of_memory_in_the_setup(prec, monkeypatch):
             ctx.set_mass(-0.2)
     assert not failed
     ctx.close()
+
+
+@pytest.mark.parametrize("prec,off", [("f64", 0), ("f32", 0), ("f32", 8)])
+def test_smoothing_in_little_memory(prec, off, monkeypatch):
+    """Room for two buffers of two fields is enough for any batch.  The steps are
+    the same numbers whether their updates are put off or not, up to the
+    rounding of the operator's forms."""
+    mem = Memory(monkeypatch)
+    cdt = np.complex128 if prec == "f64" else np.complex64
+    ctx = wdmg.Context(DIMS, DEV)
+    ctx.set_gauge(gpu(synthetic.gauge_field(DIMS, 0.3, 991)), t_bc=-1)
+    ctx.set_mass(-0.2)
+    b = gpu(synthetic.gaussian_spinor(DIMS, seed=993, nrhs=NRHS).astype(cdt))
+    real = b.real.dtype
+    flat = torch.zeros(2 * b.numel() + 2, dtype=real, device=DEV)[off // real.itemsize:]
+    x = torch.view_as_complex(flat[:2 * b.numel()].view(b.shape + (2,)))
+    assert x.data_ptr() % 16 == off
+    mem.most = 2 * (b.numel() // NRHS) * b.itemsize
+    ctx.smooth(0, x, b, 6, prec=prec)
+    mem.most = None
+    ctx2 = wdmg.Context(DIMS, DEV)
+    ctx2.set_gauge(gpu(synthetic.gauge_field(DIMS, 0.3, 991)), t_bc=-1)
+    ctx2.set_mass(-0.2)
+    want = ctx2.smooth(0, torch.zeros_like(b), b, 6, prec=prec)
+    assert float((x - want).abs().max() / want.abs().max()) < (1e-13 if prec == "f64" else 1e-6)
+    ctx.close()
+    ctx2.close()
+
+
+def test_setup_in_little_memory(monkeypatch):
+    """Room for the candidates and one field more of each is enough."""
+    mem = Memory(monkeypatch)
+    lx, ly, lz, lt = DIMS
+    v = gpu(synthetic.gaussian_vectors((NV, lt, lz, ly, lx, 4, 3), 992))
+    got = []
+    for most in (None, 2 * v.numel() * v.itemsize):
+        ctx = wdmg.Context(DIMS, DEV)
+        ctx.set_gauge(gpu(synthetic.gauge_field(DIMS, 0.3, 991)), t_bc=-1)
+        ctx.set_mass(-0.2)
+        mem.most = most
+        ctx.mg_setup([{"block": BLK, "nv": NV, "setup_iters": 7, "vectors": v}])
+        mem.most = None
+        got.append(ctx.get_prolongator(0))
+        ctx.close()
+    assert float((got[0] - got[1]).abs().max() / got[0].abs().max()) < 1e-12
