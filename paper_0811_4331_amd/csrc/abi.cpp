@@ -171,7 +171,15 @@ void smooth_half0(Ctx& c, void* x, const void* b, int nrhs, int iters) {
   to_half<float, H>(c, xi, c.ioh[0], nrhs);
   to_half<float, H>(c, ri, c.ioh[1], nrhs);
   const double omega = c.have_mg ? c.mg.omega : 0.8;
-  mr_h<H>(c, c.ioh[0], c.ioh[1], c.ioh[2], nrhs, iters, omega);
+  const size_t vol = c.lev[0].nsite;
+  for (int k = 0; k < nrhs; k += kMaxRhs) {  // there are step-size scalars for kMaxRhs
+    auto at = [&](HF h) {
+      h.v = static_cast<char*>(h.v) + k * vol * 12 * 4;
+      h.s += k * vol;
+      return h;
+    };
+    mr_h<H>(c, at(c.ioh[0]), at(c.ioh[1]), at(c.ioh[2]), std::min(kMaxRhs, nrhs - k), iters, omega);
+  }
   from_half<H, float>(c, c.ioh[0], static_cast<cx<float>*>(x), nrhs);
 }
 void need_ptr(const void* p, const char* what) {

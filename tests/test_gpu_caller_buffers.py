@@ -85,3 +85,33 @@ def test_smoothing_where_a_solution_is_the_next_right_hand_side(ctx, prec):
     both = b.reshape(-1).clone()
     ctx.smooth(0, both[n:].view((3,) + b.shape[1:]), both[:3 * n].view((3,) + b.shape[1:]), 3, prec=prec)
     assert torch.equal(both, flat)
+
+
+@pytest.mark.parametrize("prec", ["f16", "bf16"])
+def test_smoothing_of_very_many_right_hand_sides(prec):
+    """The largest batch, far beyond the 64 that there are step-size scalars for:
+    each right-hand side gets its own steps, and a solve after it gives what it
+    gave before."""
+    dims = (4, 4, 4, 4)
+    ctx = wdmg.Context(dims, DEV)
+    ctx.set_gauge(gpu(synthetic.gauge_field(dims, 0.35, 985)), t_bc=-1)
+    ctx.set_mass(-0.2)
+    v = synthetic.gaussian_vectors((4,) + ctx.fine_shape(), 986)
+    v2 = synthetic.gaussian_vectors((4, 2, 2, 2, 2, 2, 4), 987)
+    ctx.mg_setup([{"block": (2, 2, 2, 2), "nv": 4, "setup_iters": 10, "vectors": gpu(v)},
+                  {"block": (2, 2, 1, 1), "nv": 4, "setup_iters": 10, "vectors": gpu(v2)}], coarse_tol=1e-2)
+    b = gpu(synthetic.gaussian_spinor(dims, seed=988, nrhs=2))
+    before, st = ctx.solve(b, tol=1e-10, restart=20, maxit=200)
+    assert all(s["converged"] for s in st)
+    n = 65535
+    f = torch.zeros((n,) + ctx.fine_shape(), dtype=torch.complex64, device=DEV)
+    for j in (0, 63, 64, n - 1):
+        f[j] = b[j % 2]
+    x = ctx.smooth(0, torch.zeros_like(f), f, 3, prec=prec)
+    for j in (0, 63, 64, n - 1):
+        one = ctx.smooth(0, torch.zeros_like(f[j]), f[j].clone(), 3, prec=prec)
+        assert float((x[j] - one).abs().max() / one.abs().max()) < 1e-2  # 16-bit roundings of another form
+    assert not x[1:63].any() and not x[65:n - 1].any()
+    after, st2 = ctx.solve(b, tol=1e-10, restart=20, maxit=200)
+    assert torch.equal(before, after) and [s["iters"] for s in st] == [s["iters"] for s in st2]
+    ctx.close()
