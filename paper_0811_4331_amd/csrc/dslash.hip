@@ -629,7 +629,7 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(2,
     for (int k = 0; k < NL; ++k) {
       const int p = min(k * kTileThreads + tid, kTileSlots * S::NC - 1);
       const int slot = p / S::NC, c = S::kHalf ? p % S::NC : (p % S::NC) ^ swz<float>(slot);
-      off[k] = (unsigned)(tile_site(g, base, slot) * kBytes + c * 16);
+      off[k] = (unsigned)tile_site(g, base, slot) * (unsigned)kBytes + (unsigned)c * 16u;
     }
     if constexpr (S::kHalf) own = tile_site(g, base, tid >> 1);
   };
