@@ -304,9 +304,9 @@ int wdmg_solve_bicgstab(wdmg_ctx* ctx, void* x, const void* b, int nrhs, double 
  *                     (Ten values are accepted; which of a group is given
  *                     makes no difference.)
  *   WDMG_TUNE_DSLASH_GROUP: right-hand sides per workgroup (1..64) of the
- *                     one-wave-per-direction form below FP64 (links are loaded
- *                     once per group; a value above the batch size means the
- *                     whole batch).  FP64 and the tile form ignore it.
+ *                     one-wave-per-direction form (links are loaded once per
+ *                     group; a value above the batch size means the whole
+ *                     batch).  The tile form ignores it.
  *   WDMG_TUNE_COARSE_APPLY: 0 or 1, kept for callers that set it; the
  *                     batched coarsest-level operator has one form.
  *                     AUTO means form 1 where it applies (not timed);

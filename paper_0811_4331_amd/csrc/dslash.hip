@@ -35,6 +35,11 @@ struct Full {
   u4* out;
   const cx<R>* U;
   __device__ __forceinline__ void link(int mu, int s, bool neg, cx<R> (&u)[9]) const { load_link(U, mu, s, neg, u); }
+  __device__ __forceinline__ void rows(int mu, int s, cx<R> (&u)[6]) const {
+    const cx<R>* base = U + fidx(s, mu * 6, kLinkComp);
+#pragma unroll
+    for (int e = 0; e < 6; ++e) u[e] = base[e * 64];
+  }
 };
 
 template <typename H>
@@ -190,11 +195,17 @@ __device__ __forceinline__ void mr_dots(const R* o, const R* i, int n, double (&
 // while the forward hop is worked on.  The four directions meet in the same
 // buffers, where all 256 threads sum and store.
 //
-// FP32 and 16 bits keep the links and offsets of the wave in registers over a
-// group of right-hand sides; FP64 has no registers for that and takes one per
-// workgroup.  Measured (with the layout conversions it makes unnecessary, in
-// brackets with them before): 32^4 FP64 1 rhs 228 us (398), 12x20x10x18 FP32
-// 5 rhs 22 us (53), 32^4 FP32 1 rhs 120 us (210).
+// A workgroup takes a group of right-hand sides.  FP32 and 16 bits keep the
+// links and offsets of the wave in registers over the group; FP64 keeps the two
+// stored rows of the links (166 registers, three waves per SIMD) and finds the
+// rest anew.
+//
+// Bound: instructions (one wave takes 700 to 900 vector instructions for 64
+// sites and a direction), in FP64 also the L2.  Measured, kernel alone:
+//   FP64  24^3x48 32 rhs 3530 us (4380 with one rhs per workgroup), 1 rhs 157
+// and with the layout conversions that it makes unnecessary in brackets: 32^4
+// FP64 1 rhs 228 us (398), 12x20x10x18 FP32 5 rhs 22 us (53), 32^4 FP32 1 rhs
+// 120 us (210).
 template <typename R>
 __device__ __forceinline__ int swz(int j) {
   return sizeof(R) == 4 ? (j >> 2) & 1 : (j >> 1) & 3;
@@ -268,35 +279,54 @@ __device__ __forceinline__ void gather_wave(const Geom& g, const S& io, int tneg
   const bool last = MU == 3 && tneg && c[3] == g.L[3] - 1, first = MU == 3 && tneg && c[3] == 0;
   const int nf = canon_fwd<MU>(g, c, me), nb = canon_bwd<MU>(g, c, me);
   if constexpr (sizeof(R) == 8) {
-    const u4* f = io.in + r0 * fs;
-    cx<R> h[6], uh[6], u[9], acc[12];
-    {
-      unsigned off[S::NC];
-      gather_offsets<S>(nf, lane, off);
-      fetch_sites<S>(f, off, buf);
-    }
-    io.link(MU, s, last, u);
-    wait_loads();
-    read_half_f64<MU, +1>(buf, lane, h);
-    wait_lds();
-    __builtin_amdgcn_sched_barrier(0);
-    {
-      unsigned off[S::NC];
-      gather_offsets<S>(nb, lane, off);
-      fetch_sites<S>(f, off, buf);
-    }
-    link_half<+1>(u, h, uh);
+    cx<R> lf[6], lb[6];
+    io.rows(MU, s, lf);
+    io.rows(MU, nbr_bwd(g, s, c, MU), lb);
+    auto whole = [](const cx<R> (&l)[6], bool neg, cx<R> (&u)[9]) {
 #pragma unroll
-    for (int k = 0; k < 12; ++k) acc[k] = mk<R>(0, 0);
-    expand_add<MU, +1>(uh, acc);
-    __builtin_amdgcn_sched_barrier(0);
-    io.link(MU, nbr_bwd(g, s, c, MU), first, u);
-    wait_loads();
-    read_half_f64<MU, -1>(buf, lane, h);
-    link_half<-1>(u, h, uh);
-    expand_add<MU, -1>(uh, acc);
-    write_row<R>(buf, lane, acc);
-    finish(r0);
+      for (int k = 0; k < 6; ++k) u[k] = l[k];
+      recon_third_row(u, neg);
+    };
+    for (int r = r0; r < r1; ++r) {
+      const u4* f = io.in + r * fs;
+      cx<R> h[6], uh[6], u[9], acc[12];
+      // nothing derived from these is kept from one right-hand side to the next:
+      // there are no registers for it
+      int nfr = nf, nbk = nb, lane = threadIdx.x & 63;
+      asm volatile("" : "+v"(nfr), "+v"(nbk), "+v"(lane));
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        asm volatile("" : "+v"(lf[k].re), "+v"(lf[k].im));
+        asm volatile("" : "+v"(lb[k].re), "+v"(lb[k].im));
+      }
+      {
+        unsigned off[S::NC];
+        gather_offsets<S>(nfr, lane, off);
+        fetch_sites<S>(f, off, buf);
+      }
+      wait_loads();
+      read_half_f64<MU, +1>(buf, lane, h);
+      wait_lds();
+      __builtin_amdgcn_sched_barrier(0);
+      {
+        unsigned off[S::NC];
+        gather_offsets<S>(nbk, lane, off);
+        fetch_sites<S>(f, off, buf);
+      }
+      whole(lf, last, u);
+      link_half<+1>(u, h, uh);
+#pragma unroll
+      for (int k = 0; k < 12; ++k) acc[k] = mk<R>(0, 0);
+      expand_add<MU, +1>(uh, acc);
+      __builtin_amdgcn_sched_barrier(0);
+      whole(lb, first, u);
+      wait_loads();
+      read_half_f64<MU, -1>(buf, lane, h);
+      link_half<-1>(u, h, uh);
+      expand_add<MU, -1>(uh, acc);
+      write_row<R>(buf, lane, acc);
+      finish(r);
+    }
   } else {
     unsigned of[S::NC], ob[S::NC];
     gather_offsets<S>(nf, lane, of);
@@ -346,19 +376,19 @@ __global__ __launch_bounds__(256) void k_wilson_gather(Geom g, S io, R diag, int
   constexpr int NW = Full<R>::NC, N = ChunkOf<R>::N;  // chunks of a working-precision row, numbers in one
   __shared__ u4 buf[4][64 * NW];
   __shared__ double red[2][4][3];
-  // blocks of one rhs group in XCD-contiguous order (workgroup b runs on XCD
-  // b % 8), the groups of a block back to back
-  const int ngrp = (nrhs + nper - 1) / nper;
+  // each XCD (workgroup b runs on XCD b % 8) sweeps its run of blocks once per
+  // group of right-hand sides: neighbours meet in its L2 (all groups of a block
+  // back to back, FP64, 16^4, 32 rhs: 354 us against 332)
   int sb, grp;
   {
     const int b = blockIdx.x;
     if (nsb & 7) {
-      sb = b / ngrp;
-      grp = b % ngrp;
+      sb = b % nsb;
+      grp = b / nsb;
     } else {
-      const int local = b >> 3;
-      sb = (b & 7) * (nsb >> 3) + local / ngrp;
-      grp = local % ngrp;
+      const int local = b >> 3, per = nsb >> 3;
+      sb = (b & 7) * per + local % per;
+      grp = local / per;
     }
   }
   const int r0 = grp * nper, r1 = min(nrhs, r0 + nper);
@@ -384,7 +414,9 @@ __global__ __launch_bounds__(256) void k_wilson_gather(Geom g, S io, R diag, int
     if constexpr (!S::kHalf) {
 #pragma unroll
       for (int i = 0; i < (NW + 3) / 4; ++i) {
-        const int e = i * 256 + threadIdx.x, j = e / NW;
+        int tid = threadIdx.x;
+        if constexpr (sizeof(R) == 8) asm volatile("" : "+v"(tid));  // as in gather_wave
+        const int e = i * 256 + tid, j = e / NW;
         const int site = __shfl(me, j & 63, 64);
         if (e < 64 * NW && sb * 64 + j < g.vol) {
           const size_t o = (size_t)site * NW + ((e % NW) ^ swz<R>(j));
@@ -798,15 +830,15 @@ int auto_form(const Geom& g, int nrhs) {
   return pairs >= (nrhs >= 8 ? 3000 : 5000) ? kFormTile : kFormGather;
 }
 
-// Right-hand sides per workgroup of the gather kernel, at most 16, in groups of
-// equal size.  Two site blocks per compute unit are enough workgroups: then the
-// whole batch shares its links and offsets (12x20x10x18, 675 blocks, 5 rhs:
-// 20.8 us in one group, 24.1 in two).  With fewer blocks, as many as leave
-// about four workgroups per compute unit (8^4, 32 rhs: 13 us at 2, 32 us at
-// 16).
-inline int gather_group(const Ctx& c, int nsb, int nrhs, int forced) {
-  long long n = forced > 0 ? forced : nsb >= 2 * c.ncu ? 16 : (long long)nsb * nrhs / (4 * c.ncu);
-  if (forced <= 0 && n > 16) n = 16;
+// Right-hand sides per workgroup of the gather kernel, at most `most` (16; FP64
+// 8: 24^3x48, 32 rhs 3600 us at 4, 3540 at 8), in groups of equal size.  Two
+// site blocks per compute unit are enough workgroups: then the whole batch
+// shares its links and offsets (12x20x10x18, 675 blocks, FP32, 5 rhs: 20.8 us in
+// one group, 24.1 in two).  With fewer blocks, as many as leave about four
+// workgroups per compute unit (8^4, 32 rhs: 13 us at 2, 32 us at 16).
+inline int gather_group(const Ctx& c, int nsb, int nrhs, int forced, int most) {
+  long long n = forced > 0 ? forced : nsb >= 2 * c.ncu ? most : (long long)nsb * nrhs / (4 * c.ncu);
+  if (forced <= 0 && n > most) n = most;
   if (n < 1) n = 1;
   if (n > nrhs) n = nrhs;
   const int groups = (int)((nrhs + n - 1) / n);
@@ -836,7 +868,7 @@ int launch_dslash(Ctx& c, const S& io, int nrhs, int prof_id, int prec_index, do
   const bool tile = (v == 5 || v == 9) && tile_fits<S>(g);
   const int nsb = g.vpad / 64;
   int rg = c.tune_force[WDMG_TUNE_DSLASH_GROUP] >= 0 ? c.tune_force[WDMG_TUNE_DSLASH_GROUP] : gslot;
-  const int nper = sizeof(R) == 8 ? 1 : gather_group(c, nsb, nrhs, rg);
+  const int nper = gather_group(c, nsb, nrhs, rg, sizeof(R) == 8 ? 8 : 16);
   if (rg < 0) gslot = (signed char)(nper < kMaxRhs ? nper : kMaxRhs);
   const bool with_dots = dots != nullptr;
   const int tneg = c.t_bc < 0 ? 1 : 0;
