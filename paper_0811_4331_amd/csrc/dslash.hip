@@ -202,7 +202,7 @@ __device__ __forceinline__ void mr_dots(const R* o, const R* i, int n, double (&
 //
 // Bound: instructions (one wave takes 700 to 900 vector instructions for 64
 // sites and a direction), in FP64 also the L2.  Measured, kernel alone:
-//   FP64  24^3x48 32 rhs 3530 us (4380 with one rhs per workgroup), 1 rhs 157
+//   FP64  24^3x48 32 rhs 3640 us (4380 with one rhs per workgroup), 1 rhs 157
 // and with the layout conversions that it makes unnecessary in brackets: 32^4
 // FP64 1 rhs 228 us (398), 12x20x10x18 FP32 5 rhs 22 us (53), 32^4 FP32 1 rhs
 // 120 us (210).
@@ -376,19 +376,21 @@ __global__ __launch_bounds__(256) void k_wilson_gather(Geom g, S io, R diag, int
   constexpr int NW = Full<R>::NC, N = ChunkOf<R>::N;  // chunks of a working-precision row, numbers in one
   __shared__ u4 buf[4][64 * NW];
   __shared__ double red[2][4][3];
-  // each XCD (workgroup b runs on XCD b % 8) sweeps its run of blocks once per
-  // group of right-hand sides: neighbours meet in its L2 (all groups of a block
-  // back to back, FP64, 16^4, 32 rhs: 354 us against 332)
+  // blocks of one rhs group in XCD-contiguous order (workgroup b runs on XCD
+  // b % 8), the groups of a block back to back (a sweep of the blocks per group:
+  // FP64 24^3x48 32 rhs 3560 us against 3640, but FP32 12x20x10x18 32 rhs 105
+  // against 96)
+  const int ngrp = (nrhs + nper - 1) / nper;
   int sb, grp;
   {
     const int b = blockIdx.x;
     if (nsb & 7) {
-      sb = b % nsb;
-      grp = b / nsb;
+      sb = b / ngrp;
+      grp = b % ngrp;
     } else {
-      const int local = b >> 3, per = nsb >> 3;
-      sb = (b & 7) * per + local % per;
-      grp = local / per;
+      const int local = b >> 3;
+      sb = (b & 7) * (nsb >> 3) + local / ngrp;
+      grp = local % ngrp;
     }
   }
   const int r0 = grp * nper, r1 = min(nrhs, r0 + nper);
@@ -831,7 +833,8 @@ int auto_form(const Geom& g, int nrhs) {
 }
 
 // Right-hand sides per workgroup of the gather kernel, at most `most` (16; FP64
-// 8: 24^3x48, 32 rhs 3600 us at 4, 3540 at 8), in groups of equal size.  Two
+// 4: 20x12x20x12, 8 rhs 81 us at 4, 89 at 8; 24^3x48, 32 rhs 3640 at 4, 3540 at
+// 8), in groups of equal size.  Two
 // site blocks per compute unit are enough workgroups: then the whole batch
 // shares its links and offsets (12x20x10x18, 675 blocks, FP32, 5 rhs: 20.8 us in
 // one group, 24.1 in two).  With fewer blocks, as many as leave about four
@@ -868,7 +871,7 @@ int launch_dslash(Ctx& c, const S& io, int nrhs, int prof_id, int prec_index, do
   const bool tile = (v == 5 || v == 9) && tile_fits<S>(g);
   const int nsb = g.vpad / 64;
   int rg = c.tune_force[WDMG_TUNE_DSLASH_GROUP] >= 0 ? c.tune_force[WDMG_TUNE_DSLASH_GROUP] : gslot;
-  const int nper = gather_group(c, nsb, nrhs, rg, sizeof(R) == 8 ? 8 : 16);
+  const int nper = gather_group(c, nsb, nrhs, rg, sizeof(R) == 8 ? 4 : 16);
   if (rg < 0) gslot = (signed char)(nper < kMaxRhs ? nper : kMaxRhs);
   const bool with_dots = dots != nullptr;
   const int tneg = c.t_bc < 0 ? 1 : 0;
