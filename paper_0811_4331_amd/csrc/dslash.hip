@@ -56,6 +56,16 @@ struct Half {
   __device__ __forceinline__ void link(int mu, int s, bool neg, cx<float> (&u)[9]) const {
     load_link_h(U, mu, s, neg, u);
   }
+  __device__ __forceinline__ void raw(int mu, int s, unsigned (&u)[6]) const {
+    const unsigned* base = reinterpret_cast<const unsigned*>(U) + fidx(s, mu * 6, kLinkComp);
+#pragma unroll
+    for (int e = 0; e < 6; ++e) u[e] = base[e * 64];
+  }
+  static __device__ __forceinline__ void whole(const unsigned (&l)[6], bool neg, cx<float> (&u)[9]) {
+#pragma unroll
+    for (int e = 0; e < 6; ++e) u[e] = h2f(__builtin_bit_cast(cxh<H>, l[e]));
+    recon_third_row(u, neg);
+  }
 };
 
 // The numbers of stored chunk c of a site (16 bits: unscaled).
@@ -172,6 +182,21 @@ __device__ __forceinline__ void wait_lds() {
   __builtin_amdgcn_wave_barrier();
 }
 
+// Sums of three values over a wave, in its lanes 60, 61 and 62.  The first two
+// exchanges also hand the values out to the lanes, so the rest is done for one
+// value a lane instead of three.
+__device__ __forceinline__ double wave_sums3(const double (&d)[3]) {
+  const int lane = threadIdx.x & 63;
+  const bool b0 = lane & 1, b1 = lane & 2;
+  const double x = (b0 ? d[1] : d[0]) + dpp<0xb1, 0xf>(b0 ? d[0] : d[1]);  // quad_perm 1 0 3 2
+  const double z = d[2] + dpp<0xb1, 0xf>(d[2]);
+  double y = (b1 ? z : x) + dpp<0x4e, 0xf>(b1 ? x : z);  // quad_perm 2 3 0 1
+  y += dpp<0x114, 0xf>(y);                               // row_shr 4, 8
+  y += dpp<0x118, 0xf>(y);
+  y += __shfl_xor(y, 16, 64);
+  return y + __shfl_xor(y, 32, 64);
+}
+
 // MR step-size sums of one thread (Sec. 3 smoother): Re and Im of <out, in>
 // and |out|^2 over n numbers of the operator's result and input.
 template <typename R>
@@ -198,11 +223,15 @@ __device__ __forceinline__ void mr_dots(const R* o, const R* i, int n, double (&
 // A workgroup takes a group of right-hand sides.  FP32 and 16 bits keep the
 // links and offsets of the wave in registers over the group; FP64 keeps the two
 // stored rows of the links (166 registers, three waves per SIMD) and finds the
-// rest anew.
+// rest anew.  ONE: a single right-hand side in 16 bits, whose rows are half as
+// long as the sums that follow them in the buffer: both neighbours' rows are
+// fetched at once, and with the links' rows held as stored the kernel has 76
+// registers instead of 125.
 //
 // Bound: instructions (one wave takes 700 to 900 vector instructions for 64
 // sites and a direction), in FP64 also the L2.  Measured, kernel alone:
 //   FP64  24^3x48 32 rhs 3640 us (4380 with one rhs per workgroup), 1 rhs 157
+//   BF16  24^3x48 1 rhs 55 us (66 as a group of one), 32^4 86 us (102)
 // and with the layout conversions that it makes unnecessary in brackets: 32^4
 // FP64 1 rhs 228 us (398), 12x20x10x18 FP32 5 rhs 22 us (53), 32^4 FP32 1 rhs
 // 120 us (210).
@@ -270,7 +299,7 @@ __device__ __forceinline__ int canon_bwd(const Geom& g, const int (&c)[4], int m
   return c[MU] == 0 ? me + (g.L[MU] - 1) * stride_of<MU>(g) : me - stride_of<MU>(g);
 }
 
-template <int MU, class S, class Finish>
+template <int MU, class S, bool ONE, class Finish>
 __device__ __forceinline__ void gather_wave(const Geom& g, const S& io, int tneg, int s, const int (&c)[4], int me,
                                             int r0, int r1, u4* buf, Finish finish) {
   using R = typename S::T;
@@ -327,6 +356,33 @@ __device__ __forceinline__ void gather_wave(const Geom& g, const S& io, int tneg
       write_row<R>(buf, lane, acc);
       finish(r);
     }
+  } else if constexpr (ONE) {
+    const u4* f = io.in + r0 * fs;
+    {
+      unsigned of[S::NC], ob[S::NC];
+      gather_offsets<S>(nf, lane, of);
+      gather_offsets<S>(nb, lane, ob);
+      fetch_sites<S>(f, of, buf);
+      fetch_sites<S>(f, ob, buf + 64 * S::NC);
+    }
+    unsigned lf[6], lb[6];
+    io.raw(MU, s, lf);
+    io.raw(MU, nbr_bwd(g, s, c, MU), lb);
+    const float sf = io.isc[(size_t)r0 * g.vol + nf], sb = io.isc[(size_t)r0 * g.vol + nb];
+    cx<R> p[12], acc[12], u[9];
+    wait_loads();
+    read_row<S>(buf, lane, p);
+#pragma unroll
+    for (int k = 0; k < 12; ++k) acc[k] = mk<R>(0, 0);
+    io.whole(lf, last, u);
+    hop_add_scaled<MU, +1>(u, p, sf, acc);
+    __builtin_amdgcn_sched_barrier(0);
+    read_row<S>(buf + 64 * S::NC, lane, p);
+    io.whole(lb, first, u);
+    hop_add_scaled<MU, -1>(u, p, sb, acc);
+    wait_lds();
+    write_row<R>(buf, lane, acc);
+    finish(r0);
   } else {
     unsigned of[S::NC], ob[S::NC];
     gather_offsets<S>(nf, lane, of);
@@ -370,7 +426,7 @@ __device__ __forceinline__ void gather_wave(const Geom& g, const S& io, int tneg
   }
 }
 
-template <class S, bool DOTS, typename R = typename S::T>
+template <class S, bool DOTS, bool ONE, typename R = typename S::T>
 __global__ __launch_bounds__(256) void k_wilson_gather(Geom g, S io, R diag, int tneg, int nsb, int nrhs, int nper,
                                                        double* dots) {
   constexpr int NW = Full<R>::NC, N = ChunkOf<R>::N;  // chunks of a working-precision row, numbers in one
@@ -478,21 +534,17 @@ __global__ __launch_bounds__(256) void k_wilson_gather(Geom g, S io, R diag, int
       }
     }
     if constexpr (DOTS) {
-#pragma unroll
-      for (int k = 0; k < 3; ++k) d[k] = wave_sum(d[k]);
-      if (lane == 0) {
-#pragma unroll
-        for (int k = 0; k < 3; ++k) red[r & 1][wave][k] = d[k];
-      }
+      const double t = wave_sums3(d);
+      if (lane >= 60 && lane < 63) red[r & 1][wave][lane - 60] = t;
     }
     if (DOTS || r + 1 < r1) __syncthreads();
     if constexpr (DOTS) flush(r);
   };
   switch (wave) {
-    case 0: gather_wave<0, S>(g, io, tneg, s, c, me, r0, r1, buf[0], finish); break;
-    case 1: gather_wave<1, S>(g, io, tneg, s, c, me, r0, r1, buf[1], finish); break;
-    case 2: gather_wave<2, S>(g, io, tneg, s, c, me, r0, r1, buf[2], finish); break;
-    default: gather_wave<3, S>(g, io, tneg, s, c, me, r0, r1, buf[3], finish); break;
+    case 0: gather_wave<0, S, ONE>(g, io, tneg, s, c, me, r0, r1, buf[0], finish); break;
+    case 1: gather_wave<1, S, ONE>(g, io, tneg, s, c, me, r0, r1, buf[1], finish); break;
+    case 2: gather_wave<2, S, ONE>(g, io, tneg, s, c, me, r0, r1, buf[2], finish); break;
+    default: gather_wave<3, S, ONE>(g, io, tneg, s, c, me, r0, r1, buf[3], finish); break;
   }
 }
 
@@ -785,12 +837,8 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(2,
       if constexpr (DOTS) mr_dots(a, p, 12, d);
     }
     if constexpr (DOTS) {
-#pragma unroll
-      for (int k = 0; k < 3; ++k) d[k] = wave_sum(d[k]);
-      if (lane == 0) {
-#pragma unroll
-        for (int k = 0; k < 3; ++k) red[cur][wave][k] = d[k];
-      }
+      const double t = wave_sums3(d);
+      if (lane >= 60 && lane < 63) red[cur][wave][lane - 60] = t;
       fr = r;
       ft = tile;
     }
@@ -813,8 +861,8 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(2,
 //   24^3x48: 2 rhs 124 / 123, 3 rhs 162 / 179, 8 rhs 337 / 426, 32 rhs 1299 / 1649
 //   32^4:    2 rhs 189 / 191, 3 rhs 244 / 262     20^4: 6 rhs 71 / 74, 8 rhs 87 / 96
 //   16^4:    8 rhs 35 / 34, 12 rhs 47 / 49        28x12x16x36: 6 rhs 82 / 77, 8 rhs 107 / 117
-// The tile kernel pays for a prologue per tile, so it needs several right-hand
-// sides per tile and enough pairs per compute unit.
+// (FP32).  The tile kernel pays for a prologue per tile, so it needs several
+// right-hand sides per tile and enough pairs per compute unit.
 constexpr int kFormGather = 1, kFormTile = 5;
 
 template <class S>
@@ -825,11 +873,16 @@ bool tile_fits(const Geom& g) {
   return (long long)g.vol * S::NC * 16 <= 0xffffffffll;  // 32-bit byte offsets in a field
 }
 
+// 16 bits (BF16): 24^3x48: 6 rhs 284 / 286, 8 rhs 363 / 377; 32^4: 3 rhs 251 / 234,
+//   8 rhs 557 / 568; 16^4: 12 rhs 52 / 52, 16 rhs 65 / 66; 20x12x20x12: 16 rhs 69 / 68,
+//   24 rhs 91 / 95; 28x12x16x36: 12 rhs 158 / 154, 16 rhs 210 / 212.  The gather
+//   kernel moves half the bytes there, so it takes a larger batch to beat it.
 template <class S>
 int auto_form(const Geom& g, int nrhs) {
-  if (!tile_fits<S>(g) || nrhs < 2) return kFormGather;
+  if (!tile_fits<S>(g) || nrhs < (S::kHalf ? 6 : 2)) return kFormGather;
   const long long pairs = (long long)(g.vol / 256) * nrhs;
-  return pairs >= (nrhs >= 8 ? 3000 : 5000) ? kFormTile : kFormGather;
+  const long long least = S::kHalf ? (nrhs >= 16 ? 4000 : 15000) : (nrhs >= 8 ? 3000 : 5000);
+  return pairs >= least ? kFormTile : kFormGather;
 }
 
 // Right-hand sides per workgroup of the gather kernel, at most `most` (16; FP64
@@ -889,7 +942,10 @@ int launch_dslash(Ctx& c, const S& io, int nrhs, int prof_id, int prec_index, do
     }
   }
   const dim3 grid((unsigned)((long long)nsb * ((nrhs + nper - 1) / nper))), block(256);
-  const auto k = with_dots ? &k_wilson_gather<S, S::kDots, R> : &k_wilson_gather<S, false, R>;
+  auto k = with_dots ? &k_wilson_gather<S, S::kDots, false, R> : &k_wilson_gather<S, false, false, R>;
+  if constexpr (S::kHalf) {
+    if (nper == 1) k = with_dots ? &k_wilson_gather<S, S::kDots, true, R> : &k_wilson_gather<S, false, true, R>;
+  }
   hipLaunchKernelGGL(k, grid, block, 0, c.stream, g, io, diag, tneg, nsb, nrhs, nper, dots);
   WDMG_HIP(hipGetLastError());
   return nsb;

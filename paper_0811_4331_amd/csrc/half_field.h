@@ -92,17 +92,21 @@ __device__ __forceinline__ cxh<H> quantise(float re, float im, float inv) {
 }
 
 // Largest magnitude of N numbers; NaN wins, here and in the join of two parts.
+// The bits of magnitudes are ordered like the magnitudes, NaN above infinity.
+__device__ __forceinline__ float scale_join(float m, float o) {
+  const unsigned a = __builtin_bit_cast(unsigned, m), b = __builtin_bit_cast(unsigned, o);
+  return __builtin_bit_cast(float, a > b ? a : b);
+}
 template <int N>
 __device__ __forceinline__ float site_scale(const float (&a)[N]) {
-  float m = 0.0f;
+  unsigned m = 0;
 #pragma unroll
-  for (int k = 0; k < N; ++k) m = fmaxf(m, fabsf(a[k]));
-#pragma unroll
-  for (int k = 0; k < N; ++k)
-    if (a[k] != a[k]) m = a[k];
-  return m;
+  for (int k = 0; k < N; ++k) {
+    const unsigned b = __builtin_bit_cast(unsigned, a[k]) & 0x7fffffffu;
+    m = b > m ? b : m;
+  }
+  return __builtin_bit_cast(float, m);
 }
-__device__ __forceinline__ float scale_join(float m, float o) { return (m != m || o != o) ? m + o : fmaxf(m, o); }
 
 template <typename H>
 __device__ __forceinline__ void store_site_h(cxh<H>* __restrict__ v, float* __restrict__ sc, int s,
