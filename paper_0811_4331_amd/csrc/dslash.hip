@@ -428,7 +428,7 @@ __device__ __forceinline__ void gather_wave(const Geom& g, const S& io, int tneg
 
 template <class S, bool DOTS, bool ONE, typename R = typename S::T>
 __global__ __launch_bounds__(256) void k_wilson_gather(Geom g, S io, R diag, int tneg, int nsb, int nrhs, int nper,
-                                                       double* dots) {
+                                                       int g5, double* dots) {
   constexpr int NW = Full<R>::NC, N = ChunkOf<R>::N;  // chunks of a working-precision row, numbers in one
   __shared__ u4 buf[4][64 * NW];
   __shared__ double red[2][4][3];
@@ -490,6 +490,12 @@ __global__ __launch_bounds__(256) void k_wilson_gather(Geom g, S io, R diag, int
           }
 #pragma unroll
           for (int k = 0; k < 2 * N; ++k) a.v[k] = diag * p.v[k] - (R)0.5 * a.v[k];
+          if constexpr (sizeof(R) == 8) {  // a chunk is one number: components 6..11 take gamma5's sign
+            if (g5 && ((e % NW) ^ swz<R>(j)) >= 6) {
+              a.v[0] = -a.v[0];
+              a.v[1] = -a.v[1];
+            }
+          }
           io.out[r * fs + o] = a.q;
           if constexpr (DOTS) mr_dots(a.v, p.v, 2 * N, d);
         }
@@ -911,9 +917,10 @@ void allow_tile_lds() {
 }
 
 // Runs the operator; with `dots` the launch also writes the MR partial sums,
-// and the return value is the number of slots per rhs.
+// and the return value is the number of slots per rhs.  With g5 (FP64) the
+// result is gamma5 D in.
 template <class S>
-int launch_dslash(Ctx& c, const S& io, int nrhs, int prof_id, int prec_index, double* dots = nullptr) {
+int launch_dslash(Ctx& c, const S& io, int nrhs, int prof_id, int prec_index, double* dots = nullptr, int g5 = 0) {
   using R = typename S::T;
   const Geom& g = c.g0;
   const int key = nrhs < kMaxRhs ? nrhs : kMaxRhs;
@@ -946,7 +953,7 @@ int launch_dslash(Ctx& c, const S& io, int nrhs, int prof_id, int prec_index, do
   if constexpr (S::kHalf) {
     if (nper == 1) k = with_dots ? &k_wilson_gather<S, S::kDots, true, R> : &k_wilson_gather<S, false, true, R>;
   }
-  hipLaunchKernelGGL(k, grid, block, 0, c.stream, g, io, diag, tneg, nsb, nrhs, nper, dots);
+  hipLaunchKernelGGL(k, grid, block, 0, c.stream, g, io, diag, tneg, nsb, nrhs, nper, g5, dots);
   WDMG_HIP(hipGetLastError());
   return nsb;
 }
@@ -988,6 +995,10 @@ template <typename R>
 void dslash(Ctx& c, cx<R>* out, const cx<R>* in, int nrhs) {
   launch_dslash(c, full_io<R>(c, out, in), nrhs, sizeof(R) == 8 ? WDMG_K_DSLASH_F64 : WDMG_K_DSLASH_F32,
                 sizeof(R) == 8 ? WDMG_F64 : WDMG_F32);
+}
+
+void dslash_g5(Ctx& c, cx<double>* out, const cx<double>* in, int nrhs) {
+  launch_dslash(c, full_io<double>(c, out, in), nrhs, WDMG_K_DSLASH_F64, WDMG_F64, nullptr, 1);
 }
 
 template <typename H>

@@ -297,6 +297,8 @@ void init_dslash();
 // Wilson operator (dslash.hip): out = diag * in - 1/2 sum_mu hops.
 template <typename R>
 void dslash(Ctx& c, cx<R>* out, const cx<R>* in, int nrhs);
+// out = gamma5 D in.
+void dslash_g5(Ctx& c, cx<double>* out, const cx<double>* in, int nrhs);
 // The same on 16-bit fields and links, FP32 arithmetic.
 template <typename H>
 void dslash_h(Ctx& c, HF out, HF in, int nrhs);

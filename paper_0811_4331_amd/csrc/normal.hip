@@ -70,12 +70,11 @@ __device__ __forceinline__ void coarse_coords(const Geom& g, int s, int (&c)[4])
   c[3] = s / g.L[2];
 }
 
-// gamma5 on fine fields: components 6..11 (spins 2, 3)
-// change sign.
-__global__ void k_gamma5(cx<double>* f, size_t n) {
+// out = gamma5 in on fine fields: components 6..11 (spins 2, 3) change sign.
+__global__ void k_gamma5(cx<double>* __restrict__ out, const cx<double>* __restrict__ in, size_t n) {
   for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
-    const int k = (int)(i % 12);
-    if (k >= 6) f[i] = mk(-f[i].re, -f[i].im);
+    const cx<double> v = in[i];
+    out[i] = i % 12 >= 6 ? mk(-v.re, -v.im) : v;
   }
 }
 
@@ -189,8 +188,8 @@ cx<double> cdivh(cx<double> a, cx<double> b) {
   return mk((a.re * b.re + a.im * b.im) / d, (a.im * b.re - a.re * b.im) / d);
 }
 
-void gamma5(Ctx& c, cx<double>* f, size_t n) {
-  hipLaunchKernelGGL(k_gamma5, dim3(ew_grid(n)), dim3(256), 0, c.stream, f, n);
+void gamma5(Ctx& c, cx<double>* out, const cx<double>* in, size_t n) {
+  hipLaunchKernelGGL(k_gamma5, dim3(ew_grid(n)), dim3(256), 0, c.stream, out, in, n);
   WDMG_HIP(hipGetLastError());
 }
 
@@ -212,22 +211,18 @@ struct NormalWork {
   }
 };
 
-// out = A in = gamma5 D gamma5 D in on nrhs internal fine fields; tmp holds nrhs fields.
+// out = A in = gamma5 D gamma5 D in on nrhs fine fields; tmp holds nrhs fields.
+// gamma5 is part of the operator's store (24^3x48, a CG iteration 728 us; with
+// gamma5 in passes of its own 823).
 void normal_apply0(Ctx& c, cx<double>* out, const cx<double>* in, cx<double>* tmp, int nrhs) {
-  const size_t n = c.lev[0].n * nrhs;
-  dslash<double>(c, tmp, in, nrhs);
-  gamma5(c, tmp, n);
-  dslash<double>(c, out, tmp, nrhs);
-  gamma5(c, out, n);
+  dslash_g5(c, tmp, in, nrhs);
+  dslash_g5(c, out, tmp, nrhs);
 }
 
 // out = D^dagger in (one or more fields).
 void apply_Ddag0(Ctx& c, cx<double>* out, const cx<double>* in, cx<double>* tmp, int nrhs) {
-  const size_t n = c.lev[0].n * nrhs;
-  copy<double>(c, tmp, in, n);
-  gamma5(c, tmp, n);
-  dslash<double>(c, out, tmp, nrhs);
-  gamma5(c, out, n);
+  gamma5(c, tmp, in, c.lev[0].n * nrhs);
+  dslash_g5(c, out, tmp, nrhs);
 }
 
 // Coarse extents >= 3 and fine aggregates of extent >= 2 in every direction.
