@@ -10,6 +10,9 @@
 //
 // Fields of every level are [site][dof] in lexicographic site order, dof = 12
 // at level 0; the two chiralities are the two halves of dof.
+#include <algorithm>
+#include <type_traits>
+
 #include "half_field.h"
 #include "internal.h"
 
@@ -416,39 +419,78 @@ __global__ __launch_bounds__(256) void k_restrict_mm(AggMap map, int dof, VL V, 
   }
 }
 
-// ---- prolongation: one thread per element of a finer-level field and NB right-hand sides ----
+// ---- prolongation on the vector units -----------------------------------------
+// A launch over nb blocks of the field and ng groups of right-hand sides.  A
+// block's groups run on one XCD, whose L2 they share V in (rows of eight blocks;
+// without the padding 20x12x20x12, nv 20, FP16, 4 groups of one 49 us against
+// 35).  Where V is longer than the Infinity Cache they run back to back (x: 8
+// XCDs x groups, y: rows), so that it comes from memory once (24^3x48, nv 20,
+// BF16, 8 rhs 522 us against 560), else the blocks are swept once per group
+// (20^4, 133 against 142).
+struct BlockMap {
+  int b0;  // first block, or -1: x blocks, y groups
+  __device__ __forceinline__ int block() const {
+    return b0 < 0 ? (int)blockIdx.x : b0 + 8 * (int)blockIdx.y + (int)(blockIdx.x & 7);
+  }
+  __device__ __forceinline__ int group() const { return (int)(b0 < 0 ? blockIdx.y : blockIdx.x >> 3); }
+};
+template <class Launch>
+void over_blocks(size_t nb, int ng, size_t vbytes, Launch launch) {
+  const size_t rows = (nb + 7) / 8, most = 65535;  // rows of a grid
+  if (ng == 1 || vbytes <= ((size_t)256 << 20)) {
+    launch(dim3((unsigned)(8 * rows), ng), BlockMap{-1});
+    return;
+  }
+  for (size_t r = 0; r < rows; r += most)
+    launch(dim3(8 * ng, (unsigned)std::min(most, rows - r)), BlockMap{(int)(8 * r)});
+}
+
+// One thread per EP consecutive elements of a finer-level field, which belong to
+// one chirality of a site, and NB right-hand sides.
 constexpr int RB = 8;
-template <class VL, int NB>
+template <class VL, int NB, int EP>
 __global__ __launch_bounds__(256) void k_prolong(AggMap map, int dof, VL V, const cx<typename VL::T>* __restrict__ in,
-                                                 cx<typename VL::T>* __restrict__ out, int nagg, int nv, int nrhs) {
+                                                 cx<typename VL::T>* __restrict__ out, int nagg, int nv, int nrhs,
+                                                 BlockMap bm) {
   using R = typename VL::T;
   const size_t n = (size_t)map.g.vol * dof;
-  const size_t idx = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
-  const int r0 = blockIdx.y * NB, nr = min(NB, nrhs - r0);
+  const size_t idx = ((size_t)bm.block() * 256 + threadIdx.x) * EP;
+  const int r0 = bm.group() * NB, nr = min(NB, nrhs - r0);
   if (idx >= n) return;
   const int s = (int)(idx / dof), e = (int)(idx % dof);
   const int chi = e >= dof / 2;
   const cx<R>* ec = in + ((size_t)r0 * nagg + map.agg_of(s)) * 2 * nv + chi * nv;
-  cx<R> acc[NB];
+  cx<R> acc[NB][EP];
 #pragma unroll
-  for (int q = 0; q < NB; ++q) acc[q] = mk<R>(0, 0);
+  for (int q = 0; q < NB; ++q)
+#pragma unroll
+    for (int m = 0; m < EP; ++m) acc[q][m] = mk<R>(0, 0);
 #pragma unroll 4
   for (int k = 0; k < nv; ++k) {
-    const cx<R> w = V.one(k, idx);
+    cx<R> w[EP];
+#pragma unroll
+    for (int m = 0; m < EP; ++m) w[m] = V.one(k, idx + m);
 #pragma unroll
     for (int q = 0; q < NB; ++q)
-      if (q < nr) cmadd(acc[q], w, ec[(size_t)q * nagg * 2 * nv + k]);
+      if (q < nr) {
+        const cx<R> x = ec[(size_t)q * nagg * 2 * nv + k];
+#pragma unroll
+        for (int m = 0; m < EP; ++m) cmadd(acc[q][m], w[m], x);
+      }
   }
 #pragma unroll
   for (int q = 0; q < NB; ++q)
-    if (q < nr) out[(size_t)(r0 + q) * n + idx] = acc[q];
+    if (q < nr) {
+#pragma unroll
+      for (int m = 0; m < EP; ++m) out[(size_t)(r0 + q) * n + idx + m] = acc[q][m];
+    }
 }
 
 // The same into a 16-bit field, one thread per site.
 template <typename H, int NB>
 __global__ __launch_bounds__(256) void k_prolong0_h(AggMap map, VHalf<H> V, const cx<float>* __restrict__ in,
-                                                    OutHalf<H> O, int nagg, int nv, int nrhs) {
-  const int s = blockIdx.x * blockDim.x + threadIdx.x, r0 = blockIdx.y * NB, vol = map.g.vol;
+                                                    OutHalf<H> O, int nagg, int nv, int nrhs, BlockMap bm) {
+  const int s = bm.block() * 256 + threadIdx.x, r0 = bm.group() * NB, vol = map.g.vol;
   if (s >= vol) return;
   const cx<float>* ec = in + ((size_t)r0 * nagg + map.agg_of(s)) * 2 * nv;
   cx<float> acc[NB][12];
@@ -456,7 +498,8 @@ __global__ __launch_bounds__(256) void k_prolong0_h(AggMap map, VHalf<H> V, cons
   for (int q = 0; q < NB; ++q)
 #pragma unroll
     for (int m = 0; m < 12; ++m) acc[q][m] = mk(0.0f, 0.0f);
-#pragma unroll 2
+  constexpr int kUnroll = NB == 4 ? 1 : 2;  // columns at a time (BF16, 24^3x48, nv 20, 8 rhs: 523 us, 563 with two)
+#pragma unroll kUnroll
   for (int k = 0; k < nv; ++k) {
     cx<float> w[12];
     const u4* vk = reinterpret_cast<const u4*>(V.v + (size_t)k * V.stride) + (size_t)s * 3;
@@ -953,12 +996,22 @@ void restrictC(Ctx& c, const Level& f, const cx<R>* V, const cx<R>* in, cx<R>* o
 
 // The matrix-core prolongation where it applies: level 0, aggregates of whole
 // units, at most 32 columns, and a batch that fills enough of a tile's 16
-// columns: from 6 right-hand sides in FP64, 3 in FP32, 9 in 16 bits (vector
-// units / matrix cores, us, 24^3x48, nv 20: FP64 4 rhs 789 / 965, 6 rhs 1089 /
-// 1005, 16 rhs 2752 / 1233; FP32 2 rhs 411 / 380, 16 rhs 2151 / 506; BF16 4 rhs
-// 321 / 515, 8 rhs 605 / 618, 16 rhs 1162 / 820; 16^4: FP32 2 rhs 36 / 42, 3 rhs
-// 46 / 43).
-enum { kPmMinF64 = 6, kPmMinF32 = 3, kPmMinHalf = 9 };
+// columns: from 6 right-hand sides in FP64, 3 in FP32 (vector units / matrix
+// cores, us, 24^3x48, nv 20: FP64 4 rhs 789 / 965, 6 rhs 1089 / 1005, 16 rhs
+// 2752 / 1233; FP32 2 rhs 411 / 380, 16 rhs 2151 / 506; 16^4: FP32 2 rhs 36 / 42,
+// 3 rhs 46 / 43).
+enum { kPmMinF64 = 6, kPmMinF32 = 3 };
+// In 16 bits by blocks of 256 sites: up to half a block per compute unit from 17,
+// under two from 13, else from 12 in BF16 and 10 in FP16 (BF16 12x16x8x16: 14 rhs
+// 42 / 49; 16^4: 12 rhs 72 / 83, 13 rhs 88 / 85; 20^4: 14 rhs 228 / 220; 24^3x48:
+// BF16 11 rhs 664 / 688, 12 rhs 744 / 713, FP16 9 rhs 635 / 655, 10 rhs 693 / 680).
+template <typename H>
+int pm_min_half(const Ctx& c, const Level& f) {
+  const int nblk = (f.nsite + 255) / 256;
+  if (nblk <= c.ncu / 2) return 17;
+  if (nblk < 2 * c.ncu) return 13;
+  return std::is_same<H, bf16_t>::value ? 12 : 10;
+}
 inline bool pm_fits(const Level& f, int nrhs, int least) {
   return nrhs >= least && f.dof == 12 && make_map(f).bvol % kPmSites == 0 && f.nv <= 32;
 }
@@ -1002,13 +1055,19 @@ void launch_prolong(Ctx& c, const Level& f, const cx<R>* V, const cx<R>* in, cx<
     launch_prolong_mm(c, f, VFull<R>{V, f.n}, in, OutFull<R>{out}, nrhs);
     return;
   }
-  const dim3 grid((unsigned)((f.n + 255) / 256), (nrhs + RB - 1) / RB);
-  if (nrhs == 1)
-    hipLaunchKernelGGL((k_prolong<VFull<R>, 1>), grid, dim3(256), 0, c.stream, make_map(f), f.dof, VFull<R>{V, f.n}, in,
-                       out, nagg_of(f), f.nv, nrhs);
+  const size_t vbytes = (size_t)f.nv * f.n * sizeof(cx<R>);
+#define PV(NB, EP)                                                                                             \
+  over_blocks((f.n / (EP) + 255) / 256, (nrhs + (NB) - 1) / (NB), vbytes, [&](dim3 grid, BlockMap bm) {        \
+    hipLaunchKernelGGL((k_prolong<VFull<R>, NB, EP>), grid, dim3(256), 0, c.stream, make_map(f), f.dof,        \
+                       VFull<R>{V, f.n}, in, out, nagg_of(f), f.nv, nrhs, bm);                                 \
+  })
+  if (nrhs > 1)
+    PV(RB, 1);
+  else if (sizeof(R) == 4 && f.dof % 4 == 0)
+    PV(1, 2);
   else
-    hipLaunchKernelGGL((k_prolong<VFull<R>, RB>), grid, dim3(256), 0, c.stream, make_map(f), f.dof, VFull<R>{V, f.n},
-                       in, out, nagg_of(f), f.nv, nrhs);
+    PV(1, 1);
+#undef PV
   WDMG_HIP(hipGetLastError());
 }
 
@@ -1049,20 +1108,28 @@ void prolong0_h(Ctx& c, const Level& f, const void* V16, const cx<float>* in, HF
   ProfScope ps(c, WDMG_K_PROLONG_H, (long long)f.nsite * nrhs);
   const VHalf<H> V{static_cast<const cxh<H>*>(V16), f.n};
   const OutHalf<H> O{static_cast<cxh<H>*>(out.v), out.s};
-  if (pm_fits(f, nrhs, kPmMinHalf)) {
+  if (pm_fits(f, nrhs, pm_min_half<H>(c, f))) {
     launch_prolong_mm(c, f, V, in, O, nrhs);
     return;
   }
-  // four right-hand sides per thread read V once for them; where that leaves
-  // fewer than four workgroups per compute unit, one (8x8x8x16, 8 rhs: 14 us
-  // against 24; 16^4, 8 rhs: 56 us at four, 66 at one)
+  // Right-hand sides per thread, which share its part of V: one where that fills
+  // the chip no more than four workgroups a compute unit (8x8x8x16, 8 rhs: 15 us
+  // against 18 with two, 24 with four), two in FP16 and for the next larger
+  // lattices (20x12x20x12, 8 rhs: 50 us, 57 with one, 54 with four; FP16 20^4, 4
+  // rhs: 69, 73, 86), else four (BF16 24^3x48, 8 rhs: 522, 572 with two).
   const int nblk = (f.nsite + 255) / 256;
+#define PH(NB)                                                                                                  \
+  over_blocks(nblk, (nrhs + (NB) - 1) / (NB), (size_t)f.nv * f.n * 4, [&](dim3 grid, BlockMap bm) {             \
+    hipLaunchKernelGGL((k_prolong0_h<H, NB>), grid, dim3(256), 0, c.stream, make_map(f), V, in, O, nagg_of(f),  \
+                       f.nv, nrhs, bm);                                                                         \
+  })
   if ((long long)nblk * nrhs <= 4 * c.ncu)
-    hipLaunchKernelGGL((k_prolong0_h<H, 1>), dim3(nblk, nrhs), dim3(256), 0, c.stream, make_map(f), V, in, O,
-                       nagg_of(f), f.nv, nrhs);
+    PH(1);
+  else if (std::is_same<H, f16_t>::value || (long long)nblk * ((nrhs + 3) / 4) <= 2 * c.ncu)
+    PH(2);
   else
-    hipLaunchKernelGGL((k_prolong0_h<H, 4>), dim3(nblk, (nrhs + 3) / 4), dim3(256), 0, c.stream, make_map(f), V, in, O,
-                       nagg_of(f), f.nv, nrhs);
+    PH(4);
+#undef PH
   WDMG_HIP(hipGetLastError());
 }
 

@@ -237,3 +237,29 @@ def test_coarsest_solve_of_one_right_hand_side(dims):
     r = b.reshape(x.shape) - wilson.apply_D(u, x.cpu().numpy(), -0.3, -1.0)
     assert st["converged"] and np.linalg.norm(r) <= 1e-10 * np.linalg.norm(b), st
     ctx.close()
+
+
+@pytest.mark.parametrize("prec,dims,nrhs", [
+    ("f16", (20, 12, 20, 12), 5),     # two right-hand sides per thread, a last group of one; 225 blocks
+    ("bf16", (20, 20, 20, 20), 6),    # four per thread, a last group of two; 625 blocks
+    ("bf16", (24, 24, 24, 48), 5),    # groups back to back (V longer than 256 MB)
+    ("f32", (20, 12, 20, 12), 2),     # the vector units' batch in FP32
+])
+def test_prolongation_in_groups_of_right_hand_sides(prec, dims, nrhs):
+    """Groups of right-hand sides per thread, in either order of the grid, give
+    what one at a time gives: the same products in the same order."""
+    lx, ly, lz, lt = dims
+    ctx = wdmg.Context(dims, DEV)
+    u = torch.eye(3, dtype=torch.complex128, device=DEV).expand(ctx.site_shape + (4, 3, 3)).contiguous()
+    ctx.set_gauge(u, t_bc=-1)
+    ctx.set_mass(0.1)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(971)
+    nv = 12
+    v = torch.randn((nv,) + ctx.fine_shape(), generator=g, device=DEV, dtype=torch.complex128)
+    ctx.mg_setup([{"block": (4, 4, 4, 4), "nv": nv, "setup_iters": 0, "vectors": v}])
+    c = torch.randn((nrhs,) + tuple(ctx.coarse_shape(1)), generator=g, device=DEV, dtype=torch.complex64)
+    out = ctx.prolong(0, c, prec=prec)
+    for j in range(nrhs):
+        assert torch.equal(out[j], ctx.prolong(0, c[j].contiguous(), prec=prec)), j
+    ctx.close()
