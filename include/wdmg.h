@@ -308,9 +308,9 @@ int wdmg_solve_bicgstab(wdmg_ctx* ctx, void* x, const void* b, int nrhs, double 
  *                     group; a value above the batch size means the whole
  *                     batch).  The tile form ignores it.
  *   WDMG_TUNE_COARSE_APPLY: 0 or 1, kept for callers that set it; the
- *                     batched coarsest-level operator has one form.
- *                     AUTO means form 1 where it applies (not timed);
- *                     wdmg_get_tuning reports only a forced value. */
+ *                     batched coarsest-level operator has one form and reads
+ *                     the key nowhere.  wdmg_get_tuning reports only a forced
+ *                     value. */
 enum {
   WDMG_TUNE_AUTO = -1,
   WDMG_TUNE_DSLASH = 0,

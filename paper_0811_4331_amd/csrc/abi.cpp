@@ -20,8 +20,8 @@ using namespace wdmg;
 struct wdmg_ctx : Ctx {};
 
 // ---------------------------------------------------------------------------
-// Scratch of wdmg_apply_D_noalloc: the internal-layout input and output fields
-// live in this file-scope device array instead of library allocations.  Its
+// Scratch of wdmg_apply_D_noalloc: fields that cannot be worked on where they are
+// go through this file-scope device array instead of library allocations.  Its
 // device address is taken once per device in wdmg_create (with that device
 // current); host code uses only that address, never the array's name.
 static constexpr size_t kNoAllocScratchBytes = (size_t)64 << 20;

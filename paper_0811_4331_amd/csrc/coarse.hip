@@ -515,9 +515,8 @@ __global__ __launch_bounds__(576) void k_coarse_apply_h(Geom g, int n2, const cx
 // Many sites: W = 3 (three directions per wave keep loads in flight while
 // products run).  Few sites: W = 9, one direction per wave.  The tiles of
 // right-hand sides of a site follow each other on one XCD, whose L2 then holds
-// its blocks: two tiles in one workgroup are slower (BF16, 32 rhs: 89 us
-// against 88, before the directions were unrolled), and a wave per row tile, which loads the vectors once per
-// wave, far slower (218 us).
+// its blocks: two tiles in one workgroup are 1% slower (BF16, 32 rhs), and a wave
+// per row tile, which loads the vectors once per wave, takes three times as long.
 //
 // FP64 / FP32 (v_mfma 16x16x4): four real products per complex one; a lane
 // group supplies columns 4 g + u of a block of 16 in step u for both operands,

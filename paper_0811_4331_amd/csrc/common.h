@@ -85,10 +85,6 @@ struct Geom {
   int ltvol;   // log2 tvol
 };
 
-struct Coord {
-  int c[4];   // global coordinates
-};
-
 __host__ __device__ __forceinline__ int site_of(const Geom& g, int x, int y, int z, int t) {
   const int c[4] = {x, y, z, t};
   int tile = 0, loc = 0;
@@ -199,12 +195,6 @@ __device__ __forceinline__ void block_sum(double (&v)[K], double* lds) {
     for (int k = 0; k < K; ++k) v[k] = wave_sum(lane < nw ? lds[lane * K + k] : 0.0);
   }
   __syncthreads();
-}
-
-// Load that bypasses the (non-coherent) per-CU vector L1, for data written by
-// other workgroups of the same launch.
-__device__ __forceinline__ double load_coherent(const double* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 }  // namespace wdmg

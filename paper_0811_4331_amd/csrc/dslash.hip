@@ -568,13 +568,15 @@ __global__ __launch_bounds__(256) void k_wilson_gather(Geom g, S io, R diag, int
 // The grid is one workgroup per compute unit, and each walks its tiles
 // (TileWork): the work per unit is equal to one right-hand side, and the
 // prologue of a tile (links, offsets) overlaps the previous tile's last
-// right-hand side.  Neighbouring workgroups of an XCD are in step, so HBM
-// reads are within 3% of one read per spinor.  24^3x48, 32 rhs, FP32:
-// 1322 us against 2018 us for the best earlier kernel (3717 us with its layout
-// conversions); one workgroup per tile and 8 right-hand sides: 1493 us.
-// Bound: with the hops taken out it runs 4% faster, so by memory (3.3 TB/s of
-// the 4.7 TB/s a copy reaches), the reads of one right-hand side being in
-// flight for less than the whole time.
+// right-hand side.  Neighbouring workgroups of an XCD are in step: L2 misses are
+// at most 1.07 of the algorithmic bytes, where one read of every spinor is 0.53
+// (an upper bound: hits in the Infinity Cache count, and so does the counter's
+// factor for a copy's long requests).  24^3x48, 32 rhs, FP32: 1300 us against
+// 2018 us for the best earlier kernel (3717 us with its layout conversions); one
+// workgroup per tile and 8 right-hand sides: 1493 us.
+// Bound: two waves per SIMD, which hide neither all of the loads (3.3 TB/s of the
+// 4.7 TB/s a copy reaches; with the hops taken out 4% faster) nor all of the
+// instructions (vector units 53% busy in FP32, 61% in BF16).
 constexpr int kTileSlots = 256 + 8 * 64;
 constexpr int kTileChunks = kTileSlots * 6;
 constexpr int kTileThreads = 512;

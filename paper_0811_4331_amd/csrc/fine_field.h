@@ -69,13 +69,4 @@ __device__ __forceinline__ void load_link(const cx<R>* __restrict__ U, int mu, i
   recon_third_row(u, neg);
 }
 
-// Workgroup index remapped so that consecutive tiles (spatial neighbours)
-// run on the same XCD and share its L2: hardware dispatches workgroup b to
-// XCD b % 8.
-__device__ __forceinline__ int xcd_block() {
-  const int nb = gridDim.x, b = blockIdx.x;
-  if (nb & 7) return b;
-  return (b & 7) * (nb >> 3) + (b >> 3);
-}
-
 }  // namespace wdmg

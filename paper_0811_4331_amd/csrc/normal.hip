@@ -425,7 +425,7 @@ void normal_vcycle(Ctx& c, cx<double>* x, const cx<double>* b, NormalVc& v) {
 }
 
 // CG on the normal equations (precond = false) or MG-CG (precond = true) for
-// one right-hand side b (internal layout), x from 0.  Converged when the true
+// one right-hand side b, x from 0.  Converged when the true
 // residual ||b - D x|| / ||b|| <= tol, checked once the normal residual has
 // fallen below 1e-2 tol ||b|| (||b - D x|| can exceed it by the conditioning).
 int normal_solve(Ctx& c, cx<double>* x, const cx<double>* b, double tol, int maxit, bool precond,

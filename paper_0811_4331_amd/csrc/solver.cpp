@@ -475,7 +475,7 @@ template void vcycle_h<bf16_t>(Ctx&, HF, HF, int);
 // Outer flexible GCR(k) in FP64 (Sec. 5) for nrhs right-hand sides in
 // lockstep, each with its own coefficients; a converged right-hand side is
 // frozen (its steps are zero).  b (input) and x (initial guess, output) are
-// nrhs internal fields.
+// nrhs fields.
 int fgcr(Ctx& c, cx<double>* x, const cx<double>* b, int nrhs, const wdmg_solve_params& p, wdmg_solve_stats* st) {
   Level& L = c.lev[0];
   const size_t n = L.n;

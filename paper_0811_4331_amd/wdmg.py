@@ -257,9 +257,9 @@ class Context:
         return out
 
     def apply_D_noalloc(self, psi: torch.Tensor, out: torch.Tensor, prec: str = "f64"):
-        """``out = D psi`` through the entry point that allocates nothing (its
-        work fields sit in the library's fixed 64 MiB device scratch); the
-        caller provides ``out``."""
+        """``out = D psi`` through the entry point that allocates nothing (fields
+        that overlap or are not aligned to 16 bytes go through the library's
+        fixed 64 MiB device scratch); the caller provides ``out``."""
         nrhs = self._nrhs(psi, 6)
         if tuple(psi.shape[-6:]) != self.fine_shape() or out.shape != psi.shape:
             raise ValueError("fine field shape mismatch")
