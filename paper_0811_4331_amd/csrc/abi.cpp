@@ -61,6 +61,13 @@ int guarded(wdmg_ctx* c, F&& f) {
   }
 }
 
+// A call that does not use io_a and io_b.
+struct IoIdle {
+  Ctx& c;
+  explicit IoIdle(Ctx& ctx) : c(ctx) { c.io_idle = true; }
+  ~IoIdle() { c.io_idle = false; }
+};
+
 void need_gauge(Ctx& c) {
   if (!c.have_gauge) throw Error(WDMG_ERR_NOT_SETUP, "no gauge field set");
 }
@@ -558,6 +565,7 @@ int wdmg_roundtrip(wdmg_ctx* c, void* out, const void* in, int nrhs, int prec) {
 int wdmg_mg_setup(wdmg_ctx* c, const wdmg_mg_params* p) {
   return guarded(c, [&]() {
     need_ptr(p, "params");
+    IoIdle idle(*c);
     mg_setup(*c, *p);
     return WDMG_OK;
   });
@@ -675,6 +683,7 @@ int wdmg_smooth(wdmg_ctx* c, int level, void* x, const void* b, int nrhs, int it
 
 int wdmg_solve(wdmg_ctx* c, void* x, const void* b, int nrhs, const wdmg_solve_params* p, wdmg_solve_stats* stats) {
   return guarded(c, [&]() {
+    IoIdle idle(*c);
     need_ptr(x, "x");
     need_ptr(b, "b");
     need_ptr(p, "params");
@@ -767,6 +776,7 @@ int wdmg_solve(wdmg_ctx* c, void* x, const void* b, int nrhs, const wdmg_solve_p
 int wdmg_solve_bicgstab(wdmg_ctx* c, void* x, const void* b, int nrhs, double tol, int maxit,
                         wdmg_solve_stats* stats) {
   return guarded(c, [&]() {
+    IoIdle idle(*c);
     need_ptr(x, "x");
     need_ptr(b, "b");
     need_nrhs(nrhs);

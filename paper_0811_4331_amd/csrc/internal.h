@@ -188,10 +188,11 @@ struct Ctx {
   Level lev[WDMG_MAX_LEVELS];
   double setup_mass = 0.0;
 
-  // scratch fine / coarse fields for canonical <-> internal conversion
+  // scratch fields of wdmg_smooth, and of callers' buffers that cannot be worked on
   void* io_a = nullptr;
   void* io_b = nullptr;
   size_t io_abytes = 0, io_bbytes = 0;
+  bool io_idle = false;         // inside a call that uses neither: given back when memory runs out
   HF ioh[3];                    // 16-bit scratch fine fields
   int ioh_cap = 0;
 

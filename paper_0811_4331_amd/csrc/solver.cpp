@@ -23,21 +23,31 @@ namespace wdmg {
 
 // ---------------------------------------------------------------------------
 // memory
+namespace {
+void* provide(Ctx& c, size_t bytes) {  // null where there is no memory
+  if (c.alloc.alloc) return c.alloc.alloc(bytes, c.alloc.user);
+  void* p = nullptr;
+  if (hipMalloc(&p, bytes) == hipSuccess) return p;
+  (void)hipGetLastError();
+  return nullptr;
+}
+}  // namespace
+
 void* dev_alloc(Ctx& c, size_t bytes) {
   if (bytes == 0) bytes = 256;
-  void* p = nullptr;
-  if (c.alloc.alloc) {
-    p = c.alloc.alloc(bytes, c.alloc.user);
-    if (!p) throw Error(WDMG_ERR_OOM, "device allocation of " + std::to_string(bytes) + " bytes failed");
-    if (reinterpret_cast<uintptr_t>(p) & 255)  // not an allocation: never hand it to a kernel
-      throw Error(WDMG_ERR_OOM, "device allocation of " + std::to_string(bytes) +
-                                    " bytes returned a misaligned pointer");
-  } else {
-    if (hipMalloc(&p, bytes) != hipSuccess || !p) {
-      (void)hipGetLastError();
-      throw Error(WDMG_ERR_OOM, "hipMalloc of " + std::to_string(bytes) + " bytes failed");
+  void* p = provide(c, bytes);
+  if (!p && c.io_idle && (c.io_a || c.io_b)) {  // what a smoothing left behind makes room
+    WDMG_HIP(hipStreamSynchronize(c.stream));
+    c.io_abytes = c.io_bbytes = 0;
+    for (void** io : {&c.io_a, &c.io_b}) {
+      dev_free(c, *io);
+      *io = nullptr;
     }
+    p = provide(c, bytes);
   }
+  if (!p) throw Error(WDMG_ERR_OOM, "device allocation of " + std::to_string(bytes) + " bytes failed");
+  if (reinterpret_cast<uintptr_t>(p) & 255)  // not an allocation: never hand it to a kernel
+    throw Error(WDMG_ERR_OOM, "device allocation of " + std::to_string(bytes) + " bytes returned a misaligned pointer");
   c.bufs.push_back(Buf{p, bytes});
   return p;
 }

@@ -174,3 +174,48 @@ def test_setup_in_little_memory(monkeypatch):
         got.append(ctx.get_prolongator(0))
         ctx.close()
     assert float((got[0] - got[1]).abs().max() / got[0].abs().max()) < 1e-12
+
+
+def test_solve_after_a_smoothing_in_the_room_of_a_solve(monkeypatch):
+    """What a smoothing keeps does not stand in the way of a solve: in the memory
+    of the solve and four fields, the solve after a smoothing of a batch gives what
+    it gives alone."""
+    sizes, room = {}, [None]
+    alloc, delete = torch.cuda.caching_allocator_alloc, torch.cuda.caching_allocator_delete
+
+    def take(size, *rest):
+        if room[0] is not None and sum(sizes.values()) + size > room[0]:
+            raise RuntimeError("no room left for the test")
+        p = alloc(size, *rest)
+        sizes[p] = size
+        return p
+
+    def drop(p):
+        del sizes[p]
+        delete(p)
+
+    monkeypatch.setattr(torch.cuda, "caching_allocator_alloc", take)
+    monkeypatch.setattr(torch.cuda, "caching_allocator_delete", drop)
+    f = gpu(synthetic.gaussian_spinor(DIMS, seed=993, nrhs=NRHS))
+
+    def fresh():
+        c = wdmg.Context(DIMS, DEV)
+        c.set_gauge(gpu(synthetic.gauge_field(DIMS, 0.3, 991)), t_bc=-1)
+        c.set_mass(-0.2)
+        return c
+
+    ctx = fresh()
+    want = ctx.solve(f, tol=1e-6, restart=8, maxit=24, precond=False)[0]
+    peak = sum(sizes.values())
+    ctx.close()
+    ctx = fresh()
+    room[0] = peak + 4 * (f.numel() // NRHS) * f.itemsize
+    ctx.smooth(0, torch.zeros_like(f), f, 2)
+    assert torch.equal(ctx.solve(f, tol=1e-6, restart=8, maxit=24, precond=False)[0], want)
+    x = ctx.smooth(0, torch.zeros_like(f), f, 2)  # in what is left now
+    room[0] = None
+    ctx2 = fresh()
+    ref = ctx2.smooth(0, torch.zeros_like(f), f, 2)
+    assert float((x - ref).abs().max() / ref.abs().max()) < 1e-13
+    ctx.close()
+    ctx2.close()
