@@ -223,10 +223,11 @@ __device__ __forceinline__ void mr_dots(const R* o, const R* i, int n, double (&
 // A workgroup takes a group of right-hand sides.  FP32 and 16 bits keep the
 // links and offsets of the wave in registers over the group; FP64 keeps the two
 // stored rows of the links (166 registers, three waves per SIMD) and finds the
-// rest anew.  ONE: a single right-hand side in 16 bits, whose rows are half as
+// rest anew.  ONE: a single right-hand side.  In 16 bits its rows are half as
 // long as the sums that follow them in the buffer: both neighbours' rows are
 // fetched at once, and with the links' rows held as stored the kernel has 76
-// registers instead of 125.
+// registers instead of 125.  In FP64 the backward link is loaded with the
+// backward rows, so that less is waited for before the first hop.
 //
 // Bound: instructions (one wave takes 700 to 900 vector instructions for 64
 // sites and a direction), in FP64 also the L2.  Measured, kernel alone:
@@ -307,7 +308,37 @@ __device__ __forceinline__ void gather_wave(const Geom& g, const S& io, int tneg
   const size_t fs = (size_t)g.vol * S::NC;
   const bool last = MU == 3 && tneg && c[3] == g.L[3] - 1, first = MU == 3 && tneg && c[3] == 0;
   const int nf = canon_fwd<MU>(g, c, me), nb = canon_bwd<MU>(g, c, me);
-  if constexpr (sizeof(R) == 8) {
+  if constexpr (sizeof(R) == 8 && ONE) {
+    const u4* f = io.in + r0 * fs;
+    cx<R> h[6], uh[6], u[9], acc[12];
+    {
+      unsigned off[S::NC];
+      gather_offsets<S>(nf, lane, off);
+      fetch_sites<S>(f, off, buf);
+    }
+    io.link(MU, s, last, u);
+    wait_loads();
+    read_half_f64<MU, +1>(buf, lane, h);
+    wait_lds();
+    __builtin_amdgcn_sched_barrier(0);
+    {
+      unsigned off[S::NC];
+      gather_offsets<S>(nb, lane, off);
+      fetch_sites<S>(f, off, buf);
+    }
+    link_half<+1>(u, h, uh);
+#pragma unroll
+    for (int k = 0; k < 12; ++k) acc[k] = mk<R>(0, 0);
+    expand_add<MU, +1>(uh, acc);
+    __builtin_amdgcn_sched_barrier(0);
+    io.link(MU, nbr_bwd(g, s, c, MU), first, u);
+    wait_loads();
+    read_half_f64<MU, -1>(buf, lane, h);
+    link_half<-1>(u, h, uh);
+    expand_add<MU, -1>(uh, acc);
+    write_row<R>(buf, lane, acc);
+    finish(r0);
+  } else if constexpr (sizeof(R) == 8) {
     cx<R> lf[6], lb[6];
     io.rows(MU, s, lf);
     io.rows(MU, nbr_bwd(g, s, c, MU), lb);
@@ -473,7 +504,7 @@ __global__ __launch_bounds__(256) void k_wilson_gather(Geom g, S io, R diag, int
 #pragma unroll
       for (int i = 0; i < (NW + 3) / 4; ++i) {
         int tid = threadIdx.x;
-        if constexpr (sizeof(R) == 8) asm volatile("" : "+v"(tid));  // as in gather_wave
+        if constexpr (sizeof(R) == 8 && !ONE) asm volatile("" : "+v"(tid));  // as in gather_wave
         const int e = i * 256 + tid, j = e / NW;
         const int site = __shfl(me, j & 63, 64);
         if (e < 64 * NW && sb * 64 + j < g.vol) {
@@ -952,8 +983,12 @@ int launch_dslash(Ctx& c, const S& io, int nrhs, int prof_id, int prec_index, do
   }
   const dim3 grid((unsigned)((long long)nsb * ((nrhs + nper - 1) / nper))), block(256);
   auto k = with_dots ? &k_wilson_gather<S, S::kDots, false, R> : &k_wilson_gather<S, false, false, R>;
-  if constexpr (S::kHalf) {
-    if (nper == 1) k = with_dots ? &k_wilson_gather<S, S::kDots, true, R> : &k_wilson_gather<S, false, true, R>;
+  if constexpr (S::kHalf || sizeof(R) == 8) {
+    // FP64: where all workgroups run at once the latency of the first loads counts, and
+    // the backward link is better loaded later (12x20x10x18, 1 rhs 13.1 us against 13.4);
+    // with more of them the loop's lighter link rows are (24^3x48, 1 rhs 147 against 141)
+    if (nper == 1 && (S::kHalf || (long long)nsb * nrhs <= 4 * c.ncu))
+      k = with_dots ? &k_wilson_gather<S, S::kDots, true, R> : &k_wilson_gather<S, false, true, R>;
   }
   hipLaunchKernelGGL(k, grid, block, 0, c.stream, g, io, diag, tneg, nsb, nrhs, nper, g5, dots);
   WDMG_HIP(hipGetLastError());
