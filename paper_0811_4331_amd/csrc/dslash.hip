@@ -231,7 +231,8 @@ __device__ __forceinline__ void mr_dots(const R* o, const R* i, int n, double (&
 //
 // Bound: instructions (one wave takes 700 to 900 vector instructions for 64
 // sites and a direction), in FP64 also the L2.  Measured, kernel alone:
-//   FP64  24^3x48 32 rhs 3640 us (4380 with one rhs per workgroup), 1 rhs 141
+//   FP64  24^3x48 32 rhs 3770 us (4480 with one rhs per workgroup), 8 rhs 933
+//         (1102), 1 rhs 156; 32^4 8 rhs 1442 (1665); each inside a solve
 //   BF16  24^3x48 1 rhs 55 us (66 as a group of one), 32^4 86 us (102)
 // and with the layout conversions that it makes unnecessary in brackets: 32^4
 // FP64 1 rhs 222 us (398), 12x20x10x18 FP32 5 rhs 22 us (53), 32^4 FP32 1 rhs
